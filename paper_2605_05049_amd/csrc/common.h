@@ -125,11 +125,24 @@ inline int launch_status() { return hipGetLastError() == hipSuccess ? MOE_OK : M
 // Router backward pieces that live beside the router's forward kernel (router.hip) and are launched from the entry
 // point that also launches the grouped GEMM kernel (grouped_gemm.hip).
 void launch_router_prepare(hipStream_t st, const float* dlogits, const uint16_t* w_router, uint16_t* hi, uint16_t* lo, uint16_t* w_t,
-                           int32_t* offsets2, int32_t* part_order, int32_t* tile_queue, uint32_t* zero_page, int T, int E, int Epad, int Ek,
+                           int32_t* offsets2, int32_t* part_order, uint32_t* zero_page, int T, int E, int Epad, int Ek,
                            int d, int S, int part_rows);
 void launch_router_bwd_dx(hipStream_t st, const uint16_t* dl_hi, const uint16_t* dl_lo, const uint16_t* w_t, uint16_t* dx, int T, int d,
                           int E, int Epad);
 void launch_router_dw_reduce(hipStream_t st, const float* partial, float* dw, int S, int E, int d, int ldp, int accumulate);
+
+// Weight gradients of the expert FFNs (wgrad.hip): f0[e] (and f1[e]) = p0_e^T q0_e (p0_e^T q1_e) over the rows of expert e.
+struct WgradArgs {
+  const int32_t* offsets;      // [Et + 1]
+  const int32_t* order;        // [Et] experts by descending row count
+  const uint16_t* zero_page;   // 256 zeroed bytes: source of k-rows past the end of a ragged contraction
+  const uint16_t* p0; size_t p_ld; int p_dim;
+  const uint16_t* q0; const uint16_t* q1; size_t q_ld; int q_dim;
+  float* f0; float* f1; size_t f_expert_stride; size_t c_ld;
+  int Et, accumulate;
+  int n_p_tiles, n_q_tiles;    // filled by the launcher
+};
+void launch_wgrad(const char* label, hipStream_t st, WgradArgs A);
 
 // Optional per-launch timing (moe_profile_* in the ABI).  While enabled, every kernel launch of the library is
 // bracketed by two HIP events on the launch stream; disabled (the default) it costs one branch.

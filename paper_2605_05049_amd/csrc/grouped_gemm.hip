@@ -65,9 +65,6 @@ constexpr int kCusPerXcd = 32;
 #ifndef MOE_SPLIT_PART_STEPS
 #define MOE_SPLIT_PART_STEPS 16
 #endif
-#ifndef MOE_WGRAD_PERSISTENT
-#define MOE_WGRAD_PERSISTENT 1   // 0: never, 1: where the generic kernel's grid would be padded, 2: always
-#endif
 // How far ahead of their MFMAs a k-step reads its fragments (0: each group of 16 k reads its own; 1: half a group
 // ahead; 2: rolling, see the k-step): for row tiles of up to 256 rows, for tall row tiles, for the tall row tiles of the
 // SwiGLU forward, and for the weight gradients (whose transposing reads gained nothing from 2).
@@ -119,7 +116,6 @@ struct GemmArgs {
   const uint16_t* g_in; const uint16_t* u_in;              // saved G, U for the d(SwiGLU) epilogue
   float* f0; float* f1; size_t f_expert_stride;            // fp32 outputs of the wgrads
   int sum_halves;          // NQ == 2 with fp32 output: write the sum of the two halves' results to f0 (f1 unused)
-  int32_t* queue;          // weight gradients: 8 int32 (one per XCD), zeroed before the launch: tiles handed out so far
 };
 
 // One 256-wide operand of a tile, possibly made of two 128-wide halves from two tensors.
@@ -831,230 +827,6 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   else run(std::integral_constant<int, 1>{});
 }
 
-// ---------------------------------------------------------------------------------------------------------
-// Weight gradients as a persistent kernel: one block per CU takes tile after tile from a queue per XCD (the tile order
-// and the 8 x 4 super-tiles are those described above), so that a tile's start-up -- the block launch and the
-// latency of the first stage's loads, about 3 us against 16 k-steps of 1.8 us at an expert's 1000 rows, and against 5
-// at 300 -- hides behind the previous tile's stores: the next tile's first stage is requested right after the last
-// k-step, into stage 0, while the fp32 results bounce through stage 1 only.  (What it cannot hide: the first k-step's
-// wait counts the stores as well, so it also waits for their acknowledgement, which a block that simply ends leaves to
-// the next block's launch.)  Both operands R-contiguous, ragged K, one fp32 output tensor or the pair dW_gate | dW_up.
-// Where the generic kernel's grid has no padding this one is 1-4 % slower; where it has, dW_down gained up to 22 % (the
-// fine-grained workload's 0.72 -> 0.56 ms) and the pair 1-5 % (the Zipf shard's 0.92 -> 0.87 ms).
-// ---------------------------------------------------------------------------------------------------------
-struct WgradTile {
-  int state;   // 0: nothing to do (padding of the super-tile grid, or no rows to add), 1: a tile, 2: the queue has run out
-  int expert, k_len, p_row0, p_valid, q0_col, q_valid, p_tile_idx;
-  size_t krow0;
-};
-
-template <int NQ>
-__global__ __launch_bounds__(NTHREADS) void wgrad_persistent_kernel(const GemmArgs A) {
-  __shared__ __attribute__((aligned(1024))) char stage0[STAGE_BYTES];
-  __shared__ __attribute__((aligned(1024))) char stage1[STAGE_BYTES];
-  __shared__ long long next_ticket;
-  constexpr int TQ = TILE / NQ;
-  constexpr int PB = 4;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wq = wave >> 1;
-  const int late = wave >> 2;
-  const int xcd = blockIdx.x % kNumXcd;
-  const int sp = (A.n_p_tiles + 7) / 8, sq = (A.n_q_tiles + 3) / 4;
-  const int supers_per_e = sp * sq;
-  const long long n_super = (long long)supers_per_e * A.Et;
-  const long long per_xcd = (n_super + kNumXcd - 1) / kNumXcd * kCusPerXcd;   // tickets of an XCD: 32 per super-tile
-
-  auto decode = [&](long long within) __attribute__((always_inline)) -> WgradTile {
-    WgradTile t = {};
-    if (within >= per_xcd) { t.state = 2; return t; }
-    const long long sid = (within >> 5) * kNumXcd + xcd;
-    if (sid >= n_super) return t;
-    t.expert = A.sched[64 + 2 * A.max_tiles + (int)(sid / supers_per_e)];   // the (sid / supers_per_e)-th largest expert
-    const int super = (int)(sid % supers_per_e), in_super = (int)(within & 31);
-    const int pt = (super % sp) * 8 + (in_super & 7);
-    const int qt = (super / sp) * 4 + (in_super >> 3);
-    if (pt >= A.n_p_tiles || qt >= A.n_q_tiles) return t;
-    const int e_lo = A.offsets[t.expert], e_hi = A.offsets[t.expert + 1];
-    t.k_len = e_hi - e_lo;
-    if (t.k_len == 0 && A.accumulate) return t;
-    t.krow0 = (size_t)e_lo;
-    t.p_tile_idx = pt;
-    t.p_row0 = pt * TILE;
-    t.p_valid = min(TILE, A.p_dim - t.p_row0);
-    t.q0_col = qt * TQ;
-    t.q_valid = min(TQ, A.q_dim - t.q0_col);
-    t.state = 1;
-    return t;
-  };
-  // operands and per-lane load offsets of a tile, and this wavefront's 8 loads of its k-step j
-  auto describe = [&](const WgradTile& t, TileOperand& P, TileOperand& Q, unsigned (&pvo)[4], unsigned (&qvo)[4], int& iwq)
-                      __attribute__((always_inline)) {
-    P.base0 = P.base1 = A.p0 + t.krow0 * A.p_ld + t.p_row0;
-    P.ld = A.p_ld;
-    P.r_valid = t.p_valid;
-    Q.base0 = Q.base1 = A.q0 + t.krow0 * A.q_ld + t.q0_col;
-    if (NQ == 2) Q.base1 = A.q1 + t.krow0 * A.q_ld + t.q0_col;
-    Q.ld = A.q_ld;
-    Q.r_valid = t.q_valid;
-    iwq = wave ^ ((t.p_tile_idx & 1) << 2);   // (see ALTERNATE_Q in the kernel above)
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      pvo[i] = load_offset<true, false>(P, wave * 4 + i, lane);
-      qvo[i] = load_offset<true, NQ == 2>(Q, iwq * 4 + i, lane);
-    }
-  };
-  auto issue = [&](const TileOperand& P, const TileOperand& Q, const unsigned (&pvo)[4], const unsigned (&qvo)[4], int iwq, int k_len, int j,
-                   char* stage) __attribute__((always_inline)) {
-    issue_tile<true, false>(pvo, P, (ptrdiff_t)0, j * BK, k_len, A.zero_page, stage, wave, lane);
-    issue_tile<true, NQ == 2>(qvo, Q, (ptrdiff_t)0, j * BK, k_len, A.zero_page, stage + Q_STAGE_OFFSET, iwq, lane);
-  };
-
-  const int qr0 = (NQ == 2) ? wq * 32 : wq * 64;
-  const int qr1 = (NQ == 2) ? 128 + wq * 32 : wq * 64 + 32;
-  const int wp = (wave & 1) * (PB * 32);
-  constexpr int W = (NQ == 2) ? 32 : 64;       // q extent this wavefront owns per output tensor
-  constexpr int PITCH = W * 4 + 16;            // bytes per staged fp32 row
-  char* const wlds = stage1 + wave * (STAGE_BYTES / 8);   // this wavefront's 9 KB of stage 1: NQ tensors of 32 x PITCH bytes
-  const int q_base = wq * W;
-
-  unsigned p_off[PB], q_off[2];   // per-lane LDS offsets of this wavefront's fragments inside an operand area (kk = 0)
-#pragma unroll
-  for (int b = 0; b < PB; b++) p_off[b] = frag_offset<true>(wp + 32 * b, lane);
-  q_off[0] = frag_offset<true>(qr0, lane);
-  q_off[1] = frag_offset<true>(qr1, lane);
-
-  WgradTile cur = decode(blockIdx.x / kNumXcd);   // the first tile of a block is its own index in its XCD
-  bool first_stage_requested = false;
-  // Whether the stores of the previous tile's epilogue were exactly 32 instructions per wavefront, issued
-  // after the first stage's loads and with no other vector-memory instruction between them and the first k-step's wait.
-  bool stores_behind_loads = false;
-  // (32 = 4 p blocks x 8 row groups of one tensor, or x 4 row groups x 2 tensors)
-  while (cur.state != 2) {
-    // The ticket for the next tile is drawn now and not looked at before the k-steps are done: whoever needs the
-    // value of an atomic waits for everything the wavefront has in flight, which here would be the previous tile's
-    // stores and this tile's first stage.
-    int my_draw;   // (thread 0 only; left undefined elsewhere on purpose: a defined value would be merged in, i.e. waited for, right here)
-    if (tid == 0) {
-      // (an address the compiler cannot prove wave-uniform: for a uniform one it rewrites the atomic into "one lane adds
-      // the number of active lanes, the others derive theirs", which reads the result at once)
-      int zero = 0;
-      asm volatile("" : "+v"(zero));
-      my_draw = atomicAdd(A.queue + xcd + zero, 1);
-    }
-    f32x16 acc[2][PB];
-    if (cur.state == 1) {
-      TileOperand P, Q;
-      unsigned pvo[4], qvo[4];
-      int iwq;
-      describe(cur, P, Q, pvo, qvo, iwq);
-      const int nk = (cur.k_len + BK - 1) / BK;
-      if (!first_stage_requested && nk > 0) issue(P, Q, pvo, qvo, iwq, cur.k_len, 0, stage0);
-#pragma unroll
-      for (int a = 0; a < 2; a++)
-#pragma unroll
-        for (int b = 0; b < PB; b++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) acc[a][b][v] = 0.f;
-      auto k_step = [&](auto first_c, const char* stg, char* nxt, int kt) {
-        // This thread's loads of step kt have landed.  The counter is in issue order, loads and stores alike: the first
-        // stage was requested before the previous tile's stores, so after a full tile's epilogue "all but the
-        // youngest 32" means the loads, and the stores drain while the tile's first step multiplies.
-        if (decltype(first_c)::value && stores_behind_loads) __builtin_amdgcn_s_waitcnt(0x8F70);  // vmcnt(32)
-        else __builtin_amdgcn_s_waitcnt(0x0F70);                                                   // vmcnt(0)
-        __syncthreads();
-        if (late && kt + 1 < nk) issue(P, Q, pvo, qvo, iwq, cur.k_len, kt + 1, nxt);
-        const unsigned p_base = (unsigned)(size_t)(lptr_t)stg, q_base = p_base + Q_STAGE_OFFSET;
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 16) {
-          if (kk == MOE_EARLY_ISSUE_AT) {
-            __builtin_amdgcn_sched_barrier(0);
-            if (!late && kt + 1 < nk) issue(P, Q, pvo, qvo, iwq, cur.k_len, kt + 1, nxt);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          bf16x8 pf[PB], qf[2];
-          qf[0] = read_frag_at<true>(q_off[0], kk, q_base);
-          qf[1] = read_frag_at<true>(q_off[1], kk, q_base);
-#pragma unroll
-          for (int b = 0; b < PB; b++) pf[b] = read_frag_at<true>(p_off[b], kk, p_base);
-#pragma unroll
-          for (int b = 0; b < PB; b++)
-#pragma unroll
-            for (int a = 0; a < 2; a++)
-              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[a], pf[b], acc[a][b], 0, 0, 0);
-        }
-      };
-      if (nk > 0) k_step(std::true_type{}, stage0, stage1, 0);
-      for (int kt = 1; kt < nk; kt += 2) {
-        k_step(std::false_type{}, stage1, stage0, kt);
-        if (kt + 1 < nk) k_step(std::false_type{}, stage0, stage1, kt + 1);
-      }
-    }
-    asm volatile("" : "+v"(my_draw));   // (nothing that needs the drawn value may move up across the k-steps)
-    if (tid == 0) next_ticket = kCusPerXcd + (long long)my_draw;
-    __syncthreads();   // every wavefront has finished reading the stages; the next ticket is visible
-    const long long drawn = next_ticket;   // (the same for every lane: said so, which keeps the tile's description in scalar registers)
-    const WgradTile nxt = decode(((long long)__builtin_amdgcn_readfirstlane((int)(drawn >> 32)) << 32) |
-                                 (unsigned)__builtin_amdgcn_readfirstlane((int)drawn));
-    first_stage_requested = false;
-    if (nxt.state == 1 && nxt.k_len > 0) {
-      TileOperand P, Q;
-      unsigned pvo[4], qvo[4];
-      int iwq;
-      describe(nxt, P, Q, pvo, qvo, iwq);
-      issue(P, Q, pvo, qvo, iwq, nxt.k_len, 0, stage0);
-      first_stage_requested = true;
-    }
-    if (cur.state == 1) {
-      // ---- epilogue (see the kernel above): 32 rows at a time through this wavefront's patch of stage 1
-      // (the lane index as this part sees it: opaque, so that its address arithmetic is redone per tile instead of
-      // being held in registers across the K loops)
-      int elane = lane;
-      asm volatile("" : "+v"(elane));
-#pragma unroll
-      for (int b = 0; b < PB; b++) {
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-#pragma unroll
-          for (int v4 = 0; v4 < 4; v4++) {
-            const int q = (NQ == 2 ? 0 : 32 * a) + 8 * v4 + 4 * (elane >> 5);
-            float4 r = make_float4(acc[a][b][4 * v4], acc[a][b][4 * v4 + 1], acc[a][b][4 * v4 + 2], acc[a][b][4 * v4 + 3]);
-            *reinterpret_cast<float4*>(wlds + (NQ == 2 ? a * (32 * PITCH) : 0) + (elane & 31) * PITCH + q * 4) = r;
-          }
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront's own LDS writes are done
-        __builtin_amdgcn_wave_barrier();
-        constexpr int LPR = W / 4;          // lanes per row (4 q = 16 bytes of fp32 per elane)
-        constexpr int RPI = 64 / LPR;       // rows per instruction
-#pragma unroll
-        for (int it = 0; it < 32 / RPI; it++) {
-          const int r = it * RPI + elane / LPR;
-          const int q = (elane % LPR) * 4;
-          const int p = wp + 32 * b + r;
-          if (p < cur.p_valid && q_base + q < cur.q_valid) {
-            const size_t o = (size_t)cur.expert * A.f_expert_stride + (size_t)(cur.p_row0 + p) * A.c_ld + cur.q0_col + q_base + q;
-#pragma unroll
-            for (int n = 0; n < NQ; n++) {
-              float4 v = *reinterpret_cast<const float4*>(wlds + n * (32 * PITCH) + r * PITCH + q * 4);
-              float* dst = (n == 0 ? A.f0 : A.f1) + o;
-              if (A.accumulate) {
-                const float4 old = *reinterpret_cast<const float4*>(dst);
-                v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
-              }
-              *reinterpret_cast<float4*>(dst) = v;
-            }
-          }
-        }
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // the read-back is complete before the next 32 rows overwrite the patch
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    stores_behind_loads = first_stage_requested && cur.state == 1 && !A.accumulate && cur.p_valid == TILE && cur.q_valid == TQ;
-    __syncthreads();   // (the ticket slot may be rewritten)
-    cur = nxt;
-  }
-}
-
 // Row-tile schedule: one thread per expert.  sched[0] = number of row tiles; sched[1] = whether an expert's last tile
 // may be a tall one; sched[64 + u] = expert of tile u;
 // sched[64 + max_tiles + u] = index of that expert's first tile; sched[64 + 2 max_tiles + i] = expert with the i-th most rows.
@@ -1069,7 +841,6 @@ __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __r
   const int n = (e < Et) ? offsets[e + 1] - offsets[e] : 0;
   const int nt = row_tiles_of(n, tall);
   if (e == 0) sched[1] = tall;
-  if (e >= 16 && e < 48) sched[e] = 0;   // tile queues of the weight-gradient launches that follow
   scan[e] = nt;
   __syncthreads();
   for (int o = 1; o < kMaxExperts; o <<= 1) {
@@ -1112,22 +883,6 @@ static int launch_gemm(const char* label, const GemmArgs& A, long long max_block
   if (max_blocks <= 0) return MOE_OK;
   MOE_LAUNCH(label, st, kern, dim3((unsigned)grid), dim3(NTHREADS), 0, st, A);
   return MOE_OK;
-}
-
-// Weight gradients.  The generic kernel, one block per tile; or, where the tiles do not fill whole 8 x 4 super-tiles
-// (tiles along p not a multiple of 8 or along q not a multiple of 4: up to half of the generic kernel's blocks would
-// then be padding that starts, looks up its tile and ends), one persistent block per CU (256) that takes its
-// tiles from a queue per XCD, zeroed by the caller.
-template <int NQ>
-static int launch_wgrad(const char* label, const GemmArgs& A, hipStream_t st) {
-  if (A.Et <= 0 || A.n_p_tiles <= 0 || A.n_q_tiles <= 0) return MOE_OK;
-  const bool padded = (A.n_p_tiles % 8 != 0) || (A.n_q_tiles % 4 != 0);
-  // (not the router's launch, which adds the two halves in the epilogue and has 16 tiles per part: 18 -> 32 us this way)
-  if (!A.sum_halves && (MOE_WGRAD_PERSISTENT == 2 || (MOE_WGRAD_PERSISTENT == 1 && padded))) {
-    MOE_LAUNCH(label, st, wgrad_persistent_kernel<NQ>, dim3(kNumXcd * kCusPerXcd), dim3(NTHREADS), 0, st, A);
-    return MOE_OK;
-  }
-  return launch_gemm<1, true, true, NQ, 1, EPI_F32>(label, A, wgrad_blocks(A.Et, A.n_p_tiles, A.n_q_tiles), st);
 }
 
 static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_bytes, WsLayout* L) {
@@ -1240,19 +995,17 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
     MOE_TRY((launch_gemm<0, false, false, 1, 2, EPI_BF16>("ffn_bwd_dx", A, ub_tiles * A.n_q_tiles, st)));
   }
   // dWd[e] = H_e^T dY_e   (rows f, columns d)
-  A.p_dim = D.f; A.n_p_tiles = (D.f + TILE - 1) / TILE; A.q_dim = D.d; A.n_q_tiles = (D.d + TILE - 1) / TILE;
-  A.p0 = h; A.p1 = nullptr; A.p_ld = D.f;
-  A.q0 = dy_perm; A.q1 = nullptr; A.q_ld = D.d;
-  A.f0 = dw_down; A.f1 = nullptr; A.f_expert_stride = (size_t)D.f * D.d; A.c_ld = D.d;
-  A.queue = sched + 16;
-  MOE_TRY((launch_wgrad<1>("ffn_bwd_dw_down", A, st)));
+  WgradArgs W = {};
+  W.offsets = offsets; W.order = sched + 64 + 2 * max_tiles; W.zero_page = A.zero_page; W.Et = D.Et; W.accumulate = A.accumulate;
+  W.p0 = h; W.p_ld = D.f; W.p_dim = D.f;
+  W.q0 = dy_perm; W.q_ld = D.d; W.q_dim = D.d;
+  W.f0 = dw_down; W.f_expert_stride = (size_t)D.f * D.d; W.c_ld = D.d;
+  launch_wgrad("ffn_bwd_dw_down", st, W);
   // dWg[e], dWu[e] = X_e^T dG_e, X_e^T dU_e   (rows d, columns f)
-  A.p_dim = D.d; A.n_p_tiles = (D.d + TILE - 1) / TILE; A.q_dim = D.f; A.n_q_tiles = (D.f + 127) / 128;
-  A.p0 = x_perm; A.p_ld = D.d;
-  A.q0 = dg; A.q1 = du; A.q_ld = D.f;
-  A.f0 = dw_gate; A.f1 = dw_up; A.f_expert_stride = (size_t)D.d * D.f; A.c_ld = D.f;
-  A.queue = sched + 24;
-  MOE_TRY((launch_wgrad<2>("ffn_bwd_dw_gate_up", A, st)));
+  W.p0 = x_perm; W.p_ld = D.d; W.p_dim = D.d;
+  W.q0 = dg; W.q1 = du; W.q_ld = D.f; W.q_dim = D.f;
+  W.f0 = dw_gate; W.f1 = dw_up; W.c_ld = D.f;
+  launch_wgrad("ffn_bwd_dw_gate_up", st, W);
   return launch_status();
 }
 
@@ -1287,7 +1040,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   const int ldp = (int)round_up((size_t)D.E, 4);
   const int S = router_dw_parts(D);
   const int part_rows = (int)round_up((size_t)((D.T + S - 1) / S), 64);
-  launch_router_prepare(st, dlogits, w_router, dl_hi, dl_lo, skinny_dx ? w_t : nullptr, offs, sched + 64 + 2 * max_tiles, sched + 32, zero_page,
+  launch_router_prepare(st, dlogits, w_router, dl_hi, dl_lo, skinny_dx ? w_t : nullptr, offs, sched + 64 + 2 * max_tiles, zero_page,
                         (int)D.T, (int)D.E, Epad, Ek, (int)D.d, (int)S, part_rows);
   GemmArgs A = {};
   A.sched = sched; A.max_tiles = max_tiles; A.Et = 1; A.accumulate = 0;
@@ -1318,8 +1071,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   B.p0 = x; B.p_ld = D.d;
   B.q0 = dl_hi; B.q1 = dl_lo; B.q_ld = Epad;
   B.f0 = partial; B.f1 = nullptr; B.f_expert_stride = (size_t)D.d * ldp; B.c_ld = ldp; B.sum_halves = 1;
-  B.queue = sched + 32;
-  MOE_TRY((launch_wgrad<2>("router_bwd_dw", B, st)));
+  MOE_TRY((launch_gemm<1, true, true, 2, 1, EPI_F32>("router_bwd_dw", B, wgrad_blocks(B.Et, B.n_p_tiles, B.n_q_tiles), st)));
   launch_router_dw_reduce(st, partial, dw_router, (int)S, (int)D.E, (int)D.d, ldp, accumulate ? 1 : 0);
   return launch_status();
 }

@@ -409,6 +409,13 @@ def test_grouped_ffn_every_tile_height(moe, d, f, counts):
     assert not gwg[empty].any() and not gwd[empty].any()    # the empty expert
 
 
+@pytest.mark.parametrize("d,f", [(64, 64), (192, 320), (448, 128)])
+def test_weight_gradient_edges(moe, d, f):
+    """Row counts around the weight gradients' 32-row steps and their ring of three (0, 1, 2, 3, 4 steps, whole and
+    ragged), widths that leave half of a 128-row or 128-column piece of a tile empty."""
+    test_grouped_ffn_every_tile_height(moe, d, f, [1, 31, 32, 33, 64, 65, 0, 96, 97, 128, 129])
+
+
 # ---------------------------------------------------------------------------------------------------------
 # the whole layer, forward + backward, against the per-token definition
 # ---------------------------------------------------------------------------------------------------------
