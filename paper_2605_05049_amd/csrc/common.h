@@ -131,6 +131,22 @@ void launch_router_bwd_dx(hipStream_t st, const uint16_t* dl_hi, const uint16_t*
                           int E, int Epad);
 void launch_router_dw_reduce(hipStream_t st, const float* partial, float* dw, int S, int E, int d, int ldp, int accumulate);
 
+// Row-tile GEMMs of the expert FFNs in small problems (few_rows.hip).
+constexpr int kFewRows = 64, kFewCols = 64;   // rows and columns of a tile
+enum RowTileKind { ROWTILE_GATE_UP = 0, ROWTILE_DOWN = 1, ROWTILE_DH = 2, ROWTILE_DX = 3 };
+struct RowTileArgs {
+  const int32_t* sched;    // [0] = number of row tiles; [64 + u] = expert of tile u; [64 + max_tiles + u] = its first tile
+  int max_tiles;
+  const int32_t* offsets;  // [E'+1]
+  int n_q_tiles;           // filled by the launcher
+  int q_dim, k_dim;        // output columns; contraction length (per pass)
+  const uint16_t* p0; const uint16_t* p1; size_t p_ld;   // activations (p1: second pass of dX)
+  const uint16_t* q0; const uint16_t* q1; size_t q_ld; size_t q_expert_stride;   // weights (q1: W_up)
+  uint16_t* c0; uint16_t* c1; uint16_t* c2; size_t c_ld; // outputs: G, U, H / Y / dG, dU, H / dX
+  const uint16_t* g_in; const uint16_t* u_in;            // saved G, U (dH)
+};
+void launch_few_rows(const char* label, hipStream_t st, int kind, RowTileArgs A, long long row_tiles);
+
 // Weight gradients of the expert FFNs (wgrad.hip): f0[e] (and f1[e]) = p0_e^T q0_e (p0_e^T q1_e) over the rows of expert e.
 struct WgradArgs {
   const int32_t* offsets;      // [Et + 1]

@@ -256,12 +256,15 @@ __device__ __forceinline__ bf16x8 read_frag_at(unsigned off, int kk, unsigned ar
   }
 }
 
-// Row tiles of an expert with n rows.  Without tall tiles: ceil(n / 256).  With them, a remainder of at most 64 rows
-// does not get a tile of its own (which would stream the expert's whole weight panel once more for a handful of rows)
-// but rides on the last full tile, which then has up to 320 rows: max(1, ceil((n - 64) / 256)).
-__host__ __device__ __forceinline__ int row_tiles_of(int n, int tall) {
+// How a launch cuts an expert's n rows into row tiles.  TILES_PLAIN: ceil(n / 256).  TILES_TALL: a remainder of at most
+// 64 rows does not get a tile of its own (which would stream the expert's whole weight panel once more for a handful of
+// rows) but rides on the last full tile, which then has up to 320 rows: max(1, ceil((n - 64) / 256)).  TILES_FEW: the
+// tiles of the kernel for small problems.
+enum TileMode { TILES_PLAIN = 0, TILES_TALL = 1, TILES_FEW = 2 };
+__host__ __device__ __forceinline__ int row_tiles_of(int n, int mode) {
   if (n <= 0) return 0;
-  return tall ? max(1, (n - 64 + TILE - 1) / TILE) : (n + TILE - 1) / TILE;
+  if (mode == TILES_FEW) return (n + kFewRows - 1) / kFewRows;
+  return mode == TILES_TALL ? max(1, (n - 64 + TILE - 1) / TILE) : (n + TILE - 1) / TILE;
 }
 
 // KIND 0: row-tile problem (p = ragged rows of an expert, k = k_dim);  KIND 1: wgrad (k = ragged rows).
@@ -827,20 +830,20 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   else run(std::integral_constant<int, 1>{});
 }
 
-// Row-tile schedule: one thread per expert.  sched[0] = number of row tiles; sched[1] = whether an expert's last tile
-// may be a tall one; sched[64 + u] = expert of tile u;
+// Row-tile schedule: one thread per expert.  sched[0] = number of row tiles; sched[1] = how experts are cut into
+// row tiles (TileMode); sched[64 + u] = expert of tile u;
 // sched[64 + max_tiles + u] = index of that expert's first tile; sched[64 + 2 max_tiles + i] = expert with the i-th most rows.
 // Also clears the zero page and the split-tile counters.
 __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
                                                               uint32_t* __restrict__ zero_page, int32_t* __restrict__ counters,
-                                                              int Et, int max_tiles, int tall) {
+                                                              int Et, int max_tiles, int mode) {
   __shared__ int32_t scan[kMaxExperts];
   const int e = threadIdx.x;
   if (e < 64) zero_page[e] = 0u;
   if (e < kSplitCounters) counters[e] = 0;
   const int n = (e < Et) ? offsets[e + 1] - offsets[e] : 0;
-  const int nt = row_tiles_of(n, tall);
-  if (e == 0) sched[1] = tall;
+  const int nt = row_tiles_of(n, mode);
+  if (e == 0) sched[1] = mode;
   scan[e] = nt;
   __syncthreads();
   for (int o = 1; o < kMaxExperts; o <<= 1) {
@@ -897,6 +900,109 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 
 #define MOE_TRY(call) do { int rc_ = (call); if (rc_ != MOE_OK) return rc_; } while (0)
 
+// Which kernel the row-tile GEMMs of a call run on.  Both take every size; the counts are on the device, so the rule goes by
+// their upper bound.  few_rows.hip, whose 64 x 64 tiles make 16 times as many blocks and share a tile's k range among the
+// wavefronts of a block, while its tiles (of d_ffn columns) are at most about what the chip runs in two or three rounds;
+// beyond, its 2.7 times the operand bytes per multiply cost more than the idle CUs of the 256-row tiles.  The four GEMMs of
+// one call, us, few_rows.hip against the 256-row tiles, by its number of tiles (E = 8 .. 66, uniform random counts):
+//   d x f = 512 x 1024:   160: 41 / 64   256: 45 / 88   640: 69 / 135   1152: 101 / 137
+//   1024 x 2048:          512: 76 / 115   1280: 153 / 192        2048 x 1408:  704: 164 / 194   1056: 207 / 234   1760: 334 / 270
+//   1088 x 1984:          868: 121 / 132   2170: 241 / 241   4340: 420 / 324     4096 x 14336:  2240: 1063 / 1034
+constexpr long long kFewMaxTiles = 1280;
+static TileMode tile_mode(const Dims& D) {
+  return (D.N / kFewRows + D.Et) * (D.f / kFewCols) <= kFewMaxTiles ? TILES_FEW : TILES_TALL;
+}
+
+// The row-tile GEMMs of one call of the expert FFN.
+struct RowGemms {
+  const Dims& D;
+  const WsLayout& L;
+  char* ws;
+  hipStream_t st;
+  const int32_t* offsets;
+  TileMode mode;
+  int max_tiles;
+  int32_t* sched;
+  uint32_t* zero_page;
+  int32_t* counters;
+
+  RowGemms(const Dims& D_, const WsLayout& L_, void* ws_, hipStream_t st_, const int32_t* offsets_)
+      : D(D_), L(L_), ws(static_cast<char*>(ws_)), st(st_), offsets(offsets_),
+        mode(tile_mode(D_)), max_tiles((int)sched_max_tiles(D_)),
+        sched(reinterpret_cast<int32_t*>(ws + L_.sched)), zero_page(reinterpret_cast<uint32_t*>(ws + L_.zero_page)),
+        counters(reinterpret_cast<int32_t*>(ws + L_.splitk_counters)) {}
+
+  uint16_t* rows_f(size_t region) const { return reinterpret_cast<uint16_t*>(ws + region); }   // a bf16 [N, f] region of the workspace
+
+  void schedule() const {
+    MOE_LAUNCH("ffn_schedule", st, build_schedule_kernel, dim3(1), dim3(1024), 0, st, offsets, sched, zero_page, counters, D.Et, max_tiles, mode);
+  }
+
+  int launch(const char* label, int kind, RowTileArgs R) const {
+    R.sched = sched; R.max_tiles = max_tiles; R.offsets = offsets;
+    R.q_expert_stride = (size_t)D.d * D.f;
+    if (mode == TILES_FEW) {
+      launch_few_rows(label, st, kind, R, D.N / kFewRows + D.Et);   // sum_e ceil(n_e / 64) <= N / 64 + E'
+      return MOE_OK;
+    }
+    GemmArgs A = {};
+    A.sched = sched; A.max_tiles = max_tiles; A.offsets = offsets; A.Et = D.Et;
+    A.zero_page = reinterpret_cast<const uint16_t*>(zero_page);
+    A.partial = reinterpret_cast<float*>(ws + L.splitk_partial); A.counters = counters;
+    A.q_dim = R.q_dim; A.k_dim = R.k_dim;
+    A.p0 = R.p0; A.p1 = R.p1; A.p_ld = R.p_ld;
+    A.q0 = R.q0; A.q1 = R.q1; A.q_ld = R.q_ld; A.q_expert_stride = R.q_expert_stride;
+    A.c0 = R.c0; A.c1 = R.c1; A.c2 = R.c2; A.c_ld = R.c_ld; A.g_in = R.g_in; A.u_in = R.u_in;
+    const int tq = kind == ROWTILE_GATE_UP ? TILE / 2 : TILE;
+    A.n_q_tiles = (A.q_dim + tq - 1) / tq;
+    const long long blocks = (D.N / TILE + D.Et) * A.n_q_tiles;   // sum_e ceil(n_e / 256) <= N / 256 + E'
+    switch (kind) {
+      case ROWTILE_GATE_UP: return launch_gemm<0, false, true, 2, 1, EPI_SWIGLU>(label, A, blocks, st);
+      case ROWTILE_DOWN: return launch_gemm<0, false, true, 1, 1, EPI_BF16>(label, A, blocks, st);
+      case ROWTILE_DH: return launch_gemm<0, false, false, 1, 1, EPI_DSWIGLU>(label, A, blocks, st);
+      default: return launch_gemm<0, false, false, 1, 2, EPI_BF16>(label, A, blocks, st);
+    }
+  }
+
+  // G, U = X Wg, X Wu ; H = silu(G) * U
+  int gate_up(const char* label, const uint16_t* x, const uint16_t* w_gate, const uint16_t* w_up, uint16_t* g, uint16_t* u, uint16_t* h) const {
+    RowTileArgs R = {};
+    R.q_dim = D.f; R.k_dim = D.d;
+    R.p0 = x; R.p_ld = D.d;
+    R.q0 = w_gate; R.q1 = w_up; R.q_ld = D.f;
+    R.c0 = g; R.c1 = u; R.c2 = h; R.c_ld = D.f;
+    return launch(label, ROWTILE_GATE_UP, R);
+  }
+  // Y = H Wd
+  int down(const char* label, const uint16_t* h, const uint16_t* w_down, uint16_t* y) const {
+    RowTileArgs R = {};
+    R.q_dim = D.d; R.k_dim = D.f;
+    R.p0 = h; R.p_ld = D.f;
+    R.q0 = w_down; R.q_ld = D.d;
+    R.c0 = y; R.c_ld = D.d;
+    return launch(label, ROWTILE_DOWN, R);
+  }
+  // dH = dY Wd^T, then dG, dU and H from the saved G, U
+  int dh(const char* label, const uint16_t* dy, const uint16_t* w_down, const uint16_t* g, const uint16_t* u, uint16_t* dg, uint16_t* du,
+         uint16_t* h) const {
+    RowTileArgs R = {};
+    R.q_dim = D.f; R.k_dim = D.d;
+    R.p0 = dy; R.p_ld = D.d;
+    R.q0 = w_down; R.q_ld = D.d;
+    R.c0 = dg; R.c1 = du; R.c2 = h; R.c_ld = D.f; R.g_in = g; R.u_in = u;
+    return launch(label, ROWTILE_DH, R);
+  }
+  // dX = dG Wg^T + dU Wu^T
+  int dx(const char* label, const uint16_t* dg, const uint16_t* du, const uint16_t* w_gate, const uint16_t* w_up, uint16_t* dx_perm) const {
+    RowTileArgs R = {};
+    R.q_dim = D.d; R.k_dim = D.f;
+    R.p0 = dg; R.p1 = du; R.p_ld = D.f;
+    R.q0 = w_gate; R.q1 = w_up; R.q_ld = D.f;
+    R.c0 = dx_perm; R.c_ld = D.d;
+    return launch(label, ROWTILE_DX, R);
+  }
+};
+
 }  // namespace moe
 
 extern "C" int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_perm, const int32_t* offsets,
@@ -914,36 +1020,14 @@ extern "C" int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_per
   MOE_REQUIRE_ALIGNED(x_perm); MOE_REQUIRE_ALIGNED(offsets); MOE_REQUIRE_ALIGNED(w_gate); MOE_REQUIRE_ALIGNED(w_up);
   MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(y_perm); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   if (D.N == 0) return MOE_OK;
-  hipStream_t st = (hipStream_t)stream;
-  char* wsb = static_cast<char*>(ws);
+  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets);
   if (save_g == nullptr) {  // checkpointed forward: G and U go to the workspace and are not kept
-    save_g = reinterpret_cast<uint16_t*>(wsb + L.g_re);
-    save_u = reinterpret_cast<uint16_t*>(wsb + L.u_re);
+    save_g = G.rows_f(L.g_re);
+    save_u = G.rows_f(L.u_re);
   }
-  int32_t* sched = reinterpret_cast<int32_t*>(wsb + L.sched);
-  uint32_t* zero_page = reinterpret_cast<uint32_t*>(wsb + L.zero_page);
-  int32_t* counters = reinterpret_cast<int32_t*>(wsb + L.splitk_counters);
-  uint16_t* h = reinterpret_cast<uint16_t*>(wsb + L.h);
-  const int max_tiles = (int)sched_max_tiles(D);
-  const long long ub_tiles = D.N / TILE + D.Et;  // sum_e ceil(n_e/256) <= N/256 + E'
-  MOE_LAUNCH("ffn_schedule", st, build_schedule_kernel, dim3(1), dim3(1024), 0, st, offsets, sched, zero_page, counters, D.Et, max_tiles, 1);
-
-  GemmArgs A = {};
-  A.sched = sched; A.max_tiles = max_tiles; A.offsets = offsets; A.Et = D.Et;
-  A.zero_page = reinterpret_cast<const uint16_t*>(zero_page);
-  A.partial = reinterpret_cast<float*>(wsb + L.splitk_partial); A.counters = counters;
-  // G, U = X Wg, X Wu ; H = silu(G) * U
-  A.n_q_tiles = (D.f + 127) / 128; A.q_dim = D.f; A.k_dim = D.d;
-  A.p0 = x_perm; A.p_ld = D.d;
-  A.q0 = w_gate; A.q1 = w_up; A.q_ld = D.f; A.q_expert_stride = (size_t)D.d * D.f;
-  A.c0 = save_g; A.c1 = save_u; A.c2 = h; A.c_ld = D.f;
-  MOE_TRY((launch_gemm<0, false, true, 2, 1, EPI_SWIGLU>("ffn_fwd_gate_up_swiglu", A, ub_tiles * A.n_q_tiles, st)));
-  // Y = H Wd
-  A.n_q_tiles = (D.d + TILE - 1) / TILE; A.q_dim = D.d; A.k_dim = D.f;
-  A.p0 = h; A.p_ld = D.f;
-  A.q0 = w_down; A.q1 = nullptr; A.q_ld = D.d; A.q_expert_stride = (size_t)D.f * D.d;
-  A.c0 = y_perm; A.c1 = nullptr; A.c2 = nullptr; A.c_ld = D.d;
-  MOE_TRY((launch_gemm<0, false, true, 1, 1, EPI_BF16>("ffn_fwd_down", A, ub_tiles * A.n_q_tiles, st)));
+  G.schedule();
+  MOE_TRY(G.gate_up("ffn_fwd_gate_up_swiglu", x_perm, w_gate, w_up, save_g, save_u, G.rows_f(L.h)));
+  MOE_TRY(G.down("ffn_fwd_down", G.rows_f(L.h), w_down, y_perm));
   return launch_status();
 }
 
@@ -964,39 +1048,19 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   MOE_REQUIRE_ALIGNED(w_up); MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   MOE_REQUIRE_ALIGNED(dx_perm); MOE_REQUIRE_ALIGNED(dw_gate); MOE_REQUIRE_ALIGNED(dw_up); MOE_REQUIRE_ALIGNED(dw_down);
   hipStream_t st = (hipStream_t)stream;
-  char* wsb = static_cast<char*>(ws);
-  int32_t* sched = reinterpret_cast<int32_t*>(wsb + L.sched);
-  uint32_t* zero_page = reinterpret_cast<uint32_t*>(wsb + L.zero_page);
-  int32_t* counters = reinterpret_cast<int32_t*>(wsb + L.splitk_counters);
-  uint16_t* h = reinterpret_cast<uint16_t*>(wsb + L.h);
-  uint16_t* dg = reinterpret_cast<uint16_t*>(wsb + L.dg);
-  uint16_t* du = reinterpret_cast<uint16_t*>(wsb + L.du);
-  const int max_tiles = (int)sched_max_tiles(D);
-  const long long ub_tiles = D.N / TILE + D.Et;
-
-  GemmArgs A = {};
-  A.sched = sched; A.max_tiles = max_tiles; A.offsets = offsets; A.Et = D.Et; A.accumulate = accumulate ? 1 : 0;
-  A.zero_page = reinterpret_cast<const uint16_t*>(zero_page);
-  A.partial = reinterpret_cast<float*>(wsb + L.splitk_partial); A.counters = counters;
-  // (also with no rows at all: the weight gradients read the expert order from the schedule)
-  MOE_LAUNCH("ffn_schedule", st, build_schedule_kernel, dim3(1), dim3(1024), 0, st, offsets, sched, zero_page, counters, D.Et, max_tiles, 1);
+  const RowGemms G(D, L, ws, st, offsets);
+  uint16_t* const h = G.rows_f(L.h);
+  uint16_t* const dg = G.rows_f(L.dg);
+  uint16_t* const du = G.rows_f(L.du);
+  G.schedule();   // (also with no rows at all: the weight gradients read the expert order from the schedule)
   if (D.N > 0) {
-    // dH = dY Wd^T, then dG, dU and H from the saved G, U
-    A.n_q_tiles = (D.f + TILE - 1) / TILE; A.q_dim = D.f; A.k_dim = D.d;
-    A.p0 = dy_perm; A.p_ld = D.d;
-    A.q0 = w_down; A.q_ld = D.d; A.q_expert_stride = (size_t)D.f * D.d;
-    A.c0 = dg; A.c1 = du; A.c2 = h; A.c_ld = D.f; A.g_in = save_g; A.u_in = save_u;
-    MOE_TRY((launch_gemm<0, false, false, 1, 1, EPI_DSWIGLU>("ffn_bwd_dh_dswiglu", A, ub_tiles * A.n_q_tiles, st)));
-    // dX = dG Wg^T + dU Wu^T
-    A.n_q_tiles = (D.d + TILE - 1) / TILE; A.q_dim = D.d; A.k_dim = D.f;
-    A.p0 = dg; A.p1 = du; A.p_ld = D.f;
-    A.q0 = w_gate; A.q1 = w_up; A.q_ld = D.f; A.q_expert_stride = (size_t)D.d * D.f;
-    A.c0 = dx_perm; A.c1 = nullptr; A.c2 = nullptr; A.c_ld = D.d;
-    MOE_TRY((launch_gemm<0, false, false, 1, 2, EPI_BF16>("ffn_bwd_dx", A, ub_tiles * A.n_q_tiles, st)));
+    MOE_TRY(G.dh("ffn_bwd_dh_dswiglu", dy_perm, w_down, save_g, save_u, dg, du, h));
+    MOE_TRY(G.dx("ffn_bwd_dx", dg, du, w_gate, w_up, dx_perm));
   }
   // dWd[e] = H_e^T dY_e   (rows f, columns d)
   WgradArgs W = {};
-  W.offsets = offsets; W.order = sched + 64 + 2 * max_tiles; W.zero_page = A.zero_page; W.Et = D.Et; W.accumulate = A.accumulate;
+  W.offsets = offsets; W.order = G.sched + 64 + 2 * G.max_tiles; W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
+  W.Et = D.Et; W.accumulate = accumulate ? 1 : 0;
   W.p0 = h; W.p_ld = D.f; W.p_dim = D.f;
   W.q0 = dy_perm; W.q_ld = D.d; W.q_dim = D.d;
   W.f0 = dw_down; W.f_expert_stride = (size_t)D.f * D.d; W.c_ld = D.d;
@@ -1051,7 +1115,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   } else {
     // dx_router[T,d] = dlogits W_r on the grouped GEMM kernel: rows = tokens, columns = d, K = E in two passes (head,
     // remainder of dlogits); P K-contiguous in the padded copies, Q = W_r read with k = expert row (R-contiguous)
-    MOE_LAUNCH("router_schedule", st, build_schedule_kernel, dim3(1), dim3(1024), 0, st, offs, sched, zero_page, counters, 1, max_tiles, 0);
+    MOE_LAUNCH("router_schedule", st, build_schedule_kernel, dim3(1), dim3(1024), 0, st, offs, sched, zero_page, counters, 1, max_tiles, TILES_PLAIN);
     A.offsets = offs;
     A.n_q_tiles = (D.d + TILE - 1) / TILE; A.q_dim = D.d; A.k_dim = D.E;
     A.p0 = dl_hi; A.p1 = dl_lo; A.p_ld = Epad;
@@ -1091,28 +1155,14 @@ extern "C" int moe_grouped_ffn_bwd_recompute(const moe_shape* shape, const uint1
   MOE_REQUIRE_ALIGNED(dy_perm); MOE_REQUIRE_ALIGNED(x_perm); MOE_REQUIRE_ALIGNED(offsets); MOE_REQUIRE_ALIGNED(w_gate);
   MOE_REQUIRE_ALIGNED(w_up); MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(dx_perm); MOE_REQUIRE_ALIGNED(dw_gate);
   MOE_REQUIRE_ALIGNED(dw_up); MOE_REQUIRE_ALIGNED(dw_down);
-  char* wsb = static_cast<char*>(ws);
-  uint16_t* g_re = reinterpret_cast<uint16_t*>(wsb + L.g_re);
-  uint16_t* u_re = reinterpret_cast<uint16_t*>(wsb + L.u_re);
+  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets);
+  uint16_t* const g_re = G.rows_f(L.g_re);
+  uint16_t* const u_re = G.rows_f(L.u_re);
   if (D.N > 0) {
     // G, U = X Wg, X Wu once more (the same kernel as in forward, hence the same bits); its H output is overwritten
     // by the backward's own
-    hipStream_t st = (hipStream_t)stream;
-    int32_t* sched = reinterpret_cast<int32_t*>(wsb + L.sched);
-    uint32_t* zero_page = reinterpret_cast<uint32_t*>(wsb + L.zero_page);
-    int32_t* counters = reinterpret_cast<int32_t*>(wsb + L.splitk_counters);
-    const int max_tiles = (int)sched_max_tiles(D);
-    const long long ub_tiles = D.N / TILE + D.Et;
-    MOE_LAUNCH("ffn_schedule", st, build_schedule_kernel, dim3(1), dim3(1024), 0, st, offsets, sched, zero_page, counters, D.Et, max_tiles, 1);
-    GemmArgs A = {};
-    A.sched = sched; A.max_tiles = max_tiles; A.offsets = offsets; A.Et = D.Et;
-    A.zero_page = reinterpret_cast<const uint16_t*>(zero_page);
-    A.partial = reinterpret_cast<float*>(wsb + L.splitk_partial); A.counters = counters;
-    A.n_q_tiles = (D.f + 127) / 128; A.q_dim = D.f; A.k_dim = D.d;
-    A.p0 = x_perm; A.p_ld = D.d;
-    A.q0 = w_gate; A.q1 = w_up; A.q_ld = D.f; A.q_expert_stride = (size_t)D.d * D.f;
-    A.c0 = g_re; A.c1 = u_re; A.c2 = reinterpret_cast<uint16_t*>(wsb + L.h); A.c_ld = D.f;
-    MOE_TRY((launch_gemm<0, false, true, 2, 1, EPI_SWIGLU>("ffn_bwd_recompute_gate_up", A, ub_tiles * A.n_q_tiles, st)));
+    G.schedule();
+    MOE_TRY(G.gate_up("ffn_bwd_recompute_gate_up", x_perm, w_gate, w_up, g_re, u_re, G.rows_f(L.h)));
   }
   return moe_grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, g_re, u_re, dx_perm, dw_gate, dw_up, dw_down,
                              accumulate, ws, ws_bytes, stream);
