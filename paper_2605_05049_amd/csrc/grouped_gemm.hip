@@ -834,41 +834,51 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 // row tiles (TileMode); sched[64 + u] = expert of tile u;
 // sched[64 + max_tiles + u] = index of that expert's first tile; sched[64 + 2 max_tiles + i] = expert with the i-th most rows.
 // Also clears the zero page and the split-tile counters.
+// (A launch in front of every FFN call: bound by latency.  As many wavefronts as the experts need, prefix sums by lane
+// shuffles, two barriers: 3.7 -> 2.6 us at E' = 8, 5.4 -> 3.6 us at 66 against 1024 threads and a scan in LDS.)
 __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
                                                               uint32_t* __restrict__ zero_page, int32_t* __restrict__ counters,
                                                               int Et, int max_tiles, int mode) {
-  __shared__ int32_t scan[kMaxExperts];
-  const int e = threadIdx.x;
-  if (e < 64) zero_page[e] = 0u;
-  if (e < kSplitCounters) counters[e] = 0;
-  const int n = (e < Et) ? offsets[e + 1] - offsets[e] : 0;
-  const int nt = row_tiles_of(n, mode);
-  if (e == 0) sched[1] = mode;
-  scan[e] = nt;
-  __syncthreads();
-  for (int o = 1; o < kMaxExperts; o <<= 1) {
-    int v = (e >= o) ? scan[e - o] : 0;
-    __syncthreads();
-    scan[e] += v;
-    __syncthreads();
-  }
-  const int first = scan[e] - nt;
-  if (e == kMaxExperts - 1) sched[0] = scan[e];
-  // experts by descending row count (ties: lower id first): sched[64 + 2 max_tiles + rank] = expert
   __shared__ int32_t rows_of[kMaxExperts];
-  rows_of[e] = (e < Et) ? n : -1;
-  __syncthreads();
-  if (e < Et) {
-    int rank = 0;
-    for (int o = 0; o < Et; o++) rank += (rows_of[o] > n) || (rows_of[o] == n && o < e);
-    sched[64 + 2 * max_tiles + rank] = e;
+  __shared__ int32_t wave_total[kMaxExperts / kWave];
+  const int e = threadIdx.x, lane = e % kWave, wv = e / kWave;
+  const int n = (e < Et) ? offsets[e + 1] - offsets[e] : 0;
+  if (e < 64) zero_page[e] = 0u;
+  for (int i = e; i < kSplitCounters; i += blockDim.x) counters[i] = 0;
+  const int nt = row_tiles_of(n, mode);
+  rows_of[e] = n;
+  int incl = nt;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int up = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += up;
   }
+  if (lane == kWave - 1) wave_total[wv] = incl;
+  __syncthreads();
+  for (int w = 0; w < wv; w++) incl += wave_total[w];
+  const int first = incl - nt;
+  if (e == 0) sched[1] = mode;
+  if (e == (int)blockDim.x - 1) sched[0] = incl;
+  if (e >= Et) return;
+  // experts by descending row count (ties: lower id first): sched[64 + 2 max_tiles + rank] = expert
+  int rank = 0;
+#pragma unroll 8
+  for (int o = 0; o < Et; o++) {
+    const int r = rows_of[o];
+    rank += (r > n) || (r == n && o < e);
+  }
+  sched[64 + 2 * max_tiles + rank] = e;
   for (int i = 0; i < nt; i++) {
     if (first + i < max_tiles) {
       sched[64 + first + i] = e;
       sched[64 + max_tiles + first + i] = first;
     }
   }
+}
+static void launch_schedule(const char* label, hipStream_t st, const int32_t* offsets, int32_t* sched, uint32_t* zero_page, int32_t* counters,
+                            int Et, int max_tiles, int mode) {
+  const dim3 block((unsigned)round_up((size_t)Et, kWave));   // (Et <= kMaxExperts = 1024)
+  MOE_LAUNCH(label, st, build_schedule_kernel, dim3(1), block, 0, st, offsets, sched, zero_page, counters, Et, max_tiles, mode);
 }
 
 // Blocks of a weight-gradient launch: whole rounds of one 32-tile super-tile per XCD.
@@ -935,7 +945,7 @@ struct RowGemms {
   uint16_t* rows_f(size_t region) const { return reinterpret_cast<uint16_t*>(ws + region); }   // a bf16 [N, f] region of the workspace
 
   void schedule() const {
-    MOE_LAUNCH("ffn_schedule", st, build_schedule_kernel, dim3(1), dim3(1024), 0, st, offsets, sched, zero_page, counters, D.Et, max_tiles, mode);
+    launch_schedule("ffn_schedule", st, offsets, sched, zero_page, counters, D.Et, max_tiles, mode);
   }
 
   int launch(const char* label, int kind, RowTileArgs R) const {
@@ -1085,6 +1095,10 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   MOE_REQUIRE_ALIGNED(dw_router);
   if (D.T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;
+  if (router_bwd_is_small(D.T, D.E)) {
+    launch_router_bwd_small(st, x, w_router, dlogits, dx_router, dw_router, D.T, D.E, D.d, accumulate ? 1 : 0);
+    return launch_status();
+  }
   char* wsb = static_cast<char*>(ws);
   int32_t* sched = reinterpret_cast<int32_t*>(wsb + L.sched);
   uint32_t* zero_page = reinterpret_cast<uint32_t*>(wsb + L.zero_page);
@@ -1115,7 +1129,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   } else {
     // dx_router[T,d] = dlogits W_r on the grouped GEMM kernel: rows = tokens, columns = d, K = E in two passes (head,
     // remainder of dlogits); P K-contiguous in the padded copies, Q = W_r read with k = expert row (R-contiguous)
-    MOE_LAUNCH("router_schedule", st, build_schedule_kernel, dim3(1), dim3(1024), 0, st, offs, sched, zero_page, counters, 1, max_tiles, TILES_PLAIN);
+    launch_schedule("router_schedule", st, offs, sched, zero_page, counters, 1, max_tiles, TILES_PLAIN);
     A.offsets = offs;
     A.n_q_tiles = (D.d + TILE - 1) / TILE; A.q_dim = D.d; A.k_dim = D.E;
     A.p0 = dl_hi; A.p1 = dl_lo; A.p_ld = Epad;

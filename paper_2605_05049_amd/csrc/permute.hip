@@ -2,7 +2,7 @@
 // a deterministic stable counting sort of the T*K' slots by expert id, the row gather it defines, the weighted
 // combine that undoes it, and the derivatives of both.
 //
-// Counting sort = three launches, no atomics (so the order never depends on scheduling):
+// Counting sort = three launches (two for few slots), no atomics (so the order never depends on scheduling):
 //   1. rank    : each block ranks 1024 consecutive slots among the same-expert slots of the block
 //                (wave ballots give the rank inside 64 slots, an LDS table chains the 16 sub-groups) and
 //                emits its expert histogram;
@@ -144,6 +144,77 @@ __global__ __launch_bounds__(1024) void perm_scan_kernel(int32_t* __restrict__ b
         run += c[j];
       }
     }
+  }
+}
+
+// 1 + 2 in one launch for few slots: one block of 16 wavefronts ranks all of them (sub-groups of 64 slots as above, the
+// expert's counts of all sub-groups chained in LDS).  The base of a slot's rank is then its expert's offset whatever its
+// block of 1024, and that is what block_base holds for each of them.  Two launches of 3 .. 8 us each are latency only.
+constexpr int kSmallPermSlots = 4096, kSmallPermTable = 16384;   // limits: slots, entries of the table (32 KB)
+__global__ __launch_bounds__(1024) void perm_small_kernel(const int32_t* __restrict__ topk_idx, int32_t* __restrict__ lrank,
+                                                          int32_t* __restrict__ block_base, int32_t* __restrict__ counts,
+                                                          int32_t* __restrict__ offsets, int N, int Et, int nbits) {
+  extern __shared__ uint16_t sub_hist[];   // [ceil(N / 64)][Et]: count, then exclusive prefix over the sub-groups
+  __shared__ int32_t wave_total[1024 / kWave];
+  constexpr int R = kSmallPermSlots / 1024;   // sub-groups per wavefront
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int nsub = (N + kWave - 1) / kWave;
+  for (int i = tid; i < nsub * Et; i += 1024) sub_hist[i] = 0;
+  int key[R], rank_in_sub[R];
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    const int s = (r * 16 + wave) * kWave + lane;
+    key[r] = s < N ? clamp_expert(topk_idx[s], Et) : 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    const int sub = r * 16 + wave;
+    if (sub >= nsub) break;
+    const bool valid = sub * kWave + lane < N;
+    unsigned long long peers = __ballot(valid);
+    for (int b = 0; b < nbits; b++) {
+      const bool bit = (key[r] >> b) & 1;
+      const unsigned long long bal = __ballot(bit);
+      peers &= bit ? bal : ~bal;
+    }
+    const unsigned long long lower = peers & ((1ull << lane) - 1ull);
+    rank_in_sub[r] = __popcll(lower);
+    if (valid && lower == 0) sub_hist[sub * Et + key[r]] = (uint16_t)__popcll(peers);
+  }
+  __syncthreads();
+  int total = 0;
+  if (tid < Et) {
+    for (int s0 = 0; s0 < nsub; s0 += 8) {   // 8 entries in flight
+      int c[8];
+#pragma unroll
+      for (int j = 0; j < 8; j++) c[j] = s0 + j < nsub ? sub_hist[(s0 + j) * Et + tid] : 0;
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        if (s0 + j < nsub) sub_hist[(s0 + j) * Et + tid] = (uint16_t)total;
+        total += c[j];
+      }
+    }
+  }
+  int incl = total;   // inclusive scan over the experts: lane shuffles, then the wavefronts' totals
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int up = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += up;
+  }
+  if (lane == kWave - 1) wave_total[wave] = incl;
+  __syncthreads();
+  for (int w = 0; w < wave; w++) incl += wave_total[w];
+  if (tid < Et) {
+    counts[tid] = total;
+    offsets[tid] = incl - total;
+    if (tid == Et - 1) offsets[Et] = incl;
+    for (int b = 0; b * kPermSlotsPerBlock < N; b++) block_base[b * Et + tid] = incl - total;
+  }
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    const int sub = r * 16 + wave, s = sub * kWave + lane;
+    if (s < N) lrank[s] = sub_hist[sub * Et + key[r]] + rank_in_sub[r];
   }
 }
 
@@ -447,12 +518,17 @@ static int permute_launch(const Dims& D, const uint16_t* x, const int32_t* topk_
   const int nblk = perm_num_blocks(D.N);
   int nbits = 0;
   while ((1 << nbits) < D.Et) nbits++;
-  if (nblk > 0) {
-    MOE_LAUNCH("perm_rank", st, perm_rank_kernel, dim3(nblk), dim3(256), (size_t)kSub * D.Et * sizeof(uint16_t), st, topk_idx, lrank,
-                       block_hist, (int)D.N, D.Et, nbits);
+  if (D.N > 0 && D.N <= kSmallPermSlots && (D.N + kWave - 1) / kWave * D.Et <= kSmallPermTable) {
+    MOE_LAUNCH("perm_rank_scan", st, perm_small_kernel, dim3(1), dim3(1024), (size_t)((D.N + kWave - 1) / kWave) * D.Et * sizeof(uint16_t), st,
+               topk_idx, lrank, block_hist, counts, offsets, (int)D.N, D.Et, nbits);
+  } else {
+    if (nblk > 0) {
+      MOE_LAUNCH("perm_rank", st, perm_rank_kernel, dim3(nblk), dim3(256), (size_t)kSub * D.Et * sizeof(uint16_t), st, topk_idx, lrank,
+                         block_hist, (int)D.N, D.Et, nbits);
+    }
+    // with no slots the scan still defines counts = 0 and offsets = 0
+    MOE_LAUNCH("perm_scan", st, perm_scan_kernel, dim3(1), dim3(1024), 0, st, block_hist, counts, offsets, nblk, D.Et);
   }
-  // with no slots the scan still defines counts = 0 and offsets = 0
-  MOE_LAUNCH("perm_scan", st, perm_scan_kernel, dim3(1), dim3(1024), 0, st, block_hist, counts, offsets, nblk, D.Et);
   if (D.T > 0) {
     const int parts = x ? row_parts(D.d / 8) : 1;
     MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("perm_scatter_gather", st, (perm_scatter_kernel<KP>), dim3(token_blocks(D.T, parts)), dim3(256), 0, st,

@@ -226,6 +226,14 @@ def test_permute_maps_rows_and_streams(moe, T, d, E, k, Es, kind):
                  O.unpermute_combine_scale(np.abs(y64), ros_ref, np.ones((T, Kp))), what="permute_bwd")
 
 
+# the one-launch counting sort: a slot, one sub-group of 64 and its neighbours, 1024-slot blocks, both sides of its limits
+# (4096 slots, 64 x 256 table entries)
+@pytest.mark.parametrize("T,E,k,Es", [(1, 1, 1, 0), (64, 3, 1, 0), (65, 7, 1, 0), (341, 9, 3, 0), (1025, 5, 1, 1), (4096, 256, 1, 0),
+                                      (4096, 257, 1, 0), (4097, 4, 1, 0), (100, 1000, 2, 1)])
+def test_permute_few_slots(moe, T, E, k, Es):
+    test_permute_maps_rows_and_streams(moe, T, 64, E, k, Es, "skewed")
+
+
 def test_permute_is_deterministic_over_100_runs(moe):
     """The order of equal keys never depends on scheduling: 100 runs of one larger shape (64 rank blocks, 128
     experts of which a fifth are empty and a tenth are hot), every output bit for bit the first run's and the oracle's."""

@@ -68,6 +68,15 @@ def test_router_forward_and_backward(moe, T, d, E):
     assert_close(host_f32(dxr), 0.5 * rdx, 0.5 * q_x, tol=TOL, what="dx_router (never accumulated)")
 
 
+# both sides of the one-launch backward's rule (1024 tokens with E <= 8, 512 with E <= 16) and of its pieces: tokens of 16 wavefronts times
+# 16 in flight, 4 per dx wavefront, 128 and 512 columns; few tokens whose experts the forward spreads over blocks
+@pytest.mark.parametrize("T,d,E", [(1, 64, 2), (255, 576, 8), (257, 128, 5), (1024, 64, 8), (1025, 64, 8), (512, 1088, 16),
+                                   (513, 192, 13), (3, 640, 9), (16, 2048, 64), (17, 128, 100), (300, 64, 17)])
+def test_router_few_tokens(moe, T, d, E):
+    test_router_forward_and_backward(moe, T, d, E)
+
+
+
 def test_permute_bwd_add(moe):
     sh = W.MoEShape(T=300, d_model=256, d_ffn=64, E=8, k=3)
     inp = W.random_layer_inputs(sh, seed=3)
