@@ -159,7 +159,8 @@ struct WgradArgs {
   const uint16_t* q0; const uint16_t* q1; size_t q_ld; int q_dim;
   float* f0; float* f1; size_t f_expert_stride; size_t c_ld;
   int Et, accumulate;
-  int n_p_tiles, n_q_tiles;    // filled by the launcher
+  long long rows;              // of all experts together
+  int n_p_tiles, n_q_tiles, band;   // filled by the launcher
 };
 void launch_wgrad(const char* label, hipStream_t st, WgradArgs A);
 

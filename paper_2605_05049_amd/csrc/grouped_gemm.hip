@@ -1070,7 +1070,7 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   // dWd[e] = H_e^T dY_e   (rows f, columns d)
   WgradArgs W = {};
   W.offsets = offsets; W.order = G.sched + 64 + 2 * G.max_tiles; W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
-  W.Et = D.Et; W.accumulate = accumulate ? 1 : 0;
+  W.Et = D.Et; W.accumulate = accumulate ? 1 : 0; W.rows = D.N;
   W.p0 = h; W.p_ld = D.f; W.p_dim = D.f;
   W.q0 = dy_perm; W.q_ld = D.d; W.q_dim = D.d;
   W.f0 = dw_down; W.f_expert_stride = (size_t)D.f * D.d; W.c_ld = D.d;

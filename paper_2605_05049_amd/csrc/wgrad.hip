@@ -32,8 +32,7 @@ constexpr int P_BYTES = WP * WK * 2;         // 8 KB
 constexpr int Q_BYTES = WQ * WK * 2;         // 16 KB
 constexpr int W_STAGE = P_BYTES + Q_BYTES;   // 24 KB
 constexpr int W_XCDS = 8;
-constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: 8 along p x 4 along q
-constexpr int W_BAND = 8;                    // p tiles of a band
+constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
 
 // Fragment (32 r-values x 16 k-values) of an operand staged as 1 KB blocks of 4 k-rows x 128 r-values, HALVES blocks per 4
 // k-rows: lane l gets r = r0 + l % 32, k = 8 (l / 32) .. +7.  `off` is the lane's offset (w_frag_offset), `area` constant.
@@ -64,7 +63,7 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  // ---- block id -> tile.  Chunks of 32 consecutive tiles (8 p x 4 q of one expert, which share panels) are dealt
+  // ---- block id -> tile.  Chunks of 32 consecutive tiles (A.band = 8 p x 4 q of one expert, which share panels) are dealt
   // round-robin to the XCDs, experts with the most rows first (the tail of the launch is then made of short tiles).
   const int within = blockIdx.x / W_XCDS, xcd = blockIdx.x % W_XCDS;
   const long long tiles_per_e = (long long)A.n_p_tiles * A.n_q_tiles;
@@ -74,9 +73,9 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
   if (lid >= total) return;
   const int expert = A.order[(int)(lid / tiles_per_e)];
   const int local = (int)(lid % tiles_per_e);
-  const int band = local / (W_BAND * A.n_q_tiles), in_band = local - band * W_BAND * A.n_q_tiles;
-  const int band_p = min(W_BAND, A.n_p_tiles - band * W_BAND);
-  const int pt = band * W_BAND + in_band % band_p, qt = in_band / band_p;
+  const int band = local / (A.band * A.n_q_tiles), in_band = local - band * A.band * A.n_q_tiles;
+  const int band_p = min(A.band, A.n_p_tiles - band * A.band);
+  const int pt = band * A.band + in_band % band_p, qt = in_band / band_p;
   const int e_lo = A.offsets[expert], k_len = A.offsets[expert + 1] - e_lo;
   if (k_len == 0 && A.accumulate) return;   // nothing to add
   const int p_row0 = pt * WP, p_valid = min(WP, A.p_dim - p_row0);
@@ -222,6 +221,10 @@ void launch_wgrad(const char* label, hipStream_t st, WgradArgs A) {
   const int tq = A.q1 ? WQ / 2 : WQ;
   A.n_p_tiles = (A.p_dim + WP - 1) / WP;
   A.n_q_tiles = (A.q_dim + tq - 1) / tq;
+  // 8 x 4 tiles read the fewest panels; the pair, whose tiles write only 512 bytes of a row, takes 4 x 8 where an expert's rows
+  // are few and the stores all that counts (4096 x 14336, 64 rows: 769 -> 716 us, 128: 735 -> 682; 4096 x 1024, 256 rows:
+  // 1013 -> 1057)
+  A.band = (A.q1 && A.rows <= 128ll * A.Et) ? 4 : 8;
   const long long total = (long long)A.Et * A.n_p_tiles * A.n_q_tiles;
   const long long rounds = ((total + W_CHUNK - 1) / W_CHUNK + W_XCDS - 1) / W_XCDS;
   const dim3 grid((unsigned)(rounds * W_XCDS * W_CHUNK)), block(WTHREADS);
