@@ -38,16 +38,14 @@ class Shape:
     def __init__(self, T, d_model, d_ffn, E, k, E_shared=0, renorm=1):
         self.T, self.d_model, self.d_ffn, self.E, self.k = int(T), int(d_model), int(d_ffn), int(E), int(k)
         self.E_shared, self.renorm = int(E_shared), int(renorm)
+        self.E_total, self.K_slots = self.E + self.E_shared, self.k + self.E_shared
+        self.N = self.T * self.K_slots
         self._c = _CShape(self.T, self.d_model, self.d_ffn, self.E, self.k, self.E_shared, self.renorm)
 
     @classmethod
     def of(cls, s) -> "Shape":
         """From any object with the same attribute names (e.g. a workloads.MoEShape)."""
         return s if isinstance(s, Shape) else cls(s.T, s.d_model, s.d_ffn, s.E, s.k, s.E_shared, s.renorm)
-
-    E_total = property(lambda self: self.E + self.E_shared)
-    K_slots = property(lambda self: self.k + self.E_shared)
-    N = property(lambda self: self.T * (self.k + self.E_shared))
 
 
 def library_path() -> str:
@@ -146,11 +144,26 @@ def profile_records():
 # marshalling helpers
 # ------------------------------------------------------------------------------------------------------------
 
+# torch is looked up once, not imported at the top (the build does without it) nor in every call: the dozen calls of a small
+# layer's step are bound by what happens here (256 tokens: 122 us of calls around 96 us of kernels)
+_torch_module = None
+
+
+def _torch():
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
 def _ptr(t, dtype=None, numel: Optional[int] = None, name: str = "tensor"):
-    """Device pointer of a contiguous CUDA(HIP) tensor, after checking dtype and element count."""
+    """Device pointer of a contiguous CUDA(HIP) tensor, after checking dtype (one, or a tuple of them) and element count."""
     if t is None:
         return None
-    import torch
+    if (t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype or (type(dtype) is tuple and t.dtype in dtype))
+            and (numel is None or t.numel() >= numel)):
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name}: expected a device tensor")
     if not t.is_contiguous():
@@ -165,9 +178,13 @@ def _ptr(t, dtype=None, numel: Optional[int] = None, name: str = "tensor"):
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch_module or _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # (the handle alone: no Stream object is made for it)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _check(fn: str, rc: int):
@@ -175,9 +192,15 @@ def _check(fn: str, rc: int):
         raise MoeError(fn, rc)
 
 
+_bf16 = None
+
+
 def _bf16_types():
-    import torch
-    return (torch.bfloat16, torch.int16, torch.uint16)
+    global _bf16
+    if _bf16 is None:
+        torch = _torch()
+        _bf16 = (torch.bfloat16, torch.int16, torch.uint16)
+    return _bf16
 
 
 # ------------------------------------------------------------------------------------------------------------
@@ -185,7 +208,7 @@ def _bf16_types():
 # ------------------------------------------------------------------------------------------------------------
 
 def moe_route_topk(shape, logits, topk_idx, topk_w, probs_save=None, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     rc = load_library().moe_route_topk(
         ctypes.byref(s._c), _ptr(logits, torch.float32, s.T * s.E, "logits"),
@@ -195,7 +218,7 @@ def moe_route_topk(shape, logits, topk_idx, topk_w, probs_save=None, stream=None
 
 
 def moe_route_topk_bwd(shape, dtopk_w, topk_idx, topk_w, probs_save, dlogits, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     rc = load_library().moe_route_topk_bwd(
         ctypes.byref(s._c), _ptr(dtopk_w, torch.float32, s.N, "dtopk_w"), _ptr(topk_idx, torch.int32, s.N, "topk_idx"),
@@ -205,7 +228,7 @@ def moe_route_topk_bwd(shape, dtopk_w, topk_idx, topk_w, probs_save, dlogits, st
 
 
 def moe_permute(shape, x, topk_idx, x_perm, counts, offsets, row_of_slot, slot_of_row, ws, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     rc = load_library().moe_permute(
@@ -218,7 +241,7 @@ def moe_permute(shape, x, topk_idx, x_perm, counts, offsets, row_of_slot, slot_o
 
 
 def moe_permute_noalloc(shape, x, topk_idx, x_perm, counts, offsets, row_of_slot, slot_of_row, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     rc = load_library().moe_permute_noalloc(
@@ -230,7 +253,7 @@ def moe_permute_noalloc(shape, x, topk_idx, x_perm, counts, offsets, row_of_slot
 
 
 def moe_permute_bwd(shape, dx_perm, row_of_slot, dx, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     rc = load_library().moe_permute_bwd(
@@ -240,7 +263,7 @@ def moe_permute_bwd(shape, dx_perm, row_of_slot, dx, stream=None):
 
 
 def moe_permute_bwd_add(shape, dx_perm, row_of_slot, dx_addend, dx, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     rc = load_library().moe_permute_bwd_add(
@@ -251,7 +274,7 @@ def moe_permute_bwd_add(shape, dx_perm, row_of_slot, dx_addend, dx, stream=None)
 
 
 def moe_router_fwd(shape, x, w_router, logits, ws, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     rc = load_library().moe_router_fwd(
@@ -262,7 +285,7 @@ def moe_router_fwd(shape, x, w_router, logits, ws, stream=None):
 
 
 def moe_router_bwd(shape, x, w_router, dlogits, dx_router, dw_router, accumulate, ws, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     rc = load_library().moe_router_bwd(
@@ -274,7 +297,7 @@ def moe_router_bwd(shape, x, w_router, dlogits, dx_router, dw_router, accumulate
 
 
 def moe_grouped_ffn_fwd(shape, x_perm, offsets, w_gate, w_up, w_down, y_perm, save_g, save_u, ws, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     nw = s.E_total * s.d_model * s.d_ffn
@@ -290,7 +313,7 @@ def moe_grouped_ffn_fwd(shape, x_perm, offsets, w_gate, w_up, w_down, y_perm, sa
 
 def moe_grouped_ffn_bwd_recompute(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, dx_perm, dw_gate, dw_up, dw_down,
                                   accumulate, ws, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     nw = s.E_total * s.d_model * s.d_ffn
@@ -306,7 +329,7 @@ def moe_grouped_ffn_bwd_recompute(shape, dy_perm, x_perm, offsets, w_gate, w_up,
 
 def moe_grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, save_g, save_u, dx_perm,
                         dw_gate, dw_up, dw_down, accumulate, ws, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     nw = s.E_total * s.d_model * s.d_ffn
@@ -321,7 +344,7 @@ def moe_grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, s
 
 
 def moe_unpermute_combine(shape, y_perm, row_of_slot, topk_w, out, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     rc = load_library().moe_unpermute_combine(
@@ -331,7 +354,7 @@ def moe_unpermute_combine(shape, y_perm, row_of_slot, topk_w, out, stream=None):
 
 
 def moe_unpermute_combine_bwd(shape, dout, y_perm, row_of_slot, topk_w, dy_perm, dtopk_w, stream=None):
-    import torch
+    torch = _torch_module or _torch()
     s = Shape.of(shape)
     bf = _bf16_types()
     rc = load_library().moe_unpermute_combine_bwd(
