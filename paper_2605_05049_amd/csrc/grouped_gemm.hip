@@ -918,9 +918,15 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 //   d x f = 512 x 1024:   160: 41 / 64   256: 45 / 88   640: 69 / 135   1152: 101 / 137
 //   1024 x 2048:          512: 76 / 115   1280: 153 / 192        2048 x 1408:  704: 164 / 194   1056: 207 / 234   1760: 334 / 270
 //   1088 x 1984:          868: 121 / 132   2170: 241 / 241   4340: 420 / 324     4096 x 14336:  2240: 1063 / 1034
-constexpr long long kFewMaxTiles = 1280;
-static TileMode tile_mode(const Dims& D) {
-  return (D.N / kFewRows + D.Et) * (D.f / kFewCols) <= kFewMaxTiles ? TILES_FEW : TILES_TALL;
+// The data gradients, whose weights it reads in whole lines along k, keep up with the 256-row tiles for longer while experts
+// have few rows (dH + dX, 2048 x 1408, E = 66: 1496 tiles, 2 rows: 180 / 185; 2904 tiles, 64 rows: 297 / 325; 7168 x 2048,
+// E = 32, Zipf, 1536 tiles: 561 / 607; 4096 x 14336, 16 rows, 2240 tiles: 507 / 522, 64 rows, 3584: 686 / 663; but 2048 x 1408,
+// E = 16, 256 rows, 1760 tiles: 169 / 154).
+constexpr long long kFewMaxTiles = 1280, kFewMaxTilesBwd = 3000, kFewMaxRowsBwd = 128;
+static TileMode tile_mode(const Dims& D, bool backward) {
+  const long long tiles = (D.N / kFewRows + D.Et) * (D.f / kFewCols);
+  if (tiles <= kFewMaxTiles) return TILES_FEW;
+  return backward && tiles <= kFewMaxTilesBwd && D.N <= kFewMaxRowsBwd * D.Et ? TILES_FEW : TILES_TALL;
 }
 
 // The row-tile GEMMs of one call of the expert FFN.
@@ -936,9 +942,9 @@ struct RowGemms {
   uint32_t* zero_page;
   int32_t* counters;
 
-  RowGemms(const Dims& D_, const WsLayout& L_, void* ws_, hipStream_t st_, const int32_t* offsets_)
+  RowGemms(const Dims& D_, const WsLayout& L_, void* ws_, hipStream_t st_, const int32_t* offsets_, bool backward)
       : D(D_), L(L_), ws(static_cast<char*>(ws_)), st(st_), offsets(offsets_),
-        mode(tile_mode(D_)), max_tiles((int)sched_max_tiles(D_)),
+        mode(tile_mode(D_, backward)), max_tiles((int)sched_max_tiles(D_)),
         sched(reinterpret_cast<int32_t*>(ws + L_.sched)), zero_page(reinterpret_cast<uint32_t*>(ws + L_.zero_page)),
         counters(reinterpret_cast<int32_t*>(ws + L_.splitk_counters)) {}
 
@@ -1030,7 +1036,7 @@ extern "C" int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_per
   MOE_REQUIRE_ALIGNED(x_perm); MOE_REQUIRE_ALIGNED(offsets); MOE_REQUIRE_ALIGNED(w_gate); MOE_REQUIRE_ALIGNED(w_up);
   MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(y_perm); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   if (D.N == 0) return MOE_OK;
-  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets);
+  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, false);
   if (save_g == nullptr) {  // checkpointed forward: G and U go to the workspace and are not kept
     save_g = G.rows_f(L.g_re);
     save_u = G.rows_f(L.u_re);
@@ -1058,7 +1064,7 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   MOE_REQUIRE_ALIGNED(w_up); MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   MOE_REQUIRE_ALIGNED(dx_perm); MOE_REQUIRE_ALIGNED(dw_gate); MOE_REQUIRE_ALIGNED(dw_up); MOE_REQUIRE_ALIGNED(dw_down);
   hipStream_t st = (hipStream_t)stream;
-  const RowGemms G(D, L, ws, st, offsets);
+  const RowGemms G(D, L, ws, st, offsets, true);
   uint16_t* const h = G.rows_f(L.h);
   uint16_t* const dg = G.rows_f(L.dg);
   uint16_t* const du = G.rows_f(L.du);
@@ -1169,7 +1175,7 @@ extern "C" int moe_grouped_ffn_bwd_recompute(const moe_shape* shape, const uint1
   MOE_REQUIRE_ALIGNED(dy_perm); MOE_REQUIRE_ALIGNED(x_perm); MOE_REQUIRE_ALIGNED(offsets); MOE_REQUIRE_ALIGNED(w_gate);
   MOE_REQUIRE_ALIGNED(w_up); MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(dx_perm); MOE_REQUIRE_ALIGNED(dw_gate);
   MOE_REQUIRE_ALIGNED(dw_up); MOE_REQUIRE_ALIGNED(dw_down);
-  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets);
+  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, false);
   uint16_t* const g_re = G.rows_f(L.g_re);
   uint16_t* const u_re = G.rows_f(L.u_re);
   if (D.N > 0) {

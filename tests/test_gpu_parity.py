@@ -429,7 +429,8 @@ def test_weight_gradient_edges(moe, d, f):
     (64, 64, [1, 32, 33, 0]),                    # one k-step: three of four, seven of eight wavefronts have none
     (192, 576, [64, 65, 31, 0, 128]),            # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
     (1088, 128, [200, 0, 7]),                    # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
-    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100]),    # 1920 tiles: the 256-row kernel's side of the rule
+    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100]),    # 1920 tiles: the 256-row kernel's side of the forward's rule
+    (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100]),     # 3120 tiles: and of the backward's
     (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100]),    # 1272 tiles (4 wavefronts per block)
 ])
 def test_small_problem_tiles(moe, d, f, counts):
