@@ -2,7 +2,8 @@
 // (Section III-A: W_up, W_gate in R^{d x f}, W_down in R^{f x d}, per-expert token counts s_e; these are the
 // per-expert GEMMs of uneven, often small row counts that the abstract and Section II-A single out).
 //
-// One kernel template serves all seven contractions.  Every output tile is
+// One kernel template serves the four row-tile contractions of the FFN and two of the router's backward (the FFN's weight
+// gradients have a kernel of their own, wgrad.hip, and small problems another, few_rows.hip).  Every output tile is
 //     C[p, q] = sum_k  P[p, k] * Q[q, k]          (p: 256 values, q: 256 values, k in steps of 64)
 // where P is the operand whose index becomes the lane-column of the MFMA accumulator and Q the operand whose
 // index becomes the accumulator register (so that each lane owns 4 consecutive q = 4 consecutive output
@@ -14,8 +15,8 @@
 //             Y   = H Wd           P = H (KC)        Q = Wd (RC)
 //   backward  dH  = dY Wd^T        P = dY (KC)       Q = Wd (KC)       d(SwiGLU) epilogue -> dG, dU, H
 //             dX  = dG Wg^T+dU Wu^T P = dG then dU (KC) Q = Wg then Wu (KC)  one accumulator, two K passes
-//             dWd = H^T dY         P = H (RC)        Q = dY (RC)       ragged K = rows of the expert, fp32 out
-//             dWg,dWu = X^T dG, X^T dU   P = X (RC)  Q = dG | dU (RC)  two 128-wide halves, ragged K, fp32 out
+//   router    dx = dlogits W_r     P = dlogits (KC)  Q = W_r (RC)      two K passes (head and remainder), E > 128
+//             dWr^T = X^T dlogits  P = X (RC)        Q = head | remainder (RC)  ragged K = part of the tokens, fp32 out
 //
 // Tiling: 512 threads = 8 wavefronts (2 along p x 4 along q); each wavefront owns 128 p x 64 q as 4x2 MFMA
 // 32x32x16 blocks (128 fp32 accumulators per lane).  Tiles stream HBM/L2 -> LDS with the direct 16-byte
@@ -29,9 +30,9 @@
 // conflicts are avoided by choosing WHICH 16-byte chunk each lane fetches (an XOR swizzle of the chunk index with
 // row bits), and the fragment reads apply the same swizzle.  Every request is a whole 128-byte line (KC) or four of
 // them (RC): the vector L1 handles about one line per two cycles whatever part of it is used.  Rows past the end of
-// a ragged K (weight gradients) are fetched from a zeroed page.  Row tiles of the ragged dimension come from a
+// a ragged K (the router's weight gradient) are fetched from a zeroed page.  Row tiles of the ragged dimension come from a
 // device-built schedule (no host sync on the counts); the block-id -> tile map deals groups of 32 consecutive tiles
-// (super-tiles of 8 x 4 tiles for the weight gradients) round-robin to the XCDs, so that tiles sharing a panel meet in
+// (super-tiles of 8 x 4 tiles for the weight gradient) round-robin to the XCDs, so that tiles sharing a panel meet in
 // one L2 and every XCD gets the same mix of experts; inside a group the tiles that take longest come first.
 #include "common.h"
 
@@ -67,7 +68,7 @@ constexpr int kCusPerXcd = 32;
 #endif
 // How far ahead of their MFMAs a k-step reads its fragments (0: each group of 16 k reads its own; 1: half a group
 // ahead; 2: rolling, see the k-step): for row tiles of up to 256 rows, for tall row tiles, for the tall row tiles of the
-// SwiGLU forward, and for the weight gradients (whose transposing reads gained nothing from 2).
+// SwiGLU forward, and for the weight gradient (whose transposing reads gained nothing from 2).
 #ifndef MOE_FRAG_PIPELINE_ROW
 #define MOE_FRAG_PIPELINE_ROW 2
 #endif
@@ -267,7 +268,7 @@ __host__ __device__ __forceinline__ int row_tiles_of(int n, int mode) {
   return mode == TILES_TALL ? max(1, (n - 64 + TILE - 1) / TILE) : (n + TILE - 1) / TILE;
 }
 
-// KIND 0: row-tile problem (p = ragged rows of an expert, k = k_dim);  KIND 1: wgrad (k = ragged rows).
+// KIND 0: row-tile problem (p = ragged rows of an expert, k = k_dim);  KIND 1: weight gradient (k = ragged rows).
 // NQ = 2: the q tile is two 128-wide halves from q0 and q1 (acc[0] = q0 result, acc[1] = q1 result at the same q).
 template <int KIND, bool P_RC, bool Q_RC, int NQ, int NPASS, int EPI>
 __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A) {
@@ -835,7 +836,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 // sched[64 + max_tiles + u] = index of that expert's first tile; sched[64 + 2 max_tiles + i] = expert with the i-th most rows.
 // Also clears the zero page and the split-tile counters.
 // (A launch in front of every FFN call: bound by latency.  As many wavefronts as the experts need, prefix sums by lane
-// shuffles, two barriers: 3.7 -> 2.6 us at E' = 8, 5.4 -> 3.6 us at 66 against 1024 threads and a scan in LDS.)
+// shuffles, two barriers: 3.7 -> 2.5 us at E' = 8, 5.4 -> 4.8 at 66, 8.3 -> 7.1 at 128 against 1024 threads and a scan in LDS.)
 __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
                                                               uint32_t* __restrict__ zero_page, int32_t* __restrict__ counters,
                                                               int Et, int max_tiles, int mode) {
