@@ -149,7 +149,8 @@ __global__ __launch_bounds__(1024) void perm_scan_kernel(int32_t* __restrict__ b
 
 // 1 + 2 in one launch for few slots: one block of 16 wavefronts ranks all of them (sub-groups of 64 slots as above, the
 // expert's counts of all sub-groups chained in LDS).  The base of a slot's rank is then its expert's offset whatever its
-// block of 1024, and that is what block_base holds for each of them.  Two launches of 3 .. 6 us each are latency only (512 slots, E' = 8: 3.0 + 5.9 -> 3.4 us; 4012 slots, 14: 4.7 + 5.0 -> 8.8).
+// block of 1024, and that is what block_base holds for each of them.  Two launches of 3 .. 6 us each are latency only
+// (512 slots, E' = 8: 3.0 + 5.9 -> 3.4 us; 4012 slots, 14: 4.7 + 5.0 -> 8.8).
 constexpr int kSmallPermSlots = 4096, kSmallPermTable = 16384;   // limits: slots, entries of the table (32 KB)
 __global__ __launch_bounds__(1024) void perm_small_kernel(const int32_t* __restrict__ topk_idx, int32_t* __restrict__ lrank,
                                                           int32_t* __restrict__ block_base, int32_t* __restrict__ counts,
