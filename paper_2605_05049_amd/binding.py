@@ -11,7 +11,7 @@ _LIB_NAME = "libmoe_gfx950.so"
 _lib = None
 
 EXPORTED_SYMBOLS = (
-    "moe_status_str", "moe_workspace_bytes", "moe_abi_version",
+    "moe_status_str", "moe_workspace_bytes", "moe_grouped_ffn_small_tiles", "moe_abi_version",
     "moe_profile_enable", "moe_profile_count", "moe_profile_get", "moe_profile_reset",
     "moe_route_topk", "moe_route_topk_bwd", "moe_permute", "moe_permute_noalloc", "moe_permute_bwd", "moe_permute_bwd_add",
     "moe_router_fwd", "moe_router_bwd", "moe_grouped_ffn_fwd", "moe_grouped_ffn_bwd", "moe_grouped_ffn_bwd_recompute",
@@ -68,6 +68,8 @@ def load_library():
     lib.moe_status_str.argtypes = [c_int]
     lib.moe_workspace_bytes.restype = c_size_t
     lib.moe_workspace_bytes.argtypes = [sp]
+    lib.moe_grouped_ffn_small_tiles.restype = c_int
+    lib.moe_grouped_ffn_small_tiles.argtypes = [sp]
     lib.moe_abi_version.restype = c_int
     lib.moe_abi_version.argtypes = []
     lib.moe_profile_enable.restype = c_int
@@ -118,6 +120,12 @@ def abi_version() -> int:
 
 def workspace_bytes(shape) -> int:
     return int(load_library().moe_workspace_bytes(ctypes.byref(Shape.of(shape)._c)))
+
+
+def grouped_ffn_small_tiles(shape) -> tuple:
+    """The GEMMs of the grouped FFN that run on 64-row tiles at this shape, out of "gate_up", "down", "dh", "dx"."""
+    bits = load_library().moe_grouped_ffn_small_tiles(ctypes.byref(Shape.of(shape)._c))
+    return tuple(name for i, name in enumerate(("gate_up", "down", "dh", "dx")) if bits >> i & 1)
 
 
 def profile_enable(on: bool) -> None:

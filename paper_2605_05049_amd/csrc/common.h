@@ -15,7 +15,7 @@ constexpr int kPermSlotsPerBlock = 1024;  // slots ranked by one block of the co
 constexpr int kSplitParts = 256;     // K-split parts in flight at most: 32 per XCD (one per CU)
 constexpr int kSplitCounters = 128;  // split tiles at most: 16 per XCD
 constexpr int kMaxWidth = 1 << 22;   // d_model, d_ffn limit: 256 rows x 2^22 elements x 2 bytes < 2^32
-constexpr int kMinTileRows = 32;     // smallest row-tile height any GEMM schedule may use
+constexpr int kMinTileRows = 64;     // smallest row-tile height any GEMM schedule may use
 
 struct Dims {
   int T, d, f, E, k, Es, Et, Kp, renorm;
@@ -44,14 +44,15 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Workspace carve-up.  Every region starts 256-byte aligned.
 //   perm_hist : per-block expert histograms of the counting sort, then turned into per-block bases
 //   perm_rank : rank of every slot among the same-expert slots of its block
-//   sched     : tile schedule of the grouped GEMMs (header + two int arrays)
+//   sched     : tile schedule of the grouped GEMMs (header + two int arrays + experts by row count)
+//   sched_few : the same for those GEMMs of a call that run on the 64-row tiles
 //   zero_page : 256 zero bytes, the source of k-rows past the end of a ragged contraction
 //   h, dg, du : bf16 [N,f] intermediates of the expert FFN (H in forward; H, dG, dU in backward): with x_perm these are
 //               the 3 d_ffn + d_model values per row of the activation-memory model of Section III-A
 struct WsLayout {
   size_t perm_hist, perm_hist_bytes;
   size_t perm_rank, perm_rank_bytes;
-  size_t sched, sched_bytes;
+  size_t sched, sched_few, sched_bytes;
   size_t zero_page;
   size_t splitk_counters;   // kSplitCounters int32: arrivals per split tile
   size_t splitk_partial;    // kSplitParts fp32 tiles of up to 320 x 256: partial sums of the tiles whose K range is split
@@ -90,9 +91,9 @@ inline WsLayout ws_layout(const Dims& D) {
   L.perm_rank = off;
   L.perm_rank_bytes = round_up((size_t)D.N * sizeof(int32_t) + 256, 256);
   off += L.perm_rank_bytes;
-  L.sched = off;
   L.sched_bytes = round_up((size_t)(64 + 2 * sched_max_tiles(D) + kMaxExperts) * sizeof(int32_t), 256);
-  off += L.sched_bytes;
+  L.sched = off; off += L.sched_bytes;
+  L.sched_few = off; off += L.sched_bytes;
   L.zero_page = off;
   off += 256;
   L.splitk_counters = off;
@@ -149,6 +150,7 @@ struct RowTileArgs {
   const uint16_t* g_in; const uint16_t* u_in;            // saved G, U (dH)
 };
 void launch_few_rows(const char* label, hipStream_t st, int kind, RowTileArgs A, long long row_tiles);
+bool few_rows_pays(const Dims& D, RowTileKind kind);   // (grouped_gemm.hip)
 
 // Weight gradients of the expert FFNs (wgrad.hip): f0[e] (and f1[e]) = p0_e^T q0_e (p0_e^T q1_e) over the rows of expert e.
 struct WgradArgs {

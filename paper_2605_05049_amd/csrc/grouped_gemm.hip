@@ -834,18 +834,24 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 // Row-tile schedule: one thread per expert.  sched[0] = number of row tiles; sched[1] = how experts are cut into
 // row tiles (TileMode); sched[64 + u] = expert of tile u;
 // sched[64 + max_tiles + u] = index of that expert's first tile; sched[64 + 2 max_tiles + i] = expert with the i-th most rows.
-// Also clears the zero page and the split-tile counters.
+// Block 0 builds `sched` and also clears the zero page and the split-tile counters; block 1, of a call whose GEMMs do not all
+// run on the same tiles, builds `sched_few` for the 64-row ones.
 // (A launch in front of every FFN call: bound by latency.  As many wavefronts as the experts need, prefix sums by lane
 // shuffles, two barriers: 3.7 -> 2.5 us at E' = 8, 5.4 -> 4.8 at 66, 8.3 -> 7.1 at 128 against 1024 threads and a scan in LDS.)
 __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
-                                                              uint32_t* __restrict__ zero_page, int32_t* __restrict__ counters,
-                                                              int Et, int max_tiles, int mode) {
+                                                              int32_t* __restrict__ sched_few, uint32_t* __restrict__ zero_page,
+                                                              int32_t* __restrict__ counters, int Et, int max_tiles, int mode) {
   __shared__ int32_t rows_of[kMaxExperts];
   __shared__ int32_t wave_total[kMaxExperts / kWave];
   const int e = threadIdx.x, lane = e % kWave, wv = e / kWave;
   const int n = (e < Et) ? offsets[e + 1] - offsets[e] : 0;
-  if (e < 64) zero_page[e] = 0u;
-  for (int i = e; i < kSplitCounters; i += blockDim.x) counters[i] = 0;
+  if (blockIdx.x == 0) {
+    if (e < 64) zero_page[e] = 0u;
+    for (int i = e; i < kSplitCounters; i += blockDim.x) counters[i] = 0;
+  } else {
+    sched = sched_few;
+    mode = TILES_FEW;
+  }
   const int nt = row_tiles_of(n, mode);
   rows_of[e] = n;
   int incl = nt;
@@ -876,10 +882,10 @@ __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __r
     }
   }
 }
-static void launch_schedule(const char* label, hipStream_t st, const int32_t* offsets, int32_t* sched, uint32_t* zero_page, int32_t* counters,
-                            int Et, int max_tiles, int mode) {
-  const dim3 block((unsigned)round_up((size_t)Et, kWave));   // (Et <= kMaxExperts = 1024)
-  MOE_LAUNCH(label, st, build_schedule_kernel, dim3(1), block, 0, st, offsets, sched, zero_page, counters, Et, max_tiles, mode);
+static void launch_schedule(const char* label, hipStream_t st, const int32_t* offsets, int32_t* sched, int32_t* sched_few, uint32_t* zero_page,
+                            int32_t* counters, int Et, int max_tiles, TileMode mode) {
+  const dim3 grid(sched_few ? 2 : 1), block((unsigned)round_up((size_t)Et, kWave));   // (Et <= kMaxExperts = 1024)
+  MOE_LAUNCH(label, st, build_schedule_kernel, grid, block, 0, st, offsets, sched, sched_few, zero_page, counters, Et, max_tiles, mode);
 }
 
 // Blocks of a weight-gradient launch: whole rounds of one 32-tile super-tile per XCD.
@@ -911,59 +917,84 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 
 #define MOE_TRY(call) do { int rc_ = (call); if (rc_ != MOE_OK) return rc_; } while (0)
 
-// Which kernel the row-tile GEMMs of a call run on.  Both take every size; the counts are on the device, so the rule goes by
-// their upper bound.  few_rows.hip, whose 64 x 64 tiles make 16 times as many blocks and share a tile's k range among the
-// wavefronts of a block, while its tiles (of d_ffn columns) are at most about what the chip runs in two or three rounds;
-// beyond, its 2.7 times the operand bytes per multiply cost more than the idle CUs of the 256-row tiles.  The four GEMMs of
-// one call, us, few_rows.hip against the 256-row tiles, by its number of tiles (E = 8 .. 66, uniform random counts):
-//   d x f = 512 x 1024:   160: 41 / 64   256: 45 / 88   640: 69 / 135   1152: 101 / 137
-//   1024 x 2048:          512: 76 / 115   1280: 153 / 192        2048 x 1408:  704: 164 / 194   1056: 207 / 234   1760: 334 / 270
-//   1088 x 1984:          868: 121 / 132   2170: 241 / 241   4340: 420 / 324     4096 x 14336:  2240: 1063 / 1034
-// The data gradients, whose weights it reads in whole lines along k, keep up with the 256-row tiles for longer while experts
-// have few rows (dH + dX, 2048 x 1408, E = 66: 1496 tiles, 2 rows: 180 / 185; 2904 tiles, 64 rows: 297 / 325; 7168 x 2048,
-// E = 32, Zipf, 1536 tiles: 561 / 607; 4096 x 14336, 16 rows, 2240 tiles: 507 / 522, 64 rows, 3584: 686 / 663; but 2048 x 1408,
-// E = 16, 256 rows, 1760 tiles: 169 / 154).
-constexpr long long kFewMaxTiles = 1280, kFewMaxTilesBwd = 3000, kFewMaxRowsBwd = 128;
-static TileMode tile_mode(const Dims& D, bool backward) {
-  const long long tiles = (D.N / kFewRows + D.Et) * (D.f / kFewCols);
-  if (tiles <= kFewMaxTiles) return TILES_FEW;
-  return backward && tiles <= kFewMaxTilesBwd && D.N <= kFewMaxRowsBwd * D.Et ? TILES_FEW : TILES_TALL;
+// Which kernel a row-tile GEMM runs on.  Both take every size; the counts are on the device, so the rule goes by what the
+// host knows: rows per expert on average, about how many 64 x 64 tiles there will be, and the length of the contraction.
+// few_rows.hip makes 16 times as many tiles of a problem (8 times: gate | up) and spreads a tile's k range over the wavefronts
+// of a block, so it wins while its tiles are about what the chip runs in one to three rounds.  Beyond, its 4 (gate | up: 3)
+// times the operand bytes per multiply cost more than the idle CUs of the 256-row tiles, the sooner the fewer of those the
+// 256-row kernel leaves idle: its tiles of few rows take less time, and it cuts tiles of 48 k-steps or more along k.
+// The limits below are where the two cross on 27000 random shapes (64 .. 8192 x 64 .. 14336, 1 .. 128 experts, 1 .. 40000
+// rows, half as many with skewed counts); with them a GEMM is on the slower kernel by more than 5 % in 0.5 - 1.2 % of
+// those.  few_rows.hip against the 256-row tiles, us (d x f, E, rows per expert):
+//   gate | up  2048 x 1408, 4, 256: 28 / 54   32, 8: 71 / 69     4096 x 1024, 8, 512: 124 / 106     7168 x 512, 32, 256: 250 / 206
+//   down       2048 x 1408, 4, 256: 22 / 37   32, 8: 41 / 37     7168 x 512, 8, 1024: 161 / 86     4096 x 14336, 1, 8: 72 / 33
+//   dH         2048 x 1408, 4, 256: 20 / 60   32, 8: 34 / 33     7168 x 2048, 8, 8: 37 / 42     7168 x 1024, 8, 512: 123 / 123
+//   dX         2048 x 1408, 4, 256: 34 / 63   32, 8: 65 / 68     7168 x 512, 8, 1024: 248 / 128     4096 x 14336, 1, 8: 96 / 54
+constexpr int kRowClasses = 5, kStepClasses = 5;
+constexpr int kRowsBelow[kRowClasses - 1] = {16, 40, 64, 96};     // rows per expert on average
+constexpr int kStepsBelow[kStepClasses - 1] = {48, 64, 96, 128};  // k-steps of 64, both passes of dX counted
+constexpr int kFewTilesGateUp[kRowClasses] = {256, 256, 320, 480, 768};   // (the 256-row kernel never cuts these along k)
+constexpr int kFewTilesDh[kRowClasses][kStepClasses] = {
+    {512, 96, 16, 0, 0}, {512, 512, 16, 0, 0}, {768, 768, 512, 512, 0}, {2048, 1024, 1024, 768, 0}, {1536, 1536, 1024, 768, 256}};
+constexpr int kFewTilesDownDx[kRowClasses][kStepClasses] = {
+    {512, 96, 16, 0, 0}, {512, 512, 16, 0, 0}, {576, 768, 512, 0, 0}, {768, 1024, 768, 512, 0}, {1152, 960, 768, 512, 256}};
+bool few_rows_pays(const Dims& D, RowTileKind kind) {
+  const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;   // output columns f, contraction over d; else the other way round
+  const long long active = D.N < D.Et ? D.N : D.Et;                  // experts with rows, at most
+  const long long row_tiles = D.N / kFewRows + active / 2;           // every expert's last tile about half full, but one tile at least
+  const long long tiles = (row_tiles > active ? row_tiles : active) * ((to_f ? D.f : D.d) / kFewCols);
+  const int steps = (to_f ? D.d : D.f) / 64 * (kind == ROWTILE_DX ? 2 : 1);
+  int rc = 0, sc = 0;
+  while (rc < kRowClasses - 1 && D.N >= (long long)kRowsBelow[rc] * D.Et) rc++;
+  while (sc < kStepClasses - 1 && steps >= kStepsBelow[sc]) sc++;
+  if (kind == ROWTILE_GATE_UP) return tiles <= kFewTilesGateUp[rc];
+  // Many tiles of few rows: weights are all that counts, and a narrow tile's many blocks read them a little faster (dX,
+  // 4096 x 1024, 32 experts, 32 rows: 95 / 101; down, 7168 x 512, 64 experts, 8 rows: 91 / 98); between the two ranges they lose up to
+  // 15 %, the second round of blocks being almost empty.
+  if (tiles > 1024 && tiles <= 4096 && (kind == ROWTILE_DOWN ? rc == 0 && steps < 16 : rc <= 2 && steps < 64)) return true;
+  return tiles <= (kind == ROWTILE_DH ? kFewTilesDh : kFewTilesDownDx)[rc][sc];
 }
 
-// The row-tile GEMMs of one call of the expert FFN.
+// The row-tile GEMMs of one call of the expert FFN: of the forward (gate | up and down), of the backward (dH and dX) or the
+// recomputed gate | up alone.
 struct RowGemms {
   const Dims& D;
   const WsLayout& L;
   char* ws;
   hipStream_t st;
   const int32_t* offsets;
-  TileMode mode;
   int max_tiles;
-  int32_t* sched;
+  bool any_few, any_tall;   // GEMMs of this call on either kind of tile
+  int32_t* sched_tall;
+  int32_t* sched_few;
   uint32_t* zero_page;
   int32_t* counters;
 
-  RowGemms(const Dims& D_, const WsLayout& L_, void* ws_, hipStream_t st_, const int32_t* offsets_, bool backward)
-      : D(D_), L(L_), ws(static_cast<char*>(ws_)), st(st_), offsets(offsets_),
-        mode(tile_mode(D_, backward)), max_tiles((int)sched_max_tiles(D_)),
-        sched(reinterpret_cast<int32_t*>(ws + L_.sched)), zero_page(reinterpret_cast<uint32_t*>(ws + L_.zero_page)),
+  RowGemms(const Dims& D_, const WsLayout& L_, void* ws_, hipStream_t st_, const int32_t* offsets_, RowTileKind first, RowTileKind second)
+      : D(D_), L(L_), ws(static_cast<char*>(ws_)), st(st_), offsets(offsets_), max_tiles((int)sched_max_tiles(D_)),
+        any_few(few_rows_pays(D_, first) || few_rows_pays(D_, second)), any_tall(!few_rows_pays(D_, first) || !few_rows_pays(D_, second)),
+        sched_tall(reinterpret_cast<int32_t*>(ws + L_.sched)), sched_few(reinterpret_cast<int32_t*>(ws + L_.sched_few)),
+        zero_page(reinterpret_cast<uint32_t*>(ws + L_.zero_page)),
         counters(reinterpret_cast<int32_t*>(ws + L_.splitk_counters)) {}
 
   uint16_t* rows_f(size_t region) const { return reinterpret_cast<uint16_t*>(ws + region); }   // a bf16 [N, f] region of the workspace
 
   void schedule() const {
-    launch_schedule("ffn_schedule", st, offsets, sched, zero_page, counters, D.Et, max_tiles, mode);
+    launch_schedule("ffn_schedule", st, offsets, any_tall ? sched_tall : sched_few, any_tall && any_few ? sched_few : nullptr, zero_page, counters,
+                    D.Et, max_tiles, any_tall ? TILES_TALL : TILES_FEW);
   }
+  const int32_t* experts_by_rows() const { return (any_tall ? sched_tall : sched_few) + 64 + 2 * max_tiles; }
 
-  int launch(const char* label, int kind, RowTileArgs R) const {
-    R.sched = sched; R.max_tiles = max_tiles; R.offsets = offsets;
+  int launch(const char* label, RowTileKind kind, RowTileArgs R) const {
+    R.max_tiles = max_tiles; R.offsets = offsets;
     R.q_expert_stride = (size_t)D.d * D.f;
-    if (mode == TILES_FEW) {
-      launch_few_rows(label, st, kind, R, D.N / kFewRows + D.Et);   // sum_e ceil(n_e / 64) <= N / 64 + E'
+    if (few_rows_pays(D, kind)) {
+      R.sched = sched_few;
+      launch_few_rows(label, st, kind, R, D.N / kFewRows + (D.N < D.Et ? D.N : D.Et));   // sum_e ceil(n_e / 64) <= N / 64 + experts with rows
       return MOE_OK;
     }
     GemmArgs A = {};
-    A.sched = sched; A.max_tiles = max_tiles; A.offsets = offsets; A.Et = D.Et;
+    A.sched = sched_tall; A.max_tiles = max_tiles; A.offsets = offsets; A.Et = D.Et;
     A.zero_page = reinterpret_cast<const uint16_t*>(zero_page);
     A.partial = reinterpret_cast<float*>(ws + L.splitk_partial); A.counters = counters;
     A.q_dim = R.q_dim; A.k_dim = R.k_dim;
@@ -1037,7 +1068,7 @@ extern "C" int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_per
   MOE_REQUIRE_ALIGNED(x_perm); MOE_REQUIRE_ALIGNED(offsets); MOE_REQUIRE_ALIGNED(w_gate); MOE_REQUIRE_ALIGNED(w_up);
   MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(y_perm); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   if (D.N == 0) return MOE_OK;
-  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, false);
+  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, ROWTILE_GATE_UP, ROWTILE_DOWN);
   if (save_g == nullptr) {  // checkpointed forward: G and U go to the workspace and are not kept
     save_g = G.rows_f(L.g_re);
     save_u = G.rows_f(L.u_re);
@@ -1065,7 +1096,7 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   MOE_REQUIRE_ALIGNED(w_up); MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   MOE_REQUIRE_ALIGNED(dx_perm); MOE_REQUIRE_ALIGNED(dw_gate); MOE_REQUIRE_ALIGNED(dw_up); MOE_REQUIRE_ALIGNED(dw_down);
   hipStream_t st = (hipStream_t)stream;
-  const RowGemms G(D, L, ws, st, offsets, true);
+  const RowGemms G(D, L, ws, st, offsets, ROWTILE_DH, ROWTILE_DX);
   uint16_t* const h = G.rows_f(L.h);
   uint16_t* const dg = G.rows_f(L.dg);
   uint16_t* const du = G.rows_f(L.du);
@@ -1076,7 +1107,7 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   }
   // dWd[e] = H_e^T dY_e   (rows f, columns d)
   WgradArgs W = {};
-  W.offsets = offsets; W.order = G.sched + 64 + 2 * G.max_tiles; W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
+  W.offsets = offsets; W.order = G.experts_by_rows(); W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
   W.Et = D.Et; W.accumulate = accumulate ? 1 : 0; W.rows = D.N;
   W.p0 = h; W.p_ld = D.f; W.p_dim = D.f;
   W.q0 = dy_perm; W.q_ld = D.d; W.q_dim = D.d;
@@ -1136,7 +1167,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   } else {
     // dx_router[T,d] = dlogits W_r on the grouped GEMM kernel: rows = tokens, columns = d, K = E in two passes (head,
     // remainder of dlogits); P K-contiguous in the padded copies, Q = W_r read with k = expert row (R-contiguous)
-    launch_schedule("router_schedule", st, offs, sched, zero_page, counters, 1, max_tiles, TILES_PLAIN);
+    launch_schedule("router_schedule", st, offs, sched, nullptr, zero_page, counters, 1, max_tiles, TILES_PLAIN);
     A.offsets = offs;
     A.n_q_tiles = (D.d + TILE - 1) / TILE; A.q_dim = D.d; A.k_dim = D.E;
     A.p0 = dl_hi; A.p1 = dl_lo; A.p_ld = Epad;
@@ -1176,7 +1207,7 @@ extern "C" int moe_grouped_ffn_bwd_recompute(const moe_shape* shape, const uint1
   MOE_REQUIRE_ALIGNED(dy_perm); MOE_REQUIRE_ALIGNED(x_perm); MOE_REQUIRE_ALIGNED(offsets); MOE_REQUIRE_ALIGNED(w_gate);
   MOE_REQUIRE_ALIGNED(w_up); MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(dx_perm); MOE_REQUIRE_ALIGNED(dw_gate);
   MOE_REQUIRE_ALIGNED(dw_up); MOE_REQUIRE_ALIGNED(dw_down);
-  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, false);
+  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, ROWTILE_GATE_UP, ROWTILE_GATE_UP);
   uint16_t* const g_re = G.rows_f(L.g_re);
   uint16_t* const u_re = G.rows_f(L.u_re);
   if (D.N > 0) {

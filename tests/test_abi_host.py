@@ -113,3 +113,28 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(B, "_LIB_NAME", "libmoe_does_not_exist.so")
     with pytest.raises(RuntimeError, match="no CPU fallback"):
         B.load_library()
+
+
+# (T, d, f, E, k) -> the GEMMs on 64-row tiles.  Each goes by its own output width and contraction: a layer that is small in
+# d_ffn is not small in its down projection and dX (and the other way round).
+@pytest.mark.parametrize("T,d,f,E,k,expected", [
+    (256, 512, 1024, 8, 2, ("gate_up", "down", "dh", "dx")),
+    (8192, 7168, 512, 4, 1, ()),
+    (512, 7168, 512, 1, 1, ("gate_up", "down", "dh", "dx")),
+    (1024, 7168, 512, 1, 1, ("gate_up", "dh")),    # 128 tiles of gate | up and dH, 1792 of down and dX
+    (8192, 7168, 512, 8, 1, ()),                   # 17000 tiles of down and dX, twice the time on them
+    (64, 7168, 1024, 8, 1, ("gate_up",)),          # 112 k-steps of dH, which the other kernel cuts along k
+    (32, 512, 2048, 4, 1, ("gate_up", "down", "dh")),   # 64 k-steps of dX
+    (32, 512, 14336, 4, 1, ()),                    # 32 tiles of down and dX, but 224 and 448 k-steps
+    (8, 4096, 14336, 1, 1, ("gate_up",)),
+    (4096, 1024, 2048, 1, 1, ("down",)),
+    (1024, 4096, 1024, 32, 1, ("dx",)),            # 2048 tiles of few rows; 512 of dH, but 64 k-steps
+    (4096, 4096, 14336, 8, 2, ()),
+    (0, 512, 1024, 8, 2, ("gate_up", "down", "dh", "dx")),
+])
+def test_which_gemms_run_on_small_tiles(lib, T, d, f, E, k, expected):
+    assert moe.grouped_ffn_small_tiles(moe.Shape(T, d, f, E, k)) == expected
+
+
+def test_small_tiles_of_an_invalid_shape(lib):
+    assert moe.grouped_ffn_small_tiles(moe.Shape(8, 500, 64, 4, 1)) == ()
