@@ -432,6 +432,7 @@ def test_weight_gradient_edges(moe, d, f):
     (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100]),    # 1920 tiles: the 256-row kernel's side of the forward's rule
     (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100]),     # 3120 tiles: and of the backward's
     (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100]),    # 1272 tiles (4 wavefronts per block)
+    (64, 64, [4500, 0, 257, 7]),                     # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
 ])
 def test_small_problem_tiles(moe, d, f, counts):
     """The kernel for small problems and both sides of the rule that chooses it."""
