@@ -149,9 +149,17 @@ __global__ __launch_bounds__(1024) void perm_scan_kernel(int32_t* __restrict__ b
 
 // 1 + 2 in one launch for few slots: one block of 16 wavefronts ranks all of them (sub-groups of 64 slots as above, the
 // expert's counts of all sub-groups chained in LDS).  The base of a slot's rank is then its expert's offset whatever its
-// block of 1024, and that is what block_base holds for each of them.  Two launches of 3 .. 6 us each are latency only
-// (512 slots, E' = 8: 3.0 + 5.9 -> 3.4 us; 4012 slots, 14: 4.7 + 5.0 -> 8.8).
-constexpr int kSmallPermSlots = 4096, kSmallPermTable = 16384;   // limits: slots, entries of the table (32 KB)
+// block of 1024, and that is what block_base holds for each of them.  Two launches of 3 .. 6 us each are latency only, and
+// grow little with the slots, where the one block's time does; few experts make the general path's scatter slow as well.  Maps
+// of N slots and E' experts, us, three launches / two: 512, 8: 10.3 / 5.3   2048, 64: 9.3 / 7.8   3072, 24: 9.9 / 9.3
+// 3072, 128: 9.8 / 9.8   3072, 256: 10.4 / 10.2   3500, 64: 9.7 / 10.2   4096, 2: 18.8 / 10.1   4096, 12: 10.9 / 10.7
+// 4096, 16: 10.4 / 10.7   4096, 256: 10.6 / 11.9.
+constexpr int kSmallPermSlots = 4096;                              // at most (what the kernel's wavefronts hold in registers)
+constexpr int kSmallPermSlotsMany = 3072, kSmallPermExperts = 12;  // ... with more experts than this
+constexpr int kSmallPermTable = 16384;                             // entries of the table at most (32 KB)
+static bool perm_is_small(long long N, int Et) {
+  return N > 0 && N <= (Et <= kSmallPermExperts ? kSmallPermSlots : kSmallPermSlotsMany) && (N + kWave - 1) / kWave * Et <= kSmallPermTable;
+}
 __global__ __launch_bounds__(1024) void perm_small_kernel(const int32_t* __restrict__ topk_idx, int32_t* __restrict__ lrank,
                                                           int32_t* __restrict__ block_base, int32_t* __restrict__ counts,
                                                           int32_t* __restrict__ offsets, int N, int Et, int nbits) {
@@ -519,7 +527,7 @@ static int permute_launch(const Dims& D, const uint16_t* x, const int32_t* topk_
   const int nblk = perm_num_blocks(D.N);
   int nbits = 0;
   while ((1 << nbits) < D.Et) nbits++;
-  if (D.N > 0 && D.N <= kSmallPermSlots && (D.N + kWave - 1) / kWave * D.Et <= kSmallPermTable) {
+  if (perm_is_small(D.N, D.Et)) {
     MOE_LAUNCH("perm_rank_scan", st, perm_small_kernel, dim3(1), dim3(1024), (size_t)((D.N + kWave - 1) / kWave) * D.Et * sizeof(uint16_t), st,
                topk_idx, lrank, block_hist, counts, offsets, (int)D.N, D.Et, nbits);
   } else {

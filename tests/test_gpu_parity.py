@@ -226,12 +226,26 @@ def test_permute_maps_rows_and_streams(moe, T, d, E, k, Es, kind):
                  O.unpermute_combine_scale(np.abs(y64), ros_ref, np.ones((T, Kp))), what="permute_bwd")
 
 
-# the one-launch counting sort: a slot, one sub-group of 64 and its neighbours, 1024-slot blocks, both sides of its limits
-# (4096 slots, 64 x 256 table entries)
+# the one-launch counting sort: a slot, one sub-group of 64 and its neighbours, 1024-slot blocks, and sizes just past it
 @pytest.mark.parametrize("T,E,k,Es", [(1, 1, 1, 0), (64, 3, 1, 0), (65, 7, 1, 0), (341, 9, 3, 0), (1025, 5, 1, 1), (4096, 256, 1, 0),
                                       (4096, 257, 1, 0), (4097, 4, 1, 0), (100, 1000, 2, 1)])
 def test_permute_few_slots(moe, T, E, k, Es):
     test_permute_maps_rows_and_streams(moe, T, 64, E, k, Es, "skewed")
+
+
+# on which side of the one-launch sort's rule a size lies: up to 3072 slots (4096 with at most 12 experts) and 64 x 256 table entries
+@pytest.mark.parametrize("N,E,one_launch", [(1, 1000, True), (3072, 341, True), (3072, 342, False), (3073, 12, True), (3073, 13, False),
+                                            (4096, 12, True), (4097, 12, False), (4096, 256, False), (1024, 1000, True)])
+def test_permute_launches(moe, N, E, one_launch):
+    moe.profile_reset()
+    moe.profile_enable(True)
+    try:
+        test_permute_maps_rows_and_streams(moe, N, 64, E, 1, 0, "skewed")
+        labels = {label for label, _ in moe.profile_records()}
+    finally:
+        moe.profile_enable(False)
+        moe.profile_reset()
+    assert ("perm_rank_scan" in labels, "perm_scan" in labels) == (one_launch, not one_launch)
 
 
 def test_permute_is_deterministic_over_100_runs(moe):
