@@ -438,6 +438,12 @@ def test_weight_gradient_edges(moe, d, f):
     test_grouped_ffn_every_tile_height(moe, d, f, [1, 31, 32, 33, 64, 65, 0, 96, 97, 128, 129])
 
 
+def test_weight_gradient_stores_of_few_rows(moe):
+    """100 MB or more of weight gradients from at most 64 rows per expert: stored through the L2, the others past it.  Widths
+    that end inside a tile; experts of 0 .. 4 k-steps."""
+    test_grouped_ffn_every_tile_height(moe, 1088, 3392, [1, 31, 33, 0, 64, 65, 100])
+
+
 # (d, f, counts): the bound N / 64 + E of the row tiles times f / 64 is what the dispatch compares with 1280
 @pytest.mark.parametrize("d,f,counts", [
     (64, 64, [1, 32, 33, 0]),                    # one k-step: three of four, seven of eight wavefronts have none
