@@ -228,8 +228,10 @@ void launch_wgrad(const char* label, hipStream_t st, WgradArgs A) {
   A.n_q_tiles = (A.q_dim + tq - 1) / tq;
   // 8 x 4 tiles read the fewest panels; the pair, whose tiles write only 512 bytes of a row, takes 4 x 8 where an expert's rows
   // are few and the stores all that counts (4096 x 14336, 64 rows: 769 -> 716 us, 128: 735 -> 682; 4096 x 1024, 256 rows:
-  // 1013 -> 1057)
-  A.band = (A.q1 && A.rows <= 128ll * A.Et) ? 4 : 8;
+  // 1013 -> 1057), and where dW has few rows itself: with 9 .. 12 tiles along p a band of 8 leaves one of 1 .. 4 behind (1024 x
+  // 8960, 49 experts of 214 rows: 1213 -> 922; 960 .. 1536 rows of dW, 100 .. 1600 per expert: 0.97 - 1.0 of the time at the
+  // median, 0.86 - 0.96 at the tenth percentile)
+  A.band = (A.q1 && (A.rows <= 128ll * A.Et || (A.p_dim <= 12 * WP && A.rows <= 1600ll * A.Et))) ? 4 : 8;
   // Results are not read again: left in the L2 they would evict the panels (4096 x 14336, 1024 rows, the pair: 2.55 ms, past it
   // 2.13).  With few rows there are hardly any panels, and gathering the stores in the L2 is what counts (400 - 1600 MB of
   // dW_down, TB/s past the L2 / through it: 2 - 8 rows 5.2 / 6.2, 8 - 32: 5.1 / 6.1, 32 - 64: 5.0 / 5.5, 64 - 96: 4.9 / 4.8; the

@@ -431,6 +431,13 @@ def test_grouped_ffn_every_tile_height(moe, d, f, counts):
     assert not gwg[empty].any() and not gwd[empty].any()    # the empty expert
 
 
+# (the pair's bands of 4 or 8 of the 128-row tiles along d: whole ones, last ones of 1, 5 and 2 tiles)
+@pytest.mark.parametrize("d,f,counts", [(640, 192, [300, 200, 0]), (1536, 64, [300, 200, 0]), (1600, 64, [300, 200, 0]),
+                                        (1280, 64, [1700, 1601, 0])])
+def test_weight_gradient_bands(moe, d, f, counts):
+    test_grouped_ffn_every_tile_height(moe, d, f, counts)
+
+
 @pytest.mark.parametrize("d,f", [(64, 64), (192, 320), (448, 128)])
 def test_weight_gradient_edges(moe, d, f):
     """Row counts around the weight gradients' 32-row steps and their ring of three (0, 1, 2, 3, 4 steps, whole and
