@@ -33,14 +33,24 @@ class _CShape(Structure):
 
 
 class Shape:
-    """Problem statement of one layer: T tokens, d_model, d_ffn, E routed experts, top-k, E_shared, renorm."""
+    """Problem statement of one layer: T tokens, d_model, d_ffn, E routed experts, top-k, E_shared, renorm.  E_total, K_slots
+    and N follow from them (and are kept, not computed: every call reads them several times)."""
 
     def __init__(self, T, d_model, d_ffn, E, k, E_shared=0, renorm=1):
-        self.T, self.d_model, self.d_ffn, self.E, self.k = int(T), int(d_model), int(d_ffn), int(E), int(k)
-        self.E_shared, self.renorm = int(E_shared), int(renorm)
-        self.E_total, self.K_slots = self.E + self.E_shared, self.k + self.E_shared
-        self.N = self.T * self.K_slots
-        self._c = _CShape(self.T, self.d_model, self.d_ffn, self.E, self.k, self.E_shared, self.renorm)
+        T, d_model, d_ffn, E, k, E_shared, renorm = int(T), int(d_model), int(d_ffn), int(E), int(k), int(E_shared), int(renorm)
+        self.__dict__.update(T=T, d_model=d_model, d_ffn=d_ffn, E=E, k=k, E_shared=E_shared, renorm=renorm,
+                             E_total=E + E_shared, K_slots=k + E_shared, N=T * (k + E_shared),
+                             _c=_CShape(T, d_model, d_ffn, E, k, E_shared, renorm))
+
+    def __setattr__(self, name, value):
+        if name in ("E_total", "K_slots", "N"):
+            raise AttributeError(f"{name} follows from the other fields of a Shape")
+        fields = {f: self.__dict__[f] for f, _ in _CShape._fields_}
+        if name in fields:
+            fields[name] = value
+            Shape.__init__(self, **fields)
+        else:
+            object.__setattr__(self, name, value)
 
     @classmethod
     def of(cls, s) -> "Shape":

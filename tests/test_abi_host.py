@@ -1,5 +1,6 @@
 """Host-side checks of the C-ABI library that need no GPU: it loads, exports every symbol include/moe.h declares,
 and rejects bad arguments before anything is launched."""
+import copy
 import ctypes
 import os
 import re
@@ -47,6 +48,21 @@ def test_workspace_bytes_follows_the_shape(lib):
     assert moe.workspace_bytes(moe.Shape(1, 2 ** 22, 64, 8, 2)) > 0        # the widest rows the GEMM loads can address
     assert moe.workspace_bytes(moe.Shape(1, 2 ** 22 + 64, 64, 8, 2)) == 0  # beyond: the 32-bit row offsets would wrap
     assert moe.workspace_bytes(moe.Shape(1, 64, 2 ** 22 + 64, 8, 2)) == 0
+
+
+def test_shape_fields_stay_consistent():
+    s = moe.Shape(256, 512, 1024, 8, 2, 1)
+    s.T = 100
+    assert (s.N, s.K_slots, s.E_total) == (300, 3, 9) and s._c.T == 100
+    s.E_shared = 0
+    assert (s.N, s.K_slots, s.E_total) == (200, 2, 8)
+    assert moe.workspace_bytes(s) == moe.workspace_bytes(moe.Shape(100, 512, 1024, 8, 2))
+    for derived in ("N", "K_slots", "E_total"):
+        with pytest.raises(AttributeError):
+            setattr(s, derived, 1)
+    t = copy.copy(s)
+    t.T = 7
+    assert (s.N, t.N, s._c.T, t._c.T) == (200, 14, 100, 7)
 
 
 def _shape(**kw):
