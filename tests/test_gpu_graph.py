@@ -13,9 +13,13 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     ("tiny", W.WORKLOADS["tiny"]),
-    ("imbalance_scaled", W.scaled_down(W.WORKLOADS["imbalance"])),      # empty experts, ragged tiles, split tails
-    ("finegrained_scaled", W.scaled_down(W.WORKLOADS["finegrained"])),  # shared experts
+    ("imbalance_scaled", W.scaled_down(W.WORKLOADS["imbalance"])),      # empty experts, ragged tiles; down and dX on 256-row tiles
+    ("finegrained_scaled", W.scaled_down(W.WORKLOADS["finegrained"])),  # shared experts; all but dH on 256-row tiles
+    # few tokens on wide experts: dH and dX cut their tiles along k, on arrival counters that every replay finds as the last left them
+    ("split", W.Workload("split", W.MoEShape(16, 4096, 1536, 4, 1), "router")),
 ]
+SMALL_TILES = {"tiny": ("gate_up", "down", "dh", "dx"), "imbalance_scaled": ("gate_up", "dh"), "finegrained_scaled": ("dh",),
+               "split": ("gate_up", "down")}
 
 
 def _tensors(buf, with_router):
@@ -30,6 +34,7 @@ def _tensors(buf, with_router):
 def test_graph_replays_match_eager(moe, name, wl):
     sh = wl.shape
     s = moe.Shape.of(sh)
+    assert moe.grouped_ffn_small_tiles(s) == SMALL_TILES[name]
     inp = W.make_layer_inputs(wl, seed=0)
     if "logits" not in inp:
         pytest.skip("workload without router logits")

@@ -306,7 +306,7 @@ FFN_CASES = [
     (256, 512, 1024, 8, 2, 0, 0),      # the tiny workload's shape
     (700, 128, 256, 3, 1, 1, 0),       # ~230 rows per expert + a 700-row shared expert: several row tiles, ragged
     (90, 256, 128, 16, 2, 0, 5),       # experts with a handful of rows
-    (600, 256, 2048, 2, 1, 0, 0),      # few tiles and a long K in Y = H W_down and dX: the last-round tiles are split along K
+    (600, 256, 2048, 2, 1, 0, 0),      # few tiles and a long K in Y = H W_down and dX (32 and 64 k-steps)
     (513, 64, 64, 1, 1, 0, 0),         # one expert, the smallest legal widths, a one-row third tile
     (40, 128, 192, 24, 1, 0, 20),      # most experts empty: zero-filled weight gradients, experts ordered by row count
 ]
@@ -373,6 +373,7 @@ def test_grouped_ffn_fwd_bwd(moe, T, d, f, E, k, Es, dead):
         assert torch.all(gwu[e] == base)
 
 
+ALL_GEMMS = ("gate_up", "down", "dh", "dx")
 HEIGHT_COUNTS = [1, 31, 33, 64, 65, 128, 129, 256, 257, 300, 320, 321, 0, 577, 512 + 65]
 FEW_COUNTS = [33, 300, 65, 0, 130]
 MANY_TILE_COUNTS = [1300, 70, 0, 1400, 1024 + 30]   # 5 row tiles with a tall last one, 6 with a short last one, 4 with a tall one
@@ -385,13 +386,8 @@ def test_grouped_ffn_every_tile_height(moe, d, f, counts):
     """Experts whose row counts hit every height class of a row tile and both sides of every class boundary: 1..64 rows
     (one 32-row block per wavefront), 65..128, 129..256, 257..320 (a full tile that carries up to 64 more rows), 321
     (a full tile plus a short one), an empty expert, and a multi-tile expert whose remainder rides on its last tile.
-    (f = 1088 = 4 * 256 + 64 also puts a 64-wide last column tile on every class.  The last two shapes make few tiles
-    with a contraction of 48 k-steps or more, which the kernels then cut along K: d = 3072 in dH, whose arriving part
-    applies the d(SwiGLU) epilogue to the summed parts, and f = 3136 = 49 * 64 in the down projection and in dX; the
-    fifth case, on a few experts, has both dH and dX cut their tiles in one backward call, one after the other on the
-    same arrival counters.  The last case has experts of more than four row tiles, which the kernels walk column tile by
-    column tile with a tall tile first, next to one of four row tiles, walked in bands of 8 column tiles: f = 2304 is 9
-    column tiles, i.e. a full band and a band of one.)"""
+    (f = 1088 = 4 * 256 + 64 also puts a 64-wide last column tile on every class.)  These shapes are small enough for most of
+    their GEMMs to run on the 64-row tiles; test_grouped_ffn_on_256_row_tiles has the same counts on the others."""
     counts = np.array(counts, dtype=np.int64)
     E, N = counts.size, int(counts.sum())
     offsets = np.zeros(E + 1, dtype=np.int32)
@@ -451,19 +447,107 @@ def test_weight_gradient_stores_of_few_rows(moe):
     test_grouped_ffn_every_tile_height(moe, 1088, 3392, [1, 31, 33, 0, 64, 65, 100])
 
 
-# (d, f, counts): the bound N / 64 + E of the row tiles times f / 64 is what the dispatch compares with 1280
-@pytest.mark.parametrize("d,f,counts", [
-    (64, 64, [1, 32, 33, 0]),                    # one k-step: three of four, seven of eight wavefronts have none
-    (192, 576, [64, 65, 31, 0, 128]),            # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
-    (1088, 128, [200, 0, 7]),                    # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
-    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100]),    # 1920 tiles: the 256-row kernel's side of the forward's rule
-    (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100]),     # 3120 tiles: and of the backward's
-    (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100]),    # 1272 tiles (4 wavefronts per block)
-    (64, 64, [4500, 0, 257, 7]),                     # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
+# (d, f, counts, GEMMs on 64-row tiles)
+@pytest.mark.parametrize("d,f,counts,small", [
+    (64, 64, [1, 32, 33, 0], ALL_GEMMS),                     # one k-step: three of four, seven of eight wavefronts have none
+    (192, 576, [64, 65, 31, 0, 128], ALL_GEMMS),             # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
+    (1088, 128, [200, 0, 7], ALL_GEMMS),                     # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
+    (64, 64, [4500, 0, 257, 7], ALL_GEMMS),                  # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
+    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100], ("dh",)),   # dH: 1280 tiles (4 wavefronts per block) next to a dX of 320 k-steps
+    (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100], ("dh",)),    # dH: 2080 tiles
+    (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100], ()),        # 848 tiles of dH: neither one round of blocks nor many
 ])
-def test_small_problem_tiles(moe, d, f, counts):
-    """The kernel for small problems and both sides of the rule that chooses it."""
+def test_small_problem_tiles(moe, d, f, counts, small):
+    """The kernel for small problems, alone and next to the other one in a call (two schedules), and both sides of the rule
+    that chooses it for each GEMM."""
+    assert moe.grouped_ffn_small_tiles(moe.Shape(sum(counts), d, f, len(counts), 1)) == small
     test_grouped_ffn_every_tile_height(moe, d, f, counts)
+
+
+@pytest.mark.parametrize("d,f,counts,small", [
+    # every height class in all four GEMMs; column tiles of 64 (f) and 128 (d) at the end
+    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], ()),
+    # experts of more than four row tiles, which the kernel walks column tile by column tile with a tall tile first, next to one
+    # of four, walked in bands of 8 column tiles: 9 column tiles, i.e. a full band and a band of one
+    (1280, 2304, MANY_TILE_COUNTS, ()),
+    # few tiles and 48 k-steps or more: cut along k.  dH of 128 steps in up to 8 parts, a tall tile, a short one and one of 65
+    # rows among them, whose last part to arrive applies the d(SwiGLU) epilogue to the sums ...
+    (8192, 128, [300, 33, 0, 0, 65], ("gate_up",)),
+    # ... down and dX, of 128 and 256 steps ...
+    (128, 8192, [300, 33, 0, 0, 65], ("dh",)),
+    # ... and dH (64 steps, 12 tiles) and dX (48 steps, 32 tiles) in one backward call, on the same arrival counters
+    (4096, 1536, [12, 0, 31], ("gate_up", "down")),
+])
+def test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small):
+    """The kernel of large problems at whole-tensor precision."""
+    assert moe.grouped_ffn_small_tiles(moe.Shape(sum(counts), d, f, len(counts), 1)) == small
+    test_grouped_ffn_every_tile_height(moe, d, f, counts)
+
+
+def ffn_on_device(moe, d, f, counts, seed=0):
+    """Inputs and one saving forward of the grouped FFN over experts of `counts` rows, all on the device."""
+    E, N = len(counts), sum(counts)
+    s = moe.Shape(N, d, f, E, 1)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    normal = lambda *sz, std=1.0: (torch.randn(*sz, device="cuda", generator=g) * std).to(torch.bfloat16)  # noqa: E731
+    e = lambda *sz: torch.full(sz, float("nan"), dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    off = dev(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32))
+    x, dy = normal(N, d), normal(N, d)
+    w = [normal(E, d, f, std=0.05), normal(E, d, f, std=0.05), normal(E, f, d, std=0.05)]
+    ws, y, sg, su = ws_for(moe, s), e(N, d), e(N, f), e(N, f)
+    moe.moe_grouped_ffn_fwd(s, x, off, *w, y, sg, su, ws)
+    return s, x, dy, off, w, ws, y, sg, su
+
+
+EDGE_COUNTS = [1, 31, 32, 33, 64, 65, 0, 96, 97, 128, 129]
+
+
+@pytest.mark.parametrize("d,f,counts", [(64, 64, EDGE_COUNTS), (192, 320, EDGE_COUNTS), (448, 128, EDGE_COUNTS), (640, 1088, [300, 0, 577]),
+                                        (2304, 2304, [30, 0, 7, 64])])
+def test_weight_gradients_accumulate(moe, d, f, counts):
+    """accumulate = 1: every element of the three gradients is the fp32 sum of its start value and what the overwriting call
+    writes there, bit for bit, saved and recomputing call alike; an expert without rows keeps its start values."""
+    s, x, dy, off, w, ws, y, sg, su = ffn_on_device(moe, d, f, counts)
+    dx = torch.empty_like(x)
+    over = [torch.full(t.shape, float("nan"), device="cuda") for t in w]
+    moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, sg, su, dx, *over, 0, ws)
+    start = [torch.randn(t.shape, device="cuda") for t in w]
+    for recompute in (False, True):
+        got, dx2 = [t.clone() for t in start], torch.empty_like(dx)
+        if recompute:
+            moe.moe_grouped_ffn_bwd_recompute(s, dy, x, off, *w, dx2, *got, 1, ws)
+        else:
+            moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, sg, su, dx2, *got, 1, ws)
+        assert torch.equal(dx2.view(torch.int16), dx.view(torch.int16))
+        for name, a, b, c in zip(("dw_gate", "dw_up", "dw_down"), got, start, over):
+            assert bool(torch.isfinite(c).all()) and torch.equal(a, b + c), (name, recompute)
+
+
+@pytest.mark.parametrize("d,f,counts,small", [
+    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], ()),          # all on 256-row tiles
+    (256, 192, [248] * 64 + [2048, 2048], ("dh",)),               # 256-row forward, dH on 64-row tiles, dX on 256-row tiles
+    (4096, 1088, [3, 0, 31, 9, 1, 0, 12, 30, 2, 2, 0, 5, 1, 1, 1, 2], ()),   # few rows; dH cut along k
+    (8192, 128, [300, 33, 0, 0, 65], ("gate_up",)),               # the recomputed GEMM alone on 64-row tiles; dH cut along k
+    (512, 1024, [64] * 8, ALL_GEMMS),
+])
+def test_recomputing_backward_on_either_kernel(moe, d, f, counts, small):
+    """The recomputing backward gives the saving pair's bits whichever kernels its GEMMs run on (G and U, recomputed into the
+    memory of dG and dU, are read and overwritten in place)."""
+    assert moe.grouped_ffn_small_tiles(moe.Shape(sum(counts), d, f, len(counts), 1)) == small
+    s, x, dy, off, w, ws, y, sg, su = ffn_on_device(moe, d, f, counts)
+    y2 = torch.full_like(y, float("nan"))
+    moe.moe_grouped_ffn_fwd(s, x, off, *w, y2, None, None, ws)
+    outs = [y.view(torch.int16)], [y2.view(torch.int16)]
+    for recompute, out in enumerate(outs):
+        dx, dws = torch.full_like(x, float("nan")), [torch.full(t.shape, float("nan"), device="cuda") for t in w]
+        if recompute:
+            moe.moe_grouped_ffn_bwd_recompute(s, dy, x, off, *w, dx, *dws, 0, ws)
+        else:
+            moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, sg, su, dx, *dws, 0, ws)
+        assert bool(torch.isfinite(dx).all()) and all(bool(torch.isfinite(t).all()) for t in dws)
+        out += [dx.view(torch.int16)] + [t.view(torch.int32) for t in dws]
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
 
 
 # ---------------------------------------------------------------------------------------------------------
