@@ -82,7 +82,7 @@ constexpr int kCusPerXcd = 32;
 #define MOE_FRAG_PIPELINE_WGRAD 1
 #endif
 // k offset inside a step at which wavefronts 0..3 request their share of the next stage: half-way through it, or
-// (weight gradients and the SwiGLU forward, where it measured 1-2 % faster; 2 % slower in the others) after three quarters
+// (the weight gradient and the SwiGLU forward, where it measured 1-2 % faster; 2 % slower in the others) after three quarters
 #ifndef MOE_EARLY_ISSUE_AT
 #define MOE_EARLY_ISSUE_AT 32
 #endif
@@ -99,24 +99,22 @@ struct GemmArgs {
   const int32_t* offsets;  // [E'+1]
   int n_q_tiles;           // tiles along q
   int q_dim;               // extent of q (output columns)
-  int k_dim;               // contraction length per pass (row-tile problems); unused for wgrad
+  int k_dim;               // contraction length per pass (row-tile problems); unused for the weight gradient
   // operands: p side (activations) and up to two q sides (weights), and a second pass for the dX contraction
   const uint16_t* p0; size_t p_ld;
   const uint16_t* p1;
   const uint16_t* q0; const uint16_t* q1; size_t q_ld; size_t q_expert_stride;
-  // wgrad only
-  int p_dim;               // extent of p (rows of dW)
+  // weight gradient only
+  int p_dim;               // extent of p (rows of the result)
   int n_p_tiles;
-  int Et;
-  int accumulate;
+  int Et;                  // segments of K
   const uint16_t* zero_page;  // 256 zeroed bytes: source of k-rows past the end of a ragged K
   float* partial;             // [kSplitParts][256][256] fp32: partial tiles of a split K range
   int32_t* counters;          // [kSplitCounters], zeroed by the schedule kernel and again by each tile's reducing part: parts of a split tile that have arrived
   // outputs
   uint16_t* c0; uint16_t* c1; uint16_t* c2; size_t c_ld;   // bf16 outputs (row-major, ld = q_dim)
   const uint16_t* g_in; const uint16_t* u_in;              // saved G, U for the d(SwiGLU) epilogue
-  float* f0; float* f1; size_t f_expert_stride;            // fp32 outputs of the wgrads
-  int sum_halves;          // NQ == 2 with fp32 output: write the sum of the two halves' results to f0 (f1 unused)
+  float* f0; size_t f_expert_stride;                       // fp32 output of the weight gradient
 };
 
 // One 256-wide operand of a tile, possibly made of two 128-wide halves from two tensors.
@@ -268,10 +266,12 @@ __host__ __device__ __forceinline__ int row_tiles_of(int n, int mode) {
   return mode == TILES_TALL ? max(1, (n - 64 + TILE - 1) / TILE) : (n + TILE - 1) / TILE;
 }
 
-// KIND 0: row-tile problem (p = ragged rows of an expert, k = k_dim);  KIND 1: weight gradient (k = ragged rows).
+// KIND 0: row-tile problem (p = ragged rows of an expert, k = k_dim);  KIND 1: the router's weight gradient (k = the rows of a
+// segment of the tokens, EPI_F32: the sum of the two halves in fp32).
 // NQ = 2: the q tile is two 128-wide halves from q0 and q1 (acc[0] = q0 result, acc[1] = q1 result at the same q).
 template <int KIND, bool P_RC, bool Q_RC, int NQ, int NPASS, int EPI>
 __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A) {
+  static_assert((KIND == 1) == (EPI == EPI_F32) && (EPI != EPI_F32 || NQ == 2), "the fp32 epilogue adds the two halves of a weight gradient");
   // Two stages of P (up to 320 rows) | Q each.
   __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE_BYTES];
   auto p_area = [&](int s) __attribute__((always_inline)) { return lds + s * STAGE_BYTES; };
@@ -385,7 +385,6 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     p_row0 = pt * TILE;
     p_valid = min(TILE, A.p_dim - p_row0);
     q0_col = qt * TQ;
-    if (k_len == 0 && A.accumulate) return;  // nothing to add
   }
   const int q_valid = min(TQ, A.q_dim - q0_col);
 
@@ -777,23 +776,10 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
         const int p = wp + 32 * b + r;
         if (p < p_valid && q_base + q < q_valid) {
           const size_t o = (size_t)expert * A.f_expert_stride + (size_t)(p_row0 + p) * A.c_ld + q0_col + q_base + q;
-#pragma unroll
-          for (int n = 0; n < NQ; n++) {
-            float4 v = *reinterpret_cast<const float4*>(wlds + n * 8192 + r * PITCH + q * 4);
-            if (NQ == 2 && A.sum_halves) {   // (uniform over the launch)
-              if (n == 1) break;
-              const float4 v1 = *reinterpret_cast<const float4*>(wlds + 8192 + r * PITCH + q * 4);
-              v.x += v1.x; v.y += v1.y; v.z += v1.z; v.w += v1.w;
-            }
-            float* dst = (n == 0 ? A.f0 : A.f1) + o;
-            // (16-byte stores: the row pitch is a multiple of 4 and a row has room for whole groups of 4: d_model and
-            // d_ffn are multiples of 64, the router's partial results are padded to 4)
-            if (A.accumulate) {
-              const float4 old = *reinterpret_cast<const float4*>(dst);
-              v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
-            }
-            *reinterpret_cast<float4*>(dst) = v;
-          }
+          // the two halves (head and remainder of dlogits) are added; 16-byte stores: the rows are padded to 4 columns
+          const float4 v0 = *reinterpret_cast<const float4*>(wlds + r * PITCH + q * 4);
+          const float4 v1 = *reinterpret_cast<const float4*>(wlds + 8192 + r * PITCH + q * 4);
+          *reinterpret_cast<float4*>(A.f0 + o) = make_float4(v0.x + v1.x, v0.y + v1.y, v0.z + v1.z, v0.w + v1.w);
         }
       }
     } else {
@@ -1170,7 +1156,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   launch_router_prepare(st, dlogits, w_router, dl_hi, dl_lo, skinny_dx ? w_t : nullptr, offs, sched + 64 + 2 * max_tiles, zero_page,
                         (int)D.T, (int)D.E, Epad, Ek, (int)D.d, (int)S, part_rows);
   GemmArgs A = {};
-  A.sched = sched; A.max_tiles = max_tiles; A.Et = 1; A.accumulate = 0;
+  A.sched = sched; A.max_tiles = max_tiles; A.Et = 1;
   A.zero_page = reinterpret_cast<const uint16_t*>(zero_page);
   A.partial = reinterpret_cast<float*>(wsb + L.splitk_partial); A.counters = counters;
   if (skinny_dx) {
@@ -1192,12 +1178,12 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   // part's tokens; then the parts are added in order and transposed into dW_r.  (The segment order and the zero page
   // that this kernel reads of a schedule were written by the prepare kernel; a dx launch above leaves them as they are.)
   GemmArgs B = {};
-  B.sched = sched; B.max_tiles = max_tiles; B.offsets = offs + 8; B.Et = (int)S; B.accumulate = 0;
+  B.sched = sched; B.max_tiles = max_tiles; B.offsets = offs + 8; B.Et = (int)S;
   B.zero_page = reinterpret_cast<const uint16_t*>(zero_page);
   B.p_dim = D.d; B.n_p_tiles = n_p_tiles; B.q_dim = D.E; B.n_q_tiles = n_q_tiles;
   B.p0 = x; B.p_ld = D.d;
   B.q0 = dl_hi; B.q1 = dl_lo; B.q_ld = Epad;
-  B.f0 = partial; B.f1 = nullptr; B.f_expert_stride = (size_t)D.d * ldp; B.c_ld = ldp; B.sum_halves = 1;
+  B.f0 = partial; B.f_expert_stride = (size_t)D.d * ldp; B.c_ld = ldp;
   MOE_TRY((launch_gemm<1, true, true, 2, 1, EPI_F32>("router_bwd_dw", B, wgrad_blocks(B.Et, B.n_p_tiles, B.n_q_tiles), st)));
   launch_router_dw_reduce(st, partial, dw_router, (int)S, (int)D.E, (int)D.d, ldp, accumulate ? 1 : 0);
   return launch_status();
