@@ -204,9 +204,11 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 
 // One direct global->LDS load: 16 bytes per lane, lane L lands at lds_base + 16 L (lds_base is wave-uniform).
 // Written as inline assembly on purpose: the compiler does not track it, so it never makes the (transposing)
-// fragment reads of the OTHER stage wait for loads still in flight.  A kernel that uses them orders them itself: an
-// explicit s_waitcnt vmcnt(0) precedes the barrier that publishes a stage, and no compiler-tracked vector-memory
-// load is in flight while these are (the epilogue starts after the last such wait).  m0 receives the LDS base: the
+// fragment reads of the OTHER stage wait for loads still in flight.  A kernel that uses them orders them itself: before a
+// stage is read, an explicit s_waitcnt vmcnt(n) waits until this wavefront's loads of it have landed (n = how many it has
+// issued since, 0 with two stages, one stage's worth with three), and a barrier after it publishes the stage if other
+// wavefronts read it (few_rows.hip's read only what they loaded themselves).  No compiler-tracked vector-memory load is in
+// flight while these are (the epilogue starts after the last such wait, which is vmcnt(0)).  m0 receives the LDS base: the
 // backend reserves m0 (it is never allocated, and the compiler writes it only directly before an instruction of its
 // own that reads it; the kernels here have none: no LDS-direct or GDS access, no register-indexed moves, no messages).  Two
 // address forms: a 64-bit address per lane, or a scalar base plus a 32-bit byte offset per lane.

@@ -519,7 +519,7 @@ static int permute_checks(const moe_shape* shape, Dims* D, const uint16_t* x, co
   return MOE_OK;
 }
 
-// The three launches of the counting sort.  block_hist: perm_num_blocks(N) * E' int32; lrank: N int32.  Every entry of
+// The launches of the counting sort: rank and scan, or both in one, then the scatter.  block_hist: perm_num_blocks(N) * E' int32; lrank: N int32.  Every entry of
 // both that a later kernel reads is written by an earlier one of the same call, so neither has to start at zero.
 static int permute_launch(const Dims& D, const uint16_t* x, const int32_t* topk_idx, uint16_t* x_perm, int32_t* counts,
                           int32_t* offsets, int32_t* row_of_slot, int32_t* slot_of_row, int32_t* block_hist, int32_t* lrank,
