@@ -130,7 +130,7 @@ void launch_router_prepare(hipStream_t st, const float* dlogits, const uint16_t*
                            int d, int S, int part_rows);
 void launch_router_bwd_dx(hipStream_t st, const uint16_t* dl_hi, const uint16_t* dl_lo, const uint16_t* w_t, uint16_t* dx, int T, int d,
                           int E, int Epad);
-bool router_bwd_is_small(int T, int E);
+bool router_bwd_is_small(int T, int E, int d);
 void launch_router_bwd_small(hipStream_t st, const uint16_t* x, const uint16_t* w_router, const float* dlogits, uint16_t* dx, float* dw, int T,
                              int E, int d, int accumulate);
 void launch_router_dw_reduce(hipStream_t st, const float* partial, float* dw, int S, int E, int d, int ldp, int accumulate);

@@ -1130,7 +1130,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   MOE_REQUIRE_ALIGNED(dw_router);
   if (D.T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;
-  if (router_bwd_is_small(D.T, D.E)) {
+  if (router_bwd_is_small(D.T, D.E, D.d)) {
     launch_router_bwd_small(st, x, w_router, dlogits, dx_router, dw_router, D.T, D.E, D.d, accumulate ? 1 : 0);
     return launch_status();
   }

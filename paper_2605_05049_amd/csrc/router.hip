@@ -534,9 +534,15 @@ __global__ __launch_bounds__(kSmallWaves * kWave) void router_bwd_small_kernel(c
   }
 }
 
-// One block of the dW_r role does T x EP multiply-adds for its 128 columns on one CU: 256 x 8 take about 2 us, 1003 x 16 would
-// take 17 on the few CUs that d / 128 blocks are.
-bool router_bwd_is_small(int T, int E) { return E <= 16 && T <= (E <= 8 ? 1024 : 512); }
+// One block of the dW_r role does T x EP multiply-adds for its 128 columns on one CU, so the launch's time grows with T (and, as
+// rounds of blocks, with d) where the general path's hardly does.  Both, us (E, d, T; one launch / general):
+//   8, 64: T = 256: 7.0 / 15.2   1024: 16.4 / 16.1     8, 512, 1024: 16.7 / 18.3     8, 65536, 1024: 0.89 of the general path
+//   16, 64: T = 64: 14.3 / 14.8   256: 17.7 / 15.6     16, 128 .. 8192: T = 256: 0.55 - 0.61 of it   512: 0.74 - 0.95   768: 1.0 - 1.3
+//   16, 65536: T = 64: 0.73 of it   192: 1.13   512: 1.53
+bool router_bwd_is_small(int T, int E, int d) {
+  if (E <= 8) return T <= 1024;
+  return E <= 16 && T <= (d >= 128 && d <= 8192 ? 512 : 64);
+}
 void launch_router_bwd_small(hipStream_t st, const uint16_t* x, const uint16_t* w_router, const float* dlogits, uint16_t* dx, float* dw, int T,
                              int E, int d, int accumulate) {
   const int n_dw = (d + kSmallDwCols - 1) / kSmallDwCols;

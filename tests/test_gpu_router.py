@@ -68,13 +68,29 @@ def test_router_forward_and_backward(moe, T, d, E):
     assert_close(host_f32(dxr), 0.5 * rdx, 0.5 * q_x, tol=TOL, what="dx_router (never accumulated)")
 
 
-# both sides of the one-launch backward's rule (1024 tokens with E <= 8, 512 with E <= 16) and of its pieces: tokens of 16 wavefronts times
+# the one-launch backward and sizes just past it, and the edges of its pieces: tokens of 16 wavefronts times
 # 16 in flight, 4 per dx wavefront, 128 and 512 columns; few tokens whose experts the forward spreads over blocks
 @pytest.mark.parametrize("T,d,E", [(1, 64, 2), (255, 576, 8), (257, 128, 5), (1024, 64, 8), (1025, 64, 8), (512, 1088, 16),
                                    (513, 192, 13), (3, 640, 9), (16, 2048, 64), (17, 128, 100), (300, 64, 17)])
 def test_router_few_tokens(moe, T, d, E):
     test_router_forward_and_backward(moe, T, d, E)
 
+
+# on which side of the one-launch backward's rule a size lies: up to 1024 tokens with 8 experts; with 16 up to 512, or 64 where
+# the width is below 128 or above 8192
+@pytest.mark.parametrize("T,d,E,one_launch", [(1024, 64, 8, True), (1025, 128, 8, False), (512, 128, 16, True), (513, 128, 9, False),
+                                              (512, 64, 16, False), (65, 64, 9, False), (64, 64, 16, True), (64, 8256, 16, True),
+                                              (65, 8256, 16, False), (1, 64, 17, False)])
+def test_router_backward_launches(moe, T, d, E, one_launch):
+    moe.profile_reset()
+    moe.profile_enable(True)
+    try:
+        test_router_forward_and_backward(moe, T, d, E)
+        labels = {label for label, _ in moe.profile_records()}
+    finally:
+        moe.profile_enable(False)
+        moe.profile_reset()
+    assert ("router_bwd" in labels, "router_prepare" in labels) == (one_launch, not one_launch)
 
 
 def test_permute_bwd_add(moe):
