@@ -56,8 +56,7 @@ __device__ __forceinline__ w_bf16x8 w_frag(unsigned off, int kk, unsigned area) 
 
 }  // namespace
 
-// STREAMED: the results are stored past the L2 (a template argument: decided at run time, it cost the stores 4 %).
-template <int NQ, bool STREAMED>
+template <int NQ>
 __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
   __shared__ __attribute__((aligned(1024))) char ring[3 * W_STAGE];
   constexpr int TQ = WQ / NQ;
@@ -209,12 +208,10 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
       for (int v = 0; v < 16; v++) {
         float* const row = blk + (size_t)(8 * (v >> 2) + (v & 3)) * A.c_ld;
 #pragma unroll
-        for (int a = 0; a < 4; a++) {
-          if (a < n_a) {
-            if (STREAMED) __builtin_nontemporal_store(acc[b][a][v], row + lane_off + 32 * a);
-            else row[lane_off + 32 * a] = acc[b][a][v];
-          }
-        }
+        for (int a = 0; a < 4; a++)   // (not read again: left in the caches they would evict the panels, pair 2.55 -> 2.13 ms.  Through
+          // the caches the launch itself is 5 - 15 % shorter with at most 64 rows per expert, but the kernels after it pay more than
+          // that for the weights it has evicted: 704 x 1792, 27 experts of 16 rows, forward + backward 175 -> 212 us)
+          if (a < n_a) __builtin_nontemporal_store(acc[b][a][v], row + lane_off + 32 * a);
       }
     }
   }
@@ -232,19 +229,11 @@ void launch_wgrad(const char* label, hipStream_t st, WgradArgs A) {
   // 8960, 49 experts of 214 rows: 1213 -> 922; 960 .. 1536 rows of dW, 100 .. 1600 per expert: 0.97 - 1.0 of the time at the
   // median, 0.86 - 0.96 at the tenth percentile)
   A.band = (A.q1 && (A.rows <= 128ll * A.Et || (A.p_dim <= 12 * WP && A.rows <= 1600ll * A.Et))) ? 4 : 8;
-  // Results are not read again: left in the L2 they would evict the panels (4096 x 14336, 1024 rows, the pair: 2.55 ms, past it
-  // 2.13).  With few rows there are hardly any panels, and gathering the stores in the L2 is what counts (400 - 1600 MB of
-  // dW_down, TB/s past the L2 / through it: 2 - 8 rows 5.2 / 6.2, 8 - 32: 5.1 / 6.1, 32 - 64: 5.0 / 5.5, 64 - 96: 4.9 / 4.8; the
-  // pair 5.2 / 5.6, 5.1 / 5.5, 5.1 / 5.25, 5.0 / 4.9).  Below 100 MB and where the old values are read first, past the L2 is
-  // 3 % faster.
-  const long long out_bytes = 4ll * A.Et * A.p_dim * A.q_dim * (A.q1 ? 2 : 1);
-  const bool streamed = A.accumulate || A.rows > 64ll * A.Et || out_bytes < 100ll * 1000 * 1000;
   const long long total = (long long)A.Et * A.n_p_tiles * A.n_q_tiles;
   const long long rounds = ((total + W_CHUNK - 1) / W_CHUNK + W_XCDS - 1) / W_XCDS;
   const dim3 grid((unsigned)(rounds * W_XCDS * W_CHUNK)), block(WTHREADS);
-  auto launch = [&](auto kern) { MOE_LAUNCH(label, st, kern, grid, block, 0, st, A); };
-  if (A.q1) streamed ? launch(wgrad_kernel<2, true>) : launch(wgrad_kernel<2, false>);
-  else streamed ? launch(wgrad_kernel<1, true>) : launch(wgrad_kernel<1, false>);
+  if (A.q1) MOE_LAUNCH(label, st, wgrad_kernel<2>, grid, block, 0, st, A);
+  else MOE_LAUNCH(label, st, wgrad_kernel<1>, grid, block, 0, st, A);
 }
 
 }  // namespace moe

@@ -441,12 +441,6 @@ def test_weight_gradient_edges(moe, d, f):
     test_grouped_ffn_every_tile_height(moe, d, f, [1, 31, 32, 33, 64, 65, 0, 96, 97, 128, 129])
 
 
-def test_weight_gradient_stores_of_few_rows(moe):
-    """100 MB or more of weight gradients from at most 64 rows per expert: stored through the L2, the others past it.  Widths
-    that end inside a tile; experts of 0 .. 4 k-steps."""
-    test_grouped_ffn_every_tile_height(moe, 1088, 3392, [1, 31, 33, 0, 64, 65, 100])
-
-
 # (d, f, counts, GEMMs on 64-row tiles)
 @pytest.mark.parametrize("d,f,counts,small", [
     (64, 64, [1, 32, 33, 0], ALL_GEMMS),                     # one k-step: three of four, seven of eight wavefronts have none
