@@ -269,6 +269,8 @@ __host__ __device__ __forceinline__ int row_tiles_of(int n, int mode) {
 // KIND 0: row-tile problem (p = ragged rows of an expert, k = k_dim);  KIND 1: the router's weight gradient (k = the rows of a
 // segment of the tokens, EPI_F32: the sum of the two halves in fp32).
 // NQ = 2: the q tile is two 128-wide halves from q0 and q1 (acc[0] = q0 result, acc[1] = q1 result at the same q).
+__device__ __forceinline__ unsigned xcc_id() { return (unsigned)__builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xF; }   // the XCD this wavefront runs on
+
 template <int KIND, bool P_RC, bool Q_RC, int NQ, int NPASS, int EPI>
 __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A) {
   static_assert((KIND == 1) == (EPI == EPI_F32) && (EPI != EPI_F32 || NQ == 2), "the fp32 epilogue adds the two halves of a weight gradient");
@@ -713,10 +715,13 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     // All parts of a tile carry the same blockIdx.x % 8 and so run on one XCD, whose L2 they share: a store that has
     // been acknowledged (vmcnt) is then visible to the other parts at the L2, and no cache has to be written back or
     // invalidated; the reducing part reads the partial tiles at agent scope, i.e. past its own vector L1.  That
-    // placement is checked, not assumed: a part that finds itself on another XCD falls back to device-wide fences and
-    // says so in the upper half of the counter, which makes the reducing part fence as well.
+    // placement is checked, not assumed: a part that finds itself on another XCD than its index says falls back to device-wide
+    // fences and says so in the upper half of the counter, which makes the reducing part fence as well.  Which XCD
+    // index 0 goes to is a property of the hardware queue (0, 7, 6 and 5 for the four queues of a process), so it is
+    // taken from the schedule kernel, which runs on the same stream; against a fixed XCD 0, every split tile of a program
+    // with several streams took the fences (2624 x 2112, 12 experts, dX: 107 us on one queue, 212 on another).
     __shared__ int arrived_before;
-    const bool on_home_xcd = (__builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xF) == (unsigned)(blockIdx.x % kNumXcd);
+    const bool on_home_xcd = xcc_id() == (blockIdx.x + (unsigned)A.sched[2]) % kNumXcd;
     if (on_home_xcd) __builtin_amdgcn_s_waitcnt(0x0F70);  // this thread's part of the partial tile has reached the L2
     else __threadfence();
     __syncthreads();   // ... and so has every other thread's, before the arrival is counted
@@ -818,7 +823,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 }
 
 // Row-tile schedule: one thread per expert.  sched[0] = number of row tiles; sched[1] = how experts are cut into
-// row tiles (TileMode); sched[64 + u] = expert of tile u;
+// row tiles (TileMode); sched[2] = the XCD that block 0 runs on; sched[64 + u] = expert of tile u;
 // sched[64 + max_tiles + u] = index of that expert's first tile; sched[64 + 2 max_tiles + i] = expert with the i-th most rows.
 // Block 0 builds `sched` and also clears the zero page and the split-tile counters; block 1, of a call whose GEMMs do not all
 // run on the same tiles, builds `sched_few` for the 64-row ones.
@@ -850,7 +855,10 @@ __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __r
   __syncthreads();
   for (int w = 0; w < wv; w++) incl += wave_total[w];
   const int first = incl - nt;
-  if (e == 0) sched[1] = mode;
+  if (e == 0) {
+    sched[1] = mode;
+    sched[2] = (int)((xcc_id() + kNumXcd - blockIdx.x) % kNumXcd);
+  }
   if (e == (int)blockDim.x - 1) sched[0] = incl;
   if (e < Et) {
     // experts by descending row count (ties: lower id first): sched[64 + 2 max_tiles + rank] = expert
