@@ -928,9 +928,11 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 // of a block, so it wins while its tiles are about what the chip runs in one to three rounds.  Beyond, its 4 (gate | up: 3)
 // times the operand bytes per multiply cost more than the idle CUs of the 256-row tiles, the sooner the fewer of those the
 // 256-row kernel leaves idle: its tiles of few rows take less time, and it cuts tiles of 48 k-steps or more along k.
-// The limits below are where the two cross on 27000 random shapes (64 .. 8192 x 64 .. 14336, 1 .. 128 experts, 1 .. 40000
-// rows, half as many with skewed counts); with them a GEMM is on the slower kernel by more than 5 % in 0.5 - 1.2 % of
-// those.  few_rows.hip against the 256-row tiles, us (d x f, E, rows per expert):
+// The limits below are where the two cross on 29000 random shapes (64 .. 8192 x 64 .. 14336, 1 .. 130 experts, 1 .. 40000
+// rows; even, mildly and strongly skewed counts, with and without shared experts), a loss counted one and a half times: the four
+// GEMMs take 0.79 of the 256-row kernel's time at the mean and more than 1.05 of it on 1 % of the shapes (all of a call
+// decided by its tiles of f: 0.82 and 12 %).  The more uneven the counts, the longer few_rows.hip stays ahead: one
+// tall tile is then the 256-row kernel's whole time.  Us, even counts, few_rows.hip / the 256-row tiles (d x f, E, rows per expert):
 //   gate | up  2048 x 1408, 4, 256: 28 / 54   32, 8: 71 / 69     4096 x 1024, 8, 512: 124 / 106     7168 x 512, 32, 256: 250 / 206
 //   down       2048 x 1408, 4, 256: 22 / 37   32, 8: 41 / 37     7168 x 512, 8, 1024: 161 / 86     4096 x 14336, 1, 8: 72 / 33
 //   dH         2048 x 1408, 4, 256: 20 / 60   32, 8: 34 / 33     7168 x 2048, 8, 8: 37 / 42     7168 x 1024, 8, 512: 123 / 123
@@ -938,11 +940,14 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 constexpr int kRowClasses = 5, kStepClasses = 5;
 constexpr int kRowsBelow[kRowClasses - 1] = {16, 40, 64, 96};     // rows per expert on average
 constexpr int kStepsBelow[kStepClasses - 1] = {48, 64, 96, 128};  // k-steps of 64, both passes of dX counted
-constexpr int kFewTilesGateUp[kRowClasses] = {256, 256, 320, 480, 768};   // (the 256-row kernel never cuts these along k)
-constexpr int kFewTilesDh[kRowClasses][kStepClasses] = {
-    {512, 96, 16, 0, 0}, {512, 512, 16, 0, 0}, {768, 768, 512, 512, 0}, {2048, 1024, 1024, 768, 0}, {1536, 1536, 1024, 768, 256}};
-constexpr int kFewTilesDownDx[kRowClasses][kStepClasses] = {
-    {512, 96, 16, 0, 0}, {512, 512, 16, 0, 0}, {576, 768, 512, 0, 0}, {768, 1024, 768, 512, 0}, {1152, 960, 768, 512, 256}};
+constexpr int kFewTilesGateUp[kRowClasses] = {288, 640, 1024, 1024, 768};   // (the 256-row kernel never cuts these along k)
+constexpr int kFewTiles[3][kRowClasses][kStepClasses] = {
+    // down
+    {{1024, 256, 20, 12, 0}, {2560, 2048, 1600, 0, 0}, {2560, 2560, 1536, 1280, 0}, {2048, 2048, 1152, 1280, 512}, {1280, 1152, 1024, 512, 448}},
+    // dH
+    {{4096, 256, 20, 12, 0}, {4096, 2048, 1792, 768, 0}, {4096, 3072, 2176, 1536, 0}, {4096, 2560, 2048, 1536, 0}, {1920, 1536, 1280, 1024, 256}},
+    // dX
+    {{4096, 256, 20, 12, 0}, {4096, 3072, 2048, 0, 0}, {3584, 3072, 2048, 1792, 0}, {2304, 2560, 1792, 1536, 0}, {1280, 1280, 1152, 512, 256}}};
 bool few_rows_pays(const Dims& D, RowTileKind kind) {
   const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;   // output columns f, contraction over d; else the other way round
   const long long active = D.N < D.Et ? D.N : D.Et;                  // experts with rows, at most
@@ -952,12 +957,7 @@ bool few_rows_pays(const Dims& D, RowTileKind kind) {
   int rc = 0, sc = 0;
   while (rc < kRowClasses - 1 && D.N >= (long long)kRowsBelow[rc] * D.Et) rc++;
   while (sc < kStepClasses - 1 && steps >= kStepsBelow[sc]) sc++;
-  if (kind == ROWTILE_GATE_UP) return tiles <= kFewTilesGateUp[rc];
-  // Many tiles of few rows: weights are all that counts, and a narrow tile's many blocks read them a little faster (dX,
-  // 4096 x 1024, 32 experts, 32 rows: 95 / 101; down, 7168 x 512, 64 experts, 8 rows: 91 / 98); between the two ranges they lose up to
-  // 15 %, the second round of blocks being almost empty.
-  if (tiles > 1024 && tiles <= 4096 && (kind == ROWTILE_DOWN ? rc == 0 && steps < 16 : rc <= 2 && steps < 64)) return true;
-  return tiles <= (kind == ROWTILE_DH ? kFewTilesDh : kFewTilesDownDx)[rc][sc];
+  return tiles <= (kind == ROWTILE_GATE_UP ? kFewTilesGateUp[rc] : kFewTiles[kind - ROWTILE_DOWN][rc][sc]);
 }
 
 // The row-tile GEMMs of one call of the expert FFN: of the forward (gate | up and down), of the backward (dH and dX) or the

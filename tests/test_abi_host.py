@@ -139,12 +139,12 @@ def test_missing_library_fails_loudly(monkeypatch):
     (512, 7168, 512, 1, 1, ("gate_up", "down", "dh", "dx")),
     (1024, 7168, 512, 1, 1, ("gate_up", "dh")),    # 128 tiles of gate | up and dH, 1792 of down and dX
     (8192, 7168, 512, 8, 1, ()),                   # 17000 tiles of down and dX, twice the time on them
-    (64, 7168, 1024, 8, 1, ("gate_up",)),          # 112 k-steps of dH, which the other kernel cuts along k
+    (64, 7168, 1024, 8, 1, ("gate_up", "down", "dx")),   # 112 k-steps of dH, which the other kernel cuts along k
     (32, 512, 2048, 4, 1, ("gate_up", "down", "dh")),   # 64 k-steps of dX
-    (32, 512, 14336, 4, 1, ()),                    # 32 tiles of down and dX, but 224 and 448 k-steps
+    (32, 512, 14336, 4, 1, ("dh",)),               # 32 tiles of down and dX, but 224 and 448 k-steps
     (8, 4096, 14336, 1, 1, ("gate_up",)),
-    (4096, 1024, 2048, 1, 1, ("down",)),
-    (1024, 4096, 1024, 32, 1, ("dx",)),            # 2048 tiles of few rows; 512 of dH, but 64 k-steps
+    (4096, 1024, 2048, 1, 1, ("down", "dx")),      # 1024 tiles of down and dX, 2048 of the others
+    (2048, 1024, 2048, 32, 1, ("down", "dh", "dx")),     # 1536 tiles of gate | up, 768 of down and dX
     (4096, 4096, 14336, 8, 2, ()),
     (0, 512, 1024, 8, 2, ("gate_up", "down", "dh", "dx")),
 ])

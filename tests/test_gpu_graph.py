@@ -14,11 +14,11 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ("tiny", W.WORKLOADS["tiny"]),
     ("imbalance_scaled", W.scaled_down(W.WORKLOADS["imbalance"])),      # empty experts, ragged tiles; down and dX on 256-row tiles
-    ("finegrained_scaled", W.scaled_down(W.WORKLOADS["finegrained"])),  # shared experts; all but dH on 256-row tiles
+    ("finegrained_scaled", W.scaled_down(W.WORKLOADS["finegrained"])),  # shared experts; gate | up on 256-row tiles
     # few tokens on wide experts: dH and dX cut their tiles along k, on arrival counters that every replay finds as the last left them
-    ("split", W.Workload("split", W.MoEShape(16, 4096, 1536, 4, 1), "router")),
+    ("split", W.Workload("split", W.MoEShape(16, 4096, 2048, 4, 1), "router")),
 ]
-SMALL_TILES = {"tiny": ("gate_up", "down", "dh", "dx"), "imbalance_scaled": ("gate_up", "dh"), "finegrained_scaled": ("dh",),
+SMALL_TILES = {"tiny": ("gate_up", "down", "dh", "dx"), "imbalance_scaled": ("gate_up", "dh"), "finegrained_scaled": ("down", "dh", "dx"),
                "split": ("gate_up", "down")}
 
 

@@ -447,9 +447,10 @@ def test_weight_gradient_edges(moe, d, f):
     (192, 576, [64, 65, 31, 0, 128], ALL_GEMMS),             # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
     (1088, 128, [200, 0, 7], ALL_GEMMS),                     # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
     (64, 64, [4500, 0, 257, 7], ALL_GEMMS),                  # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
-    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100], ("dh",)),   # dH: 1280 tiles (4 wavefronts per block) next to a dX of 320 k-steps
-    (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100], ("dh",)),    # dH: 2080 tiles
-    (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100], ()),        # 848 tiles of dH: neither one round of blocks nor many
+    # 8 row tiles of gate | up and dH on either side of a limit (1024 tiles for gate | up), next to a dX of 212 .. 520 k-steps
+    (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100], ("gate_up", "down", "dh")),
+    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100], ("dh",)),
+    (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100], ("dh",)),
 ])
 def test_small_problem_tiles(moe, d, f, counts, small):
     """The kernel for small problems, alone and next to the other one in a call (two schedules), and both sides of the rule
@@ -463,14 +464,14 @@ def test_small_problem_tiles(moe, d, f, counts, small):
     (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], ()),
     # experts of more than four row tiles, which the kernel walks column tile by column tile with a tall tile first, next to one
     # of four, walked in bands of 8 column tiles: 9 column tiles, i.e. a full band and a band of one
-    (1280, 2304, MANY_TILE_COUNTS, ()),
+    (1408, 2304, MANY_TILE_COUNTS, ()),
     # few tiles and 48 k-steps or more: cut along k.  dH of 128 steps in up to 8 parts, a tall tile, a short one and one of 65
     # rows among them, whose last part to arrive applies the d(SwiGLU) epilogue to the sums ...
-    (8192, 128, [300, 33, 0, 0, 65], ("gate_up",)),
+    (8192, 128, [300, 33, 0, 0, 65], ("gate_up", "down", "dx")),
     # ... down and dX, of 128 and 256 steps ...
-    (128, 8192, [300, 33, 0, 0, 65], ("dh",)),
-    # ... and dH (64 steps, 12 tiles) and dX (48 steps, 32 tiles) in one backward call, on the same arrival counters
-    (4096, 1536, [12, 0, 31], ("gate_up", "down")),
+    (128, 8192, [300, 33, 0, 0, 0, 0, 65], ("dh",)),
+    # ... and dH and dX (64 steps each, 16 and 32 tiles) in one backward call, on the same arrival counters
+    (4096, 2048, [12, 0, 31], ("gate_up", "down")),
 ])
 def test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small):
     """The kernel of large problems at whole-tensor precision."""
@@ -520,8 +521,8 @@ def test_weight_gradients_accumulate(moe, d, f, counts):
 @pytest.mark.parametrize("d,f,counts,small", [
     (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], ()),          # all on 256-row tiles
     (256, 192, [248] * 64 + [2048, 2048], ("dh",)),               # 256-row forward, dH on 64-row tiles, dX on 256-row tiles
-    (4096, 1088, [3, 0, 31, 9, 1, 0, 12, 30, 2, 2, 0, 5, 1, 1, 1, 2], ()),   # few rows; dH cut along k
-    (8192, 128, [300, 33, 0, 0, 65], ("gate_up",)),               # the recomputed GEMM alone on 64-row tiles; dH cut along k
+    (4096, 1088, [3, 0, 31, 9, 1, 0, 12, 30, 2, 2, 0, 5, 1, 1, 1, 2, 4], ("dx",)),   # few rows; dH cut along k
+    (8192, 128, [300, 33, 0, 0, 65], ("gate_up", "down", "dx")),  # all but dH, cut along k, on 64-row tiles
     (512, 1024, [64] * 8, ALL_GEMMS),
 ])
 def test_recomputing_backward_on_either_kernel(moe, d, f, counts, small):
