@@ -940,7 +940,7 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 constexpr int kRowClasses = 5, kStepClasses = 5;
 constexpr int kRowsBelow[kRowClasses - 1] = {16, 40, 64, 96};     // rows per expert on average
 constexpr int kStepsBelow[kStepClasses - 1] = {48, 64, 96, 128};  // k-steps of 64, both passes of dX counted
-constexpr int kFewTilesGateUp[kRowClasses] = {288, 640, 1024, 1024, 768};   // (the 256-row kernel never cuts these along k)
+constexpr int kFewTilesGateUp[kRowClasses] = {288, 1600, 1600, 1024, 768};   // (the 256-row kernel never cuts these along k)
 constexpr int kFewTiles[3][kRowClasses][kStepClasses] = {
     // down
     {{1024, 256, 20, 12, 0}, {2560, 2048, 1600, 0, 0}, {2560, 2560, 1536, 1280, 0}, {2048, 2048, 1152, 1280, 512}, {1280, 1152, 1024, 512, 448}},

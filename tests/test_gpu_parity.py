@@ -447,9 +447,9 @@ def test_weight_gradient_edges(moe, d, f):
     (192, 576, [64, 65, 31, 0, 128], ALL_GEMMS),             # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
     (1088, 128, [200, 0, 7], ALL_GEMMS),                     # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
     (64, 64, [4500, 0, 257, 7], ALL_GEMMS),                  # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
-    # 8 row tiles of gate | up and dH on either side of a limit (1024 tiles for gate | up), next to a dX of 212 .. 520 k-steps
+    # 8 row tiles of gate | up and dH on either side of a limit (1600 tiles for gate | up), next to a dX of 212 .. 520 k-steps
     (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100], ("gate_up", "down", "dh")),
-    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100], ("dh",)),
+    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100], ("gate_up", "dh")),
     (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100], ("dh",)),
 ])
 def test_small_problem_tiles(moe, d, f, counts, small):
@@ -469,7 +469,7 @@ def test_small_problem_tiles(moe, d, f, counts, small):
     # rows among them, whose last part to arrive applies the d(SwiGLU) epilogue to the sums ...
     (8192, 128, [300, 33, 0, 0, 65], ("gate_up", "down", "dx")),
     # ... down and dX, of 128 and 256 steps ...
-    (128, 8192, [300, 33, 0, 0, 0, 0, 65], ("dh",)),
+    (128, 8192, [300, 33, 0, 0, 0, 0, 65], ("gate_up", "dh")),
     # ... and dH and dX (64 steps each, 16 and 32 tiles) in one backward call, on the same arrival counters
     (4096, 2048, [12, 0, 31], ("gate_up", "down")),
 ])
