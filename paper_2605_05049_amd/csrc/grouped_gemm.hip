@@ -18,15 +18,18 @@
 //   router    dx = dlogits W_r     P = dlogits (KC)  Q = W_r (RC)      two K passes (head and remainder), E > 128
 //             dWr^T = X^T dlogits  P = X (RC)        Q = head | remainder (RC)  ragged K = part of the tokens, fp32 out
 //
-// Tiling: 512 threads = 8 wavefronts (2 along p x 4 along q); each wavefront owns 128 p x 64 q as 4x2 MFMA
-// 32x32x16 blocks (128 fp32 accumulators per lane).  Tiles stream HBM/L2 -> LDS with the direct 16-byte
-// global->LDS load (no register staging) into two 64 KB stages; step k+1 is in flight while step k is
-// multiplied, one barrier per step.  A direct load is addressed by a scalar base (advanced once per step) plus one
-// 32-bit per-lane offset that never changes, so the K loop does no per-lane address arithmetic.  The two wavefronts
-// that share a SIMD request their parts of the next stage at different times of a step (one right after the
-// barrier, the other half-way through its MFMAs): a wavefront is held up while its loads are accepted, and this way
-// its partner has MFMAs to issue meanwhile; fragment reads run ahead of their MFMAs so that the partner, alone on
-// the matrix pipe, does not stall on LDS latency.  The LDS destination of a direct load is fixed by the lane id, so bank
+// Tiling: 512 threads = 8 wavefronts (2 along p x 4 along q); each wavefront owns 128 p x 64 q as 8 x 4 MFMA
+// 16x16x32 blocks (128 fp32 accumulators per lane).  (That shape moves fewer accumulator bytes per multiply than 32x32x16, and
+// the chip, whose clock follows its power, runs it faster: 2.04 against 1.80 PFLOP/s in a loop of nothing but MFMAs on normal
+// values.)  Tiles stream HBM/L2 -> LDS with the direct 16-byte global->LDS load (no register staging) into two stages of 64 k.
+// The two wavefronts of a SIMD take turns: one reads fragments and requests loads while the other multiplies, 32 MFMAs at a
+// time, with a barrier between the turns (see the K loop); a load is in flight for up to a step and a half.  8192 rows on 8 equal
+// experts of 4096 x 14336: dX 1507 -> 1336 us (1440 TFLOP/s; matrix pipes busy 0.83 of the cycles at 1.66 GHz), down 764 -> 681,
+// gate | up 1554 -> 1498, dH 917 -> 876 against a schedule in which both wavefronts read, multiplied and loaded through the
+// whole step on 32x32x16 MFMAs; without any loads the loop is 5 % shorter in cycles, without fragment reads the same: what is
+// left is the turns (20 %) and the clock.
+// A direct load is addressed by a scalar base (advanced once per step) plus one 32-bit per-lane offset that never changes, so
+// the K loop does no per-lane address arithmetic.  The LDS destination of a direct load is fixed by the lane id, so bank
 // conflicts are avoided by choosing WHICH 16-byte chunk each lane fetches (an XOR swizzle of the chunk index with
 // row bits), and the fragment reads apply the same swizzle.  Every request is a whole 128-byte line (KC) or four of
 // them (RC): the vector L1 handles about one line per two cycles whatever part of it is used.  Rows past the end of
@@ -43,7 +46,6 @@ namespace moe {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BK = 64;                          // k step
@@ -51,10 +53,7 @@ constexpr int TILE = 256;                       // p extent, and (virtual) q ext
 constexpr int NTHREADS = 512;
 constexpr int TALL = TILE + 64;                 // rows of a tall tile: an expert's last full row tile plus up to 64 rows
 constexpr int OPERAND_BYTES = TILE * BK * 2;    // 32 KB per 256-row operand per stage
-constexpr int Q_STAGE_OFFSET = TALL * BK * 2;   // the Q operand follows the (up to 320-row, 40 KB) P operand
-constexpr int P_AREA_BYTES = Q_STAGE_OFFSET;    // a stage's P operand
-constexpr int STAGE_BYTES = Q_STAGE_OFFSET + OPERAND_BYTES;  // P + Q = 72 KB
-                                                // two stages = 144 KB of the 160 KB of LDS
+constexpr int LDS_BYTES = 2 * (TALL * BK * 2 + OPERAND_BYTES);   // two stages of a tall tile, or three of one of 128 rows: 144 of 160 KB
 constexpr int kNumXcd = 8;
 constexpr int kCusPerXcd = 32;
 // A tile is cut along K only if it has at least MOE_SPLIT_MIN_STEPS k-steps, into parts of at least MOE_SPLIT_PART_STEPS
@@ -66,30 +65,6 @@ constexpr int kCusPerXcd = 32;
 #ifndef MOE_SPLIT_PART_STEPS
 #define MOE_SPLIT_PART_STEPS 16
 #endif
-// How far ahead of their MFMAs a k-step reads its fragments (0: each group of 16 k reads its own; 1: half a group
-// ahead; 2: rolling, see the k-step): for row tiles of up to 256 rows, for tall row tiles, for the tall row tiles of the
-// SwiGLU forward, and for the weight gradient (whose transposing reads gained nothing from 2).
-#ifndef MOE_FRAG_PIPELINE_ROW
-#define MOE_FRAG_PIPELINE_ROW 2
-#endif
-#ifndef MOE_FRAG_PIPELINE_TALL
-#define MOE_FRAG_PIPELINE_TALL 2
-#endif
-#ifndef MOE_FRAG_PIPELINE_TALL_SWIGLU
-#define MOE_FRAG_PIPELINE_TALL_SWIGLU 1
-#endif
-#ifndef MOE_FRAG_PIPELINE_WGRAD
-#define MOE_FRAG_PIPELINE_WGRAD 1
-#endif
-// k offset inside a step at which wavefronts 0..3 request their share of the next stage: half-way through it, or
-// (the weight gradient and the SwiGLU forward, where it measured 1-2 % faster; 2 % slower in the others) after three quarters
-#ifndef MOE_EARLY_ISSUE_AT
-#define MOE_EARLY_ISSUE_AT 32
-#endif
-#ifndef MOE_EARLY_ISSUE_AT_WIDE
-#define MOE_EARLY_ISSUE_AT_WIDE 48
-#endif
-
 enum Epilogue { EPI_BF16 = 0, EPI_SWIGLU = 1, EPI_DSWIGLU = 2, EPI_F32 = 3 };
 
 struct GemmArgs {
@@ -125,6 +100,11 @@ struct TileOperand {
   int r_valid;              // valid r per half (<= 128 when split, <= 256 otherwise); beyond: clamped, never stored
 };
 
+// Position of chunk c (8 r-values of 16 chunks) inside k-row k's 256 bytes of a staged R-contiguous operand: the four k-rows that
+// a transposing read takes together lie in different quarters of the LDS banks, and so do, pair by pair, the k-rows 8 apart that
+// its lane groups take.
+__device__ __forceinline__ int rc_swizzle(int c, int k) { return c ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1); }
+
 // A 32 KB operand stage is filled by 32 direct-load instructions of 1 KB (instruction n fills LDS bytes [1024 n, +1024),
 // lane L the 16 bytes at +16 L); wavefront w issues instructions 4w..4w+3.  This returns the byte offset of lane L's 16
 // source bytes from the origin of the stage in global memory, i.e. from element (r = 0, k = first k of the step) of
@@ -145,34 +125,25 @@ __device__ __forceinline__ unsigned load_offset(const TileOperand& op, int n, in
     return (unsigned)(((size_t)rr * op.ld + c * 8) * 2);
   } else {
     const int kr = (n >> 1) * 4 + (lane >> 4);
-    const int c = (lane & 15) ^ ((kr & 3) << 2);
+    const int c = rc_swizzle(lane & 15, kr);
     int col = c * 8 + ((!SPLIT && (n & 1)) ? 128 : 0);
     col = col < op.r_valid ? col : max(op.r_valid - 8, 0);  // (operands narrower than 8 are padded by their owner)
     return (unsigned)(((size_t)kr * op.ld + col) * 2);
   }
 }
 
-// Issues this wavefront's 4 direct loads of one operand stage for the 64 k-values starting at k0 (`delta`: element
-// offset of the pass's tensors from the first pass's).
-template <bool RC, bool SPLIT, bool NARROW = false>
-__device__ __forceinline__ void issue_tile(const unsigned (&voff)[4], const TileOperand& op, ptrdiff_t delta, int k0, int k_end,
-                                           const uint16_t* zero_page, char* lds_tile, int wave, int lane) {
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int n = wave * 4 + i;
-    // Instructions that would only fetch rows or columns past the operand's valid extent are left out (short row
-    // tiles, the last column tile of a width that is not a multiple of 256, the router's skinny problems); those LDS
-    // rows then hold stale data, which only ever reaches accumulators that are never stored (an accumulator row or
-    // column depends on its own operand row alone)
-    if (NARROW && (RC ? (!SPLIT && (n & 1) && op.r_valid <= 128) : n * 8 >= op.r_valid)) continue;
-    const uint16_t* sb = ((RC && SPLIT && (n & 1)) ? op.base1 : op.base0) + delta + (RC ? (size_t)k0 * op.ld : (size_t)k0);
-    if (RC && k0 + BK > k_end) {  // the ragged end of K: k-rows past it come from the zeroed page
-      const int kr = (n >> 1) * 4 + (lane >> 4);
-      const char* g = (k0 + kr < k_end) ? reinterpret_cast<const char*>(sb) + voff[i] : reinterpret_cast<const char*>(zero_page);
-      direct_load16(g, lds_tile + n * 1024);
-    } else {
-      direct_load16(sb, voff[i], lds_tile + n * 1024);
-    }
+// Issues direct load n of an operand stage for the 64 k-values starting at k0 (`delta`: element offset of the pass's tensors
+// from the first pass's).
+template <bool RC, bool SPLIT, bool RAGGED_K>
+__device__ __forceinline__ void issue_load(unsigned voff, const TileOperand& op, ptrdiff_t delta, int k0, int k_end,
+                                           const uint16_t* zero_page, char* lds_tile, int n, int lane) {
+  const uint16_t* sb = ((RC && SPLIT && (n & 1)) ? op.base1 : op.base0) + delta + (RC ? (size_t)k0 * op.ld : (size_t)k0);
+  if (RC && RAGGED_K && k0 + BK > k_end) {  // the ragged end of K: k-rows past it come from the zeroed page
+    const int kr = (n >> 1) * 4 + (lane >> 4);
+    const char* g = (k0 + kr < k_end) ? reinterpret_cast<const char*>(sb) + voff : reinterpret_cast<const char*>(zero_page);
+    direct_load16(g, lds_tile + n * 1024);
+  } else {
+    direct_load16(sb, voff, lds_tile + n * 1024);
   }
 }
 
@@ -191,51 +162,26 @@ __device__ __forceinline__ void load8_agent(f32x4 (&v)[8], const float* p0, cons
       : "memory");
 }
 
-// MFMA operand fragment: 32 r-values x 16 k-values; lane l gets r = r0 + l%32, k = kk + 8*(l/32) .. +7.
+// MFMA operand fragment: 16 r-values x 32 k-values; lane l gets r = r0 + l%16, k = kk + 8*(l/16) .. +7.  It is addressed in
+// three parts: `off` = the lane's byte offset inside an operand area for kk = 0 (frag_offset), kk, and `area` = a wave-uniform
+// constant (the LDS address of the operand area, plus 2048 bytes for every 16 rows further down a K-contiguous operand,
+// whose swizzle has a period of 16 rows).  kk flips an address bit (K-contiguous: the 16-byte chunk index is XORed with the
+// row's swizzle, and kk / 8 occupies a bit of it that the lane's own part leaves clear) or adds 512 bytes per k-row pair
+// (R-contiguous).  Written this way the loop-invariant part, off ^ 2 kk or off, is one register per operand and kk
+// (K-contiguous) or per fragment (R-contiguous), and the rest goes into the read instruction's 16-bit offset field.
 template <bool RC>
-__device__ __forceinline__ bf16x8 read_frag(const char* tile, int r0, int kk, int lane) {
+__device__ __forceinline__ unsigned frag_offset(int r0, int lane) {
   if (!RC) {
-    const int r = r0 + (lane & 31);
-    const int c = (kk >> 3) + (lane >> 5);
-    return *reinterpret_cast<const bf16x8*>(tile + r * 128 + ((c ^ ((r >> 1) & 7)) << 4));
+    const int r = r0 + (lane & 15);
+    return (unsigned)(r * 128 + (((lane >> 4) ^ ((r >> 1) & 7)) << 4));
   } else {
     // Transposing read: inside each group of 16 lanes, lane p supplies the address of 4 consecutive r at k-row
     // p/4, r-chunk p%4, and receives the 4 k-rows of r = (group base) + p.
     const int p = lane & 15;
-    const int k = kk + 8 * (lane >> 5) + (p >> 2);
-    const int relem = r0 + 16 * ((lane >> 4) & 1) + 4 * (p & 3);
+    const int k = 8 * (lane >> 4) + (p >> 2);
+    const int relem = r0 + 4 * (p & 3);
     const int c = relem >> 3;  // 0..31: bit 4 = r-half, bits 0..3 = chunk inside the half
-    const char* a = tile + ((((k >> 2) << 1) + (c >> 4)) << 10) + ((k & 3) << 8) + (((c & 15) ^ ((k & 3) << 2)) << 4) +
-                    ((relem & 7) << 1);
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(a));
-    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(a + 2048));  // k + 4: the next group of 4 k-rows
-    union { struct { s16x4 lo, hi; } s; bf16x8 v; } u;
-    u.s.lo = lo;
-    u.s.hi = hi;
-    return u.v;
-  }
-}
-
-// The same fragment addressed in three parts: `off` = the lane's byte offset inside an operand area for kk = 0
-// (frag_offset), kk, and `area` = a wave-uniform constant (the LDS address of the operand area, plus 4096 bytes for every
-// 32 rows further down a K-contiguous operand, whose swizzle has a period of 16 rows).  kk flips two address bits
-// (K-contiguous: the 16-byte chunk index is XORed with the row's swizzle, and kk / 8 occupies bits of it that the
-// lane's own part leaves clear) or adds 512 bytes per k-row pair (R-contiguous).  Written this way the loop-invariant
-// part, off ^ 2 kk or off, is one register per operand and kk (K-contiguous) or per fragment (R-contiguous), and the
-// rest goes into the read instruction's 16-bit offset field: 8 to 12 address registers over the K loop where one
-// address per fragment, stage and kk took 48.
-template <bool RC>
-__device__ __forceinline__ unsigned frag_offset(int r0, int lane) {
-  if (!RC) {
-    const int r = r0 + (lane & 31);
-    return (unsigned)(r * 128 + (((lane >> 5) ^ ((r >> 1) & 7)) << 4));
-  } else {
-    const int p = lane & 15;
-    const int k = 8 * (lane >> 5) + (p >> 2);
-    const int relem = r0 + 16 * ((lane >> 4) & 1) + 4 * (p & 3);
-    const int c = relem >> 3;
-    return (unsigned)(((((k >> 2) << 1) + (c >> 4)) << 10) + ((k & 3) << 8) + (((c & 15) ^ ((k & 3) << 2)) << 4) + ((relem & 7) << 1));
+    return (unsigned)(((((k >> 2) << 1) + (c >> 4)) << 10) + ((k & 3) << 8) + (rc_swizzle(c & 15, k) << 4) + ((relem & 7) << 1));
   }
 }
 template <bool RC>
@@ -247,12 +193,27 @@ __device__ __forceinline__ bf16x8 read_frag_at(unsigned off, int kk, unsigned ar
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
     const unsigned a = off + (unsigned)(kk * 512) + area;
     s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(size_t)a);
-    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(size_t)(a + 2048u));
+    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(size_t)(a + 2048u));   // k + 4: the next group of 4 k-rows
     union { struct { s16x4 lo, hi; } s; bf16x8 v; } u;
     u.s.lo = lo;
     u.s.hi = hi;
     return u.v;
   }
+}
+
+// s_waitcnt vmcnt(n), the other counters not waited for
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N < 64, "vmcnt has 6 bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+// A barrier that nothing moves across, without the waits of __syncthreads (what has to have landed is waited for by the caller).
+__device__ __forceinline__ void bare_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // How a launch cuts an expert's n rows into row tiles.  TILES_PLAIN: ceil(n / 256).  TILES_TALL: a remainder of at most
@@ -274,17 +235,15 @@ __device__ __forceinline__ unsigned xcc_id() { return (unsigned)__builtin_amdgcn
 template <int KIND, bool P_RC, bool Q_RC, int NQ, int NPASS, int EPI>
 __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A) {
   static_assert((KIND == 1) == (EPI == EPI_F32) && (EPI != EPI_F32 || NQ == 2), "the fp32 epilogue adds the two halves of a weight gradient");
-  // Two stages of P (up to 320 rows) | Q each.
-  __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE_BYTES];
-  auto p_area = [&](int s) __attribute__((always_inline)) { return lds + s * STAGE_BYTES; };
-  auto q_area = [&](int s) __attribute__((always_inline)) { return lds + s * STAGE_BYTES + P_AREA_BYTES; };
+  __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
   constexpr int TQ = TILE / NQ;  // q extent per output tensor
+  constexpr bool RAGGED_K = KIND == 1 || (NPASS == 2 && Q_RC);   // the router's: the FFN's contractions over d and f are whole steps
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wq = wave >> 1;         // 0..3 along q
-  const int late = wave >> 2;       // wavefronts 4..7 share their SIMDs with 0..3 and load at another time of the step
+  const int second_half = wave >> 2;   // wavefronts 4..7 share their SIMDs with 0..3 and run one phase behind them
 
   // ---- block id -> tile ----
   int expert, p_row0 = 0, p_valid, q0_col, k_len;
@@ -390,9 +349,8 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   }
   const int q_valid = min(TQ, A.q_dim - q0_col);
 
-  // LDS row origin of this wavefront's two q fragments
-  const int qr0 = (NQ == 2) ? wq * 32 : wq * 64;
-  const int qr1 = (NQ == 2) ? 128 + wq * 32 : wq * 64 + 32;
+  // LDS row origin of this wavefront's four q fragments
+  auto qr = [&](int a) __attribute__((always_inline)) { return NQ == 2 ? (a >> 1) * 128 + wq * 32 + (a & 1) * 16 : wq * 64 + a * 16; };
 
   TileOperand P, Q;
   ptrdiff_t p_pass_delta = 0, q_pass_delta = 0;  // second K pass (dX): same rows of the second pair of tensors
@@ -418,225 +376,213 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     Q.ld = A.q_ld;
     Q.r_valid = q_valid;
   }
-  // Tiles that are neighbours along p share their q panel and run side by side on one XCD, in step with each other.
-  // In every other one of them each wavefront issues the q loads of the wavefront that loads at the other time of
-  // the step (any wavefront may issue any instruction of a stage: the LDS destination comes with the instruction).
-  // Each half of the shared panel is then requested right after the barrier by half of its users, and the requests
-  // the other half makes half a step later find it in, or on its way to, the L2.  (Left out where it measured
-  // slower or was not measured: the forward down projection and the router's skinny problems.)
-  constexpr bool ALTERNATE_Q = !(KIND == 0 && Q_RC && NQ == 1 && EPI == EPI_BF16);
-  const int iwq = ALTERNATE_Q ? (wave ^ ((p_tile_idx & 1) << 2)) : wave;
-  unsigned pvo[4], qvo[4];
+  unsigned qvo[4];
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    pvo[i] = load_offset<P_RC, false>(P, wave * 4 + i, lane);
-    qvo[i] = load_offset<Q_RC, NQ == 2>(Q, iwq * 4 + i, lane);
-  }
+  for (int i = 0; i < 4; i++) qvo[i] = load_offset<Q_RC, NQ == 2>(Q, wave * 4 + i, lane);
   const int nk_pass = (k_len + BK - 1) / BK;  // k-steps per K pass
   const int nk = nk_pass * NPASS;             // k-steps of the whole contraction
-  // this wavefront's 8 direct loads of step j of the contraction
-  auto issue_as = [&](auto narrow_p, int j, char* p_dst, char* q_dst) __attribute__((always_inline)) {
-    const bool second = (NPASS == 2) && j >= nk_pass;
-    const int k0 = (second ? j - nk_pass : j) * BK;
-    issue_tile<P_RC, false, decltype(narrow_p)::value>(pvo, P, second ? p_pass_delta : (ptrdiff_t)0, k0, k_len, A.zero_page, p_dst, wave, lane);
-    issue_tile<Q_RC, NQ == 2>(qvo, Q, second ? q_pass_delta : (ptrdiff_t)0, k0, k_len, A.zero_page, q_dst, iwq, lane);
-  };
   // the k-steps this block multiplies: all of them, or its part of a split tile
   const int kt_per = (nk + split - 1) / split;
   const int kt_begin = part * kt_per, kt_end = min(nk, kt_begin + kt_per);
-  // (the first stage is requested before anything else is set up; rows a short tile does not have are clamped here)
-  if (kt_begin < kt_end) issue_as(std::false_type{}, kt_begin, p_area(0), q_area(0));
-  // Height class of the tile: each of the two wavefronts along p multiplies PB blocks of 32 rows (4, 2 or 1), so a
-  // ragged last row tile of an expert issues MFMAs and row loads for its class (256, 128 or 64 rows) only.
+  // Height class of the tile: the two wavefronts along p multiply PB blocks of 32 rows each (5, 4, 2 or 1), so a
+  // ragged last row tile of an expert issues MFMAs and row loads for its class (320, 256, 128 or 64 rows) only.
   auto run = [&](auto pb_c) __attribute__((always_inline)) {
   constexpr int PB = decltype(pb_c)::value;
-  // (a short tile leaves out the loads of the rows it does not have)
-  // a tall tile's rows 256.. are one more instruction per wavefront (instruction 32 + wave: rows 256 + 8 wave .. +7)
-  const unsigned pvo_tall = (PB == 5) ? load_offset<P_RC, false>(P, 32 + wave, lane) : 0u;
-  auto issue_tall = [&](int j, char* p_dst) __attribute__((always_inline)) {
-    if (PB == 5 && (32 + wave) * 8 < p_valid) {
-      const bool second = (NPASS == 2) && j >= nk_pass;
-      const int k0 = (second ? j - nk_pass : j) * BK;
-      direct_load16(P.base0 + (second ? p_pass_delta : (ptrdiff_t)0) + k0, pvo_tall, p_dst + (32 + wave) * 1024);
-    }
+  // A tile's rows are worked on in parts of 128 (a wavefront: 64, or 4 blocks of 16), a tall tile's last 64 in a third.
+  constexpr int PARTS = PB == 5 ? 3 : PB == 4 ? 2 : 1;
+  constexpr int P_STAGE = PB == 5 ? TALL * BK * 2 : PB * 64 * BK * 2;   // bytes of a stage's P operand
+  constexpr int STAGES = PARTS == 1 ? 3 : 2;
+  static_assert(STAGES * (P_STAGE + OPERAND_BYTES) <= LDS_BYTES, "the stages fit");
+  // (all stages of P, then all of Q: an operand's stages then share their address registers)
+  auto p_area = [&](int s) __attribute__((always_inline)) { return lds + s * P_STAGE; };
+  auto q_area = [&](int s) __attribute__((always_inline)) { return lds + STAGES * P_STAGE + s * OPERAND_BYTES; };
+  // first row of block b (32 rows) of this wavefront
+  auto p_row = [&](int b) __attribute__((always_inline)) {
+    return PB == 1 ? (wave & 1) * 32 : b == 4 ? 256 + (wave & 1) * 32 : (b >> 1) * 128 + (wave & 1) * 64 + (b & 1) * 32;
   };
-  auto issue = [&](int j, int s) __attribute__((always_inline)) {
-    issue_as(std::integral_constant<bool, (PB < 4)>{}, j, p_area(s), q_area(s));
-    issue_tall(j, p_area(s));
+  f32x4 acc[4][2 * PB];  // [q block][p block]
+#pragma unroll
+  for (int a = 0; a < 4; a++)
+#pragma unroll
+    for (int b = 0; b < 2 * PB; b++)
+#pragma unroll
+      for (int v = 0; v < 4; v++) acc[a][b][v] = 0.f;
+  // Direct loads.  P: part h (128 rows) is 16 instructions, two of each wavefront (K-contiguous: instruction n = rows 8 n ..; R-
+  // contiguous: n = 2 j + h); a tall tile's rows 256.. are one more of each.  Q: four of each.
+  auto p_instr = [&](int h, int i) __attribute__((always_inline)) {
+    return PB == 1 ? wave : h == 2 ? 32 + wave : P_RC ? 2 * (2 * wave + i) + h : 16 * h + 2 * wave + i;
   };
-  if (kt_begin < kt_end) issue_tall(kt_begin, p_area(0));   // (the rest of the first stage was requested above)
-  const int wp = (wave & 1) * (PB * 32);  // p origin of this wavefront
-  f32x16 acc[2][PB];  // [q sub-tile a][p sub-tile b]
+  constexpr int P_LOADS = PB == 5 ? 5 : PB == 1 ? 1 : PB;
+  unsigned pvo[P_LOADS];
 #pragma unroll
-  for (int a = 0; a < 2; a++)
+  for (int i = 0; i < P_LOADS; i++) pvo[i] = load_offset<P_RC, false>(P, p_instr(i >> 1, i & 1), lane);
+  auto issue_p = [&](int h, int j, int s) __attribute__((always_inline)) {   // part h of step j
+    const bool second = (NPASS == 2) && j >= nk_pass;
+    const int k0 = (second ? j - nk_pass : j) * BK;
 #pragma unroll
-    for (int b = 0; b < PB; b++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) acc[a][b][v] = 0.f;
-
-  // One k-step: wait for stage `cur`, multiply it, and meanwhile fill `nxt` with step kt+1.  The two wavefronts of a
-  // SIMD request their share of the next stage at different times of the step (one before its MFMAs, the other
-  // between its two halves of them), so that while one is held up issuing loads the other keeps the matrix pipe busy.
-  // (next to a tall tile's 160 accumulator registers the SwiGLU forward, with its two q tensors, has room for half a
-  // group of fragments in flight only; a register spilled inside the K loop is ruinous here: its reload waits on the
-  // counter that the direct loads share)
-  constexpr int FRAG_PIPELINE = (PB == 5) ? (EPI == EPI_SWIGLU ? MOE_FRAG_PIPELINE_TALL_SWIGLU : MOE_FRAG_PIPELINE_TALL)
-                                          : (KIND == 0) ? MOE_FRAG_PIPELINE_ROW : MOE_FRAG_PIPELINE_WGRAD;
-  // Per-lane LDS offsets of this wavefront's fragments (at kk = 0) from the start of a stage.
-  unsigned p_off[PB], q_off[2];
-#pragma unroll
-  for (int b = 0; b < PB; b++) p_off[b] = frag_offset<P_RC>(wp + 32 * b, lane);
-  q_off[0] = frag_offset<Q_RC>(qr0, lane);
-  q_off[1] = frag_offset<Q_RC>(qr1, lane);
-  auto k_step = [&](int cur, int nxt, int kt) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this thread's loads of step kt have landed in LDS
-    __syncthreads();                     // ... and everyone's; everyone is also done reading the other stage
-    if (late && kt + 1 < kt_end) issue(kt + 1, nxt);
-    const unsigned p_base = (unsigned)(size_t)(lptr_t)p_area(cur), q_base = (unsigned)(size_t)(lptr_t)q_area(cur);
-    // (K-contiguous operand: 32 rows further is 4096 bytes further with the same swizzle, so all fragments of the
-    // operand share the address register of the first and differ in the instruction's offset field)
-    auto rp = [&](int b, int kk) __attribute__((always_inline)) {
-      return P_RC ? read_frag_at<P_RC>(p_off[b], kk, p_base) : read_frag_at<P_RC>(p_off[0], kk, p_base + 4096u * b);
-    };
-    auto rq = [&](int a, int kk) __attribute__((always_inline)) {
-      return Q_RC ? read_frag_at<Q_RC>(q_off[a], kk, q_base) : read_frag_at<Q_RC>(q_off[0], kk, q_base + 128u * (NQ == 2 ? 128 : 32) * a);
-    };
-    constexpr int EARLY_AT = (KIND == 1 || EPI == EPI_SWIGLU) ? MOE_EARLY_ISSUE_AT_WIDE : MOE_EARLY_ISSUE_AT;
-    auto early_issue = [&](int kk) __attribute__((always_inline)) {
-      if (kk == EARLY_AT) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (!late && kt + 1 < kt_end) issue(kt + 1, nxt);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    if constexpr (FRAG_PIPELINE == 0) {
-#pragma unroll
-      for (int kk = 0; kk < BK; kk += 16) {
-        early_issue(kk);
-        bf16x8 pf[PB], qf[2];
-        qf[0] = rq(0, kk);
-        qf[1] = rq(1, kk);
-#pragma unroll
-        for (int b = 0; b < PB; b++) pf[b] = rp(b, kk);
-#pragma unroll
-        for (int b = 0; b < PB; b++)
-#pragma unroll
-          for (int a = 0; a < 2; a++)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[a], pf[b], acc[a][b], 0, 0, 0);
-      }
-    } else if constexpr (FRAG_PIPELINE == 1) {
-      // The fragments of a group of 16 k are read half a group ahead of the MFMAs that use them: the p blocks of a
-      // group's second half while its first half multiplies, the q fragments (two sets) and the first p blocks of
-      // the next group while the second half does.
-      constexpr int HA = (PB + 1) / 2;   // p blocks of the first half
-      bf16x8 pf[PB], qf[2][2];
-      auto read_half_a = [&](int kk, bf16x8 (&q)[2]) __attribute__((always_inline)) {
-        q[0] = rq(0, kk);
-        q[1] = rq(1, kk);
-#pragma unroll
-        for (int b = 0; b < HA; b++) pf[b] = rp(b, kk);
-      };
-      read_half_a(0, qf[0]);
-#pragma unroll
-      for (int g = 0; g < BK / 16; g++) {
-        const int kk = 16 * g;
-        early_issue(kk);
-#pragma unroll
-        for (int b = HA; b < PB; b++) pf[b] = rp(b, kk);
-#pragma unroll
-        for (int b = 0; b < HA; b++)
-#pragma unroll
-          for (int a = 0; a < 2; a++)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[g & 1][a], pf[b], acc[a][b], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (g + 1 < BK / 16) read_half_a(kk + 16, qf[(g + 1) & 1]);
-#pragma unroll
-        for (int b = HA; b < PB; b++)
-#pragma unroll
-          for (int a = 0; a < 2; a++)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[g & 1][a], pf[b], acc[a][b], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    } else {
-      // Rolling fragments: a p fragment is read again, for the next group of 16 k, right after the two MFMAs that use
-      // it; the two q fragments, which every MFMA of a group uses, alternate between two sets.  A wavefront that is
-      // alone on its SIMD's matrix pipe (its partner is held up issuing loads) then does not stall on the LDS latency
-      // between groups, and the LDS reads are spread evenly between the MFMAs.
-      bf16x8 pf[PB], qf[2][2];
-      qf[0][0] = rq(0, 0);
-      qf[0][1] = rq(1, 0);
-#pragma unroll
-      for (int b = 0; b < PB; b++) pf[b] = rp(b, 0);
-#pragma unroll
-      for (int g = 0; g < BK / 16; g++) {
-        const int kk = 16 * g;
-        const bool more = g + 1 < BK / 16;
-        early_issue(kk);
-#pragma unroll
-        for (int b = 0; b < PB; b++) {
-          acc[0][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[g & 1][0], pf[b], acc[0][b], 0, 0, 0);
-          acc[1][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[g & 1][1], pf[b], acc[1][b], 0, 0, 0);
-          if (more) {
-            pf[b] = rp(b, kk + 16);
-            if (b == 0) qf[(g + 1) & 1][0] = rq(0, kk + 16);
-            if (b == (PB > 2 ? 1 : 0)) qf[(g + 1) & 1][1] = rq(1, kk + 16);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
+    for (int i = 0; i < (h == 2 || PB == 1 ? 1 : 2); i++)
+      issue_load<P_RC, false, RAGGED_K>(pvo[2 * h + i], P, second ? p_pass_delta : (ptrdiff_t)0, k0, k_len, A.zero_page, p_area(s), p_instr(h, i), lane);
   };
-  // Tiles of at most 64 rows (PB == 1) multiply little per step and are bound by the latency of their loads, and
-  // their P operand needs 8 KB of a stage's 40: they run a ring of three slots, two steps ahead instead of one.
-  //   slot 0: the first stage's areas (the first stage was requested above)
-  //   slot 1: the second stage's areas
-  //   slot 2: P at 8 KB into the second P area, Q at 8 KB into the first (rows 64.. of P areas, which these tiles never read)
-  // Every wavefront issues one P instruction (rows 8 w .. 8 w + 7, clamped onto the tile's last row) and its four Q
-  // instructions per step: 5 loads, the same for all, so that "all but the youngest step" is vmcnt(5).
+  auto issue_q = [&](int j, int s) __attribute__((always_inline)) {
+    const bool second = (NPASS == 2) && j >= nk_pass;
+    const int k0 = (second ? j - nk_pass : j) * BK;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      issue_load<Q_RC, NQ == 2, RAGGED_K>(qvo[i], Q, second ? q_pass_delta : (ptrdiff_t)0, k0, k_len, A.zero_page, q_area(s), wave * 4 + i, lane);
+  };
+  const unsigned p_off0 = frag_offset<P_RC>(p_row(0), lane), p_off1 = frag_offset<P_RC>(p_row(0) + 16, lane);
+  const unsigned p_off2 = P_RC ? frag_offset<P_RC>(p_row(0) + 32, lane) : 0u, p_off3 = P_RC ? frag_offset<P_RC>(p_row(0) + 48, lane) : 0u;
+  unsigned q_off[4];
+#pragma unroll
+  for (int a = 0; a < 4; a++) q_off[a] = frag_offset<Q_RC>(qr(a), lane) + (unsigned)(size_t)(lptr_t)q_area(0);
+  const unsigned p_off_tall = PB == 5 ? frag_offset<P_RC>(p_row(4), lane) : 0u;
+  // fragment of p block b (16 rows, 0..3) of part h / of q block a, k-values kk .. kk + 31 of the step in stage s
+  // (K-contiguous: 16 rows further is 2048 bytes further with the same swizzle, so the fragments of the operand share an
+  // address register and differ in the instruction's offset field)
+  auto rp = [&](int h, int b, int kk, int s) __attribute__((always_inline)) {
+    const unsigned base = (unsigned)(size_t)(lptr_t)p_area(s);
+    if (P_RC) return read_frag_at<P_RC>(b == 0 ? p_off0 : b == 1 ? p_off1 : b == 2 ? p_off2 : p_off3, kk, base + 1024u * h);
+    return h == 2 ? read_frag_at<P_RC>(p_off_tall, kk, base + 2048u * b) : read_frag_at<P_RC>(p_off0, kk, base + 16384u * h + 2048u * b);
+  };
+  auto rq = [&](int a, int kk, int s) __attribute__((always_inline)) {
+    const unsigned base = (unsigned)(s * OPERAND_BYTES);
+    if (Q_RC) return read_frag_at<Q_RC>(q_off[a], kk, base);
+    static_assert(Q_RC || NQ == 1, "a pair of q tensors is R-contiguous");
+    return read_frag_at<Q_RC>(q_off[0], kk, base + 2048u * a);
+  };
   if constexpr (PB == 1) {
-    const unsigned pvo1 = load_offset<P_RC, false>(P, wave, lane);
-    auto issue1 = [&](int j, char* p_dst, char* q_dst) __attribute__((always_inline)) {
-      const bool second = (NPASS == 2) && j >= nk_pass;
-      const int k0 = (second ? j - nk_pass : j) * BK;
-      direct_load16(P.base0 + (second ? p_pass_delta : (ptrdiff_t)0) + k0, pvo1, p_dst + wave * 1024);
-      issue_tile<Q_RC, NQ == 2>(qvo, Q, second ? q_pass_delta : (ptrdiff_t)0, k0, k_len, A.zero_page, q_dst, iwq, lane);
-    };
-    auto ring_step = [&](const char* p_lds, const char* q_lds, char* p_fill, char* q_fill, int kt) {
-      if (kt + 1 < kt_end) __builtin_amdgcn_s_waitcnt(0x0F75);  // vmcnt(5): all but the 5 loads of step kt + 1
-      else __builtin_amdgcn_s_waitcnt(0x0F70);
-      __syncthreads();   // step kt has landed for everyone; everyone is done with step kt - 1, whose slot step kt + 2 takes
-      if (late && kt + 2 < kt_end) issue1(kt + 2, p_fill, q_fill);
+    // Tiles of at most 64 rows multiply little per step and are bound by the latency of their loads: a ring of three stages of 8 +
+    // 32 KB, two steps ahead, one barrier per step.  5 loads of each wavefront per step, so that "all but the youngest step" is
+    // vmcnt(5).
+    if (kt_begin < kt_end) { issue_p(0, kt_begin, 0); issue_q(kt_begin, 0); }
+    if (kt_begin + 1 < kt_end) { issue_p(0, kt_begin + 1, 1); issue_q(kt_begin + 1, 1); }
+    auto ring_step = [&](int s, int fill, int kt) __attribute__((always_inline)) {
+      if (kt + 1 < kt_end) wait_loads<5>();
+      else wait_loads<0>();
+      __syncthreads();   // step kt has landed for everyone; everyone is done with step kt - 1, whose stage step kt + 2 takes
+      auto fill_next = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (kt + 2 < kt_end) { issue_p(0, kt + 2, fill); issue_q(kt + 2, fill); }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      if (second_half) fill_next();
 #pragma unroll
-      for (int kk = 0; kk < BK; kk += 16) {
-        if (kk == MOE_EARLY_ISSUE_AT) {
-          __builtin_amdgcn_sched_barrier(0);
-          if (!late && kt + 2 < kt_end) issue1(kt + 2, p_fill, q_fill);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        const bf16x8 q0f = read_frag<Q_RC>(q_lds, qr0, kk, lane), q1f = read_frag<Q_RC>(q_lds, qr1, kk, lane);
-        const bf16x8 p0f = read_frag<P_RC>(p_lds, wp, kk, lane);
-        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0f, p0f, acc[0][0], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q1f, p0f, acc[1][0], 0, 0, 0);
+      for (int kk = 0; kk < BK; kk += 32) {
+        if (kk == 32 && !second_half) fill_next();
+        bf16x8 qf[4], pf[2];
+#pragma unroll
+        for (int a = 0; a < 4; a++) qf[a] = rq(a, kk, s);
+#pragma unroll
+        for (int b = 0; b < 2; b++) pf[b] = rp(0, b, kk, s);
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+          for (int a = 0; a < 4; a++) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[a], pf[b], acc[a][b], 0, 0, 0);
       }
     };
-    char* const rp[3] = {p_area(0), p_area(1), p_area(1) + 8192};
-    char* const rq[3] = {q_area(0), q_area(1), p_area(0) + 8192};
-    if (kt_begin + 1 < kt_end) issue1(kt_begin + 1, rp[1], rq[1]);
     for (int kt = kt_begin; kt < kt_end; kt += 3) {
-      ring_step(rp[0], rq[0], rp[2], rq[2], kt);
-      if (kt + 1 < kt_end) ring_step(rp[1], rq[1], rp[0], rq[0], kt + 1);
-      if (kt + 2 < kt_end) ring_step(rp[2], rq[2], rp[1], rq[1], kt + 2);
+      ring_step(0, 2, kt);
+      if (kt + 1 < kt_end) ring_step(1, 0, kt + 1);
+      if (kt + 2 < kt_end) ring_step(2, 1, kt + 2);
     }
   } else {
-    for (int kt = kt_begin; kt < kt_end; kt += 2) {
-      k_step(0, 1, kt);
-      if (kt + 1 < kt_end) k_step(1, 0, kt + 1);
+    // Two wavefronts share a SIMD, and at any time one multiplies while the other uses the memory.  A step has PARTS phases of two
+    // halves each: in the first a wavefront reads the fragments of a part of its rows (and, in the first phase, of its q columns) from
+    // LDS and requests some of the coming steps' data, in the second it issues nothing but MFMAs (32 of a part of 64 rows: 512
+    // cycles).  Every half ends with a barrier, and wavefronts 4..7 start one half later than 0..3.
+    //
+    // What a phase has read is free for the loads of a later step (two steps on; with three stages the step whose stage the one
+    // before last has left) from the next phase on: the wavefronts that run behind have read it, and waited for it, one half
+    // after the first.  So in phase h > 0 of step j a wavefront requests part h - 1 of step j + 2 (with part 0 also q), in phase 0
+    // the last part of step j + 1 (with three stages everything of step j + 2): a load has four to six halves to land.  It is
+    // waited for by its count: before the barrier in front of the half that reads it, all but the loads that a wavefront
+    // has issued after it (the first four wavefronts wait behind their MFMAs, the others behind their reads).
+    constexpr int N0 = 6, N1 = PARTS >= 2 ? 2 : 0, N2 = PARTS == 3 ? 1 : 0, NS = N0 + N1 + N2;   // loads of the parts; of a step
+    const int n_steps = kt_end - kt_begin;
+    auto request = [&](int h, int j, int s) __attribute__((always_inline)) {   // part h of step j (counted from kt_begin)
+      if (j < n_steps) {
+        issue_p(h, kt_begin + j, s);
+        if (h == 0) issue_q(kt_begin + j, s);
+      }
+    };
+    // all loads of part h of step j have landed: what may be outstanding when phase h - 1 of step j (h = 0: the last of j - 1) ends
+    auto landed = [&](int h, int j) __attribute__((always_inline)) {
+      if (j + 1 < n_steps) {
+        if (PARTS == 1) wait_loads<NS>();
+        else if (h == 0) wait_loads<PARTS == 1 ? 0 : 2 * NS - N0 - (PARTS == 2 ? N1 : N2)>();   // (the last part of step j + 1 is not requested yet)
+        else if (h == 1) wait_loads<N2 + NS>();
+        else if (j + 2 < n_steps) wait_loads<NS + N0>();
+        else wait_loads<NS>();
+      } else {
+        if (h == 0) wait_loads<N1 + N2>();
+        else if (h == 1) wait_loads<N2>();
+        else wait_loads<0>();
+      }
+    };
+    request(0, 0, 0);
+    if (PARTS >= 2) request(1, 0, 0);
+    if (PARTS == 3) request(2, 0, 0);
+    request(0, 1, 1);
+    if (PARTS == 3) request(1, 1, 1);
+    landed(0, 0);
+    bare_barrier();
+    if (second_half) bare_barrier();
+    bf16x8 qf[4][2], pf[4][2];
+    auto step = [&](int j, int s, int s1, int s2) __attribute__((always_inline)) {   // stages of steps j, j + 1, j + 2
+#pragma unroll
+      for (int h = 0; h < PARTS; h++) {
+        const int nb = h == 2 ? 2 : 4;   // p blocks of the part
+        if (h == 0) {
+#pragma unroll
+          for (int g = 0; g < 2; g++)
+#pragma unroll
+            for (int a = 0; a < 4; a++) qf[a][g] = rq(a, 32 * g, s);
+        }
+#pragma unroll
+        for (int g = 0; g < 2; g++)
+#pragma unroll
+          for (int b = 0; b < nb; b++) pf[b][g] = rp(h, b, 32 * g, s);
+        __builtin_amdgcn_sched_barrier(0);
+        if (PARTS == 1) request(0, j + 2, s2);
+        else if (h == 0) request(PARTS - 1, j + 1, s1);
+        else request(h - 1, j + 2, s2);
+        const int nh = h + 1 < PARTS ? h + 1 : 0, nj = h + 1 < PARTS ? j : j + 1;   // the next phase
+        if (second_half) landed(nh, nj);
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the fragments are in registers
+        bare_barrier();
+        __builtin_amdgcn_s_setprio(1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < 2; g++)
+#pragma unroll
+          for (int b = 0; b < nb; b++)
+#pragma unroll
+            for (int a = 0; a < 4; a++)
+              acc[a][4 * h + b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[a][g], pf[b][g], acc[a][4 * h + b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
+        if (!second_half) landed(nh, nj);
+        bare_barrier();
+      }
+    };
+    if constexpr (STAGES == 2) {
+      for (int j = 0; j < n_steps; j += 2) {
+        step(j, 0, 1, 0);
+        if (j + 1 < n_steps) step(j + 1, 1, 0, 1);
+      }
+    } else {
+      for (int j = 0; j < n_steps; j += 3) {
+        step(j, 0, 1, 2);
+        if (j + 1 < n_steps) step(j + 1, 1, 2, 0);
+        if (j + 2 < n_steps) step(j + 2, 2, 0, 1);
+      }
     }
+    if (!second_half) bare_barrier();
   }
 
-  // ---- epilogue.  acc[a][b][v] holds  p = wp + 32b + lane%32,  q (inside the output's tile) =
-  //      NQ == 1: 64 wq + 32a + 8(v/4) + 4(lane/32) + v%4      NQ == 2: 32 wq + 8(v/4) + 4(lane/32) + v%4 of output a.
-  // Lanes 0..31 of an accumulator own 32 different rows, so storing from the accumulators would touch 64 cache lines
+  // ---- epilogue.  acc[a][2 b + i][v] holds  p = p_row(b) + 16 i + lane%16,  q (inside the output's tile) =
+  //      NQ == 1: 64 wq + 16 a + 4 (lane/16) + v      NQ == 2: 32 wq + 16 (a%2) + 4 (lane/16) + v of output a/2.
+  // The lanes of an accumulator own 16 different rows, so storing from the accumulators would touch 16 cache lines
   // per instruction.  Instead each wavefront bounces 32 rows at a time through its own 16 KB of the (now idle) LDS
   // and reads them back row-wise: every global access is then 16 bytes per lane over 64..256 contiguous bytes per row,
   // and the SwiGLU element-wise math runs on that side (8 consecutive q per lane).
@@ -689,13 +635,10 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 #pragma unroll
     for (int b = 0; b < PB; b++) {
 #pragma unroll
-      for (int a = 0; a < 2; a++)
+      for (int a = 0; a < 4; a++)
 #pragma unroll
-        for (int v4 = 0; v4 < 4; v4++) {
-          const int q = 32 * a + 8 * v4 + 4 * (lane >> 5);
-          float4 r = make_float4(acc[a][b][4 * v4], acc[a][b][4 * v4 + 1], acc[a][b][4 * v4 + 2], acc[a][b][4 * v4 + 3]);
-          *reinterpret_cast<float4*>(wlds + (lane & 31) * PITCH + q * 4) = r;
-        }
+        for (int i = 0; i < 2; i++)
+          *reinterpret_cast<f32x4*>(wlds + (16 * i + (lane & 15)) * PITCH + (16 * a + 4 * (lane >> 4)) * 4) = acc[a][2 * b + i];
       __builtin_amdgcn_s_waitcnt(0xC07F);
       __builtin_amdgcn_wave_barrier();
       constexpr int LPR = W / 4;          // lanes per row (4 fp32 per lane)
@@ -704,8 +647,8 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
       for (int it = 0; it < 32 / RPI; it++) {
         const int r = it * RPI + lane / LPR;
         const int q = (lane % LPR) * 4;
-        if (wp + 32 * b + r < p_valid && q_base + q < q_valid) {  // (the reduction reads only valid rows and columns)
-          *reinterpret_cast<float4*>(mine + (size_t)(wp + 32 * b + r) * TILE + q_base + q) =
+        if (p_row(b) + r < p_valid && q_base + q < q_valid) {  // (the reduction reads only valid rows and columns)
+          *reinterpret_cast<float4*>(mine + (size_t)(p_row(b) + r) * TILE + q_base + q) =
               *reinterpret_cast<const float4*>(wlds + r * PITCH + q * 4);
         }
       }
@@ -761,12 +704,11 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   for (int b = 0; b < PB; b++) {
     // registers -> LDS (fp32), 32 rows x W columns per output tensor (second tensor at +8 KB when NQ == 2)
 #pragma unroll
-    for (int a = 0; a < 2; a++)
+    for (int a = 0; a < 4; a++)
 #pragma unroll
-      for (int v4 = 0; v4 < 4; v4++) {
-        const int q = (NQ == 2 ? 0 : 32 * a) + 8 * v4 + 4 * (lane >> 5);
-        float4 r = make_float4(acc[a][b][4 * v4], acc[a][b][4 * v4 + 1], acc[a][b][4 * v4 + 2], acc[a][b][4 * v4 + 3]);
-        *reinterpret_cast<float4*>(wlds + (NQ == 2 ? a * 8192 : 0) + (lane & 31) * PITCH + q * 4) = r;
+      for (int i = 0; i < 2; i++) {
+        const int q = 16 * (NQ == 2 ? a & 1 : a) + 4 * (lane >> 4);
+        *reinterpret_cast<f32x4*>(wlds + (NQ == 2 ? (a >> 1) * 8192 : 0) + (16 * i + (lane & 15)) * PITCH + q * 4) = acc[a][2 * b + i];
       }
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront's own LDS writes are done
     __builtin_amdgcn_wave_barrier();
@@ -778,7 +720,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
       for (int it = 0; it < 32 / RPI; it++) {
         const int r = it * RPI + lane / LPR;
         const int q = (lane % LPR) * 4;
-        const int p = wp + 32 * b + r;
+        const int p = p_row(b) + r;
         if (p < p_valid && q_base + q < q_valid) {
           const size_t o = (size_t)expert * A.f_expert_stride + (size_t)(p_row0 + p) * A.c_ld + q0_col + q_base + q;
           // the two halves (head and remainder of dlogits) are added; 16-byte stores: the rows are padded to 4 columns
@@ -795,7 +737,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
       for (int it = 0; it < 32 / RPI; it++) {
         const int r = it * RPI + lane / LPR;
         const int q = (lane % LPR) * 8;
-        const int p = wp + 32 * b + r;
+        const int p = p_row(b) + r;
         if (p < p_valid && q_base + q < q_valid) {
           const size_t o = (size_t)(p_row0 + p) * A.c_ld + q0_col + q_base + q;
           const float4 x0 = *reinterpret_cast<const float4*>(wlds + r * PITCH + q * 4);
@@ -815,7 +757,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     __builtin_amdgcn_wave_barrier();
   }
   };
-  constexpr bool CAN_BE_TALL = (KIND == 0 && !P_RC);   // (tall tiles add rows to a K-contiguous P stage)
+  constexpr bool CAN_BE_TALL = KIND == 0 && !RAGGED_K;   // (the router's rows are cut plainly)
   if (CAN_BE_TALL && p_valid > TILE) run(std::integral_constant<int, CAN_BE_TALL ? 5 : 4>{});
   else if (KIND == 1 || p_valid > 128) run(std::integral_constant<int, 4>{});
   else if (p_valid > 64) run(std::integral_constant<int, 2>{});
