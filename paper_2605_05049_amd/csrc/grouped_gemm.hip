@@ -584,50 +584,47 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   //      NQ == 1: 64 wq + 16 a + 4 (lane/16) + v      NQ == 2: 32 wq + 16 (a%2) + 4 (lane/16) + v of output a/2.
   // The lanes of an accumulator own 16 different rows, so storing from the accumulators would touch 16 cache lines
   // per instruction.  Instead each wavefront bounces 32 rows at a time through its own 16 KB of the (now idle) LDS
-  // and reads them back row-wise: every global access is then 16 bytes per lane over 64..256 contiguous bytes per row,
-  // and the SwiGLU element-wise math runs on that side (8 consecutive q per lane).
+  // and reads them back row-wise: every global access is then 16 bytes per lane over 64..256 contiguous bytes per row.  A
+  // wavefront's LDS accesses happen in the order of its instructions, so a bounce needs no wait of its own.
   constexpr int W = (NQ == 2) ? 32 : 64;       // q extent this wavefront owns per output tensor
   constexpr int PITCH = W * 4 + 16;            // bytes per staged fp32 row; the +16 keeps 16-byte accesses conflict-free
   __syncthreads();                             // every wavefront has finished reading the stages
   char* wlds = lds + wave * 16384;
   const int q_base = wq * W;                   // first q of this wavefront inside the output's tile
-  // 8 consecutive outputs of a row: x (and, for the SwiGLU forward, the matching values y of the second tensor) ->
-  // the kernel's bf16 outputs at element offset o
-  auto emit8 = [&](size_t o, const float (&x)[8], const float (&y)[8]) __attribute__((always_inline)) {
-    if (EPI == EPI_BF16) {
-      *reinterpret_cast<uint4*>(A.c0 + o) =
-          make_uint4(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7]));
-    } else if (EPI == EPI_SWIGLU) {  // x = G, y = U
-      float h[8];
+  auto bounced = []() __attribute__((always_inline)) {   // nothing moves across: what the lanes wrote is read by other lanes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  // bf16 stores, and the loads of the saved G and U: 8 q per lane (16 bytes).  An address is a scalar base (tensor, first row of
+  // the instruction, first column of the wavefront) plus this lane's offset.
+  constexpr int LPR = W / 8;                   // lanes per row
+  constexpr int RPI = 64 / LPR;                // rows per instruction
+  const int r_lane = lane / LPR, q_lane = (lane % LPR) * 8;
+  const unsigned lane_off = (unsigned)r_lane * (unsigned)A.c_ld + (unsigned)q_lane;
+  const size_t tile_off = (size_t)p_row0 * A.c_ld + q0_col + q_base;
+  const bool col_in = q_base + q_lane < q_valid;
+  // rows r_lane of the RPI from row p on of the tile: do they exist, and where are they
+  auto row_in = [&](int p) __attribute__((always_inline)) { return col_in && r_lane < p_valid - p; };
+  auto at = [&](auto* tensor, int p) __attribute__((always_inline)) { return tensor + (tile_off + (size_t)p * A.c_ld) + lane_off; };
+  auto pack8 = [](const float (&x)[8]) __attribute__((always_inline)) {
+    return make_uint4(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7]));
+  };
+  auto swiglu = [](float g, float u) __attribute__((always_inline)) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u; };   // (rcp: 1 ulp, bf16 result)
+  // dH (x) and the saved G, U -> dG, dU, H
+  auto dswiglu8 = [&](const float (&x)[8], uint4 gi, uint4 ui, uint4& dgo, uint4& duo, uint4& ho) __attribute__((always_inline)) {
+    const float g[8] = {bf16lo(gi.x), bf16hi(gi.x), bf16lo(gi.y), bf16hi(gi.y), bf16lo(gi.z), bf16hi(gi.z), bf16lo(gi.w), bf16hi(gi.w)};
+    const float u[8] = {bf16lo(ui.x), bf16hi(ui.x), bf16lo(ui.y), bf16hi(ui.y), bf16lo(ui.z), bf16hi(ui.z), bf16lo(ui.w), bf16hi(ui.w)};
+    float dg[8], du[8], h[8];
 #pragma unroll
-      for (int i = 0; i < 8; i++) h[i] = x[i] * __builtin_amdgcn_rcpf(1.0f + __expf(-x[i])) * y[i];   // (rcp: 1 ulp, bf16 result)
-      *reinterpret_cast<uint4*>(A.c0 + o) =
-          make_uint4(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7]));
-      *reinterpret_cast<uint4*>(A.c1 + o) =
-          make_uint4(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]), pack_bf16(y[4], y[5]), pack_bf16(y[6], y[7]));
-      *reinterpret_cast<uint4*>(A.c2 + o) =
-          make_uint4(pack_bf16(h[0], h[1]), pack_bf16(h[2], h[3]), pack_bf16(h[4], h[5]), pack_bf16(h[6], h[7]));
-    } else if (EPI == EPI_DSWIGLU) {  // x = dH; read saved G, U; write dG, dU, H
-      const uint4 gi = *reinterpret_cast<const uint4*>(A.g_in + o);
-      const uint4 ui = *reinterpret_cast<const uint4*>(A.u_in + o);
-      const float g[8] = {bf16lo(gi.x), bf16hi(gi.x), bf16lo(gi.y), bf16hi(gi.y), bf16lo(gi.z), bf16hi(gi.z), bf16lo(gi.w), bf16hi(gi.w)};
-      const float u[8] = {bf16lo(ui.x), bf16hi(ui.x), bf16lo(ui.y), bf16hi(ui.y), bf16lo(ui.z), bf16hi(ui.z), bf16lo(ui.w), bf16hi(ui.w)};
-      float dg[8], du[8], h[8];
-#pragma unroll
-      for (int i = 0; i < 8; i++) {
-        const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-g[i]));   // (rcp: 1 ulp, bf16 results)
-        const float sl = g[i] * sg;
-        h[i] = sl * u[i];
-        du[i] = x[i] * sl;
-        dg[i] = x[i] * u[i] * (sg * (1.0f + g[i] * (1.0f - sg)));
-      }
-      *reinterpret_cast<uint4*>(A.c0 + o) =
-          make_uint4(pack_bf16(dg[0], dg[1]), pack_bf16(dg[2], dg[3]), pack_bf16(dg[4], dg[5]), pack_bf16(dg[6], dg[7]));
-      *reinterpret_cast<uint4*>(A.c1 + o) =
-          make_uint4(pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3]), pack_bf16(du[4], du[5]), pack_bf16(du[6], du[7]));
-      *reinterpret_cast<uint4*>(A.c2 + o) =
-          make_uint4(pack_bf16(h[0], h[1]), pack_bf16(h[2], h[3]), pack_bf16(h[4], h[5]), pack_bf16(h[6], h[7]));
+    for (int i = 0; i < 8; i++) {
+      const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-g[i]));   // (rcp: 1 ulp, bf16 results)
+      const float sl = g[i] * sg;
+      h[i] = sl * u[i];
+      du[i] = x[i] * sl;
+      dg[i] = x[i] * u[i] * (sg * (1.0f + g[i] * (1.0f - sg)));
     }
+    dgo = pack8(dg); duo = pack8(du); ho = pack8(h);
   };
   if (SPLITK && split > 1) {
     // ---- a part of a split tile: fp32 partial tile [row][256] -> workspace, then whoever arrives last reduces
@@ -639,21 +636,19 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 #pragma unroll
         for (int i = 0; i < 2; i++)
           *reinterpret_cast<f32x4*>(wlds + (16 * i + (lane & 15)) * PITCH + (16 * a + 4 * (lane >> 4)) * 4) = acc[a][2 * b + i];
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-      __builtin_amdgcn_wave_barrier();
-      constexpr int LPR = W / 4;          // lanes per row (4 fp32 per lane)
-      constexpr int RPI = 64 / LPR;       // rows per instruction
+      bounced();
+      constexpr int LPR4 = W / 4;         // lanes per row (4 fp32 per lane)
+      constexpr int RPI4 = 64 / LPR4;     // rows per instruction
 #pragma unroll
-      for (int it = 0; it < 32 / RPI; it++) {
-        const int r = it * RPI + lane / LPR;
-        const int q = (lane % LPR) * 4;
+      for (int it = 0; it < 32 / RPI4; it++) {
+        const int r = it * RPI4 + lane / LPR4;
+        const int q = (lane % LPR4) * 4;
         if (p_row(b) + r < p_valid && q_base + q < q_valid) {  // (the reduction reads only valid rows and columns)
           *reinterpret_cast<float4*>(mine + (size_t)(p_row(b) + r) * TILE + q_base + q) =
               *reinterpret_cast<const float4*>(wlds + r * PITCH + q * 4);
         }
       }
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-      __builtin_amdgcn_wave_barrier();
+      bounced();
     }
     // All parts of a tile carry the same blockIdx.x % 8 and so run on one XCD, whose L2 they share: a store that has
     // been acknowledged (vmcnt) is then visible to the other parts at the L2, and no cache has to be written back or
@@ -682,7 +677,6 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     for (int idx = tid; idx < n_items; idx += NTHREADS) {
       const int p = idx / nqv, q = (idx - p * nqv) * 8;
       float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      const float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       const float* src = parts + p * TILE + q;
       for (int sp = 0; sp < split; sp += 4) {   // four parts' 32 bytes in flight (parts past the last: the last again, not added)
         f32x4 v[8];
@@ -696,13 +690,21 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
           }
         }
       }
-      emit8((size_t)(p_row0 + p) * A.c_ld + q0_col + q, x, y);
+      const size_t o = (size_t)(p_row0 + p) * A.c_ld + q0_col + q;
+      if (EPI == EPI_DSWIGLU) {
+        uint4 dg, du, h;
+        dswiglu8(x, *reinterpret_cast<const uint4*>(A.g_in + o), *reinterpret_cast<const uint4*>(A.u_in + o), dg, du, h);
+        *reinterpret_cast<uint4*>(A.c0 + o) = dg;
+        *reinterpret_cast<uint4*>(A.c1 + o) = du;
+        *reinterpret_cast<uint4*>(A.c2 + o) = h;
+      } else {
+        *reinterpret_cast<uint4*>(A.c0 + o) = pack8(x);
+      }
     }
     return;
   }
-#pragma unroll
-  for (int b = 0; b < PB; b++) {
-    // registers -> LDS (fp32), 32 rows x W columns per output tensor (second tensor at +8 KB when NQ == 2)
+  // fp32 accumulators of 32 rows x W columns per output tensor -> LDS (second tensor at +8 KB when NQ == 2)
+  auto bounce_f32 = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
     for (int a = 0; a < 4; a++)
 #pragma unroll
@@ -710,16 +712,75 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
         const int q = 16 * (NQ == 2 ? a & 1 : a) + 4 * (lane >> 4);
         *reinterpret_cast<f32x4*>(wlds + (NQ == 2 ? (a >> 1) * 8192 : 0) + (16 * i + (lane & 15)) * PITCH + q * 4) = acc[a][2 * b + i];
       }
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront's own LDS writes are done
-    __builtin_amdgcn_wave_barrier();
-    if (EPI == EPI_F32) {
-      // 4 q per lane (16 bytes of fp32)
-      constexpr int LPR = W / 4;          // lanes per row
-      constexpr int RPI = 64 / LPR;       // rows per instruction
+    bounced();
+  };
+  if constexpr (EPI == EPI_BF16 || EPI == EPI_SWIGLU) {
+    // The bf16 results are made from the accumulators (of the SwiGLU forward a lane holds G and U of the same elements) and
+    // bounced as such, half the LDS bytes of the sums.
+    constexpr int PITCH16 = W * 2 + 16, TENSORS = EPI == EPI_SWIGLU ? 3 : 1;
+#pragma unroll
+    for (int b = 0; b < PB; b++) {
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int a = 0; a < W / 16; a++) {
+          char* const dst = wlds + (16 * i + (lane & 15)) * PITCH16 + (16 * a + 4 * (lane >> 4)) * 2;
+          const f32x4 x = acc[a][2 * b + i];
+          *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]));
+          if constexpr (EPI == EPI_SWIGLU) {
+            const f32x4 y = acc[a + 2][2 * b + i];
+            *reinterpret_cast<uint2*>(dst + 32 * PITCH16) = make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
+            *reinterpret_cast<uint2*>(dst + 64 * PITCH16) =
+                make_uint2(pack_bf16(swiglu(x[0], y[0]), swiglu(x[1], y[1])), pack_bf16(swiglu(x[2], y[2]), swiglu(x[3], y[3])));
+          }
+        }
+      bounced();
 #pragma unroll
       for (int it = 0; it < 32 / RPI; it++) {
-        const int r = it * RPI + lane / LPR;
-        const int q = (lane % LPR) * 4;
+        const int p = p_row(b) + it * RPI;
+        const char* const src = wlds + (it * RPI + r_lane) * PITCH16 + q_lane * 2;
+        if (row_in(p)) {
+#pragma unroll
+          for (int t = 0; t < TENSORS; t++)
+            *reinterpret_cast<uint4*>(at(t == 0 ? A.c0 : t == 1 ? A.c1 : A.c2, p)) = *reinterpret_cast<const uint4*>(src + t * 32 * PITCH16);
+        }
+      }
+      bounced();
+    }
+  } else if constexpr (EPI == EPI_DSWIGLU) {
+    // The fp32 sums are bounced and meet the saved G and U row-wise.  (G and U may lie where dG and dU go: the same elements by the
+    // same lane.)
+    // (G and U of the next rows requested ahead: 1 % slower.  All CUs are in their epilogues together, and the 640 KB that a tile
+    // reads and writes there run at 5 TB/s: 30 us of a 125 us tile of 4096 x 14336.)
+#pragma unroll
+    for (int b = 0; b < PB; b++) {
+      bounce_f32(b);
+#pragma unroll
+      for (int it = 0; it < 32 / RPI; it++) {
+        const int p = p_row(b) + it * RPI;
+        if (row_in(p)) {
+          const char* const src = wlds + (it * RPI + r_lane) * PITCH + q_lane * 4;
+          const float4 x0 = *reinterpret_cast<const float4*>(src), x1 = *reinterpret_cast<const float4*>(src + 16);
+          const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+          uint4 dg, du, h;
+          dswiglu8(x, *reinterpret_cast<const uint4*>(at(A.g_in, p)), *reinterpret_cast<const uint4*>(at(A.u_in, p)), dg, du, h);
+          *reinterpret_cast<uint4*>(at(A.c0, p)) = dg;
+          *reinterpret_cast<uint4*>(at(A.c1, p)) = du;
+          *reinterpret_cast<uint4*>(at(A.c2, p)) = h;
+        }
+      }
+      bounced();
+    }
+  } else {
+    constexpr int LPR4 = W / 4;          // lanes per row (4 q, 16 bytes of fp32, per lane)
+    constexpr int RPI4 = 64 / LPR4;      // rows per instruction
+#pragma unroll
+    for (int b = 0; b < PB; b++) {
+      bounce_f32(b);
+#pragma unroll
+      for (int it = 0; it < 32 / RPI4; it++) {
+        const int r = it * RPI4 + lane / LPR4;
+        const int q = (lane % LPR4) * 4;
         const int p = p_row(b) + r;
         if (p < p_valid && q_base + q < q_valid) {
           const size_t o = (size_t)expert * A.f_expert_stride + (size_t)(p_row0 + p) * A.c_ld + q0_col + q_base + q;
@@ -729,32 +790,8 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
           *reinterpret_cast<float4*>(A.f0 + o) = make_float4(v0.x + v1.x, v0.y + v1.y, v0.z + v1.z, v0.w + v1.w);
         }
       }
-    } else {
-      // 8 q per lane (16 bytes of bf16)
-      constexpr int LPR = W / 8;
-      constexpr int RPI = 64 / LPR;
-#pragma unroll
-      for (int it = 0; it < 32 / RPI; it++) {
-        const int r = it * RPI + lane / LPR;
-        const int q = (lane % LPR) * 8;
-        const int p = p_row(b) + r;
-        if (p < p_valid && q_base + q < q_valid) {
-          const size_t o = (size_t)(p_row0 + p) * A.c_ld + q0_col + q_base + q;
-          const float4 x0 = *reinterpret_cast<const float4*>(wlds + r * PITCH + q * 4);
-          const float4 x1 = *reinterpret_cast<const float4*>(wlds + r * PITCH + q * 4 + 16);
-          const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-          float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-          if (EPI == EPI_SWIGLU) {  // the second staged tensor is U
-            const float4 y0 = *reinterpret_cast<const float4*>(wlds + 8192 + r * PITCH + q * 4);
-            const float4 y1 = *reinterpret_cast<const float4*>(wlds + 8192 + r * PITCH + q * 4 + 16);
-            y[0] = y0.x; y[1] = y0.y; y[2] = y0.z; y[3] = y0.w; y[4] = y1.x; y[5] = y1.y; y[6] = y1.z; y[7] = y1.w;
-          }
-          emit8(o, x, y);
-        }
-      }
+      bounced();
     }
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // the read-back is complete before the next 32 rows overwrite the buffer
-    __builtin_amdgcn_wave_barrier();
   }
   };
   constexpr bool CAN_BE_TALL = KIND == 0 && !RAGGED_K;   // (the router's rows are cut plainly)
