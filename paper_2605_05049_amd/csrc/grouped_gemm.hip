@@ -384,44 +384,44 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   // the k-steps this block multiplies: all of them, or its part of a split tile
   const int kt_per = (nk + split - 1) / split;
   const int kt_begin = part * kt_per, kt_end = min(nk, kt_begin + kt_per);
-  // Height class of the tile: the two wavefronts along p multiply PB blocks of 32 rows each (5, 4, 2 or 1), so a
-  // ragged last row tile of an expert issues MFMAs and row loads for its class (320, 256, 128 or 64 rows) only.
-  auto run = [&](auto pb_c) __attribute__((always_inline)) {
-  constexpr int PB = decltype(pb_c)::value;
-  // A tile's rows are worked on in parts of 128 (a wavefront: 64, or 4 blocks of 16), a tall tile's last 64 in a third.
-  constexpr int PARTS = PB == 5 ? 3 : PB == 4 ? 2 : 1;
-  constexpr int P_STAGE = PB == 5 ? TALL * BK * 2 : PB * 64 * BK * 2;   // bytes of a stage's P operand
+  // Height class of the tile: the two wavefronts along p multiply NB blocks of 16 rows each (10, 9, 8, 6, 4 or 2), so a
+  // ragged last row tile of an expert issues MFMAs and row loads for its class (320, 288, 256, 192, 128 or 64 rows) only.
+  auto run = [&](auto nb_c) __attribute__((always_inline)) {
+  constexpr int NB = decltype(nb_c)::value;
+  // A tile's rows are worked on in parts of 128 (a wavefront: 64, or 4 blocks), and what its class has beyond.
+  constexpr int PARTS = (NB + 3) / 4, LAST = PARTS - 1, LAST_NB = NB - 4 * LAST;
+  constexpr int P_STAGE = (PARTS == 3 ? TALL : 32 * NB) * BK * 2;   // bytes of a stage's P operand
   constexpr int STAGES = PARTS == 1 ? 3 : 2;
   static_assert(STAGES * (P_STAGE + OPERAND_BYTES) <= LDS_BYTES, "the stages fit");
   // (all stages of P, then all of Q: an operand's stages then share their address registers)
   auto p_area = [&](int s) __attribute__((always_inline)) { return lds + s * P_STAGE; };
   auto q_area = [&](int s) __attribute__((always_inline)) { return lds + STAGES * P_STAGE + s * OPERAND_BYTES; };
-  // first row of block b (32 rows) of this wavefront
-  auto p_row = [&](int b) __attribute__((always_inline)) {
-    return PB == 1 ? (wave & 1) * 32 : b == 4 ? 256 + (wave & 1) * 32 : (b >> 1) * 128 + (wave & 1) * 64 + (b & 1) * 32;
-  };
-  f32x4 acc[4][2 * PB];  // [q block][p block]
+  // first row of block b of this wavefront
+  auto p_row = [&](int b) __attribute__((always_inline)) { return (b >> 2) * 128 + (wave & 1) * 16 * ((b >> 2) == LAST ? LAST_NB : 4) + (b & 3) * 16; };
+  f32x4 acc[4][NB];  // [q block][p block]
 #pragma unroll
   for (int a = 0; a < 4; a++)
 #pragma unroll
-    for (int b = 0; b < 2 * PB; b++)
+    for (int b = 0; b < NB; b++)
 #pragma unroll
       for (int v = 0; v < 4; v++) acc[a][b][v] = 0.f;
-  // Direct loads.  P: part h (128 rows) is 16 instructions, two of each wavefront (K-contiguous: instruction n = rows 8 n ..; R-
-  // contiguous: n = 2 j + h); a tall tile's rows 256.. are one more of each.  Q: four of each.
+  // Direct loads.  P: part h is 16 instructions, two of each wavefront (K-contiguous: instruction n = rows 8 n ..; R-
+  // contiguous: n = 2 j + h), or 8 where it has at most 64 rows.  Q: four of each.
+  constexpr int LAST_LOADS = LAST_NB > 2 ? 2 : 1;
   auto p_instr = [&](int h, int i) __attribute__((always_inline)) {
-    return PB == 1 ? wave : h == 2 ? 32 + wave : P_RC ? 2 * (2 * wave + i) + h : 16 * h + 2 * wave + i;
+    return h == LAST && LAST_LOADS == 1 ? 16 * h + wave : P_RC ? 2 * (2 * wave + i) + h : 16 * h + 2 * wave + i;
   };
-  constexpr int P_LOADS = PB == 5 ? 5 : PB == 1 ? 1 : PB;
-  unsigned pvo[P_LOADS];
+  unsigned pvo[PARTS][2];
 #pragma unroll
-  for (int i = 0; i < P_LOADS; i++) pvo[i] = load_offset<P_RC, false>(P, p_instr(i >> 1, i & 1), lane);
+  for (int h = 0; h < PARTS; h++)
+#pragma unroll
+    for (int i = 0; i < (h == LAST ? LAST_LOADS : 2); i++) pvo[h][i] = load_offset<P_RC, false>(P, p_instr(h, i), lane);
   auto issue_p = [&](int h, int j, int s) __attribute__((always_inline)) {   // part h of step j
     const bool second = (NPASS == 2) && j >= nk_pass;
     const int k0 = (second ? j - nk_pass : j) * BK;
 #pragma unroll
-    for (int i = 0; i < (h == 2 || PB == 1 ? 1 : 2); i++)
-      issue_load<P_RC, false, RAGGED_K>(pvo[2 * h + i], P, second ? p_pass_delta : (ptrdiff_t)0, k0, k_len, A.zero_page, p_area(s), p_instr(h, i), lane);
+    for (int i = 0; i < (h == LAST ? LAST_LOADS : 2); i++)
+      issue_load<P_RC, false, RAGGED_K>(pvo[h][i], P, second ? p_pass_delta : (ptrdiff_t)0, k0, k_len, A.zero_page, p_area(s), p_instr(h, i), lane);
   };
   auto issue_q = [&](int j, int s) __attribute__((always_inline)) {
     const bool second = (NPASS == 2) && j >= nk_pass;
@@ -432,17 +432,19 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   };
   const unsigned p_off0 = frag_offset<P_RC>(p_row(0), lane), p_off1 = frag_offset<P_RC>(p_row(0) + 16, lane);
   const unsigned p_off2 = P_RC ? frag_offset<P_RC>(p_row(0) + 32, lane) : 0u, p_off3 = P_RC ? frag_offset<P_RC>(p_row(0) + 48, lane) : 0u;
+  static_assert(!P_RC || NB == 8, "an R-contiguous P has whole parts");
   unsigned q_off[4];
 #pragma unroll
   for (int a = 0; a < 4; a++) q_off[a] = frag_offset<Q_RC>(qr(a), lane) + (unsigned)(size_t)(lptr_t)q_area(0);
-  const unsigned p_off_tall = PB == 5 ? frag_offset<P_RC>(p_row(4), lane) : 0u;
+  const unsigned p_off_last = LAST > 0 && LAST_NB < 4 ? frag_offset<P_RC>(p_row(4 * LAST), lane) : 0u;
   // fragment of p block b (16 rows, 0..3) of part h / of q block a, k-values kk .. kk + 31 of the step in stage s
   // (K-contiguous: 16 rows further is 2048 bytes further with the same swizzle, so the fragments of the operand share an
   // address register and differ in the instruction's offset field)
   auto rp = [&](int h, int b, int kk, int s) __attribute__((always_inline)) {
     const unsigned base = (unsigned)(size_t)(lptr_t)p_area(s);
     if (P_RC) return read_frag_at<P_RC>(b == 0 ? p_off0 : b == 1 ? p_off1 : b == 2 ? p_off2 : p_off3, kk, base + 1024u * h);
-    return h == 2 ? read_frag_at<P_RC>(p_off_tall, kk, base + 2048u * b) : read_frag_at<P_RC>(p_off0, kk, base + 16384u * h + 2048u * b);
+    if (h == LAST && LAST > 0 && LAST_NB < 4) return read_frag_at<P_RC>(p_off_last, kk, base + 2048u * b);
+    return read_frag_at<P_RC>(p_off0, kk, base + 16384u * h + 2048u * b);
   };
   auto rq = [&](int a, int kk, int s) __attribute__((always_inline)) {
     const unsigned base = (unsigned)(s * OPERAND_BYTES);
@@ -450,7 +452,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     static_assert(Q_RC || NQ == 1, "a pair of q tensors is R-contiguous");
     return read_frag_at<Q_RC>(q_off[0], kk, base + 2048u * a);
   };
-  if constexpr (PB == 1) {
+  if constexpr (NB == 2) {
     // Tiles of at most 64 rows multiply little per step and are bound by the latency of their loads: a ring of three stages of 8 +
     // 32 KB, two steps ahead, one barrier per step.  5 loads of each wavefront per step, so that "all but the youngest step" is
     // vmcnt(5).
@@ -497,7 +499,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     // the last part of step j + 1 (with three stages everything of step j + 2): a load has four to six halves to land.  It is
     // waited for by its count: before the barrier in front of the half that reads it, all but the loads that a wavefront
     // has issued after it (the first four wavefronts wait behind their MFMAs, the others behind their reads).
-    constexpr int N0 = 6, N1 = PARTS >= 2 ? 2 : 0, N2 = PARTS == 3 ? 1 : 0, NS = N0 + N1 + N2;   // loads of the parts; of a step
+    constexpr int N0 = 6, N1 = PARTS == 2 ? LAST_LOADS : PARTS == 3 ? 2 : 0, N2 = PARTS == 3 ? 1 : 0, NS = N0 + N1 + N2;   // loads of the parts; of a step
     const int n_steps = kt_end - kt_begin;
     auto request = [&](int h, int j, int s) __attribute__((always_inline)) {   // part h of step j (counted from kt_begin)
       if (j < n_steps) {
@@ -531,7 +533,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     auto step = [&](int j, int s, int s1, int s2) __attribute__((always_inline)) {   // stages of steps j, j + 1, j + 2
 #pragma unroll
       for (int h = 0; h < PARTS; h++) {
-        const int nb = h == 2 ? 2 : 4;   // p blocks of the part
+        const int nb = h == LAST ? LAST_NB : 4;   // p blocks of the part
         if (h == 0) {
 #pragma unroll
           for (int g = 0; g < 2; g++)
@@ -580,7 +582,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     if (!second_half) bare_barrier();
   }
 
-  // ---- epilogue.  acc[a][2 b + i][v] holds  p = p_row(b) + 16 i + lane%16,  q (inside the output's tile) =
+  // ---- epilogue.  acc[a][b][v] holds  p = p_row(b) + lane%16,  q (inside the output's tile) =
   //      NQ == 1: 64 wq + 16 a + 4 (lane/16) + v      NQ == 2: 32 wq + 16 (a%2) + 4 (lane/16) + v of output a/2.
   // The lanes of an accumulator own 16 different rows, so storing from the accumulators would touch 16 cache lines
   // per instruction.  Instead each wavefront bounces 32 rows at a time through its own 16 KB of the (now idle) LDS
@@ -595,6 +597,19 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  // The accumulators are taken two blocks of rows at a time (a class of 9: the last by itself).
+  auto rows_at = [](int b) __attribute__((always_inline)) { return b + 1 < NB ? 32 : 16; };
+  // fp32 accumulators of blocks b and b + 1 x W columns per output tensor -> LDS (second tensor at +8 KB when NQ == 2)
+  auto bounce_f32 = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < 4; a++)
+#pragma unroll
+      for (int i = 0; i < rows_at(b) / 16; i++) {
+        const int q = 16 * (NQ == 2 ? a & 1 : a) + 4 * (lane >> 4);
+        *reinterpret_cast<f32x4*>(wlds + (NQ == 2 ? (a >> 1) * 8192 : 0) + (16 * i + (lane & 15)) * PITCH + q * 4) = acc[a][b + i];
+      }
+    bounced();
   };
   // bf16 stores, and the loads of the saved G and U: 8 q per lane (16 bytes).  An address is a scalar base (tensor, first row of
   // the instruction, first column of the wavefront) plus this lane's offset.
@@ -630,17 +645,12 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     // ---- a part of a split tile: fp32 partial tile [row][256] -> workspace, then whoever arrives last reduces
     float* mine = A.partial + (size_t)part_slot * (TALL * TILE);
 #pragma unroll
-    for (int b = 0; b < PB; b++) {
-#pragma unroll
-      for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-          *reinterpret_cast<f32x4*>(wlds + (16 * i + (lane & 15)) * PITCH + (16 * a + 4 * (lane >> 4)) * 4) = acc[a][2 * b + i];
-      bounced();
+    for (int b = 0; b < NB; b += 2) {
+      bounce_f32(b);
       constexpr int LPR4 = W / 4;         // lanes per row (4 fp32 per lane)
       constexpr int RPI4 = 64 / LPR4;     // rows per instruction
 #pragma unroll
-      for (int it = 0; it < 32 / RPI4; it++) {
+      for (int it = 0; it < rows_at(b) / RPI4; it++) {
         const int r = it * RPI4 + lane / LPR4;
         const int q = (lane % LPR4) * 4;
         if (p_row(b) + r < p_valid && q_base + q < q_valid) {  // (the reduction reads only valid rows and columns)
@@ -703,32 +713,21 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     }
     return;
   }
-  // fp32 accumulators of 32 rows x W columns per output tensor -> LDS (second tensor at +8 KB when NQ == 2)
-  auto bounce_f32 = [&](int b) __attribute__((always_inline)) {
-#pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-      for (int i = 0; i < 2; i++) {
-        const int q = 16 * (NQ == 2 ? a & 1 : a) + 4 * (lane >> 4);
-        *reinterpret_cast<f32x4*>(wlds + (NQ == 2 ? (a >> 1) * 8192 : 0) + (16 * i + (lane & 15)) * PITCH + q * 4) = acc[a][2 * b + i];
-      }
-    bounced();
-  };
   if constexpr (EPI == EPI_BF16 || EPI == EPI_SWIGLU) {
     // The bf16 results are made from the accumulators (of the SwiGLU forward a lane holds G and U of the same elements) and
     // bounced as such, half the LDS bytes of the sums.
     constexpr int PITCH16 = W * 2 + 16, TENSORS = EPI == EPI_SWIGLU ? 3 : 1;
 #pragma unroll
-    for (int b = 0; b < PB; b++) {
+    for (int b = 0; b < NB; b += 2) {
 #pragma unroll
-      for (int i = 0; i < 2; i++)
+      for (int i = 0; i < rows_at(b) / 16; i++)
 #pragma unroll
         for (int a = 0; a < W / 16; a++) {
           char* const dst = wlds + (16 * i + (lane & 15)) * PITCH16 + (16 * a + 4 * (lane >> 4)) * 2;
-          const f32x4 x = acc[a][2 * b + i];
+          const f32x4 x = acc[a][b + i];
           *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]));
           if constexpr (EPI == EPI_SWIGLU) {
-            const f32x4 y = acc[a + 2][2 * b + i];
+            const f32x4 y = acc[a + 2][b + i];
             *reinterpret_cast<uint2*>(dst + 32 * PITCH16) = make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
             *reinterpret_cast<uint2*>(dst + 64 * PITCH16) =
                 make_uint2(pack_bf16(swiglu(x[0], y[0]), swiglu(x[1], y[1])), pack_bf16(swiglu(x[2], y[2]), swiglu(x[3], y[3])));
@@ -736,7 +735,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
         }
       bounced();
 #pragma unroll
-      for (int it = 0; it < 32 / RPI; it++) {
+      for (int it = 0; it < rows_at(b) / RPI; it++) {
         const int p = p_row(b) + it * RPI;
         const char* const src = wlds + (it * RPI + r_lane) * PITCH16 + q_lane * 2;
         if (row_in(p)) {
@@ -753,10 +752,10 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     // (G and U of the next rows requested ahead: 1 % slower.  All CUs are in their epilogues together, and the 640 KB that a tile
     // reads and writes there run at 5 TB/s: 30 us of a 125 us tile of 4096 x 14336.)
 #pragma unroll
-    for (int b = 0; b < PB; b++) {
+    for (int b = 0; b < NB; b += 2) {
       bounce_f32(b);
 #pragma unroll
-      for (int it = 0; it < 32 / RPI; it++) {
+      for (int it = 0; it < rows_at(b) / RPI; it++) {
         const int p = p_row(b) + it * RPI;
         if (row_in(p)) {
           const char* const src = wlds + (it * RPI + r_lane) * PITCH + q_lane * 4;
@@ -775,10 +774,10 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     constexpr int LPR4 = W / 4;          // lanes per row (4 q, 16 bytes of fp32, per lane)
     constexpr int RPI4 = 64 / LPR4;      // rows per instruction
 #pragma unroll
-    for (int b = 0; b < PB; b++) {
+    for (int b = 0; b < NB; b += 2) {
       bounce_f32(b);
 #pragma unroll
-      for (int it = 0; it < 32 / RPI4; it++) {
+      for (int it = 0; it < rows_at(b) / RPI4; it++) {
         const int r = it * RPI4 + lane / LPR4;
         const int q = (lane % LPR4) * 4;
         const int p = p_row(b) + r;
@@ -795,10 +794,13 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   }
   };
   constexpr bool CAN_BE_TALL = KIND == 0 && !RAGGED_K;   // (the router's rows are cut plainly)
-  if (CAN_BE_TALL && p_valid > TILE) run(std::integral_constant<int, CAN_BE_TALL ? 5 : 4>{});
-  else if (KIND == 1 || p_valid > 128) run(std::integral_constant<int, 4>{});
-  else if (p_valid > 64) run(std::integral_constant<int, 2>{});
-  else run(std::integral_constant<int, 1>{});
+  constexpr int MOST = KIND == 1 ? 8 : 0;   // (the router's weight gradient: whole tiles only)
+  if (CAN_BE_TALL && p_valid > TILE + 32) run(std::integral_constant<int, CAN_BE_TALL ? 10 : 8>{});
+  else if (CAN_BE_TALL && p_valid > TILE) run(std::integral_constant<int, CAN_BE_TALL ? 9 : 8>{});
+  else if (KIND == 1 || p_valid > 192) run(std::integral_constant<int, 8>{});
+  else if (p_valid > 128) run(std::integral_constant<int, MOST ? MOST : 6>{});
+  else if (p_valid > 64) run(std::integral_constant<int, MOST ? MOST : 4>{});
+  else run(std::integral_constant<int, MOST ? MOST : 2>{});
 }
 
 // Row-tile schedule: one thread per expert.  sched[0] = number of row tiles; sched[1] = how experts are cut into
