@@ -479,6 +479,20 @@ def test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small):
     test_grouped_ffn_every_tile_height(moe, d, f, counts)
 
 
+# rows on either side of every class boundary (128, 192, 256, 288, 320), in its middle, and one expert of three tiles
+CLASS_COUNTS = [129, 160, 161, 192, 193, 224, 257, 272, 273, 288, 289, 319, 0, 512 + 33, 100, 66]
+
+
+@pytest.mark.parametrize("d,f,counts,small", [
+    (64, 4096, CLASS_COUNTS, ("down", "dx")),          # gate | up and dH of 1 step: fewer than the stages of any class
+    (192, 4096, CLASS_COUNTS, ("down", "dx")),         # of 3 steps
+    (4096, 128, CLASS_COUNTS, ("gate_up", "dh")),      # down of 2 steps, dX of 4
+    (1088, 1600, 4 * CLASS_COUNTS, ()),                # all four: 17, 25 and 50 steps
+])
+def test_row_tile_classes(moe, d, f, counts, small):
+    test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small)
+
+
 def ffn_on_device(moe, d, f, counts, seed=0):
     """Inputs and one saving forward of the grouped FFN over experts of `counts` rows, all on the device."""
     E, N = len(counts), sum(counts)
