@@ -153,18 +153,22 @@ void launch_few_rows(const char* label, hipStream_t st, int kind, RowTileArgs A,
 bool few_rows_pays(const Dims& D, RowTileKind kind);   // (grouped_gemm.hip)
 
 // Weight gradients of the expert FFNs (wgrad.hip): f0[e] (and f1[e]) = p0_e^T q0_e (p0_e^T q1_e) over the rows of expert e.
+struct WgradProblem {
+  const uint16_t* p0; size_t p_ld; int p_dim;
+  const uint16_t* q0; const uint16_t* q1; size_t q_ld; int q_dim;
+  float* f0; float* f1; size_t c_ld;
+  int n_p_tiles, n_q_tiles, band, chunks;   // filled by the launcher
+};
 struct WgradArgs {
   const int32_t* offsets;      // [Et + 1]
   const int32_t* order;        // [Et] experts by descending row count
   const uint16_t* zero_page;   // 256 zeroed bytes: source of k-rows past the end of a ragged contraction
-  const uint16_t* p0; size_t p_ld; int p_dim;
-  const uint16_t* q0; const uint16_t* q1; size_t q_ld; int q_dim;
-  float* f0; float* f1; size_t f_expert_stride; size_t c_ld;
   int Et, accumulate;
   long long rows;              // of all experts together
-  int n_p_tiles, n_q_tiles, band;   // filled by the launcher
+  size_t f_expert_stride;
+  WgradProblem a, b;           // dW_gate | dW_up and dW_down
 };
-void launch_wgrad(const char* label, hipStream_t st, WgradArgs A);
+void launch_wgrad(hipStream_t st, WgradArgs A);
 
 // Optional per-launch timing (moe_profile_* in the ABI).  While enabled, every kernel launch of the library is
 // bracketed by two HIP events on the launch stream; disabled (the default) it costs one branch.

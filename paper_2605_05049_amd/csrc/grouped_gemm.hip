@@ -1091,19 +1091,18 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
     MOE_TRY(G.dh("ffn_bwd_dh_dswiglu", dy_perm, w_down, save_g, save_u, dg, du, h));
     MOE_TRY(G.dx("ffn_bwd_dx", dg, du, w_gate, w_up, dx_perm));
   }
-  // dWd[e] = H_e^T dY_e   (rows f, columns d)
   WgradArgs W = {};
   W.offsets = offsets; W.order = G.experts_by_rows(); W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
-  W.Et = D.Et; W.accumulate = accumulate ? 1 : 0; W.rows = D.N;
-  W.p0 = h; W.p_ld = D.f; W.p_dim = D.f;
-  W.q0 = dy_perm; W.q_ld = D.d; W.q_dim = D.d;
-  W.f0 = dw_down; W.f_expert_stride = (size_t)D.f * D.d; W.c_ld = D.d;
-  launch_wgrad("ffn_bwd_dw_down", st, W);
+  W.Et = D.Et; W.accumulate = accumulate ? 1 : 0; W.rows = D.N; W.f_expert_stride = (size_t)D.f * D.d;
   // dWg[e], dWu[e] = X_e^T dG_e, X_e^T dU_e   (rows d, columns f)
-  W.p0 = x_perm; W.p_ld = D.d; W.p_dim = D.d;
-  W.q0 = dg; W.q1 = du; W.q_ld = D.f; W.q_dim = D.f;
-  W.f0 = dw_gate; W.f1 = dw_up; W.c_ld = D.f;
-  launch_wgrad("ffn_bwd_dw_gate_up", st, W);
+  W.a.p0 = x_perm; W.a.p_ld = D.d; W.a.p_dim = D.d;
+  W.a.q0 = dg; W.a.q1 = du; W.a.q_ld = D.f; W.a.q_dim = D.f;
+  W.a.f0 = dw_gate; W.a.f1 = dw_up; W.a.c_ld = D.f;
+  // dWd[e] = H_e^T dY_e   (rows f, columns d)
+  W.b.p0 = h; W.b.p_ld = D.f; W.b.p_dim = D.f;
+  W.b.q0 = dy_perm; W.b.q_ld = D.d; W.b.q_dim = D.d;
+  W.b.f0 = dw_down; W.b.c_ld = D.d;
+  launch_wgrad(st, W);
   return launch_status();
 }
 

@@ -19,6 +19,8 @@
 // store instruction writes whole 128-byte lines from registers, without a bounce through LDS and without a barrier.
 #include "common.h"
 
+#include <limits.h>
+
 namespace moe {
 
 typedef __bf16 w_bf16x8 __attribute__((ext_vector_type(8)));
@@ -35,6 +37,7 @@ constexpr int P_BYTES = WP * WK * 2;         // 8 KB
 constexpr int Q_BYTES = WQ * WK * 2;         // 16 KB
 constexpr int W_STAGE = P_BYTES + Q_BYTES;   // 24 KB
 constexpr int W_XCDS = 8;
+constexpr int W_MERGE_CHUNKS = 1024;         // both problems in one launch up to here
 constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
 
 // Position of 8 r-values (chunk c of 16) inside k-row k's 256 bytes: the four k-rows that a transposing read takes together
@@ -72,50 +75,51 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
   // ---- block id -> tile.  Chunks of 32 consecutive tiles (A.band = 8 p x 4 q of one expert, which share panels) are dealt
   // round-robin to the XCDs, experts with the most rows first (the tail of the launch is then made of short tiles).
   const int within = blockIdx.x / W_XCDS, xcd = blockIdx.x % W_XCDS;
-  const long long tiles_per_e = (long long)A.n_p_tiles * A.n_q_tiles;
-  const long long total = tiles_per_e * A.Et;
-  const long long chunk = (long long)(within / W_CHUNK) * W_XCDS + xcd;
-  const long long lid = chunk * W_CHUNK + within % W_CHUNK;
-  if (lid >= total) return;
+  const long long launch_chunk = (long long)(within / W_CHUNK) * W_XCDS + xcd;
+  const bool is_b = launch_chunk >= A.a.chunks;   // (a launch may carry two problems, the second's chunks after the first's)
+  const WgradProblem B = is_b ? A.b : A.a;
+  const long long tiles_per_e = (long long)B.n_p_tiles * B.n_q_tiles;
+  const long long lid = (launch_chunk - (is_b ? A.a.chunks : 0)) * W_CHUNK + within % W_CHUNK;
+  if (lid >= tiles_per_e * A.Et) return;
   const int expert = A.order[(int)(lid / tiles_per_e)];
   const int local = (int)(lid % tiles_per_e);
-  const int band = local / (A.band * A.n_q_tiles), in_band = local - band * A.band * A.n_q_tiles;
-  const int band_p = min(A.band, A.n_p_tiles - band * A.band);
-  const int pt = band * A.band + in_band % band_p, qt = in_band / band_p;
+  const int band = local / (B.band * B.n_q_tiles), in_band = local - band * B.band * B.n_q_tiles;
+  const int band_p = min(B.band, B.n_p_tiles - band * B.band);
+  const int pt = band * B.band + in_band % band_p, qt = in_band / band_p;
   const int e_lo = A.offsets[expert], k_len = A.offsets[expert + 1] - e_lo;
   if (k_len == 0 && A.accumulate) return;   // nothing to add
-  const int p_row0 = pt * WP, p_valid = min(WP, A.p_dim - p_row0);
+  const int p_row0 = pt * WP, p_valid = min(WP, B.p_dim - p_row0);
   // the tile's two halves of 128 columns: the same columns of either tensor of a pair, or neighbours in one tensor (the second
   // may lie past its end: then it loads the first's columns and stores nothing)
-  const bool pair = A.q1 != nullptr;
+  const bool pair = B.q1 != nullptr;
   const int col0 = qt * (pair ? WH : WQ), half1_col = pair ? col0 : col0 + WH;
-  const bool half1_in = half1_col < A.q_dim;
+  const bool half1_in = half1_col < B.q_dim;
   const int col1 = half1_in ? half1_col : col0;
 
   // ---- loads: P instruction n = k-rows 4n .. 4n+3, 128 columns; Q instruction n = k-rows 4 (n/2) .. +3, columns half n%2
   // (the second half from the second tensor of a pair).  Wavefront w issues P 2w, 2w+1 and Q 4w .. 4w+3.  Columns past the
   // end are clamped onto the last 8 (their results are never stored), k-rows past the end come from the zero page.
-  const uint16_t* const p_base = A.p0 + (size_t)e_lo * A.p_ld + p_row0;
-  const uint16_t* const q_base0 = A.q0 + (size_t)e_lo * A.q_ld + col0;
-  const uint16_t* const q_base1 = (pair ? A.q1 : A.q0) + (size_t)e_lo * A.q_ld + col1;
+  const uint16_t* const p_base = B.p0 + (size_t)e_lo * B.p_ld + p_row0;
+  const uint16_t* const q_base0 = B.q0 + (size_t)e_lo * B.q_ld + col0;
+  const uint16_t* const q_base1 = (pair ? B.q1 : B.q0) + (size_t)e_lo * B.q_ld + col1;
   unsigned pvo[2], qvo[4];
 #pragma unroll
   for (int i = 0; i < 2; i++) {
     const int kr = 4 * (2 * wave + i) + (lane >> 4);
     const int col = min(8 * w_swizzle(lane & 15, kr), p_valid - 8);
-    pvo[i] = (unsigned)(((size_t)kr * A.p_ld + col) * 2);
+    pvo[i] = (unsigned)(((size_t)kr * B.p_ld + col) * 2);
   }
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     const int n = 4 * wave + i, kr = 4 * (n >> 1) + (lane >> 4);
-    const int col = min(8 * w_swizzle(lane & 15, kr), A.q_dim - ((n & 1) ? col1 : col0) - 8);
-    qvo[i] = (unsigned)(((size_t)kr * A.q_ld + col) * 2);
+    const int col = min(8 * w_swizzle(lane & 15, kr), B.q_dim - ((n & 1) ? col1 : col0) - 8);
+    qvo[i] = (unsigned)(((size_t)kr * B.q_ld + col) * 2);
   }
   auto issue = [&](int step, char* stage) __attribute__((always_inline)) {
     const int k0 = step * WK;
-    const uint16_t* const pb = p_base + (size_t)k0 * A.p_ld;
-    const uint16_t* const qb0 = q_base0 + (size_t)k0 * A.q_ld;
-    const uint16_t* const qb1 = q_base1 + (size_t)k0 * A.q_ld;
+    const uint16_t* const pb = p_base + (size_t)k0 * B.p_ld;
+    const uint16_t* const qb0 = q_base0 + (size_t)k0 * B.q_ld;
+    const uint16_t* const qb1 = q_base1 + (size_t)k0 * B.q_ld;
     char* const pl = stage + wave * 2048;
     char* const ql = stage + P_BYTES + wave * 4096;
     if (k0 + WK <= k_len) {
@@ -199,13 +203,13 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
   // wavefront's 128], 64 bytes of a row of dW.  The odd lane rows of block a change places with the even ones of block a + 1, and
   // 32 lanes hold 128 bytes: rows v | 4 + v (first result) and 8 + v | 12 + v (second), columns 16 a + lane%32.
   const int col = half1 ? col1 : col0;
-  float* const out = (half1 && pair ? A.f1 : A.f0) + (size_t)expert * A.f_expert_stride + (size_t)p_row0 * A.c_ld + col;
-  const unsigned lane_off = (unsigned)(4 * (lane >> 5)) * (unsigned)A.c_ld + (unsigned)(lane & 31);
-  const int n_a = idle ? 0 : min(4, (A.q_dim - col) / 32);   // (widths are multiples of 64)
+  float* const out = (half1 && pair ? B.f1 : B.f0) + (size_t)expert * A.f_expert_stride + (size_t)p_row0 * B.c_ld + col;
+  const unsigned lane_off = (unsigned)(4 * (lane >> 5)) * (unsigned)B.c_ld + (unsigned)(lane & 31);
+  const int n_a = idle ? 0 : min(4, (B.q_dim - col) / 32);   // (widths are multiples of 64)
 #pragma unroll
   for (int b = 0; b < 2; b++) {
     if (wp + 32 * b < p_valid) {
-      float* const blk = out + (size_t)(wp + 32 * b) * A.c_ld;
+      float* const blk = out + (size_t)(wp + 32 * b) * B.c_ld;
       float r[16][4];   // [i: row 8 (i / 4) + i % 4 (+ 4 for lanes 32..)][32 columns]
 #pragma unroll
       for (int i = 0; i < 2; i++)
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
           if (a < n_a) {
             float old[16];
 #pragma unroll
-            for (int i = 0; i < 16; i++) old[i] = (blk + (size_t)(8 * (i >> 2) + (i & 3)) * A.c_ld)[lane_off + 32 * a];
+            for (int i = 0; i < 16; i++) old[i] = (blk + (size_t)(8 * (i >> 2) + (i & 3)) * B.c_ld)[lane_off + 32 * a];
 #pragma unroll
             for (int i = 0; i < 16; i++) r[i][a] += old[i];
           }
@@ -231,7 +235,7 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
       }
 #pragma unroll
       for (int i = 0; i < 16; i++) {
-        float* const row = blk + (size_t)(8 * (i >> 2) + (i & 3)) * A.c_ld;
+        float* const row = blk + (size_t)(8 * (i >> 2) + (i & 3)) * B.c_ld;
 #pragma unroll
         for (int a = 0; a < 4; a++)   // (not read again: left in the caches they would evict the panels, pair 2.55 -> 2.13 ms.  Through
           // the caches the launch itself is 5 - 15 % shorter with at most 64 rows per expert, but the kernels after it pay more than
@@ -242,22 +246,41 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
   }
 }
 
-// Launches the weight gradients of one tensor (q1, f1 null) or of a pair that shares p.
-void launch_wgrad(const char* label, hipStream_t st, WgradArgs A) {
-  if (A.Et <= 0) return;
-  A.n_p_tiles = (A.p_dim + WP - 1) / WP;
-  const int tq = A.q1 ? WH : WQ;
-  A.n_q_tiles = (A.q_dim + tq - 1) / tq;
+// Fills in how a problem is cut into tiles and chunks.
+static void plan_wgrad(WgradProblem& B, int Et, long long rows) {
+  B.n_p_tiles = (B.p_dim + WP - 1) / WP;
+  const int tq = B.q1 ? WH : WQ;
+  B.n_q_tiles = (B.q_dim + tq - 1) / tq;
   // A chunk of 8 x 4 tiles reads the fewest panels, but it should write 4 KB of a row of dW side by side: runs of 2 KB, which 4
   // of the pair's tiles are, store at 4.1 - 5.5 TB/s and of 4 KB at 5.2 - 6.2 (stores alone).  So 8 x 4 of one tensor and 4 x 8 of
   // a pair (4096 x 14336: 1024 rows per expert 1902 -> 1837 us, 64 rows 775 -> 697; 150 random shapes: 0.99 of the time), except
   // where 8 tiles are a row of dW or more and the experts have rows enough for the panels to count (4096 x 1024, 512 rows: 1737
   // against 1694).
-  A.band = (A.q1 && !(A.q_dim <= 8 * WH && A.p_dim > 12 * WP && A.rows > 128ll * A.Et)) ? 4 : 8;
-  const long long total = (long long)A.Et * A.n_p_tiles * A.n_q_tiles;
-  const long long rounds = ((total + W_CHUNK - 1) / W_CHUNK + W_XCDS - 1) / W_XCDS;
-  const dim3 grid((unsigned)(rounds * W_XCDS * W_CHUNK)), block(WTHREADS);
-  MOE_LAUNCH(label, st, wgrad_kernel, grid, block, 0, st, A);
+  B.band = (B.q1 && !(B.q_dim <= 8 * WH && B.p_dim > 12 * WP && rows > 128ll * Et)) ? 4 : 8;
+  const long long chunks = ((long long)Et * B.n_p_tiles * B.n_q_tiles + W_CHUNK - 1) / W_CHUNK;
+  B.chunks = (int)chunks;
+}
+
+// Launches the weight gradients of the pair and of the single tensor.
+void launch_wgrad(hipStream_t st, WgradArgs A) {
+  if (A.Et <= 0) return;
+  plan_wgrad(A.a, A.Et, A.rows);
+  plan_wgrad(A.b, A.Et, A.rows);
+  auto grid = [](long long chunks) { return dim3((unsigned)((chunks + W_XCDS - 1) / W_XCDS * W_XCDS * W_CHUNK)); };
+  const dim3 block(WTHREADS);
+  // In one launch, unless it is long: two launches have two starts and two last rounds.  Time of the one against the two, 200
+  // random shapes: 0.73 at fewer than 64 chunks, 0.91 at 64 .. 128, 0.94 up to 256, 0.97 up to 512, 0.98 up to 1024, 0.99 - 1.0
+  // beyond.
+  if (A.a.chunks + A.b.chunks <= W_MERGE_CHUNKS) {
+    MOE_LAUNCH("ffn_bwd_dw", st, wgrad_kernel, grid(A.a.chunks + A.b.chunks), block, 0, st, A);
+    return;
+  }
+  const dim3 pair_grid = grid(A.a.chunks), down_grid = grid(A.b.chunks);
+  A.a.chunks = A.b.chunks = INT_MAX;   // every block of these launches belongs to the first problem
+  WgradArgs down = A;
+  down.a = A.b;
+  MOE_LAUNCH("ffn_bwd_dw_down", st, wgrad_kernel, down_grid, block, 0, st, down);
+  MOE_LAUNCH("ffn_bwd_dw_gate_up", st, wgrad_kernel, pair_grid, block, 0, st, A);
 }
 
 }  // namespace moe

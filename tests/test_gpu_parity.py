@@ -685,6 +685,31 @@ def test_recomputing_backward_is_bit_identical(moe):
     assert_close(host_f32(y2), Y, O.grouped_ffn_fwd_scales(xpf, offsets, wgf, wuf, wdf)[0], what="checkpointed forward y_perm")
 
 
+def test_weight_gradient_launches(moe):
+    """Both weight-gradient problems in one launch, and in two beyond its limit (here between 600 and 612 experts): an expert's
+    gradients are the same bits either way."""
+    d = f = 768
+    E, E1 = 612, 600
+    s, x, dy, off, w, ws, _, sg, su = ffn_on_device(moe, d, f, [5] * E)
+    got = []
+    for e in (E, E1):
+        sh = moe.Shape(5 * e, d, f, e, 1)
+        dw = [torch.full(sz, float("nan"), device="cuda") for sz in ((e, d, f), (e, d, f), (e, f, d))]
+        moe.profile_reset()
+        moe.profile_enable(True)
+        moe.moe_grouped_ffn_bwd(sh, dy[:5 * e], x[:5 * e], off[:e + 1], *(v[:e] for v in w), sg[:5 * e], su[:5 * e], torch.empty_like(x[:5 * e]), *dw,
+                                False, ws)
+        torch.cuda.synchronize()
+        moe.profile_enable(False)
+        labels = {label for label, _ in moe.profile_records()}
+        moe.profile_reset()
+        assert ("ffn_bwd_dw" in labels, "ffn_bwd_dw_down" in labels) == (e == E1, e == E)
+        got.append(dw)
+    assert moe.grouped_ffn_small_tiles(s) == moe.grouped_ffn_small_tiles(moe.Shape(5 * E1, d, f, E1, 1))
+    for a, b in zip(*got):
+        assert torch.equal(a[:E1], b)   # (not equal where one was left unwritten)
+
+
 def test_grouped_ffn_with_no_rows(moe):
     """T = 0: nothing to compute, but overwritten weight gradients must be exact zeros and accumulated ones untouched."""
     shape = W.MoEShape(0, 128, 64, 4, 2)
