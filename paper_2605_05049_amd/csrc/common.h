@@ -138,8 +138,12 @@ void launch_router_dw_reduce(hipStream_t st, const float* partial, float* dw, in
 // Row-tile GEMMs of the expert FFNs in small problems (few_rows.hip).
 constexpr int kFewRows = 64, kFewCols = 64;   // rows and columns of a tile
 enum RowTileKind { ROWTILE_GATE_UP = 0, ROWTILE_DOWN = 1, ROWTILE_DH = 2, ROWTILE_DX = 3 };
+constexpr int kFewSelfExperts = 2 * kWave;    // experts at most for whose tiles the kernel needs no schedule
 struct RowTileArgs {
-  const int32_t* sched;    // [0] = number of row tiles; [64 + u] = expert of tile u; [64 + max_tiles + u] = its first tile
+  const int32_t* sched;    // [0] = number of row tiles; [64 + u] = expert of tile u; [64 + max_tiles + u] = its first tile; or null:
+  int Et;                  // the blocks find their tiles from the offsets of Et <= kFewSelfExperts experts
+  int32_t* order;          // (dH of a call without a schedule) what the weight gradients read of one: [Et] experts by descending row
+  uint32_t* zero_page;     // count, and 256 bytes to be cleared
   int max_tiles;
   const int32_t* offsets;  // [E'+1]
   int n_q_tiles;           // filled by the launcher

@@ -57,6 +57,18 @@ __device__ __forceinline__ t_bf16x8 rc_frag(unsigned a) {
   return u.v;
 }
 
+// Inclusive sum over the lanes of a wavefront, in registers: inside the rows of 16 lanes, then from the last lane of a row
+// (of the first half) to the rows (the half) after it.
+__device__ __forceinline__ int wave_prefix_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);   // row_shr:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
 __device__ __forceinline__ float sigmoid(float v) { return __builtin_amdgcn_rcpf(1.0f + __expf(-v)); }   // (rcp: 1 ulp, bf16 results)
 __device__ __forceinline__ uint4 pack8(const float (&x)[8]) {
   return make_uint4(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7]));
@@ -82,11 +94,53 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void few_rows_kernel(const RowTil
   // dealt round-robin to the XCDs
   const int within = blockIdx.x / F_XCDS, xcd = blockIdx.x % F_XCDS;
   const long long lid = ((long long)(within / F_CHUNK) * F_XCDS + xcd) * F_CHUNK + within % F_CHUNK;
-  if (lid >= (long long)A.sched[0] * A.n_q_tiles) return;
   const int ut = (int)(lid / A.n_q_tiles);   // some row tile of the expert this block works for
-  const int expert = A.sched[64 + ut];
-  const int first = A.sched[64 + A.max_tiles + ut];   // index of the expert's first row tile
-  const int e_lo = A.offsets[expert], e_hi = A.offsets[expert + 1];
+  int expert, first, e_lo, e_hi;             // first: index of the expert's first row tile
+  if (A.sched) {
+    if (ut >= A.sched[0]) return;
+    expert = A.sched[64 + ut];
+    first = A.sched[64 + A.max_tiles + ut];
+    e_lo = A.offsets[expert];
+    e_hi = A.offsets[expert + 1];
+  } else {
+    // One expert per lane, twice: where the running sum of their row tiles passes ut is the expert.  (A schedule is a launch of its
+    // own, 4 - 5 us in front of every call of the expert FFN, and three loads that wait for each other in every block; this
+    // is one load and a sum over the lanes.  Replayed step of 256
+    // tokens, 8 + 2 experts, 512 x 1024: 94.5 -> 89.7 us)
+    if (KIND == ROWTILE_DH && A.order && blockIdx.x == gridDim.x - 1) {   // one block more: what the weight gradients read of a schedule
+      int* const rows_of = reinterpret_cast<int*>(lds);
+      const int n = tid < A.Et ? A.offsets[tid + 1] - A.offsets[tid] : 0;
+      if (tid < kFewSelfExperts) rows_of[tid] = n;
+      if (tid < 64) A.zero_page[tid] = 0u;
+      __syncthreads();
+      if (tid < A.Et) {
+        int rank = 0;   // (ties: lower id first)
+        for (int o = 0; o < A.Et; o++) rank += (rows_of[o] > n) || (rows_of[o] == n && o < tid);
+        A.order[rank] = tid;
+      }
+      return;
+    }
+    int lo[2], hi[2], nt[2], incl[2];
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const int e = j * kWave + lane;
+      lo[j] = A.offsets[min(e, A.Et)];
+      hi[j] = A.offsets[min(e + 1, A.Et)];
+    }
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      nt[j] = (hi[j] - lo[j] + FP - 1) / FP;
+      incl[j] = wave_prefix_sum(nt[j]);
+    }
+    const int half = __builtin_amdgcn_readlane(incl[0], kWave - 1);   // row tiles of the first 64 experts
+    if (ut >= half + __builtin_amdgcn_readlane(incl[1], kWave - 1)) return;
+    const bool upper = ut >= half;
+    const int l = __builtin_ctzll(__ballot((upper ? half + incl[1] : incl[0]) > ut));
+    expert = (upper ? kWave : 0) + l;
+    first = upper ? half + __builtin_amdgcn_readlane(incl[1] - nt[1], l) : __builtin_amdgcn_readlane(incl[0] - nt[0], l);
+    e_lo = __builtin_amdgcn_readlane(upper ? lo[1] : lo[0], l);
+    e_hi = __builtin_amdgcn_readlane(upper ? hi[1] : hi[0], l);
+  }
   const int e_tiles = (e_hi - e_lo + FP - 1) / FP;
   const int local = (int)(lid - (long long)first * A.n_q_tiles);
   const int qt = local / e_tiles, mt = local - qt * e_tiles;
@@ -248,7 +302,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void few_rows_kernel(const RowTil
 
 template <int KIND>
 static void launch_few(const char* label, hipStream_t st, const RowTileArgs& A, long long tiles) {
-  const dim3 grid((unsigned)((tiles + F_XCDS * F_CHUNK - 1) / (F_XCDS * F_CHUNK) * (F_XCDS * F_CHUNK)));
+  const dim3 grid((unsigned)((tiles + F_XCDS * F_CHUNK - 1) / (F_XCDS * F_CHUNK) * (F_XCDS * F_CHUNK)) + (A.order ? 1u : 0u));
   // 8 wavefronts per block, one block per CU, where that is all the blocks there are; else 4, two blocks per CU
   if (tiles <= 256) MOE_LAUNCH(label, st, (few_rows_kernel<KIND, 8>), grid, dim3(8 * kWave), 0, st, A);
   else MOE_LAUNCH(label, st, (few_rows_kernel<KIND, 4>), grid, dim3(4 * kWave), 0, st, A);

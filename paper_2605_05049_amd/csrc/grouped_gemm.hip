@@ -965,7 +965,10 @@ struct RowGemms {
 
   uint16_t* rows_f(size_t region) const { return reinterpret_cast<uint16_t*>(ws + region); }   // a bf16 [N, f] region of the workspace
 
+  // A call whose GEMMs all run on the 64-row tiles needs no schedule, up to kFewSelfExperts experts.
+  bool self_scheduled() const { return !any_tall && D.Et <= kFewSelfExperts && D.N > 0; }
   void schedule() const {
+    if (self_scheduled()) return;
     launch_schedule("ffn_schedule", st, offsets, any_tall ? sched_tall : sched_few, any_tall && any_few ? sched_few : nullptr, zero_page, counters,
                     D.Et, max_tiles, any_tall ? TILES_TALL : TILES_FEW);
   }
@@ -975,7 +978,12 @@ struct RowGemms {
     R.max_tiles = max_tiles; R.offsets = offsets;
     R.q_expert_stride = (size_t)D.d * D.f;
     if (few_rows_pays(D, kind)) {
-      R.sched = sched_few;
+      R.sched = self_scheduled() ? nullptr : sched_few;
+      R.Et = D.Et;
+      if (kind == ROWTILE_DH && self_scheduled()) {
+        R.order = sched_few + 64 + 2 * max_tiles;
+        R.zero_page = zero_page;
+      }
       launch_few_rows(label, st, kind, R, D.N / kFewRows + (D.N < D.Et ? D.N : D.Et));   // sum_e ceil(n_e / 64) <= N / 64 + experts with rows
       return MOE_OK;
     }

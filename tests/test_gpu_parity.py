@@ -447,6 +447,12 @@ def test_weight_gradient_edges(moe, d, f):
     (192, 576, [64, 65, 31, 0, 128], ALL_GEMMS),             # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
     (1088, 128, [200, 0, 7], ALL_GEMMS),                     # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
     (64, 64, [4500, 0, 257, 7], ALL_GEMMS),                  # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
+    # tiles found without a schedule: experts on either side of a wavefront's 64 lanes, 128 of them, the first and last ones empty
+    # or not; and one expert too many for that
+    (64, 128, [0, 65] + 61 * [3] + [130, 70, 0, 5], ALL_GEMMS),
+    (64, 64, [0] + 62 * [1] + [0, 0] + 62 * [2] + [129], ALL_GEMMS),
+    (64, 64, 64 * [0] + [3] + 63 * [0], ALL_GEMMS),
+    (64, 64, 129 * [2] + [0], ALL_GEMMS),
     # 8 row tiles of gate | up and dH on either side of a limit (1600 tiles for gate | up), next to a dX of 212 .. 520 k-steps
     (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100], ("gate_up", "down", "dh")),
     (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100], ("gate_up", "dh")),
