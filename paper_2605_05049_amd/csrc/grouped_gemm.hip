@@ -112,7 +112,7 @@ __device__ __forceinline__ int rc_swizzle(int c, int k) { return c ^ ((k & 3) <<
 //   KC: instruction n = rows 8n..8n+7, whole 128-byte lines; LDS row r = 8 chunks of 8 k-values, chunk c at position
 //       c ^ ((r >> 1) & 7).
 //   RC: instruction n = k-rows 4(n/2)..+3, r-half n%2 (128 r-values, from the second tensor when split); inside the
-//       1 KB, k-row j%4 takes 256 bytes = 16 chunks of 8 r-values, chunk c at position c ^ ((j & 3) << 2).
+//       1 KB, k-row j%4 takes 256 bytes = 16 chunks of 8 r-values, chunk c at position rc_swizzle(c, j).
 // The offset does not depend on the step, so one 32-bit register per instruction addresses the whole K loop on top
 // of a scalar base that advances by one step at a time.
 template <bool RC, bool SPLIT>
