@@ -914,10 +914,14 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 // GEMMs take 0.79 of the 256-row kernel's time at the mean and more than 1.05 of it on 1 % of the shapes (all of a call
 // decided by its tiles of f: 0.82 and 12 %).  The more uneven the counts, the longer few_rows.hip stays ahead: one
 // tall tile is then the 256-row kernel's whole time.  Us, even counts, few_rows.hip / the 256-row tiles (d x f, E, rows per expert):
-//   gate | up  2048 x 1408, 4, 256: 28 / 54   32, 8: 71 / 69     4096 x 1024, 8, 512: 124 / 106     7168 x 512, 32, 256: 250 / 206
-//   down       2048 x 1408, 4, 256: 22 / 37   32, 8: 41 / 37     7168 x 512, 8, 1024: 161 / 86     4096 x 14336, 1, 8: 72 / 33
-//   dH         2048 x 1408, 4, 256: 20 / 60   32, 8: 34 / 33     7168 x 2048, 8, 8: 37 / 42     7168 x 1024, 8, 512: 123 / 123
-//   dX         2048 x 1408, 4, 256: 34 / 63   32, 8: 65 / 68     7168 x 512, 8, 1024: 248 / 128     4096 x 14336, 1, 8: 96 / 54
+//   gate | up  2048 x 1408, 4, 256: 29 / 45   32, 8: 72 / 70     4096 x 1024, 8, 512: 110 / 88      7168 x 512, 32, 256: 220 / 170
+//   down       2048 x 1408, 4, 256: 17 / 32   32, 8: 41 / 37     7168 x 512, 8, 1024: 173 / 84      4096 x 14336, 1, 8: 71 / 33
+//   dH         2048 x 1408, 4, 256: 22 / 51   32, 8: 35 / 32     7168 x 2048, 8, 8: 37 / 41         7168 x 1024, 8, 512: 105 / 111
+//   dX         2048 x 1408, 4, 256: 24 / 54   32, 8: 65 / 67     7168 x 512, 8, 1024: 248 / 126     4096 x 14336, 1, 8: 97 / 53
+// (The fit is older than the 256-row kernel's present loop.  With that, on 6000 shapes drawn around the limits: 0.86 of its time at
+// the mean, more than 1.05 on 7 %, where the better kernel for each GEMM would give 0.84; furthest off is gate | up of 16 .. 96
+// rows per expert, 1.07 - 1.10 of the better one.  But a call that leaves the 64-row tiles needs a schedule, 5 us, which takes most
+// of that back, so the limits stand.)
 constexpr int kRowClasses = 5, kStepClasses = 5;
 constexpr int kRowsBelow[kRowClasses - 1] = {16, 40, 64, 96};     // rows per expert on average
 constexpr int kStepsBelow[kStepClasses - 1] = {48, 64, 96, 128};  // k-steps of 64, both passes of dX counted
