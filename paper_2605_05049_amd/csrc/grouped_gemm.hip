@@ -23,8 +23,8 @@
 // the chip, whose clock follows its power, runs it faster: 2.04 against 1.80 PFLOP/s in a loop of nothing but MFMAs on normal
 // values.)  Tiles stream HBM/L2 -> LDS with the direct 16-byte global->LDS load (no register staging) into two stages of 64 k.
 // The two wavefronts of a SIMD take turns: one reads fragments and requests loads while the other multiplies, 32 MFMAs at a
-// time, with a barrier between the turns (see the K loop); a load is in flight for up to a step and a half.  8192 rows on 8 equal
-// experts of 4096 x 14336: dX 1507 -> 1336 us (1440 TFLOP/s; matrix pipes busy 0.83 of the cycles at 1.66 GHz), down 764 -> 681,
+// time, with a barrier between the turns (see the K loops; the router's contractions have one of their own); a load is in flight
+// for up to a step and a half.  8192 rows on 8 equal experts of 4096 x 14336: dX 1507 -> 1336 us (1440 TFLOP/s; matrix pipes busy 0.83 of the cycles at 1.66 GHz), down 764 -> 681,
 // gate | up 1554 -> 1498, dH 917 -> 876 against a schedule in which both wavefronts read, multiplied and loaded through the
 // whole step on 32x32x16 MFMAs; without any loads the loop is 5 % shorter in cycles, without fragment reads the same: what is
 // left is the turns (20 %) and the clock.
@@ -238,6 +238,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
   constexpr int TQ = TILE / NQ;  // q extent per output tensor
   constexpr bool RAGGED_K = KIND == 1 || (NPASS == 2 && Q_RC);   // the router's: the FFN's contractions over d and f are whole steps
+  constexpr bool TURNS = !RAGGED_K;   // (see the K loops)
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -396,8 +397,11 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   // (all stages of P, then all of Q: an operand's stages then share their address registers)
   auto p_area = [&](int s) __attribute__((always_inline)) { return lds + s * P_STAGE; };
   auto q_area = [&](int s) __attribute__((always_inline)) { return lds + STAGES * P_STAGE + s * OPERAND_BYTES; };
-  // first row of block b of this wavefront
-  auto p_row = [&](int b) __attribute__((always_inline)) { return (b >> 2) * 128 + (wave & 1) * 16 * ((b >> 2) == LAST ? LAST_NB : 4) + (b & 3) * 16; };
+  // first row of block b of this wavefront (of the router's weight gradient 128 rows in a row: its epilogue, which is most of the
+  // time of a contraction of one or two steps, stores them faster: 600 tokens x 2048, 256 experts 21.9 -> 17.5 us)
+  auto p_row = [&](int b) __attribute__((always_inline)) {
+    return KIND == 1 ? (wave & 1) * 128 + b * 16 : (b >> 2) * 128 + (wave & 1) * 16 * ((b >> 2) == LAST ? LAST_NB : 4) + (b & 3) * 16;
+  };
   f32x4 acc[4][NB];  // [q block][p block]
 #pragma unroll
   for (int a = 0; a < 4; a++)
@@ -406,10 +410,10 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 #pragma unroll
       for (int v = 0; v < 4; v++) acc[a][b][v] = 0.f;
   // Direct loads.  P: part h is 16 instructions, two of each wavefront (K-contiguous: instruction n = rows 8 n ..; R-
-  // contiguous: n = 2 j + h), or 8 where it has at most 64 rows.  Q: four of each.
+  // contiguous: four in a row of each wavefront, two per part), or 8 where it has at most 64 rows.  Q: four of each.
   constexpr int LAST_LOADS = LAST_NB > 2 ? 2 : 1;
   auto p_instr = [&](int h, int i) __attribute__((always_inline)) {
-    return h == LAST && LAST_LOADS == 1 ? 16 * h + wave : P_RC ? 2 * (2 * wave + i) + h : 16 * h + 2 * wave + i;
+    return h == LAST && LAST_LOADS == 1 ? 16 * h + wave : P_RC ? 4 * wave + 2 * h + i : 16 * h + 2 * wave + i;
   };
   unsigned pvo[PARTS][2];
 #pragma unroll
@@ -442,7 +446,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   // address register and differ in the instruction's offset field)
   auto rp = [&](int h, int b, int kk, int s) __attribute__((always_inline)) {
     const unsigned base = (unsigned)(size_t)(lptr_t)p_area(s);
-    if (P_RC) return read_frag_at<P_RC>(b == 0 ? p_off0 : b == 1 ? p_off1 : b == 2 ? p_off2 : p_off3, kk, base + 1024u * h);
+    if (P_RC) return read_frag_at<P_RC>((b == 0 ? p_off0 : b == 1 ? p_off1 : b == 2 ? p_off2 : p_off3) ^ (h ? 128u : 0u), kk, base);   // (64 rows: bit 3 of the chunk)
     if (h == LAST && LAST > 0 && LAST_NB < 4) return read_frag_at<P_RC>(p_off_last, kk, base + 2048u * b);
     return read_frag_at<P_RC>(p_off0, kk, base + 16384u * h + 2048u * b);
   };
@@ -486,6 +490,48 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
       ring_step(0, 2, kt);
       if (kt + 1 < kt_end) ring_step(1, 0, kt + 1);
       if (kt + 2 < kt_end) ring_step(2, 1, kt + 2);
+    }
+  } else if constexpr (!TURNS) {
+    // The router's GEMMs: both wavefronts of a SIMD read, multiply and request loads all through a step, one barrier per step and
+    // one step of loads in flight, which wavefronts 4..7 request right after the barrier and 0..3 after three quarters of their
+    // MFMAs.  Fragments roll three p blocks ahead of their MFMAs.  (Their contractions are short, 1 to 32 steps, and their
+    // R-contiguous fragments are two LDS instructions each; the turns below begin with a burst of them.  With the turns, 700
+    // random shapes: dW_r 1.12 of the time at the mean, 30000 tokens x 1088, 8 experts 34.4 us for 27.9 here, 16384 x 1024, 128
+    // experts 24.9 for 21.5; shorter, 0.9 - 0.96, only where an XCD has 36 .. 56 tiles of 16 steps or more.  dx of 129 .. 1000
+    // experts 1.10 at the mean, 600 x 2048, 1000 experts 47.3 for 41.6; from 512 experts and 16384 x 4096 on 0.93.)
+    auto request_all = [&](int kt, int s) __attribute__((always_inline)) {
+#pragma unroll
+      for (int h = 0; h < PARTS; h++) issue_p(h, kt, s);
+      issue_q(kt, s);
+    };
+    if (kt_begin < kt_end) request_all(kt_begin, 0);
+    auto rolling_step = [&](int s, int fill, int kt) __attribute__((always_inline)) {
+      wait_loads<0>();
+      __syncthreads();   // step kt has landed for everyone; everyone is done with step kt - 1, whose stage step kt + 1 takes
+      if (second_half && kt + 1 < kt_end) request_all(kt + 1, fill);
+      constexpr int AHEAD = 3;
+      bf16x8 qf[2][4], pf[NB];
+      auto read_p = [&](int i) __attribute__((always_inline)) { pf[i % NB] = rp((i % NB) >> 2, (i % NB) & 3, 32 * (i / NB), s); };
+#pragma unroll
+      for (int a = 0; a < 4; a++) qf[0][a] = rq(a, 0, s);
+#pragma unroll
+      for (int i = 0; i < AHEAD; i++) read_p(i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 2 * NB; i++) {   // p block i % NB, k-values 32 (i / NB) ..
+        const int g = i / NB, b = i % NB;
+        if (i == 2 * NB * 3 / 4 && !second_half && kt + 1 < kt_end) request_all(kt + 1, fill);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 0; a < 4; a++) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[g][a], pf[b], acc[a][b], 0, 0, 0);
+        if (i + AHEAD < 2 * NB) read_p(i + AHEAD);
+        if (g == 0 && b >= NB - 4) qf[1][b - (NB - 4)] = rq(b - (NB - 4), 32, s);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    for (int kt = kt_begin; kt < kt_end; kt += 2) {
+      rolling_step(0, 1, kt);
+      if (kt + 1 < kt_end) rolling_step(1, 0, kt + 1);
     }
   } else {
     // Two wavefronts share a SIMD, and at any time one multiplies while the other uses the memory.  A step has PARTS phases of two

@@ -76,6 +76,14 @@ def test_router_few_tokens(moe, T, d, E):
     test_router_forward_and_backward(moe, T, d, E)
 
 
+# dx of more than 128 experts: last row tiles of every class (64, 128, 192 and 256 rows), after whole ones and alone, over
+# contractions of 3, 4 and 16 steps per pass, whole and ragged
+@pytest.mark.parametrize("T,d,E", [(256 + 40, 320, 130), (512 + 100, 64, 200), (256 + 160, 576, 150), (40, 256, 1000), (100, 320, 256),
+                                   (160, 128, 192), (256 + 193, 192, 1000), (129, 64, 129), (64, 64, 255)])
+def test_router_many_experts_tile_heights(moe, T, d, E):
+    test_router_forward_and_backward(moe, T, d, E)
+
+
 # on which side of the one-launch backward's rule a size lies: up to 1024 tokens with 8 experts; with 16 up to 512, or 64 where
 # the width is below 128 or above 8192
 @pytest.mark.parametrize("T,d,E,one_launch", [(1024, 64, 8, True), (1025, 128, 8, False), (512, 128, 16, True), (513, 128, 9, False),
