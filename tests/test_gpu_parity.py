@@ -387,7 +387,10 @@ def test_grouped_ffn_every_tile_height(moe, d, f, counts):
     (one 32-row block per wavefront), 65..128, 129..256, 257..320 (a full tile that carries up to 64 more rows), 321
     (a full tile plus a short one), an empty expert, and a multi-tile expert whose remainder rides on its last tile.
     (f = 1088 = 4 * 256 + 64 also puts a 64-wide last column tile on every class.)  These shapes are small enough for most of
-    their GEMMs to run on the 64-row tiles; test_grouped_ffn_on_256_row_tiles has the same counts on the others."""
+    their GEMMs to run on the 64-row tiles; test_grouped_ffn_on_256_row_tiles has the same counts on the others.
+
+    The workspace holds NaN and -1 before either call: neither reads what it has not written (the schedule, the order of the
+    experts, the zero page)."""
     counts = np.array(counts, dtype=np.int64)
     E, N = counts.size, int(counts.sum())
     offsets = np.zeros(E + 1, dtype=np.int32)
@@ -404,6 +407,7 @@ def test_grouped_ffn_every_tile_height(moe, d, f, counts):
     y = torch.full((N, d), float("nan"), dtype=torch.bfloat16, device="cuda")
     sg = torch.full((N, f), float("nan"), dtype=torch.bfloat16, device="cuda")
     su = torch.full((N, f), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws.fill_(255)
     moe.moe_grouped_ffn_fwd(s, d_xp, d_off, d_wg, d_wu, d_wd, y, sg, su, ws)
     xp, dyp = W.bf16_bits_to_f32(xp_bits), W.bf16_bits_to_f32(dy_bits)
     wg, wu, wd = W.bf16_bits_to_f32(wgb), W.bf16_bits_to_f32(wub), W.bf16_bits_to_f32(wdb)
@@ -416,6 +420,7 @@ def test_grouped_ffn_every_tile_height(moe, d, f, counts):
     gwg = torch.full((E, d, f), 7.0, dtype=torch.float32, device="cuda")
     gwu = torch.full((E, d, f), 7.0, dtype=torch.float32, device="cuda")
     gwd = torch.full((E, f, d), 7.0, dtype=torch.float32, device="cuda")
+    ws.fill_(255)
     moe.moe_grouped_ffn_bwd(s, dev_bf16(dy_bits), d_xp, d_off, d_wg, d_wu, d_wd, sg, su, dxp, gwg, gwu, gwd, 0, ws)
     dX, dWg, dWu, dWd = O.grouped_ffn_bwd(dyp, xp, offsets, wg, wu, wd)
     qX, qWg, qWu, qWd = O.grouped_ffn_bwd_scales(dyp, xp, offsets, wg, wu, wd)
@@ -448,10 +453,11 @@ def test_weight_gradient_edges(moe, d, f):
     (1088, 128, [200, 0, 7], ALL_GEMMS),                     # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
     (64, 64, [4500, 0, 257, 7], ALL_GEMMS),                  # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
     # tiles found without a schedule: experts on either side of a wavefront's 64 lanes, 128 of them, the first and last ones empty
-    # or not; and one expert too many for that
+    # or not; and one and two experts too many for that
     (64, 128, [0, 65] + 61 * [3] + [130, 70, 0, 5], ALL_GEMMS),
     (64, 64, [0] + 62 * [1] + [0, 0] + 62 * [2] + [129], ALL_GEMMS),
     (64, 64, 64 * [0] + [3] + 63 * [0], ALL_GEMMS),
+    (64, 64, 128 * [2] + [0], ALL_GEMMS),
     (64, 64, 129 * [2] + [0], ALL_GEMMS),
     # 8 row tiles of gate | up and dH on either side of a limit (1600 tiles for gate | up), next to a dX of 212 .. 520 k-steps
     (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100], ("gate_up", "down", "dh")),
@@ -460,9 +466,18 @@ def test_weight_gradient_edges(moe, d, f):
 ])
 def test_small_problem_tiles(moe, d, f, counts, small):
     """The kernel for small problems, alone and next to the other one in a call (two schedules), and both sides of the rule
-    that chooses it for each GEMM."""
+    that chooses it for each GEMM.  Only a call whose two GEMMs both run on it, with at most 128 experts, launches no schedule."""
     assert moe.grouped_ffn_small_tiles(moe.Shape(sum(counts), d, f, len(counts), 1)) == small
-    test_grouped_ffn_every_tile_height(moe, d, f, counts)
+    moe.profile_reset()
+    moe.profile_enable(True)
+    try:
+        test_grouped_ffn_every_tile_height(moe, d, f, counts)
+        labels = [label for label, _ in moe.profile_records()]
+    finally:
+        moe.profile_enable(False)
+        moe.profile_reset()
+    calls = ("gate_up", "down"), ("dh", "dx")
+    assert labels.count("ffn_schedule") == sum(len(counts) > 128 or not set(call) <= set(small) for call in calls)
 
 
 @pytest.mark.parametrize("d,f,counts,small", [
