@@ -383,11 +383,12 @@ MANY_TILE_COUNTS = [1300, 70, 0, 1400, 1024 + 30]   # 5 row tiles with a tall la
                                         (128, 3136, HEIGHT_COUNTS), (3072, 1536, FEW_COUNTS),
                                         (256, 2304, MANY_TILE_COUNTS)])
 def test_grouped_ffn_every_tile_height(moe, d, f, counts):
-    """Experts whose row counts hit every height class of a row tile and both sides of every class boundary: 1..64 rows
-    (one 32-row block per wavefront), 65..128, 129..256, 257..320 (a full tile that carries up to 64 more rows), 321
-    (a full tile plus a short one), an empty expert, and a multi-tile expert whose remainder rides on its last tile.
+    """Experts whose row counts fall into the height classes of a row tile: 1..64 rows (two 16-row blocks per wavefront), 65..128
+    (four), 129..192 (six), 193..256 (eight), 257..288 and 289..320 (nine and ten: a full tile that carries up to 64 more
+    rows), 321 (a full tile plus a short one), an empty expert, and a multi-tile expert whose remainder rides on its last tile.
     (f = 1088 = 4 * 256 + 64 also puts a 64-wide last column tile on every class.)  These shapes are small enough for most of
-    their GEMMs to run on the 64-row tiles; test_grouped_ffn_on_256_row_tiles has the same counts on the others.
+    their GEMMs to run on the 64-row tiles; test_grouped_ffn_on_256_row_tiles has the same counts on the others, and
+    test_row_tile_classes both sides of every class boundary.
 
     The workspace holds NaN and -1 before either call: neither reads what it has not written (the schedule, the order of the
     experts, the zero page)."""
@@ -500,8 +501,9 @@ def test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small):
     test_grouped_ffn_every_tile_height(moe, d, f, counts)
 
 
-# rows on either side of every class boundary (128, 192, 256, 288, 320), in its middle, and one expert of three tiles
-CLASS_COUNTS = [129, 160, 161, 192, 193, 224, 257, 272, 273, 288, 289, 319, 0, 512 + 33, 100, 66]
+# rows on either side of every class boundary (64, 128, 192, 256, 288, 320), inside the classes, and experts of two and three tiles
+# whose last ones are of the classes of 320 and 192 rows
+CLASS_COUNTS = [64, 65, 128, 129, 161, 192, 193, 256, 257, 272, 288, 289, 320, 0, 512 + 33, 512 + 160, 321, 100, 224]
 
 
 @pytest.mark.parametrize("d,f,counts,small", [
