@@ -254,7 +254,6 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   // partial tile to the workspace and the part that arrives last adds them up (no part ever waits for another).
   constexpr bool SPLITK = (KIND == 0 && NQ == 1);   // (the SwiGLU forward, with two output tensors per tile, measured no gain)
   int split = 1, part = 0, part_slot = 0;
-  int p_tile_idx;  // index of the tile along p
   if (KIND == 0) {
     // Groups of 32 consecutive tiles of the logical order (about 4 row tiles x 8 column tiles of one expert: the tiles
     // that share panels) are dealt round-robin to the XCDs, so that every XCD gets the same mix of experts and of tile
@@ -319,7 +318,6 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     const int mt = tall_last ? (m == 0 ? e_tiles - 1 : m - 1) : m;
     p_row0 = e_lo + mt * TILE;
     p_valid = (mt == e_tiles - 1) ? e_hi - p_row0 : TILE;   // (the last tile may be a tall one: up to 320 rows)
-    p_tile_idx = mt;
     q0_col = qt * TQ;
     k_len = A.k_dim;
   } else {
@@ -340,7 +338,6 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     const int pt = (super % sp) * 8 + (in_super & 7);
     const int qt = (super / sp) * 4 + (in_super >> 3);
     if (pt >= A.n_p_tiles || qt >= A.n_q_tiles) return;  // padding of the super-tile grid
-    p_tile_idx = pt;
     const int e_lo = A.offsets[expert], e_hi = A.offsets[expert + 1];
     k_len = e_hi - e_lo;
     krow0 = (size_t)e_lo;
