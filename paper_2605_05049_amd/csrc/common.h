@@ -14,7 +14,7 @@ constexpr int kMaxExperts = 1024;    // E' limit of the ABI
 constexpr int kPermSlotsPerBlock = 1024;  // slots ranked by one block of the counting sort
 constexpr int kSplitParts = 256;     // K-split parts in flight at most: 32 per XCD (one per CU)
 constexpr int kSplitCounters = 128;  // split tiles at most: 16 per XCD
-constexpr int kMaxWidth = 1 << 22;   // d_model, d_ffn limit: 256 rows x 2^22 elements x 2 bytes < 2^32
+constexpr int kMaxWidth = 1 << 22;   // d_model, d_ffn limit: 320 rows x 2^22 elements x 2 bytes < 2^32
 constexpr int kMinTileRows = 64;     // smallest row-tile height any GEMM schedule may use
 
 struct Dims {
@@ -140,10 +140,11 @@ constexpr int kFewRows = 64, kFewCols = 64;   // rows and columns of a tile
 enum RowTileKind { ROWTILE_GATE_UP = 0, ROWTILE_DOWN = 1, ROWTILE_DH = 2, ROWTILE_DX = 3 };
 constexpr int kFewSelfExperts = 2 * kWave;    // experts at most for whose tiles the kernel needs no schedule
 struct RowTileArgs {
-  const int32_t* sched;    // [0] = number of row tiles; [64 + u] = expert of tile u; [64 + max_tiles + u] = its first tile; or null:
-  int Et;                  // the blocks find their tiles from the offsets of Et <= kFewSelfExperts experts
-  int32_t* order;          // (dH of a call without a schedule) what the weight gradients read of one: [Et] experts by descending row
-  uint32_t* zero_page;     // count, and 256 bytes to be cleared
+  const int32_t* sched;    // [0] = number of row tiles; [64 + u] = expert of tile u; [64 + max_tiles + u] = its first tile.  Null: the
+                           // blocks find their tiles from the offsets of Et <= kFewSelfExperts experts
+  int Et;
+  int32_t* order;          // dH without a schedule writes what the weight gradients read of one: [Et] experts by descending row count
+  uint32_t* zero_page;     // ... and clears these 256 bytes
   int max_tiles;
   const int32_t* offsets;  // [E'+1]
   int n_q_tiles;           // filled by the launcher
@@ -213,8 +214,8 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 // One direct global->LDS load: 16 bytes per lane, lane L lands at lds_base + 16 L (lds_base is wave-uniform).
 // Written as inline assembly on purpose: the compiler does not track it, so it never makes the (transposing)
 // fragment reads of the OTHER stage wait for loads still in flight.  A kernel that uses them orders them itself: before a
-// stage is read, an explicit s_waitcnt vmcnt(n) waits until this wavefront's loads of it have landed (n = how many it has
-// issued since, 0 with two stages, one stage's worth with three), and a barrier after it publishes the stage if other
+// stage (or the part of one that is read next) is read, an explicit s_waitcnt vmcnt(n) waits until this wavefront's loads of it
+// have landed (n = how many it has issued since), and a barrier after it publishes the stage if other
 // wavefronts read it (few_rows.hip's read only what they loaded themselves).  No compiler-tracked vector-memory load is in
 // flight while these are (the epilogue starts after the last such wait, which is vmcnt(0)).  m0 receives the LDS base: the
 // backend reserves m0 (it is never allocated, and the compiler writes it only directly before an instruction of its

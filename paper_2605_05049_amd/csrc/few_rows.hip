@@ -104,9 +104,8 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void few_rows_kernel(const RowTil
     e_hi = A.offsets[expert + 1];
   } else {
     // One expert per lane, twice: where the running sum of their row tiles passes ut is the expert.  (A schedule is a launch of its
-    // own, 4 - 5 us in front of every call of the expert FFN, and three loads that wait for each other in every block; this
-    // is one load and a sum over the lanes.  Replayed step of 256
-    // tokens, 8 + 2 experts, 512 x 1024: 94.5 -> 89.7 us)
+    // own, 4 - 5 us, and three loads that wait for each other in every block; these are four that do not, and a sum over the
+    // lanes.  Replayed step of 256 tokens, top-2 of 8 experts, 512 x 1024: 94.5 -> 89.7 us)
     if (KIND == ROWTILE_DH && A.order && blockIdx.x == gridDim.x - 1) {   // one block more: what the weight gradients read of a schedule
       int* const rows_of = reinterpret_cast<int*>(lds);
       const int n = tid < A.Et ? A.offsets[tid + 1] - A.offsets[tid] : 0;

@@ -21,7 +21,8 @@
 // Tiling: 512 threads = 8 wavefronts (2 along p x 4 along q); each wavefront owns 128 p x 64 q as 8 x 4 MFMA
 // 16x16x32 blocks (128 fp32 accumulators per lane).  (That shape moves fewer accumulator bytes per multiply than 32x32x16, and
 // the chip, whose clock follows its power, runs it faster: 2.04 against 1.80 PFLOP/s in a loop of nothing but MFMAs on normal
-// values.)  Tiles stream HBM/L2 -> LDS with the direct 16-byte global->LDS load (no register staging) into two stages of 64 k.
+// values.)  Tiles stream HBM/L2 -> LDS with the direct 16-byte global->LDS load (no register staging) into two stages of 64 k
+// (three of tiles of 128 or 64 rows).
 // The two wavefronts of a SIMD take turns: one reads fragments and requests loads while the other multiplies, 32 MFMAs at a
 // time, with a barrier between the turns (see the K loops; the router's contractions have one of their own); a load is in flight
 // for up to a step and a half.  8192 rows on 8 equal experts of 4096 x 14336: dX 1507 -> 1336 us (1440 TFLOP/s; matrix pipes busy 0.83 of the cycles at 1.66 GHz), down 764 -> 681,
@@ -851,7 +852,8 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 // sched[64 + max_tiles + u] = index of that expert's first tile; sched[64 + 2 max_tiles + i] = expert with the i-th most rows.
 // Block 0 builds `sched` and also clears the zero page and the split-tile counters; block 1, of a call whose GEMMs do not all
 // run on the same tiles, builds `sched_few` for the 64-row ones.
-// (A launch in front of every FFN call: bound by latency.  As many wavefronts as the experts need, prefix sums by lane
+// (A launch in front of the GEMMs of every FFN call that has one on 256-row tiles, or more than kFewSelfExperts experts: bound
+// by latency.  As many wavefronts as the experts need, prefix sums by lane
 // shuffles, two barriers: 3.7 -> 2.5 us at E' = 8, 5.4 -> 4.8 at 66, 8.3 -> 7.1 at 128 against 1024 threads and a scan in LDS.)
 __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
                                                               int32_t* __restrict__ sched_few, uint32_t* __restrict__ zero_page,
@@ -962,9 +964,10 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 //   dH         2048 x 1408, 4, 256: 22 / 51   32, 8: 35 / 32     7168 x 2048, 8, 8: 37 / 41         7168 x 1024, 8, 512: 105 / 111
 //   dX         2048 x 1408, 4, 256: 24 / 54   32, 8: 65 / 67     7168 x 512, 8, 1024: 248 / 126     4096 x 14336, 1, 8: 97 / 53
 // (The fit is older than the 256-row kernel's present loop.  With that, on 6000 shapes drawn around the limits: 0.86 of its time at
-// the mean, more than 1.05 on 7 %, where the better kernel for each GEMM would give 0.84; furthest off is gate | up of 16 .. 96
-// rows per expert, 1.07 - 1.10 of the better one.  But a call that leaves the 64-row tiles needs a schedule, 5 us, which takes most
-// of that back, so the limits stand.)
+// the mean, more than 1.05 on 7 %, where the better kernel for each GEMM would give 0.84.  Furthest off is gate | up of 16 .. 96
+// rows per expert: 1.08 of the better one where down is on these tiles too, 1.13 where it is not.  In the first case the other
+// kernel would need a schedule, 5 us, which takes most of the gain back, if there are at most kFewSelfExperts experts; where the
+// call has one anyway the limits are too high.)
 constexpr int kRowClasses = 5, kStepClasses = 5;
 constexpr int kRowsBelow[kRowClasses - 1] = {16, 40, 64, 96};     // rows per expert on average
 constexpr int kStepsBelow[kStepClasses - 1] = {48, 64, 96, 128};  // k-steps of 64, both passes of dX counted

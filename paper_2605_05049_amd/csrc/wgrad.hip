@@ -72,8 +72,8 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  // ---- block id -> tile.  Chunks of 32 consecutive tiles (A.band = 8 p x 4 q of one expert, which share panels) are dealt
-  // round-robin to the XCDs, experts with the most rows first (the tail of the launch is then made of short tiles).
+  // ---- block id -> tile.  Chunks of 32 consecutive tiles (B.band p x 32 / B.band q of one expert, which share panels) are dealt
+  // round-robin to the XCDs, of each problem the experts with the most rows first (its last tiles are then short ones).
   const int within = blockIdx.x / W_XCDS, xcd = blockIdx.x % W_XCDS;
   const long long launch_chunk = (long long)(within / W_CHUNK) * W_XCDS + xcd;
   const bool is_b = launch_chunk >= A.a.chunks;   // (a launch may carry two problems, the second's chunks after the first's)
@@ -253,9 +253,13 @@ static void plan_wgrad(WgradProblem& B, int Et, long long rows) {
   B.n_q_tiles = (B.q_dim + tq - 1) / tq;
   // A chunk of 8 x 4 tiles reads the fewest panels, but it should write 4 KB of a row of dW side by side: runs of 2 KB, which 4
   // of the pair's tiles are, store at 4.1 - 5.5 TB/s and of 4 KB at 5.2 - 6.2 (stores alone).  So 8 x 4 of one tensor and 4 x 8 of
-  // a pair (4096 x 14336: 1024 rows per expert 1902 -> 1837 us, 64 rows 775 -> 697; 150 random shapes: 0.99 of the time), except
-  // where 8 tiles are a row of dW or more and the experts have rows enough for the panels to count (4096 x 1024, 512 rows: 1737
-  // against 1694).
+  // a pair (4096 x 14336: 1024 rows per expert 1902 -> 1837 us, 64 rows 775 -> 697), except where 8 tiles are a row of dW or more
+  // and the experts have rows enough for the panels to count.  Time of 8 x 4 against 4 x 8, both weight gradients of 700 random
+  // shapes (64 .. 3072 columns of the pair, 24 .. 3000 rows per expert): where the exception holds 0.987 at the mean and 0.88 at
+  // best (156 shapes; 4096 x 1024, 512 rows: 1694 us against 1737), with at most 128 rows 0.998, with more than 1024 columns 1.002
+  // and 1.07 at worst.  (A dW of at most 12 tiles along p is left out because a band of 8 leaves 1 .. 4 of them behind; there it
+  // is 0.990 on 23 shapes of few columns and up to 1.07 of many.)  The rule is 0.5 % off the better one at the mean, 4 x 8
+  // everywhere 0.8 %.
   B.band = (B.q1 && !(B.q_dim <= 8 * WH && B.p_dim > 12 * WP && rows > 128ll * Et)) ? 4 : 8;
   const long long chunks = ((long long)Et * B.n_p_tiles * B.n_q_tiles + W_CHUNK - 1) / W_CHUNK;
   B.chunks = (int)chunks;
