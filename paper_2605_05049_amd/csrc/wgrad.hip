@@ -115,8 +115,18 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
     const int col = min(8 * w_swizzle(lane & 15, kr), B.q_dim - ((n & 1) ? col1 : col0) - 8);
     qvo[i] = (unsigned)(((size_t)kr * B.q_ld + col) * 2);
   }
+  const int nk = (k_len + WK - 1) / WK;
+  // The 32 tiles of a chunk run together, and those that share a panel would ask for the same lines at the same time and all wait for
+  // the same misses.  So each begins at another step and goes round (of the first 8, 4 of many; along either direction of the chunk
+  // neighbours differ): a line is then waited for by one of them and in the L2 for the others.  (Further apart, by an eighth of the
+  // steps, the panels have left the L2 when the last tile comes to them: pair of 8 x 1024 rows, 4096 x 14336, 1800 -> 2450 us.  128
+  // experts of 0 .. 3100 rows, 4096 x 1024: dW_down 876 -> 765 us, the pair 1600 -> 1480 .. 1560; 3968 x 1536, 31 of 230: both 574 ->
+  // 543; 2048 x 8192, 8 of 2048: 1396 -> 1391, and 1372 over 8 steps, which costs 8 x 1024 rows of 4096 x 14336 1 %.)
+  const int ring_p = in_band % band_p, ring_q = in_band / band_p;
+  const int begin = B.band == 4 ? 2 * ring_p + ring_q : ring_p + 2 * ring_q;
+  const int rot = nk > 24 ? begin & 3 : nk >= 8 ? begin & 7 : nk >= 4 ? (begin & 7) * nk / 8 : 0;
   auto issue = [&](int step, char* stage) __attribute__((always_inline)) {
-    const int k0 = step * WK;
+    const int turned = step + rot, k0 = (turned >= nk ? turned - nk : turned) * WK;
     const uint16_t* const pb = p_base + (size_t)k0 * B.p_ld;
     const uint16_t* const qb0 = q_base0 + (size_t)k0 * B.q_ld;
     const uint16_t* const qb1 = q_base1 + (size_t)k0 * B.q_ld;
@@ -142,7 +152,6 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
     }
   };
 
-  const int nk = (k_len + WK - 1) / WK;
   // The two blocks of a CU start together, and with experts of equal size they stay in step: both multiply, then both store, and
   // neither covers the other.  So every other 32 blocks of an XCD (one of the two on each CU) issue before their partners: they
   // finish their multiplies first and store while the others catch up.  (dW_down of 8 experts x 1024 rows, 4096 x 14336: 1097
