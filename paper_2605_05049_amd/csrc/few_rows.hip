@@ -268,12 +268,16 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void few_rows_kernel(const RowTil
       if (item < ITEMS && p < p_valid) {
         const size_t o = (size_t)(p_row0 + p) * A.c_ld + q0_col + 8 * (item & 7);
         if (KIND == ROWTILE_GATE_UP) {
-          float h[8];
+          if (A.c0) {   // (what the caller does not want is null)
+            *reinterpret_cast<uint4*>(A.c0 + o) = pack8(x[0][i]);
+            *reinterpret_cast<uint4*>(A.c1 + o) = pack8(x[NQ - 1][i]);
+          }
+          if (A.c2) {
+            float h[8];
 #pragma unroll
-          for (int j = 0; j < 8; j++) h[j] = x[0][i][j] * sigmoid(x[0][i][j]) * x[NQ - 1][i][j];
-          *reinterpret_cast<uint4*>(A.c0 + o) = pack8(x[0][i]);
-          *reinterpret_cast<uint4*>(A.c1 + o) = pack8(x[NQ - 1][i]);
-          *reinterpret_cast<uint4*>(A.c2 + o) = pack8(h);
+            for (int j = 0; j < 8; j++) h[j] = x[0][i][j] * sigmoid(x[0][i][j]) * x[NQ - 1][i][j];
+            *reinterpret_cast<uint4*>(A.c2 + o) = pack8(h);
+          }
         } else if (KIND == ROWTILE_DH) {
           float g[8], u[8], dg[8], du[8], h[8];
           unpack8(gi[i], g);

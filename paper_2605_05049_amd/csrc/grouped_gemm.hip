@@ -66,7 +66,8 @@ constexpr int kCusPerXcd = 32;
 #ifndef MOE_SPLIT_PART_STEPS
 #define MOE_SPLIT_PART_STEPS 16
 #endif
-enum Epilogue { EPI_BF16 = 0, EPI_SWIGLU = 1, EPI_DSWIGLU = 2, EPI_F32 = 3 };
+enum Epilogue { EPI_BF16 = 0, EPI_SWIGLU = 1, EPI_DSWIGLU = 2, EPI_F32 = 3,
+                EPI_SWIGLU_H = 4, EPI_SWIGLU_GU = 5 };   // of the SwiGLU forward H alone (G and U are not kept), G and U alone (recomputed)
 
 struct GemmArgs {
   // row-tile problems (forward / dgrad): schedule built on the device
@@ -240,6 +241,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   constexpr int TQ = TILE / NQ;  // q extent per output tensor
   constexpr bool RAGGED_K = KIND == 1 || (NPASS == 2 && Q_RC);   // the router's: the FFN's contractions over d and f are whole steps
   constexpr bool TURNS = !RAGGED_K;   // (see the K loops)
+  constexpr bool IS_SWIGLU = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_H || EPI == EPI_SWIGLU_GU;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -757,10 +759,13 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     }
     return;
   }
-  if constexpr (EPI == EPI_BF16 || EPI == EPI_SWIGLU) {
+  if constexpr (EPI == EPI_BF16 || IS_SWIGLU) {
     // The bf16 results are made from the accumulators (of the SwiGLU forward a lane holds G and U of the same elements) and
     // bounced as such, half the LDS bytes of the sums.
-    constexpr int PITCH16 = W * 2 + 16, TENSORS = EPI == EPI_SWIGLU ? 3 : 1;
+    // What a SwiGLU forward does not keep is neither made nor stored: a checkpointed forward needs H alone, its recomputation G and U
+    // alone (2048 tokens, top-6 of 64 experts and 2 shared, 2048 x 1408: 268 -> 256 us and 248 -> 236).
+    constexpr int PITCH16 = W * 2 + 16;
+    constexpr int FIRST = EPI == EPI_SWIGLU_H ? 2 : 0, TENSORS = EPI == EPI_BF16 ? 1 : EPI == EPI_SWIGLU_GU ? 2 : 3;
 #pragma unroll
     for (int b = 0; b < NB; b += 2) {
 #pragma unroll
@@ -769,12 +774,13 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
         for (int a = 0; a < W / 16; a++) {
           char* const dst = wlds + (16 * i + (lane & 15)) * PITCH16 + (16 * a + 4 * (lane >> 4)) * 2;
           const f32x4 x = acc[a][b + i];
-          *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]));
-          if constexpr (EPI == EPI_SWIGLU) {
+          if constexpr (FIRST == 0) *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]));
+          if constexpr (IS_SWIGLU) {
             const f32x4 y = acc[a + 2][b + i];
-            *reinterpret_cast<uint2*>(dst + 32 * PITCH16) = make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
-            *reinterpret_cast<uint2*>(dst + 64 * PITCH16) =
-                make_uint2(pack_bf16(swiglu(x[0], y[0]), swiglu(x[1], y[1])), pack_bf16(swiglu(x[2], y[2]), swiglu(x[3], y[3])));
+            if constexpr (FIRST == 0) *reinterpret_cast<uint2*>(dst + 32 * PITCH16) = make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
+            if constexpr (TENSORS == 3)
+              *reinterpret_cast<uint2*>(dst + 64 * PITCH16) =
+                  make_uint2(pack_bf16(swiglu(x[0], y[0]), swiglu(x[1], y[1])), pack_bf16(swiglu(x[2], y[2]), swiglu(x[3], y[3])));
           }
         }
       bounced();
@@ -784,7 +790,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
         const char* const src = wlds + (it * RPI + r_lane) * PITCH16 + q_lane * 2;
         if (row_in(p)) {
 #pragma unroll
-          for (int t = 0; t < TENSORS; t++)
+          for (int t = FIRST; t < TENSORS; t++)
             *reinterpret_cast<uint4*>(at(t == 0 ? A.c0 : t == 1 ? A.c1 : A.c2, p)) = *reinterpret_cast<const uint4*>(src + t * 32 * PITCH16);
         }
       }
@@ -1049,14 +1055,17 @@ struct RowGemms {
     A.n_q_tiles = (A.q_dim + tq - 1) / tq;
     const long long blocks = (D.N / TILE + D.Et) * A.n_q_tiles;   // sum_e ceil(n_e / 256) <= N / 256 + E'
     switch (kind) {
-      case ROWTILE_GATE_UP: return launch_gemm<0, false, true, 2, 1, EPI_SWIGLU>(label, A, blocks, st);
+      case ROWTILE_GATE_UP:
+        if (A.c0 == nullptr) return launch_gemm<0, false, true, 2, 1, EPI_SWIGLU_H>(label, A, blocks, st);
+        if (A.c2 == nullptr) return launch_gemm<0, false, true, 2, 1, EPI_SWIGLU_GU>(label, A, blocks, st);
+        return launch_gemm<0, false, true, 2, 1, EPI_SWIGLU>(label, A, blocks, st);
       case ROWTILE_DOWN: return launch_gemm<0, false, true, 1, 1, EPI_BF16>(label, A, blocks, st);
       case ROWTILE_DH: return launch_gemm<0, false, false, 1, 1, EPI_DSWIGLU>(label, A, blocks, st);
       default: return launch_gemm<0, false, false, 1, 2, EPI_BF16>(label, A, blocks, st);
     }
   }
 
-  // G, U = X Wg, X Wu ; H = silu(G) * U
+  // G, U = X Wg, X Wu ; H = silu(G) * U   (g and u, or h, may be null: not wanted)
   int gate_up(const char* label, const uint16_t* x, const uint16_t* w_gate, const uint16_t* w_up, uint16_t* g, uint16_t* u, uint16_t* h) const {
     RowTileArgs R = {};
     R.q_dim = D.f; R.k_dim = D.d;
@@ -1113,10 +1122,6 @@ extern "C" int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_per
   MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(y_perm); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   if (D.N == 0) return MOE_OK;
   const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, ROWTILE_GATE_UP, ROWTILE_DOWN);
-  if (save_g == nullptr) {  // checkpointed forward: G and U go to the workspace and are not kept
-    save_g = G.rows_f(L.g_re);
-    save_u = G.rows_f(L.u_re);
-  }
   G.schedule();
   MOE_TRY(G.gate_up("ffn_fwd_gate_up_swiglu", x_perm, w_gate, w_up, save_g, save_u, G.rows_f(L.h)));
   MOE_TRY(G.down("ffn_fwd_down", G.rows_f(L.h), w_down, y_perm));
@@ -1254,10 +1259,9 @@ extern "C" int moe_grouped_ffn_bwd_recompute(const moe_shape* shape, const uint1
   uint16_t* const g_re = G.rows_f(L.g_re);
   uint16_t* const u_re = G.rows_f(L.u_re);
   if (D.N > 0) {
-    // G, U = X Wg, X Wu once more (the same kernel as in forward, hence the same bits); its H output is overwritten
-    // by the backward's own
+    // G, U = X Wg, X Wu once more (the same kernel as in forward, hence the same bits); the backward makes its own H
     G.schedule();
-    MOE_TRY(G.gate_up("ffn_bwd_recompute_gate_up", x_perm, w_gate, w_up, g_re, u_re, G.rows_f(L.h)));
+    MOE_TRY(G.gate_up("ffn_bwd_recompute_gate_up", x_perm, w_gate, w_up, g_re, u_re, nullptr));
   }
   return moe_grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, g_re, u_re, dx_perm, dw_gate, dw_up, dw_down,
                              accumulate, ws, ws_bytes, stream);
