@@ -79,7 +79,8 @@ def gemm_flops_per_launch(label, shape):
     unit = 2.0 * shape.d_model * shape.d_ffn * shape.N
     return {"ffn_fwd_gate_up_swiglu": 2 * unit, "ffn_fwd_down": unit, "ffn_bwd_dh_dswiglu": unit,
             "ffn_bwd_dx": 2 * unit, "ffn_bwd_dw_down": unit, "ffn_bwd_dw_gate_up": 2 * unit,
-            "ffn_bwd_dw": 3 * unit}.get(label)   # (both weight-gradient problems in one launch)
+            "ffn_bwd_dw": 3 * unit,               # (both weight-gradient problems in one launch,
+            "ffn_bwd_dx_dw": 5 * unit}.get(label)   # ... and dX with them)
 
 
 def gemm_bytes_per_launch(label, shape, n_active):
@@ -91,7 +92,8 @@ def gemm_bytes_per_launch(label, shape, n_active):
     return {"ffn_fwd_gate_up_swiglu": act_d + 2 * w1 + 3 * act_f, "ffn_fwd_down": act_f + w1 + act_d,
             "ffn_bwd_dh_dswiglu": act_d + w1 + 2 * act_f + 3 * act_f, "ffn_bwd_dx": 2 * act_f + 2 * w1 + act_d,
             "ffn_bwd_dw_down": act_f + act_d + Et * d * f * 4, "ffn_bwd_dw_gate_up": act_d + 2 * act_f + 2 * Et * d * f * 4,
-            "ffn_bwd_dw": 2 * act_d + 3 * act_f + 3 * Et * d * f * 4}.get(label)
+            "ffn_bwd_dw": 2 * act_d + 3 * act_f + 3 * Et * d * f * 4,
+            "ffn_bwd_dx_dw": 3 * act_d + 5 * act_f + 2 * w1 + 3 * Et * d * f * 4}.get(label)
 
 
 def gemm_roofline(label, shape, n_active, avg_ms):

@@ -173,7 +173,7 @@ struct WgradArgs {
   size_t f_expert_stride;
   WgradProblem a, b;           // dW_gate | dW_up and dW_down
 };
-void launch_wgrad(hipStream_t st, WgradArgs A);
+void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles);   // (dx_tiles > 0: and dX on 64-row tiles)
 
 // Optional per-launch timing (moe_profile_* in the ABI).  While enabled, every kernel launch of the library is
 // bracketed by two HIP events on the launch stream; disabled (the default) it costs one branch.

@@ -1030,17 +1030,25 @@ struct RowGemms {
   }
   const int32_t* experts_by_rows() const { return (any_tall ? sched_tall : sched_few) + 64 + 2 * max_tiles; }
 
+  // what every launch on the 64-row tiles takes
+  void prepare_few(RowTileArgs& R) const {
+    R.max_tiles = max_tiles; R.offsets = offsets;
+    R.q_expert_stride = (size_t)D.d * D.f;
+    R.sched = self_scheduled() ? nullptr : sched_few;
+    R.Et = D.Et;
+  }
+  long long few_row_tiles() const { return D.N / kFewRows + (D.N < D.Et ? D.N : D.Et); }   // sum_e ceil(n_e / 64) <= N / 64 + experts with rows
+
   int launch(const char* label, RowTileKind kind, RowTileArgs R) const {
     R.max_tiles = max_tiles; R.offsets = offsets;
     R.q_expert_stride = (size_t)D.d * D.f;
     if (few_rows_pays(D, kind)) {
-      R.sched = self_scheduled() ? nullptr : sched_few;
-      R.Et = D.Et;
+      prepare_few(R);
       if (kind == ROWTILE_DH && self_scheduled()) {
         R.order = sched_few + 64 + 2 * max_tiles;
         R.zero_page = zero_page;
       }
-      launch_few_rows(label, st, kind, R, D.N / kFewRows + (D.N < D.Et ? D.N : D.Et));   // sum_e ceil(n_e / 64) <= N / 64 + experts with rows
+      launch_few_rows(label, st, kind, R, few_row_tiles());
       return MOE_OK;
     }
     GemmArgs A = {};
@@ -1094,13 +1102,13 @@ struct RowGemms {
     return launch(label, ROWTILE_DH, R);
   }
   // dX = dG Wg^T + dU Wu^T
-  int dx(const char* label, const uint16_t* dg, const uint16_t* du, const uint16_t* w_gate, const uint16_t* w_up, uint16_t* dx_perm) const {
+  RowTileArgs dx_args(const uint16_t* dg, const uint16_t* du, const uint16_t* w_gate, const uint16_t* w_up, uint16_t* dx_perm) const {
     RowTileArgs R = {};
     R.q_dim = D.d; R.k_dim = D.f;
     R.p0 = dg; R.p1 = du; R.p_ld = D.f;
     R.q0 = w_gate; R.q1 = w_up; R.q_ld = D.f;
     R.c0 = dx_perm; R.c_ld = D.d;
-    return launch(label, ROWTILE_DX, R);
+    return R;
   }
 };
 
@@ -1152,7 +1160,6 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   G.schedule();   // (also with no rows at all: the weight gradients read the expert order from the schedule)
   if (D.N > 0) {
     MOE_TRY(G.dh("ffn_bwd_dh_dswiglu", dy_perm, w_down, save_g, save_u, dg, du, h));
-    MOE_TRY(G.dx("ffn_bwd_dx", dg, du, w_gate, w_up, dx_perm));
   }
   WgradArgs W = {};
   W.offsets = offsets; W.order = G.experts_by_rows(); W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
@@ -1165,7 +1172,12 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   W.b.p0 = h; W.b.p_ld = D.f; W.b.p_dim = D.f;
   W.b.q0 = dy_perm; W.b.q_ld = D.d; W.b.q_dim = D.d;
   W.b.f0 = dw_down; W.b.c_ld = D.d;
-  launch_wgrad(st, W);
+  // dX needs dH's results as the weight gradients do, and on the 64-row tiles it may share their launch
+  RowTileArgs X = G.dx_args(dg, du, w_gate, w_up, dx_perm);
+  const bool dx_few = D.N > 0 && few_rows_pays(D, ROWTILE_DX);
+  if (dx_few) G.prepare_few(X);
+  else if (D.N > 0) MOE_TRY(G.launch("ffn_bwd_dx", ROWTILE_DX, X));
+  launch_wgrad(st, W, X, dx_few ? G.few_row_tiles() : 0);
   return launch_status();
 }
 

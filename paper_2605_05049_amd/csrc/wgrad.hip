@@ -17,7 +17,7 @@
 // stage, a ring of three stages (72 KB, two blocks fit the CU's 160 KB), two steps ahead.  P is the MFMA's A operand, so
 // that 16 lanes of an accumulator register hold 16 consecutive columns of one row of dW; two registers exchange lane rows, and a
 // store instruction writes whole 128-byte lines from registers, without a bounce through LDS and without a barrier.
-#include "common.h"
+#include "few_rows.h"
 
 #include <limits.h>
 
@@ -38,6 +38,7 @@ constexpr int Q_BYTES = WQ * WK * 2;         // 16 KB
 constexpr int W_STAGE = P_BYTES + Q_BYTES;   // 24 KB
 constexpr int W_XCDS = 8;
 constexpr int W_MERGE_CHUNKS = 1024;         // both problems in one launch up to here
+constexpr int W_DX_CHUNKS = 256;             // ... and dX on 64-row tiles with them up to here
 constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
 
 // Position of 8 r-values (chunk c of 16) inside k-row k's 256 bytes: the four k-rows that a transposing read takes together
@@ -67,14 +68,13 @@ __device__ __forceinline__ w_bf16x8 w_frag(unsigned off, unsigned area) {
 
 }  // namespace
 
-__global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
-  __shared__ __attribute__((aligned(1024))) char ring[3 * W_STAGE];
+__device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsigned block) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
   // ---- block id -> tile.  Chunks of 32 consecutive tiles (B.band p x 32 / B.band q of one expert, which share panels) are dealt
   // round-robin to the XCDs, of each problem the experts with the most rows first (its last tiles are then short ones).
-  const int within = blockIdx.x / W_XCDS, xcd = blockIdx.x % W_XCDS;
+  const int within = (int)(block / W_XCDS), xcd = (int)(block % W_XCDS);
   const long long launch_chunk = (long long)(within / W_CHUNK) * W_XCDS + xcd;
   const bool is_b = launch_chunk >= A.a.chunks;   // (a launch may carry two problems, the second's chunks after the first's)
   const WgradProblem B = is_b ? A.b : A.a;
@@ -255,6 +255,28 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
   }
 }
 
+__global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
+  __shared__ __attribute__((aligned(1024))) char ring[3 * W_STAGE];
+  wgrad_block(A, ring, blockIdx.x);
+}
+
+// dX of a small problem in front of the weight gradients, in one launch: neither needs the other, and each alone leaves CUs idle while
+// its chains of loads wait or its last blocks run.  dX's blocks come first, since theirs is the longer chain; they have four wavefronts
+// (eight, one block per CU, where dX has a launch of its own and at most 256 tiles).  us of the two launches -> of this one (forward +
+// backward: 512 x 512, 4 experts of 16 rows 68.9 -> 59.2; 512 x 1024, 8 of 64 74.2 -> 69.9; 1472 x 576, 8 of 233 134 -> 124;
+// 640 x 640, 63 of 12 163 -> 155; 1024 x 1600, 45 of 19 384 -> 374.)
+struct DxWgradArgs {
+  RowTileArgs dx;
+  WgradArgs dw;
+  unsigned dx_blocks;
+};
+__global__ __launch_bounds__(WTHREADS, 2) void dx_wgrad_kernel(const DxWgradArgs A) {
+  __shared__ __attribute__((aligned(1024))) char lds[3 * W_STAGE];
+  static_assert(WTHREADS == 4 * kWave && 4 * F_PATCH <= 3 * W_STAGE, "a dX tile of four wavefronts fits");
+  if (blockIdx.x < A.dx_blocks) few_rows_block<ROWTILE_DX, 4>(A.dx, lds, blockIdx.x, A.dx_blocks);
+  else wgrad_block(A.dw, lds, blockIdx.x - A.dx_blocks);
+}
+
 // Fills in how a problem is cut into tiles and chunks.
 static void plan_wgrad(WgradProblem& B, int Et, long long rows) {
   B.n_p_tiles = (B.p_dim + WP - 1) / WP;
@@ -274,13 +296,26 @@ static void plan_wgrad(WgradProblem& B, int Et, long long rows) {
   B.chunks = (int)chunks;
 }
 
-// Launches the weight gradients of the pair and of the single tensor.
-void launch_wgrad(hipStream_t st, WgradArgs A) {
+// Launches the weight gradients of the pair and of the single tensor, and dX where it runs on 64-row tiles (at most dx_tiles of them;
+// 0: it does not).
+void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles) {
   if (A.Et <= 0) return;
   plan_wgrad(A.a, A.Et, A.rows);
   plan_wgrad(A.b, A.Et, A.rows);
   auto grid = [](long long chunks) { return dim3((unsigned)((chunks + W_XCDS - 1) / W_XCDS * W_XCDS * W_CHUNK)); };
   const dim3 block(WTHREADS);
+  if (dx_tiles > 0) {
+    // (2048 x 1408, 66 experts, 528 chunks, forward + backward: 837 us with dX in a launch of its own, 842 with one for all.)
+    if (A.a.chunks + A.b.chunks <= W_DX_CHUNKS) {
+      DxWgradArgs X = {};
+      X.dx = dx; X.dw = A;
+      X.dx.n_q_tiles = dx.q_dim / FQ;
+      X.dx_blocks = few_rows_grid(dx_tiles * X.dx.n_q_tiles);
+      MOE_LAUNCH("ffn_bwd_dx_dw", st, dx_wgrad_kernel, dim3(X.dx_blocks + grid(A.a.chunks + A.b.chunks).x), block, 0, st, X);
+      return;
+    }
+    launch_few_rows("ffn_bwd_dx", st, ROWTILE_DX, dx, dx_tiles);
+  }
   // In one launch, unless it is long: two launches have two starts and two last rounds.  Time of the one against the two, 200
   // random shapes: 0.73 at fewer than 64 chunks, 0.91 at 64 .. 128, 0.94 up to 256, 0.97 up to 512, 0.98 up to 1024, 0.99 - 1.0
   // beyond.

@@ -740,6 +740,36 @@ def test_weight_gradient_launches(moe):
         assert torch.equal(a[:E1], b)   # (not equal where one was left unwritten)
 
 
+@pytest.mark.parametrize("E", [151, 152])
+def test_dx_beside_the_weight_gradients(moe, E):
+    """dX on 64-row tiles shares the weight gradients' launch up to 256 of their chunks (here 151 experts of 54 tiles) and has one of its
+    own beyond: against fp32 on the saved activations."""
+    d = f = 768
+    s, x, dy, off, w, ws, _, sg, su = ffn_on_device(moe, d, f, [70, 0, 1] + [5] * (E - 3))
+    dx = torch.full((s.N, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dw = [torch.full(t.shape, float("nan"), device="cuda") for t in w]
+    moe.profile_reset()
+    moe.profile_enable(True)
+    moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, sg, su, dx, *dw, False, ws)
+    torch.cuda.synchronize()
+    labels = [label for label, _ in moe.profile_records()]
+    moe.profile_enable(False)
+    moe.profile_reset()
+    assert ("ffn_bwd_dx_dw" in labels, "ffn_bwd_dx" in labels) == (E == 151, E == 152)
+    bounds = off.tolist()
+    for e in (0, 1, 2, 3, E - 1):
+        r = slice(bounds[e], bounds[e + 1])
+        g, u = sg[r].float(), su[r].float()
+        dh = dy[r].float() @ w[2][e].float().T
+        sig = torch.sigmoid(g)
+        # dG, dU and H are rounded to bf16 between the GEMMs: an error of 2^-9 of each, in quadrature over the contraction, so 2^-8
+        # of the norm of a result bounds it with room
+        h, du, dg = (z.to(torch.bfloat16).float() for z in (g * sig * u, dh * g * sig, dh * u * sig * (1 + g * (1 - sig))))
+        want = (dg @ w[0][e].float().T + du @ w[1][e].float().T, x[r].float().T @ dg, x[r].float().T @ du, h.T @ dy[r].float())
+        for got, ref in zip((dx[r].float(), dw[0][e], dw[1][e], dw[2][e]), want):
+            assert bool(torch.isfinite(got).all()) and float((got - ref).norm()) <= 2.0 ** -8 * float(ref.norm())
+
+
 def test_grouped_ffn_with_no_rows(moe):
     """T = 0: nothing to compute, but overwritten weight gradients must be exact zeros and accumulated ones untouched."""
     shape = W.MoEShape(0, 128, 64, 4, 2)
