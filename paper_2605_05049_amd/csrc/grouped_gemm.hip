@@ -301,7 +301,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     const int e_tiles = row_tiles_of(e_hi - e_lo, A.sched[1]);
     const int first = A.sched[64 + A.max_tiles + u];  // index of the expert's first row tile
     // Order inside an expert: column tile after column tile, each with all its row tiles (32 consecutive tiles, which
-    // an XCD runs together, are then about 4 row tiles x 8 column tiles: 4 + 8 panels), a tall last row tile first.
+    // an XCD runs together, are then about 8 row tiles x 4 column tiles: 8 + 4 panels), a tall last row tile first.
     // Blocks are handed to CUs in order as CUs become free, so a tile that takes longer should come early in its
     // group of 32: an expert of at most 4 row tiles, whose 8 column tiles fill a group, is therefore walked row
     // tile after row tile inside each band of 8 column tiles (the same 32 tiles, the 8 tall ones first: the CUs that
@@ -314,8 +314,19 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
       qt = band * 8 + in_band % band_q;
       m = in_band / band_q;
     } else {
-      qt = local / e_tiles;
-      m = local % e_tiles;
+      // With more than 12 row tiles, 32 of one column or two would read that many row panels for one or two of the columns: the rows
+      // are cut into equal bands of at most 8 and each is walked by itself (8 + 4 panels).  Forward + backward, us: 2 experts of 6000
+      // rows, 4096 x 4096 3028 -> 2929; of 7000, 7168 x 2048 3385 -> 3303; 8 of 4970 and a shared one, 1792 x 3968 5043 -> 4977.
+      // (9 tiles as 5 + 4: gate | up 450 -> 458.)
+      const int n_bands = e_tiles > 12 ? (e_tiles + 7) / 8 : 1;
+      const int low = e_tiles / n_bands, n_high = e_tiles - low * n_bands;   // n_high bands of low + 1 rows, then those of low
+      const int high_tiles = n_high * (low + 1) * A.n_q_tiles;
+      const bool high = local < high_tiles;
+      const int rows = high ? low + 1 : low;
+      const int in_part = high ? local : local - high_tiles;
+      const int band = in_part / (rows * A.n_q_tiles), in_band = in_part - band * rows * A.n_q_tiles;
+      qt = in_band / rows;
+      m = (high ? 0 : n_high * (low + 1)) + band * rows + in_band - qt * rows;
     }
     const bool tall_last = (e_hi - e_lo) - (e_tiles - 1) * TILE > TILE;
     const int mt = tall_last ? (m == 0 ? e_tiles - 1 : m - 1) : m;

@@ -494,6 +494,8 @@ def test_small_problem_tiles(moe, d, f, counts, small):
     # experts of more than four row tiles, which the kernel walks column tile by column tile with a tall tile first, next to one
     # of four, walked in bands of 8 column tiles: 9 column tiles, i.e. a full band and a band of one
     (1408, 2304, MANY_TILE_COUNTS, ()),
+    # experts of 18, 14, 13 (the last a tall one) and 11 row tiles: three and two bands of rows, of equal and of unequal height, and none
+    (640, 832, [4500, 0, 3400, 3392, 2817], ()),
     # few tiles and 48 k-steps or more: cut along k.  dH of 128 steps in up to 8 parts, a tall tile, a short one and one of 65
     # rows among them, whose last part to arrive applies the d(SwiGLU) epilogue to the sums ...
     (8192, 128, [300, 33, 0, 0, 65], ("gate_up", "down", "dx")),
