@@ -2,7 +2,7 @@
 // a deterministic stable counting sort of the T*K' slots by expert id, the row gather it defines, the weighted
 // combine that undoes it, and the derivatives of both.
 //
-// Counting sort = three launches (two for few slots), no atomics (so the order never depends on scheduling):
+// Counting sort = three launches (two or one for few slots), no atomics on an order (so it never depends on scheduling):
 //   1. rank    : each block ranks 1024 consecutive slots among the same-expert slots of the block
 //                (wave ballots give the rank inside 64 slots, an LDS table chains the 16 sub-groups) and
 //                emits its expert histogram;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(1024) void perm_scan_kernel(int32_t* __restrict__ b
   }
 }
 
-// 1 + 2 in one launch for few slots: one block of 16 wavefronts ranks all of them (sub-groups of 64 slots as above, the
+// 1 + 2 in one launch for few slots that the scatter does not rank itself (below): one block of 16 wavefronts ranks all of them (sub-groups of 64 slots as above, the
 // expert's counts of all sub-groups chained in LDS).  The base of a slot's rank is then its expert's offset whatever its
 // block of 1024, and that is what block_base holds for each of them.  Two launches of 3 .. 6 us each are latency only, and
 // grow little with the slots, where the one block's time does; few experts make the general path's scatter slow as well.  Maps
@@ -256,11 +256,63 @@ template <bool NT> __device__ __forceinline__ void st_row(u32x4* p, u32x4 v) {
 // ---------------------------------------------------------------------------------------------------------
 // 3. scatter the maps and gather the rows
 // ---------------------------------------------------------------------------------------------------------
-template <int KP>
+// RANKS: the whole sort in this launch, for so few slots that ranking them again in every wavefront costs less than the launches in
+// front (3 .. 5 us each with their gaps, bound by latency).  With key = expert x 4096 + slot the row of a slot is the number of smaller
+// keys, which ballots count 64 at a time for all K' slots of a token: one round trip to memory, and neither LDS nor a barrier.  One block
+// more adds up the experts' counts.  A wavefront's time grows with N K' and that of all of them with their number times N, hence the two
+// limits.  Graph of calls, us, N slots, K' per token, E' experts, d (before / ranked here):
+//   128, 8, 66, 2048: 7.0 / 4.8     512, 2, 8, 512: 5.6 / 3.1       1024, 2, 64, 2048: 7.1 / 4.3     1536, 1, 64, 4096: 9.2 / 8.0
+//   2048, 8, 128, 4096: 12.2 / 11.5     2896, 2, 100, 1024: 10.6 / 8.5     4012, 4, 14, 1088: 12.4 / 11.4    4096, 4, 8, 512: 10.9 / 9.0
+// and beyond them 2880, 8, 64, 7168: 18.3 / 19.3   3500, 5, 100, 2048: 13.2 / 13.2    4096, 8, 66, 512: 11.4 / 14.4 (N K')
+//   2048, 1, 64, 4096: 11.0 / 11.2 (2048 tokens of 4 wavefronts).
+constexpr int kRankedSlots = 4096, kRankedExperts = 128, kRankedSlotsPerToken = 8;   // at most
+constexpr int kRankedOwnKeys = 16384;          // N K' at most
+constexpr int kRankedSlotsAlways = 1536;
+constexpr long long kRankedKeys = 1ll << 23;   // with more slots than that: wavefronts x N at most
+static bool perm_is_ranked_by_scatter(const Dims& D, int parts) {
+  return D.N > 0 && D.N <= kRankedSlots && D.Et <= kRankedExperts && D.Kp <= kRankedSlotsPerToken && D.N * D.Kp <= kRankedOwnKeys &&
+         (D.N <= kRankedSlotsAlways || (long long)D.T * parts * D.N <= kRankedKeys);
+}
+__device__ __forceinline__ void count_experts(const int32_t* __restrict__ topk_idx, int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int N, int Et) {
+  __shared__ int32_t hist[kRankedExperts];   // (sums of ones: the same whatever their order)
+  const int tid = threadIdx.x;
+  if (tid < kRankedExperts) hist[tid] = 0;
+  __syncthreads();
+  for (int i = tid; i < N; i += 256) atomicAdd(&hist[clamp_expert(topk_idx[i], Et)], 1);
+  __syncthreads();
+  if (tid >= kWave) return;
+  static_assert(kRankedExperts == 2 * kWave, "two experts per lane");
+  const int c0 = hist[2 * tid], c1 = hist[2 * tid + 1];
+  int incl = c0 + c1;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int up = __shfl_up(incl, o, kWave);
+    if (tid >= o) incl += up;
+  }
+  if (2 * tid < Et) {
+    counts[2 * tid] = c0;
+    offsets[2 * tid] = incl - c1 - c0;
+  }
+  if (2 * tid + 1 < Et) {
+    counts[2 * tid + 1] = c1;
+    offsets[2 * tid + 1] = incl - c1;
+  }
+  if (tid == 0) offsets[Et] = N;
+}
+
+template <int KP, bool RANKS>
 __global__ __launch_bounds__(256) void perm_scatter_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ topk_idx,
                                                            const int32_t* __restrict__ lrank, const int32_t* __restrict__ block_base,
                                                            u32x4* __restrict__ x_perm, int32_t* __restrict__ row_of_slot,
-                                                           int32_t* __restrict__ slot_of_row, int T, int Kp, int Et, int dvec, int parts) {
+                                                           int32_t* __restrict__ slot_of_row, int32_t* __restrict__ counts,
+                                                           int32_t* __restrict__ offsets, int T, int Kp, int Et, int dvec, int parts) {
+  static_assert(!RANKS || KP > 0, "the ranking form keeps a token's slots in registers");
+  if constexpr (RANKS) {
+    if (blockIdx.x == gridDim.x - 1) {
+      count_experts(topk_idx, counts, offsets, T * KP, Et);
+      return;
+    }
+  }
   const int lane = threadIdx.x % kWave;
   const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + threadIdx.x / kWave);
   const int t = wid / parts, part = wid % parts;
@@ -270,11 +322,35 @@ __global__ __launch_bounds__(256) void perm_scatter_kernel(const u32x4* __restri
   const u32x4* src = x ? x + (size_t)t * dvec : nullptr;
   if (KP > 0) {
     int rows[KP > 0 ? KP : 1];
+    if constexpr (RANKS) {
+      int own[KP];
 #pragma unroll
-    for (int j = 0; j < KP; j++) {
-      const int s = t * KP + j;
-      const int e = clamp_expert(topk_idx[s], Et);
-      rows[j] = block_base[(size_t)(s / kPermSlotsPerBlock) * Et + e] + lrank[s];
+      for (int j = 0; j < KP; j++) {
+        const int s = t * KP + j;
+        own[j] = clamp_expert(topk_idx[s], Et) * kRankedSlots + s;
+        rows[j] = 0;
+      }
+      const int N = T * KP;
+      constexpr int AHEAD = 8;   // groups of 64 keys in flight
+      for (int i0 = 0; i0 < N; i0 += AHEAD * kWave) {
+        int id[AHEAD];
+#pragma unroll
+        for (int g = 0; g < AHEAD; g++) id[g] = topk_idx[min(i0 + g * kWave + lane, N - 1)];
+#pragma unroll
+        for (int g = 0; g < AHEAD; g++) {
+          const int i = i0 + g * kWave + lane;
+          const int key = i < N ? clamp_expert(id[g], Et) * kRankedSlots + i : 0x7fffffff;
+#pragma unroll
+          for (int j = 0; j < KP; j++) rows[j] += __popcll(__ballot(key < own[j]));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < KP; j++) {
+        const int s = t * KP + j;
+        const int e = clamp_expert(topk_idx[s], Et);
+        rows[j] = block_base[(size_t)(s / kPermSlotsPerBlock) * Et + e] + lrank[s];
+      }
     }
     if (part == 0 && lane < KP) {
       int row = rows[0];
@@ -519,11 +595,19 @@ static int permute_checks(const moe_shape* shape, Dims* D, const uint16_t* x, co
   return MOE_OK;
 }
 
-// The launches of the counting sort: rank and scan, or both in one, then the scatter.  block_hist: perm_num_blocks(N) * E' int32; lrank: N int32.  Every entry of
+// The launches of the counting sort: rank and scan, or both in one, then the scatter; or the scatter alone.  block_hist: perm_num_blocks(N) * E' int32; lrank: N int32.  Every entry of
 // both that a later kernel reads is written by an earlier one of the same call, so neither has to start at zero.
 static int permute_launch(const Dims& D, const uint16_t* x, const int32_t* topk_idx, uint16_t* x_perm, int32_t* counts,
                           int32_t* offsets, int32_t* row_of_slot, int32_t* slot_of_row, int32_t* block_hist, int32_t* lrank,
                           hipStream_t st) {
+  const int parts = x ? row_parts(D.d / 8) : 1;
+  if (perm_is_ranked_by_scatter(D, parts)) {
+    MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("perm_sort_scatter_gather", st, (perm_scatter_kernel<(KP > 0 ? KP : 1), true>), dim3(token_blocks(D.T, parts) + 1),
+                                     dim3(256), 0, st, reinterpret_cast<const u32x4*>(x), topk_idx, (const int32_t*)nullptr,
+                                     (const int32_t*)nullptr, reinterpret_cast<u32x4*>(x_perm), row_of_slot, slot_of_row, counts, offsets, D.T,
+                                     D.Kp, D.Et, D.d / 8, parts));
+    return launch_status();
+  }
   const int nblk = perm_num_blocks(D.N);
   int nbits = 0;
   while ((1 << nbits) < D.Et) nbits++;
@@ -539,10 +623,9 @@ static int permute_launch(const Dims& D, const uint16_t* x, const int32_t* topk_
     MOE_LAUNCH("perm_scan", st, perm_scan_kernel, dim3(1), dim3(1024), 0, st, block_hist, counts, offsets, nblk, D.Et);
   }
   if (D.T > 0) {
-    const int parts = x ? row_parts(D.d / 8) : 1;
-    MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("perm_scatter_gather", st, (perm_scatter_kernel<KP>), dim3(token_blocks(D.T, parts)), dim3(256), 0, st,
+    MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("perm_scatter_gather", st, (perm_scatter_kernel<KP, false>), dim3(token_blocks(D.T, parts)), dim3(256), 0, st,
                                      reinterpret_cast<const u32x4*>(x), topk_idx, lrank, block_hist, reinterpret_cast<u32x4*>(x_perm),
-                                     row_of_slot, slot_of_row, D.T, D.Kp, D.Et, D.d / 8, parts));
+                                     row_of_slot, slot_of_row, counts, offsets, D.T, D.Kp, D.Et, D.d / 8, parts));
   }
   return launch_status();
 }

@@ -248,6 +248,24 @@ def test_permute_launches(moe, N, E, one_launch):
     assert ("perm_rank_scan" in labels, "perm_scan" in labels) == (one_launch, not one_launch)
 
 
+# the sort inside the scatter: one slot, a group of 64 and 8 of them (and their neighbours), and both sides of its limits (4096 slots,
+# 128 experts, 8 slots per token, N K' of 16384, wavefronts x N of 2^23 beyond 1536 slots)
+@pytest.mark.parametrize("T,d,E,k,Es,one_launch", [(1, 64, 1, 1, 0, True), (64, 64, 128, 1, 0, True), (65, 64, 126, 1, 2, True), (171, 1024, 5, 3, 0, True),
+                                                   (256, 2048, 127, 8, 0, True), (257, 64, 127, 8, 0, False), (1024, 64, 9, 4, 0, True),
+                                                   (2896, 64, 3, 1, 0, True), (2897, 64, 3, 1, 0, False), (1536, 2048, 3, 1, 0, True),
+                                                   (100, 64, 129, 1, 0, False), (100, 64, 64, 7, 2, False)])
+def test_permute_ranked_by_the_scatter(moe, T, d, E, k, Es, one_launch):
+    moe.profile_reset()
+    moe.profile_enable(True)
+    try:
+        test_permute_maps_rows_and_streams(moe, T, d, E, k, Es, "skewed")
+        labels = {label for label, _ in moe.profile_records()}
+    finally:
+        moe.profile_enable(False)
+        moe.profile_reset()
+    assert ("perm_sort_scatter_gather" in labels, "perm_scatter_gather" in labels) == (one_launch, not one_launch)
+
+
 def test_permute_is_deterministic_over_100_runs(moe):
     """The order of equal keys never depends on scheduling: 100 runs of one larger shape (64 rank blocks, 128
     experts of which a fifth are empty and a tenth are hot), every output bit for bit the first run's and the oracle's."""
