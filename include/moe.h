@@ -201,6 +201,12 @@ int moe_unpermute_combine_bwd(const moe_shape* shape, const uint16_t* dout, cons
                               const int32_t* row_of_slot, const float* topk_w, uint16_t* dy_perm,
                               float* dtopk_w, void* stream);
 
+/* moe_unpermute_combine_bwd and moe_route_topk_bwd in one: dlogits needs the token's dtopk_w only, so that the latter is not a launch of
+ * its own after the experts' backward.  Arguments as those of the two calls. */
+int moe_unpermute_combine_route_bwd(const moe_shape* shape, const uint16_t* dout, const uint16_t* y_perm,
+                                    const int32_t* row_of_slot, const int32_t* topk_idx, const float* topk_w,
+                                    const float* probs_save, uint16_t* dy_perm, float* dtopk_w, float* dlogits, void* stream);
+
 /* ---- The single-GPU steps of the hierarchical all-to-all (Section V, Algorithm 1).  One rank's send buffer S has
  * N = num_nodes * R rows (R ranks per node) of row_bytes bytes (a multiple of 16; any element type): row n*R + l goes
  * to local rank l of node n.  M = num_nodes - 1; "the i-th remote node" counts the nodes other than node_id in

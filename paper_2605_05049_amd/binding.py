@@ -15,7 +15,7 @@ EXPORTED_SYMBOLS = (
     "moe_profile_enable", "moe_profile_count", "moe_profile_get", "moe_profile_reset",
     "moe_route_topk", "moe_route_topk_bwd", "moe_permute", "moe_permute_noalloc", "moe_permute_bwd", "moe_permute_bwd_add",
     "moe_router_fwd", "moe_router_bwd", "moe_grouped_ffn_fwd", "moe_grouped_ffn_bwd", "moe_grouped_ffn_bwd_recompute",
-    "moe_unpermute_combine", "moe_unpermute_combine_bwd",
+    "moe_unpermute_combine", "moe_unpermute_combine_bwd", "moe_unpermute_combine_route_bwd",
     "moe_load_accumulate", "moe_load_imbalance", "moe_rebalance_experts",
     "moe_halo_pack_remote", "moe_halo_repack", "moe_halo_unpack",
 )
@@ -105,6 +105,7 @@ def load_library():
         "moe_grouped_ffn_bwd_recompute": [sp, V, V, V, V, V, V, V, V, V, V, c_int, V, c_size_t, V],
         "moe_unpermute_combine": [sp, V, V, V, V, V],
         "moe_unpermute_combine_bwd": [sp, V, V, V, V, V, V, V],
+        "moe_unpermute_combine_route_bwd": [sp, V, V, V, V, V, V, V, V, V, V],
     }
     sigs["moe_halo_pack_remote"] = [V, V, c_int, c_int, c_size_t, c_int, V]
     sigs["moe_halo_repack"] = [V, V, c_int, c_int, c_size_t, V]
@@ -380,6 +381,19 @@ def moe_unpermute_combine_bwd(shape, dout, y_perm, row_of_slot, topk_w, dy_perm,
         _ptr(row_of_slot, torch.int32, s.N, "row_of_slot"), _ptr(topk_w, torch.float32, s.N, "topk_w"),
         _ptr(dy_perm, bf, s.N * s.d_model, "dy_perm"), _ptr(dtopk_w, torch.float32, s.N, "dtopk_w"), _stream(stream))
     _check("moe_unpermute_combine_bwd", rc)
+
+
+def moe_unpermute_combine_route_bwd(shape, dout, y_perm, row_of_slot, topk_idx, topk_w, probs_save, dy_perm, dtopk_w, dlogits, stream=None):
+    torch = _torch_module or _torch()
+    s = Shape.of(shape)
+    bf = _bf16_types()
+    rc = load_library().moe_unpermute_combine_route_bwd(
+        ctypes.byref(s._c), _ptr(dout, bf, s.T * s.d_model, "dout"), _ptr(y_perm, bf, s.N * s.d_model, "y_perm"),
+        _ptr(row_of_slot, torch.int32, s.N, "row_of_slot"), _ptr(topk_idx, torch.int32, s.N, "topk_idx"),
+        _ptr(topk_w, torch.float32, s.N, "topk_w"), _ptr(probs_save, torch.float32, s.T * s.E, "probs_save"),
+        _ptr(dy_perm, bf, s.N * s.d_model, "dy_perm"), _ptr(dtopk_w, torch.float32, s.N, "dtopk_w"),
+        _ptr(dlogits, torch.float32, s.T * s.E, "dlogits"), _stream(stream))
+    _check("moe_unpermute_combine_route_bwd", rc)
 
 
 # ---- single-GPU steps of the hierarchical all-to-all (device tensors; rows of any dtype, 16-byte multiples) -----

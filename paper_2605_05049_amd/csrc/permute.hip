@@ -464,12 +464,23 @@ __global__ __launch_bounds__(256) void combine_kernel(const u32x4* __restrict__ 
   }
 }
 
+// What the derivative of the gating takes (the formulas are those of route_topk_bwd_kernel).
+struct GateBwdArgs {
+  const int32_t* topk_idx;
+  const float* probs;
+  float* dlogits;
+  int E, k, renorm;
+};
+
 // combine_bwd: dy[row] = bf16(w * dout[t]);  dw[t,j] = <dout[t], y[row]>
-template <int KP>
+// GATE: and dlogits[t, 0 .. E-1].  A token's need its dw only, which one wavefront holds here when the dot products have been added, so
+// the launch that would read them back after the experts' backward is left out.
+template <int KP, bool GATE>
 __global__ __launch_bounds__(256) void combine_bwd_kernel(const u32x4* __restrict__ dout, const u32x4* __restrict__ y,
                                                           const int32_t* __restrict__ row_of_slot, const float* __restrict__ topk_w,
                                                           u32x4* __restrict__ dy, float* __restrict__ dtopk_w, int T, int Kp, int dvec,
-                                                          int parts) {
+                                                          int parts, GateBwdArgs G) {
+  static_assert(!GATE || KP > 0, "the gate's derivative is made from a token's slots in registers");
   // dot products of the parts of a row meet in LDS and are added in part order (the result never depends on timing)
   extern __shared__ float part_dot[];   // [4 wavefronts][K']
   const int lane = threadIdx.x % kWave;
@@ -529,10 +540,33 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(const u32x4* __restric
       if (lane == 0) part_dot[wave * KP + j] = dsum;
     }
     __syncthreads();
-    if (active && part == 0 && lane < KP) {
+    if (active && part == 0) {
       float dsum = 0.f;
-      for (int p2 = 0; p2 < parts; p2++) dsum += part_dot[(wave + p2) * KP + lane];
-      dtopk_w[(size_t)t * KP + lane] = dsum;
+      if (lane < KP) {
+        for (int p2 = 0; p2 < parts; p2++) dsum += part_dot[(wave + p2) * KP + lane];
+        dtopk_w[(size_t)t * KP + lane] = dsum;
+      }
+      if constexpr (GATE) {
+        int idx[KP];
+        float dw[KP], mine = 0.f;
+#pragma unroll
+        for (int j = 0; j < KP; j++) {
+          idx[j] = j < G.k ? G.topk_idx[(size_t)t * KP + j] : -1;   // (a shared expert's slot has no logit)
+          dw[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dsum), j));
+          if (lane == j && j < G.k) mine = w[j] * dw[j];
+        }
+        float inner = mine;   // (in the order of a group of 8 lanes, which route_topk_bwd sums it in: the lanes beyond hold zeros)
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) inner += __shfl_xor(inner, o, kWave);
+        for (int e = lane; e < G.E; e += kWave) {
+          const float pe = G.renorm ? 0.f : G.probs[(size_t)t * G.E + e];
+          float dl = G.renorm ? 0.f : -pe * inner;
+#pragma unroll
+          for (int j = 0; j < KP; j++)
+            if (idx[j] == e) dl += G.renorm ? w[j] * (dw[j] - inner) : pe * dw[j];
+          G.dlogits[(size_t)t * G.E + e] = dl;
+        }
+      }
     }
   } else {
     for (int j = 0; j < Kp; j++) {
@@ -735,23 +769,61 @@ extern "C" int moe_unpermute_combine(const moe_shape* shape, const uint16_t* y_p
   return launch_status();
 }
 
-extern "C" int moe_unpermute_combine_bwd(const moe_shape* shape, const uint16_t* dout, const uint16_t* y_perm,
-                                         const int32_t* row_of_slot, const float* topk_w, uint16_t* dy_perm,
-                                         float* dtopk_w, void* stream) {
-  using namespace moe;
-  Dims D;
-  int rc = check_shape(shape, &D);
+namespace moe {
+
+static int combine_bwd_checks(const moe_shape* shape, Dims* D, const uint16_t* dout, const uint16_t* y_perm, const int32_t* row_of_slot,
+                              const float* topk_w, const uint16_t* dy_perm, const float* dtopk_w) {
+  int rc = check_shape(shape, D);
   if (rc != MOE_OK) return rc;
   MOE_REQUIRE_PTR(dout); MOE_REQUIRE_PTR(y_perm); MOE_REQUIRE_PTR(row_of_slot); MOE_REQUIRE_PTR(topk_w);
   MOE_REQUIRE_PTR(dy_perm); MOE_REQUIRE_PTR(dtopk_w);
   MOE_REQUIRE_ALIGNED(dout); MOE_REQUIRE_ALIGNED(y_perm); MOE_REQUIRE_ALIGNED(row_of_slot); MOE_REQUIRE_ALIGNED(topk_w);
   MOE_REQUIRE_ALIGNED(dy_perm); MOE_REQUIRE_ALIGNED(dtopk_w);
+  return MOE_OK;
+}
+
+}  // namespace moe
+
+extern "C" int moe_unpermute_combine_bwd(const moe_shape* shape, const uint16_t* dout, const uint16_t* y_perm,
+                                         const int32_t* row_of_slot, const float* topk_w, uint16_t* dy_perm,
+                                         float* dtopk_w, void* stream) {
+  using namespace moe;
+  Dims D;
+  int rc = combine_bwd_checks(shape, &D, dout, y_perm, row_of_slot, topk_w, dy_perm, dtopk_w);
+  if (rc != MOE_OK) return rc;
   if (D.T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;
   const int parts = row_parts(D.d / 8);
-  MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("unpermute_combine_bwd", st, (combine_bwd_kernel<KP>), dim3(token_blocks(D.T, parts)), dim3(256),
+  MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("unpermute_combine_bwd", st, (combine_bwd_kernel<KP, false>), dim3(token_blocks(D.T, parts)), dim3(256),
                                    4 * (size_t)D.Kp * sizeof(float), st,
                                    reinterpret_cast<const u32x4*>(dout), reinterpret_cast<const u32x4*>(y_perm), row_of_slot,
-                                   topk_w, reinterpret_cast<u32x4*>(dy_perm), dtopk_w, D.T, D.Kp, D.d / 8, parts));
+                                   topk_w, reinterpret_cast<u32x4*>(dy_perm), dtopk_w, D.T, D.Kp, D.d / 8, parts, GateBwdArgs{}));
+  return launch_status();
+}
+
+extern "C" int moe_unpermute_combine_route_bwd(const moe_shape* shape, const uint16_t* dout, const uint16_t* y_perm,
+                                               const int32_t* row_of_slot, const int32_t* topk_idx, const float* topk_w,
+                                               const float* probs_save, uint16_t* dy_perm, float* dtopk_w, float* dlogits,
+                                               void* stream) {
+  using namespace moe;
+  Dims D;
+  int rc = combine_bwd_checks(shape, &D, dout, y_perm, row_of_slot, topk_w, dy_perm, dtopk_w);
+  if (rc != MOE_OK) return rc;
+  MOE_REQUIRE_PTR(topk_idx); MOE_REQUIRE_PTR(dlogits);
+  if (!D.renorm) MOE_REQUIRE_PTR(probs_save);
+  MOE_REQUIRE_ALIGNED(topk_idx); MOE_REQUIRE_ALIGNED(probs_save); MOE_REQUIRE_ALIGNED(dlogits);
+  if (D.Kp > 8) {   // (the slots of a token are not held in registers)
+    rc = moe_unpermute_combine_bwd(shape, dout, y_perm, row_of_slot, topk_w, dy_perm, dtopk_w, stream);
+    if (rc != MOE_OK) return rc;
+    return moe_route_topk_bwd(shape, dtopk_w, topk_idx, topk_w, probs_save, dlogits, stream);
+  }
+  if (D.T == 0) return MOE_OK;
+  hipStream_t st = (hipStream_t)stream;
+  const int parts = row_parts(D.d / 8);
+  const GateBwdArgs G = {topk_idx, probs_save, dlogits, D.E, D.k, D.renorm};
+  MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("unpermute_combine_route_bwd", st, (combine_bwd_kernel<(KP > 0 ? KP : 1), true>), dim3(token_blocks(D.T, parts)),
+                                   dim3(256), 4 * (size_t)D.Kp * sizeof(float), st,
+                                   reinterpret_cast<const u32x4*>(dout), reinterpret_cast<const u32x4*>(y_perm), row_of_slot,
+                                   topk_w, reinterpret_cast<u32x4*>(dy_perm), dtopk_w, D.T, D.Kp, D.d / 8, parts, G));
   return launch_status();
 }

@@ -64,24 +64,23 @@ def layer_forward(buf: MoeLayerBuffers, x, w_gate, w_up, w_down, logits=None, w_
 
 def layer_backward(buf: MoeLayerBuffers, dout, w_gate, w_up, w_down, accumulate=False, with_router=True, x=None,
                    w_router=None, stream=None):
-    """combine_bwd -> grouped FFN bwd -> permute_bwd -> route_bwd.  Results land in buf.dx, buf.dw_*, buf.dtopk_w,
-    buf.dlogits.  With `x` and `w_router` the layer is closed from x: route_bwd -> router_bwd come before the
+    """combine_bwd and route_bwd (one launch) -> grouped FFN bwd -> permute_bwd.  Results land in buf.dx, buf.dw_*,
+    buf.dtopk_w, buf.dlogits.  With `x` and `w_router` the layer is closed from x: router_bwd comes before the
     un-permutation, buf.dx then holds the expert-path term plus the router's term, and buf.dw_router is filled."""
     s = buf.shape
-    if w_router is not None:
+    gated = with_router and buf.dlogits is not None
+    if gated or w_router is not None:   # (a token's dlogits need no more than its dtopk_w: made with it, not after the experts' backward)
+        B.moe_unpermute_combine_route_bwd(s, dout, buf.y_perm, buf.row_of_slot, buf.topk_idx, buf.topk_w, buf.probs, buf.dy_perm, buf.dtopk_w,
+                                          buf.dlogits, stream)
+    else:
         B.moe_unpermute_combine_bwd(s, dout, buf.y_perm, buf.row_of_slot, buf.topk_w, buf.dy_perm, buf.dtopk_w, stream)
-        B.moe_grouped_ffn_bwd(s, buf.dy_perm, buf.x_perm, buf.offsets, w_gate, w_up, w_down, buf.save_g, buf.save_u,
-                              buf.dx_perm, buf.dw_gate, buf.dw_up, buf.dw_down, accumulate, buf.ws, stream)
-        B.moe_route_topk_bwd(s, buf.dtopk_w, buf.topk_idx, buf.topk_w, buf.probs, buf.dlogits, stream)
-        B.moe_router_bwd(s, x, w_router, buf.dlogits, buf.dx_router, buf.dw_router, accumulate, buf.ws, stream)
-        B.moe_permute_bwd_add(s, buf.dx_perm, buf.row_of_slot, buf.dx_router, buf.dx, stream)
-        return
-    B.moe_unpermute_combine_bwd(s, dout, buf.y_perm, buf.row_of_slot, buf.topk_w, buf.dy_perm, buf.dtopk_w, stream)
     B.moe_grouped_ffn_bwd(s, buf.dy_perm, buf.x_perm, buf.offsets, w_gate, w_up, w_down, buf.save_g, buf.save_u,
                           buf.dx_perm, buf.dw_gate, buf.dw_up, buf.dw_down, accumulate, buf.ws, stream)
-    B.moe_permute_bwd(s, buf.dx_perm, buf.row_of_slot, buf.dx, stream)
-    if with_router and buf.dlogits is not None:
-        B.moe_route_topk_bwd(s, buf.dtopk_w, buf.topk_idx, buf.topk_w, buf.probs, buf.dlogits, stream)
+    if w_router is not None:
+        B.moe_router_bwd(s, x, w_router, buf.dlogits, buf.dx_router, buf.dw_router, accumulate, buf.ws, stream)
+        B.moe_permute_bwd_add(s, buf.dx_perm, buf.row_of_slot, buf.dx_router, buf.dx, stream)
+    else:
+        B.moe_permute_bwd(s, buf.dx_perm, buf.row_of_slot, buf.dx, stream)
 
 
 class CapturedLayerStep:

@@ -760,6 +760,30 @@ def test_weight_gradient_launches(moe):
         assert torch.equal(a[:E1], b)   # (not equal where one was left unwritten)
 
 
+# one wavefront's experts and beyond, 1, 2 and 4 wavefronts per token, as many slots as are held in registers and one more
+@pytest.mark.parametrize("T,d,E,k,Es,renorm", [(1, 64, 1, 1, 0, 1), (37, 512, 8, 2, 0, 1), (37, 512, 9, 3, 1, 0), (50, 1088, 64, 6, 2, 0), (50, 2112, 65, 8, 0, 1),
+                                               (33, 2048, 200, 7, 1, 0), (20, 64, 1000, 8, 1, 1)])
+def test_combine_and_route_backward_in_one(moe, T, d, E, k, Es, renorm):
+    """dlogits made with dtopk_w: what the two calls give, which are compared with the oracle above (the same sums in the same order)."""
+    s = moe.Shape(T, d, 64, E, k, Es, renorm)
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    idx = torch.empty(T, s.K_slots, dtype=torch.int32, device="cuda")
+    w, dw, dw1 = (torch.empty(T, s.K_slots, device="cuda") for _ in range(3))
+    probs, dl, dl1 = (torch.full((T, E), float("nan"), device="cuda") for _ in range(3))
+    moe.moe_route_topk(s, torch.randn(T, E, device="cuda", generator=g), idx, w, probs)
+    rows = torch.randperm(s.N, device="cuda", generator=g).to(torch.int32)
+    dout, y = (torch.randn(n, d, device="cuda", generator=g).to(torch.bfloat16) for n in (T, s.N))
+    dy, dy1 = torch.zeros_like(y), torch.zeros_like(y)
+    moe.moe_unpermute_combine_bwd(s, dout, y, rows, w, dy, dw)
+    moe.moe_route_topk_bwd(s, dw, idx, w, probs, dl)
+    moe.moe_unpermute_combine_route_bwd(s, dout, y, rows, idx, w, probs, dy1, dw1, dl1)
+    assert torch.equal(dy, dy1) and torch.equal(dw, dw1)
+    # (the sums are alike, but for which of their products the compiler fuses with an addition: 2^-23 of each of the terms, of which a
+    # logit's derivative has at most k + 1)
+    bound = 2.0 ** -23 * 2 * (k + 1) * (w * dw).abs().sum(1, keepdim=True)
+    assert bool(((dl - dl1).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("E", [151, 152])
 def test_dx_beside_the_weight_gradients(moe, E):
     """dX on 64-row tiles shares the weight gradients' launch up to 256 of their chunks (here 151 experts of 54 tiles) and has one of its
