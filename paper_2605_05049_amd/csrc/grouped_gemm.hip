@@ -59,13 +59,15 @@ constexpr int kNumXcd = 8;
 constexpr int kCusPerXcd = 32;
 // A tile is cut along K only if it has at least MOE_SPLIT_MIN_STEPS k-steps, into parts of at least MOE_SPLIT_PART_STEPS
 // (writing a part's fp32 tile and adding the parts costs about as much as 20 k-steps: a 32-step tile cut in four
-// measured 4 % slower than left whole).
+// measured 4 % slower than left whole).  Tiles that have at least kRowCutRows rows on average are cut along their rows instead, below
+// kRowCutSteps k-steps (see the block that does it).
 #ifndef MOE_SPLIT_MIN_STEPS
 #define MOE_SPLIT_MIN_STEPS 48
 #endif
 #ifndef MOE_SPLIT_PART_STEPS
 #define MOE_SPLIT_PART_STEPS 16
 #endif
+constexpr int kRowCutRows = 128, kRowCutSteps = 96;
 enum Epilogue { EPI_BF16 = 0, EPI_SWIGLU = 1, EPI_DSWIGLU = 2, EPI_F32 = 3,
                 EPI_SWIGLU_H = 4, EPI_SWIGLU_GU = 5 };   // of the SwiGLU forward H alone (G and U are not kept), G and U alone (recomputed)
 
@@ -85,6 +87,7 @@ struct GemmArgs {
   int p_dim;               // extent of p (rows of the result)
   int n_p_tiles;
   int Et;                  // segments of K
+  long long rows;          // of all experts
   const uint16_t* zero_page;  // 256 zeroed bytes: source of k-rows past the end of a ragged K
   float* partial;             // [kSplitParts][256][256] fp32: partial tiles of a split K range
   int32_t* counters;          // [kSplitCounters], zeroed by the schedule kernel and again by each tile's reducing part: parts of a split tile that have arrived
@@ -256,7 +259,15 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   // 32 CUs, each of those tiles is cut along K into `split` parts that run side by side; a part writes its fp32
   // partial tile to the workspace and the part that arrives last adds them up (no part ever waits for another).
   constexpr bool SPLITK = (KIND == 0 && NQ == 1);   // (the SwiGLU forward, with two output tensors per tile, measured no gain)
-  int split = 1, part = 0, part_slot = 0;
+  // Row split: in the SwiGLU forward, and where the contraction is too short to be cut, such a tile falls into up to 5 pieces of whole 64
+  // rows, which read the same columns of the weights and need no sum.  70 random shapes of 1000 .. 40000 rows, the kernels that had
+  // left-over tiles of this kind, time with the pieces / without: gate | up 0.94 (704 x 2112, 6 experts of 283 rows: 31.5 -> 25.3 us), down
+  // 0.92, dH 0.90, dX 0.90 (768 x 1344, 14 of 576: 71 -> 53); 2048 x 1408, 66 experts, 16384 rows: dH 201 -> 181.
+  // Against the K split, 130 kernels (time of the pieces / of the parts): tiles of 128 rows or more on average, 48 .. 96 k-steps
+  // 0.63 .. 1.01, 97 .. 118 0.79 .. 1.06, 124 .. 200 0.86 .. 1.38, beyond 0.96 .. 2.1; tiles of fewer rows, which give fewer pieces,
+  // 1.1 .. 3.4.
+  constexpr bool SPLIT_ROWS = KIND == 0 && !RAGGED_K;
+  int split = 1, part = 0, part_slot = 0, row_parts = 1, row_part = 0;
   if (KIND == 0) {
     // Groups of 32 consecutive tiles of the logical order (about 4 row tiles x 8 column tiles of one expert: the tiles
     // that share panels) are dealt round-robin to the XCDs, so that every XCD gets the same mix of experts and of tile
@@ -276,18 +287,31 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     if (SPLITK) {
       const int rem = (int)(cnt % kCusPerXcd);
       const int nk_all = ((A.k_dim + BK - 1) / BK) * NPASS;
-      if (rem > 0 && rem <= kCusPerXcd / 2 && nk_all >= MOE_SPLIT_MIN_STEPS) {
+      const bool rows_first = SPLIT_ROWS && A.rows >= (long long)kRowCutRows * n_row_tiles;
+      if (rem > 0 && rem <= kCusPerXcd / 2 && nk_all >= (rows_first ? kRowCutSteps : MOE_SPLIT_MIN_STEPS)) {
         split = min(min(kCusPerXcd / rem, 8), nk_all / MOE_SPLIT_PART_STEPS);
+        full = cnt - rem;
+      }
+    }
+    if (SPLIT_ROWS && full == cnt) {
+      const int rem = (int)(cnt % kCusPerXcd);
+      if (rem > 0 && rem <= kCusPerXcd / 2) {
+        row_parts = min(kCusPerXcd / rem, (TILE + 64) / 64);
         full = cnt - rem;
       }
     }
     long long lid;
     if (within < dealt) {
       lid = ((within / kCusPerXcd) * kNumXcd + xcd) * kCusPerXcd + within % kCusPerXcd;
-      split = 1;
+      split = row_parts = 1;
     } else if (within - dealt < full) {
       lid = lo + (within - dealt);
-      split = 1;
+      split = row_parts = 1;
+    } else if (SPLIT_ROWS && row_parts > 1) {
+      const long long u = within - dealt - full;
+      if (u >= (cnt - full) * row_parts) return;
+      lid = lo + full + u / row_parts;
+      row_part = (int)(u % row_parts);
     } else {
       const long long u = within - dealt - full;
       if (u >= (cnt - full) * split) return;
@@ -332,6 +356,12 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     const int mt = tall_last ? (m == 0 ? e_tiles - 1 : m - 1) : m;
     p_row0 = e_lo + mt * TILE;
     p_valid = (mt == e_tiles - 1) ? e_hi - p_row0 : TILE;   // (the last tile may be a tall one: up to 320 rows)
+    if (SPLIT_ROWS && row_parts > 1) {
+      const int rows = ((p_valid + row_parts - 1) / row_parts + 63) / 64 * 64;   // of a piece
+      p_row0 += row_part * rows;
+      p_valid = min(rows, p_valid - row_part * rows);
+      if (p_valid <= 0) return;   // (fewer pieces than that: another part of the tile has them)
+    }
     q0_col = qt * TQ;
     k_len = A.k_dim;
   } else {
@@ -945,8 +975,8 @@ static long long wgrad_blocks(int Et, int n_p_tiles, int n_q_tiles) {
 template <int KIND, bool P_RC, bool Q_RC, int NQ, int NPASS, int EPI>
 static int launch_gemm(const char* label, const GemmArgs& A, long long max_blocks, hipStream_t st) {
   auto kern = grouped_gemm_kernel<KIND, P_RC, Q_RC, NQ, NPASS, EPI>;
-  // bf16-output row-tile problems may cut the tiles of an XCD's last round into up to 32 parts in all
-  const long long per_xcd = (max_blocks + kNumXcd - 1) / kNumXcd + ((KIND == 0 && NQ == 1) ? kCusPerXcd : 0);
+  // row-tile problems may cut the tiles of an XCD's last round into up to 32 parts in all
+  const long long per_xcd = (max_blocks + kNumXcd - 1) / kNumXcd + (KIND == 0 ? kCusPerXcd : 0);
   const long long grid = per_xcd * kNumXcd;
   if (max_blocks <= 0) return MOE_OK;
   MOE_LAUNCH(label, st, kern, dim3((unsigned)grid), dim3(NTHREADS), 0, st, A);
@@ -1063,7 +1093,7 @@ struct RowGemms {
       return MOE_OK;
     }
     GemmArgs A = {};
-    A.sched = sched_tall; A.max_tiles = max_tiles; A.offsets = offsets; A.Et = D.Et;
+    A.sched = sched_tall; A.max_tiles = max_tiles; A.offsets = offsets; A.Et = D.Et; A.rows = D.N;
     A.zero_page = reinterpret_cast<const uint16_t*>(zero_page);
     A.partial = reinterpret_cast<float*>(ws + L.splitk_partial); A.counters = counters;
     A.q_dim = R.q_dim; A.k_dim = R.k_dim;

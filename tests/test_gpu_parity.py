@@ -543,6 +543,13 @@ def test_row_tile_classes(moe, d, f, counts, small):
     test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small)
 
 
+# left-over tiles in pieces of whole 64 rows, (gate | up, down, dH, dX): 2, 3, none and 3 pieces (dX of 50 steps); 5, 4, 5 and 4, more
+# than some of the tiles have rows for; tall tiles, 2 .. 3 pieces of up to 192 rows
+@pytest.mark.parametrize("d,f,counts", [(1088, 1600, 3 * CLASS_COUNTS), (448, 1216, 7 * CLASS_COUNTS), (1088, 1600, 12 * [320] + [289, 0, 257, 200])])
+def test_row_tiles_cut_along_rows(moe, d, f, counts):
+    test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, ())
+
+
 def ffn_on_device(moe, d, f, counts, seed=0):
     """Inputs and one saving forward of the grouped FFN over experts of `counts` rows, all on the device."""
     E, N = len(counts), sum(counts)
