@@ -104,6 +104,10 @@ int moe_route_topk_bwd(const moe_shape* shape, const float* dtopk_w, const int32
 int moe_router_fwd(const moe_shape* shape, const uint16_t* x, const uint16_t* w_router, float* logits,
                    void* ws, size_t ws_bytes, void* stream);
 
+/* moe_router_fwd and moe_route_topk in one: the gating is made where the logits are.  Arguments as those of the two calls. */
+int moe_router_route_fwd(const moe_shape* shape, const uint16_t* x, const uint16_t* w_router, float* logits, int32_t* topk_idx,
+                         float* topk_w, float* probs_save, void* ws, size_t ws_bytes, void* stream);
+
 /* Derivative of moe_router_fwd:
  *   dx_router[t] = sum_e dlogits[t,e] w_router[e]     [T,d] bf16 out (one rounding)
  *   dw_router[e] = sum_t dlogits[t,e] x[t]            [E,d] fp32, overwritten (accumulate == 0) or added to

@@ -14,7 +14,7 @@ EXPORTED_SYMBOLS = (
     "moe_status_str", "moe_workspace_bytes", "moe_grouped_ffn_small_tiles", "moe_abi_version",
     "moe_profile_enable", "moe_profile_count", "moe_profile_get", "moe_profile_reset",
     "moe_route_topk", "moe_route_topk_bwd", "moe_permute", "moe_permute_noalloc", "moe_permute_bwd", "moe_permute_bwd_add",
-    "moe_router_fwd", "moe_router_bwd", "moe_grouped_ffn_fwd", "moe_grouped_ffn_bwd", "moe_grouped_ffn_bwd_recompute",
+    "moe_router_fwd", "moe_router_route_fwd", "moe_router_bwd", "moe_grouped_ffn_fwd", "moe_grouped_ffn_bwd", "moe_grouped_ffn_bwd_recompute",
     "moe_unpermute_combine", "moe_unpermute_combine_bwd", "moe_unpermute_combine_route_bwd",
     "moe_load_accumulate", "moe_load_imbalance", "moe_rebalance_experts",
     "moe_halo_pack_remote", "moe_halo_repack", "moe_halo_unpack",
@@ -99,6 +99,7 @@ def load_library():
         "moe_permute_bwd": [sp, V, V, V, V],
         "moe_permute_bwd_add": [sp, V, V, V, V, V],
         "moe_router_fwd": [sp, V, V, V, V, c_size_t, V],
+        "moe_router_route_fwd": [sp, V, V, V, V, V, V, V, c_size_t, V],
         "moe_router_bwd": [sp, V, V, V, V, V, c_int, V, c_size_t, V],
         "moe_grouped_ffn_fwd": [sp, V, V, V, V, V, V, V, V, V, c_size_t, V],
         "moe_grouped_ffn_bwd": [sp, V, V, V, V, V, V, V, V, V, V, V, V, c_int, V, c_size_t, V],
@@ -301,6 +302,18 @@ def moe_router_fwd(shape, x, w_router, logits, ws, stream=None):
         _ptr(logits, torch.float32, s.T * s.E, "logits"), _ptr(ws, None, None, "ws"), ws.numel() * ws.element_size(),
         _stream(stream))
     _check("moe_router_fwd", rc)
+
+
+def moe_router_route_fwd(shape, x, w_router, logits, topk_idx, topk_w, probs_save, ws, stream=None):
+    torch = _torch_module or _torch()
+    s = Shape.of(shape)
+    bf = _bf16_types()
+    rc = load_library().moe_router_route_fwd(
+        ctypes.byref(s._c), _ptr(x, bf, s.T * s.d_model, "x"), _ptr(w_router, bf, s.E * s.d_model, "w_router"),
+        _ptr(logits, torch.float32, s.T * s.E, "logits"), _ptr(topk_idx, torch.int32, s.N, "topk_idx"),
+        _ptr(topk_w, torch.float32, s.N, "topk_w"), _ptr(probs_save, torch.float32, s.T * s.E, "probs_save"),
+        _ptr(ws, None, None, "ws"), ws.numel() * ws.element_size(), _stream(stream))
+    _check("moe_router_route_fwd", rc)
 
 
 def moe_router_bwd(shape, x, w_router, dlogits, dx_router, dw_router, accumulate, ws, stream=None):

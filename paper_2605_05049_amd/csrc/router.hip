@@ -13,7 +13,7 @@
 //
 // MFMA 16x16x32 bf16: A = 16 experts x 32 k (lane l: expert l%16, k = 8 (l/16) .. +7), B = 16 tokens x 32 k (same
 // pattern), D[expert][token]: lane l holds token l%16 and experts 4 (l/16) .. +3, i.e. 4 consecutive logits of a row.
-#include "common.h"
+#include "route.h"
 
 #include <type_traits>
 
@@ -25,9 +25,21 @@ typedef float r_f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kRouterWaves = 8;          // parts of K per block
 constexpr int kRouterExpertTile = 128;   // experts per block at most (grid.y walks the tiles)
 
-template <int TB, int NEB>
+// ROUTE: and the gating of the block's 16 tokens, whose logits (up to 32 of each) it holds when the partial sums have been added: what
+// a launch of its own would read back (step of 256 tokens, 8 experts, as a graph: 79.5 -> 75.9 us).  More experts are spread over blocks
+// or take more lanes than the block has for its tokens, more tokens fill the chip anyway.
+struct RouterGateArgs {
+  int32_t* topk_idx;
+  float* topk_w;
+  float* probs;
+  int k, Es, renorm;
+};
+
+template <int TB, int NEB, bool ROUTE>
 __global__ __launch_bounds__(kRouterWaves * kWave) void router_fwd_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router,
-                                                                         float* __restrict__ logits, int T, int E, int d) {
+                                                                         float* __restrict__ logits, int T, int E, int d, RouterGateArgs G) {
+  static_assert(!ROUTE || (TB == 1 && NEB <= 2), "a group of lanes for each of the tokens, all of their logits in the block");
+  __shared__ float rows[ROUTE ? 16 : 1][16 * NEB + 1];
   constexpr int NBLK = (NEB * TB < 16) ? NEB * TB : 16;   // 16 x 16 blocks of partial logits that meet in LDS at a time
   __shared__ float part_sum[kRouterWaves][NBLK][16 * 16];   // (up to 128 KB)
   const int lane = threadIdx.x % kWave;
@@ -116,7 +128,19 @@ __global__ __launch_bounds__(kRouterWaves * kWave) void router_fwd_kernel(const 
       for (int p = 0; p < kRouterWaves; p++) sum += part_sum[p][j][idx];
       const int t = t0 + 16 * (q % TB) + (idx >> 4), e = e0 + 16 * (q / TB) + (idx & 15);
       if (t < T && e < E) logits[(size_t)t * E + e] = sum;
+      if constexpr (ROUTE) rows[idx >> 4][16 * q + (idx & 15)] = sum;
     }
+  }
+  if constexpr (ROUTE) {
+    __syncthreads();
+    auto gate = [&](auto w_c) __attribute__((always_inline)) {   // (W as route_topk takes it for E: the same sums in the same order)
+      constexpr int W = decltype(w_c)::value;
+      const int tt = threadIdx.x / W;
+      if (tt < 16 && t0 + tt < T) route_token<W, 1>(rows[tt], t0 + tt, threadIdx.x % W, G.topk_idx, G.topk_w, G.probs, E, G.k, G.Es, G.renorm);
+    };
+    if constexpr (NEB == 2) gate(std::integral_constant<int, 32>{});
+    else if (E <= 8) gate(std::integral_constant<int, 8>{});
+    else gate(std::integral_constant<int, 16>{});
   }
 }
 
@@ -215,10 +239,11 @@ __global__ __launch_bounds__(kRouterWaves * kWave) void router_fwd_wide_kernel(c
 template <int TB>
 static void launch_router_fwd(hipStream_t st, dim3 grid, int neb, const uint16_t* x, const uint16_t* w_router, float* logits, int T, int E, int d) {
   const dim3 block(kRouterWaves * kWave);
-  if (neb <= 1) MOE_LAUNCH("router_fwd", st, (router_fwd_kernel<TB, 1>), grid, block, 0, st, x, w_router, logits, T, E, d);
-  else if (neb <= 2) MOE_LAUNCH("router_fwd", st, (router_fwd_kernel<TB, 2>), grid, block, 0, st, x, w_router, logits, T, E, d);
-  else if (neb <= 4) MOE_LAUNCH("router_fwd", st, (router_fwd_kernel<TB, 4>), grid, block, 0, st, x, w_router, logits, T, E, d);
-  else MOE_LAUNCH("router_fwd", st, (router_fwd_kernel<TB, 8>), grid, block, 0, st, x, w_router, logits, T, E, d);
+  const RouterGateArgs G = {};
+  if (neb <= 1) MOE_LAUNCH("router_fwd", st, (router_fwd_kernel<TB, 1, false>), grid, block, 0, st, x, w_router, logits, T, E, d, G);
+  else if (neb <= 2) MOE_LAUNCH("router_fwd", st, (router_fwd_kernel<TB, 2, false>), grid, block, 0, st, x, w_router, logits, T, E, d, G);
+  else if (neb <= 4) MOE_LAUNCH("router_fwd", st, (router_fwd_kernel<TB, 4, false>), grid, block, 0, st, x, w_router, logits, T, E, d, G);
+  else MOE_LAUNCH("router_fwd", st, (router_fwd_kernel<TB, 8, false>), grid, block, 0, st, x, w_router, logits, T, E, d, G);
 }
 
 
@@ -580,17 +605,39 @@ void launch_router_dw_reduce(hipStream_t st, const float* partial, float* dw, in
 
 }  // namespace moe
 
+namespace moe {
+
+static int router_fwd_checks(const moe_shape* shape, Dims* D, const uint16_t* x, const uint16_t* w_router, const float* logits, void* ws,
+                             size_t ws_bytes) {
+  int rc = check_shape(shape, D);
+  if (rc != MOE_OK) return rc;
+  if (!ws) return MOE_ERR_NULL;
+  if (!aligned(ws, 256)) return MOE_ERR_ALIGN;
+  if (ws_bytes < ws_layout(*D).total) return MOE_ERR_WORKSPACE;   // (kept in the signature; this kernel needs no scratch)
+  MOE_REQUIRE_PTR(x); MOE_REQUIRE_PTR(w_router); MOE_REQUIRE_PTR(logits);
+  MOE_REQUIRE_ALIGNED(x); MOE_REQUIRE_ALIGNED(w_router); MOE_REQUIRE_ALIGNED(logits);
+  return MOE_OK;
+}
+
+// Tokens per block: 64 when that still gives every CU a block, else 32 or 16 (in units of 16).
+static int router_token_blocks(const Dims& D) { return (D.T >= 64 * 256) ? 4 : (D.T >= 32 * 256 ? 2 : 1); }
+// Expert blocks of 16 per tile: all of them (up to 8) where the token tiles fill the chip; with few tokens the experts
+// are spread over blocks too, down to one block of 16 (16 tokens, E = 64, d = 2048: 13.2 us in one block of the grid).
+static int router_expert_blocks(const Dims& D, unsigned t_tiles) {
+  int neb = (min(D.E, kRouterExpertTile) + 15) / 16;
+  neb = neb <= 2 ? neb : (neb <= 4 ? 4 : 8);
+  while (neb > 1 && (long long)t_tiles * ((D.E + 16 * neb - 1) / (16 * neb)) < 256) neb >>= 1;
+  return neb;
+}
+
+}  // namespace moe
+
 extern "C" int moe_router_fwd(const moe_shape* shape, const uint16_t* x, const uint16_t* w_router, float* logits,
                               void* ws, size_t ws_bytes, void* stream) {
   using namespace moe;
   Dims D;
-  int rc = check_shape(shape, &D);
+  int rc = router_fwd_checks(shape, &D, x, w_router, logits, ws, ws_bytes);
   if (rc != MOE_OK) return rc;
-  if (!ws) return MOE_ERR_NULL;
-  if (!aligned(ws, 256)) return MOE_ERR_ALIGN;
-  if (ws_bytes < ws_layout(D).total) return MOE_ERR_WORKSPACE;   // (kept in the signature; this kernel needs no scratch)
-  MOE_REQUIRE_PTR(x); MOE_REQUIRE_PTR(w_router); MOE_REQUIRE_PTR(logits);
-  MOE_REQUIRE_ALIGNED(x); MOE_REQUIRE_ALIGNED(w_router); MOE_REQUIRE_ALIGNED(logits);
   if (D.T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;
   if (D.E > 32 && D.T >= 8192) {   // many experts, many tokens: both operands through LDS
@@ -604,17 +651,36 @@ extern "C" int moe_router_fwd(const moe_shape* shape, const uint16_t* x, const u
     }
     return launch_status();
   }
-  // tokens per block: 64 when that still gives every CU a block, else 32 or 16
-  const int tb = (D.T >= 64 * 256) ? 4 : (D.T >= 32 * 256 ? 2 : 1);
+  const int tb = router_token_blocks(D);
   const unsigned t_tiles = (unsigned)((D.T + tb * 16 - 1) / (tb * 16));
-  // expert blocks of 16 per tile: all of them (up to 8) where the token tiles fill the chip; with few tokens the experts
-  // are spread over blocks too, down to one block of 16 (16 tokens, E = 64, d = 2048: 13.2 us in one block of the grid)
-  int neb = (min(D.E, kRouterExpertTile) + 15) / 16;
-  neb = neb <= 2 ? neb : (neb <= 4 ? 4 : 8);
-  while (neb > 1 && (long long)t_tiles * ((D.E + 16 * neb - 1) / (16 * neb)) < 256) neb >>= 1;
+  const int neb = router_expert_blocks(D, t_tiles);
   const dim3 grid(t_tiles, (unsigned)((D.E + 16 * neb - 1) / (16 * neb)));
   if (tb == 4) launch_router_fwd<4>(st, grid, neb, x, w_router, logits, D.T, D.E, D.d);
   else if (tb == 2) launch_router_fwd<2>(st, grid, neb, x, w_router, logits, D.T, D.E, D.d);
   else launch_router_fwd<1>(st, grid, neb, x, w_router, logits, D.T, D.E, D.d);
+  return launch_status();
+}
+
+extern "C" int moe_router_route_fwd(const moe_shape* shape, const uint16_t* x, const uint16_t* w_router, float* logits,
+                                    int32_t* topk_idx, float* topk_w, float* probs_save, void* ws, size_t ws_bytes, void* stream) {
+  using namespace moe;
+  Dims D;
+  int rc = router_fwd_checks(shape, &D, x, w_router, logits, ws, ws_bytes);
+  if (rc != MOE_OK) return rc;
+  MOE_REQUIRE_PTR(topk_idx); MOE_REQUIRE_PTR(topk_w);
+  MOE_REQUIRE_ALIGNED(topk_idx); MOE_REQUIRE_ALIGNED(topk_w); MOE_REQUIRE_ALIGNED(probs_save);
+  if (D.T == 0) return MOE_OK;
+  // in one launch where a block has all of its 16 tokens' logits, up to 32 (lanes of a token's group)
+  const unsigned t_tiles = (unsigned)((D.T + 15) / 16);
+  const int neb = router_expert_blocks(D, t_tiles);
+  if (router_token_blocks(D) > 1 || D.E > 16 * neb || neb > 2) {
+    rc = moe_router_fwd(shape, x, w_router, logits, ws, ws_bytes, stream);
+    return rc != MOE_OK ? rc : moe_route_topk(shape, logits, topk_idx, topk_w, probs_save, stream);
+  }
+  hipStream_t st = (hipStream_t)stream;
+  const dim3 block(kRouterWaves * kWave);
+  const RouterGateArgs G = {topk_idx, topk_w, probs_save, D.k, D.Es, D.renorm};
+  if (neb == 1) MOE_LAUNCH("router_route_fwd", st, (router_fwd_kernel<1, 1, true>), dim3(t_tiles), block, 0, st, x, w_router, logits, D.T, D.E, D.d, G);
+  else MOE_LAUNCH("router_route_fwd", st, (router_fwd_kernel<1, 2, true>), dim3(t_tiles), block, 0, st, x, w_router, logits, D.T, D.E, D.d, G);
   return launch_status();
 }

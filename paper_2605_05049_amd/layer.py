@@ -52,9 +52,8 @@ def layer_forward(buf: MoeLayerBuffers, x, w_gate, w_up, w_down, logits=None, w_
     (buf.logits = x W_r^T).  Returns buf.out."""
     s = buf.shape
     if w_router is not None:
-        B.moe_router_fwd(s, x, w_router, buf.logits, buf.ws, stream)
-        logits = buf.logits
-    if logits is not None:
+        B.moe_router_route_fwd(s, x, w_router, buf.logits, buf.topk_idx, buf.topk_w, buf.probs, buf.ws, stream)
+    elif logits is not None:
         B.moe_route_topk(s, logits, buf.topk_idx, buf.topk_w, buf.probs, stream)
     B.moe_permute(s, x, buf.topk_idx, buf.x_perm, buf.counts, buf.offsets, buf.row_of_slot, buf.slot_of_row, buf.ws, stream)
     B.moe_grouped_ffn_fwd(s, buf.x_perm, buf.offsets, w_gate, w_up, w_down, buf.y_perm, buf.save_g, buf.save_u, buf.ws, stream)

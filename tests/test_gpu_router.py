@@ -179,3 +179,30 @@ def test_closed_layer(moe, name):
     assert_close(buf.dw_gate.cpu().numpy(), g["dw_gate"], q["dw_gate"], what="dw_gate")
     assert_close(buf.dw_up.cpu().numpy(), g["dw_up"], q["dw_up"], what="dw_up")
     assert_close(buf.dw_down.cpu().numpy(), g["dw_down"], q["dw_down"], what="dw_down")
+
+
+# one launch: a group of 8, 16 and 32 lanes per token, whole and partial blocks of 16 tokens; two: experts spread over blocks, more than 32
+# of them, blocks of 32 tokens
+@pytest.mark.parametrize("T,d,E,k,Es,renorm,one_launch", [(1, 64, 1, 1, 0, 1, True), (37, 512, 8, 2, 0, 1, True), (48, 1088, 9, 3, 1, 0, True),
+                                                          (1003, 192, 16, 16, 2, 1, True), (4097, 64, 17, 4, 0, 0, True), (4096, 64, 32, 8, 1, 1, True),
+                                                          (4064, 64, 32, 2, 0, 1, False), (4096, 64, 33, 2, 0, 1, False), (8191, 64, 5, 2, 0, 1, True),
+                                                          (8192, 64, 5, 2, 0, 1, False)])
+def test_router_and_gating_in_one(moe, T, d, E, k, Es, renorm, one_launch):
+    """What the two calls give, bit for bit."""
+    s = moe.Shape(T, d, 64, E, k, Es, renorm)
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    x, w = (torch.randn(n, d, device="cuda", generator=g).to(torch.bfloat16) for n in (T, E))
+    ws = torch.empty(max(moe.workspace_bytes(s), 256), dtype=torch.uint8, device="cuda")
+    two, one = ([torch.full(sz, float("nan"), device="cuda") for sz in ((T, E), (T, s.K_slots), (T, E))] for _ in range(2))
+    idx, idx1 = (torch.full((T, s.K_slots), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    moe.moe_router_fwd(s, x, w, two[0], ws)
+    moe.moe_route_topk(s, two[0], idx, two[1], two[2])
+    moe.profile_reset()
+    moe.profile_enable(True)
+    moe.moe_router_route_fwd(s, x, w, one[0], idx1, one[1], one[2], ws)
+    torch.cuda.synchronize()
+    labels = [label for label, _ in moe.profile_records()]
+    moe.profile_enable(False)
+    moe.profile_reset()
+    assert labels == (["router_route_fwd"] if one_launch else ["router_fwd", "route_topk"])
+    assert torch.equal(idx, idx1) and all(torch.equal(a, b) for a, b in zip(two, one))
