@@ -11,6 +11,17 @@ __device__ __forceinline__ float group_max(float v) {
   for (int o = W / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, W));
   return v;
 }
+// Maximum over the 64 lanes, in registers: inside the rows of 16 lanes, then from the last lane of a row (of the first half) to the rows
+// (the half) after it; lane 63 has it in the end.
+__device__ __forceinline__ float wave_max(float v) {
+  const int ninf = __float_as_int(-__builtin_inff());   // of lanes without a source: changes nothing
+#define MOE_MAX_STEP(ctrl, rows) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(ninf, __float_as_int(v), ctrl, rows, 0xF, false)))
+  MOE_MAX_STEP(0x111, 0xF); MOE_MAX_STEP(0x112, 0xF); MOE_MAX_STEP(0x114, 0xF); MOE_MAX_STEP(0x118, 0xF);   // row_shr:1, 2, 4, 8
+  MOE_MAX_STEP(0x142, 0xA);   // row_bcast:15 into rows 1 and 3
+  MOE_MAX_STEP(0x143, 0xC);   // row_bcast:31 into rows 2 and 3
+#undef MOE_MAX_STEP
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
+}
 template <int W>
 __device__ __forceinline__ float group_sum(float v) {
 #pragma unroll
@@ -39,7 +50,7 @@ __device__ __forceinline__ void route_token(const float* row, int t, int g, int3
   float m = NEG_INF;
 #pragma unroll
   for (int p = 0; p < PER; p++) m = fmaxf(m, val[p]);
-  m = group_max<W>(m);
+  m = W == kWave ? wave_max(m) : group_max<W>(m);
   float ex[PER];
   float z = 0.f;
 #pragma unroll
@@ -63,17 +74,37 @@ __device__ __forceinline__ void route_token(const float* row, int t, int g, int3
     float bv = NEG_INF;
     int bi = 0x7fffffff;
     float bp = 0.f;
+    if constexpr (W == kWave && PER <= 4) {
+      // A wavefront's token: the largest value by lane moves, whose lanes a ballot finds.  Six rounds of exchanging value, expert and
+      // probability through LDS instead bounded the kernel: 8192 tokens, top-6 of 64 12.9 -> 6.6 us; 16384, top-4 of 128 17.8 -> 11.2;
+      // 64, top-6 of 64 5.3 -> 3.5; 4096, top-8 of 256 11.5 -> 9.5.  With 16 values per lane a lane's own search is what counts:
+      // 4096, top-8 of 1000 27.0 -> 27.5, so not there.
 #pragma unroll
-    for (int p = 0; p < PER; p++) {
-      int e = g + p * W;
-      if (!taken[p] && better(val[p], e, bv, bi)) { bv = val[p]; bi = e; bp = ex[p]; }
-    }
+      for (int p = 0; p < PER; p++)
+        if (!taken[p]) bv = fmaxf(bv, val[p]);
+      bv = wave_max(bv);
 #pragma unroll
-    for (int o = W / 2; o > 0; o >>= 1) {
-      float ov = __shfl_xor(bv, o, W);
-      int oi = __shfl_xor(bi, o, W);
-      float op = __shfl_xor(bp, o, W);
-      if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; bp = op; }
+      for (int p = PER - 1; p >= 0; p--) {   // (of equal values the lowest expert: the last to be written)
+        const unsigned long long at = __ballot(!taken[p] && val[p] == bv);
+        if (at != 0) {
+          const int l = __builtin_ctzll(at);
+          bi = p * W + l;
+          bp = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ex[p]), l));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int p = 0; p < PER; p++) {
+        int e = g + p * W;
+        if (!taken[p] && better(val[p], e, bv, bi)) { bv = val[p]; bi = e; bp = ex[p]; }
+      }
+#pragma unroll
+      for (int o = W / 2; o > 0; o >>= 1) {
+        float ov = __shfl_xor(bv, o, W);
+        int oi = __shfl_xor(bi, o, W);
+        float op = __shfl_xor(bp, o, W);
+        if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; bp = op; }
+      }
     }
     // bi is now the same on every lane of the group
 #pragma unroll
