@@ -31,7 +31,6 @@ constexpr int FP = kFewRows, FQ = kFewCols, FK = 64;   // rows, columns (per out
 constexpr int F_PITCH = FQ * 4 + 16;             // bytes per fp32 row of a partial sum
 constexpr int F_PATCH = FP * F_PITCH;            // a wavefront's LDS: P 8 KB | Q 8 KB in the loop, 64 x 64 partial sums after it
 constexpr int F_XCDS = 8;
-constexpr int F_CHUNK = 32;                      // consecutive tiles that one XCD takes
 
 // K-contiguous patch: row r at 128 r, its 16-byte chunk c (8 k) at position c ^ ((r >> 1) & 7); the lane's offset of the
 // fragment of rows 0 .. 31 at k = 0 (k flips bits of it: offset ^ 2 k; 32 rows further is 4096 bytes further).
@@ -82,8 +81,18 @@ __device__ __forceinline__ void unpack8(const uint4& u, float (&x)[8]) {
 
 }  // namespace
 
-// Blocks of at most `tiles` tiles: whole rounds of one chunk per XCD.
-inline unsigned few_rows_grid(long long tiles) { return (unsigned)((tiles + F_XCDS * F_CHUNK - 1) / (F_XCDS * F_CHUNK) * (F_XCDS * F_CHUNK)); }
+// Of at most `row_tiles` x `n_q_tiles` tiles: log2 of the consecutive ones that an XCD takes at a time.  With 32 of them a few hundred tiles
+// run on some of the XCDs only, or on some for one chunk longer; with 8 there is less that the tiles of an XCD share, which counts where
+// experts have more than 128 rows (2 tiles, besides the one that rounding up allows each).  Forward, us, 32 -> 8 (d x f, E, rows per expert):
+//   3136 x 832, 3, 10: 32.6 -> 22.6    512 x 1024, 8, 64: 21.5 -> 16.4    4096 x 576, 10, 15: 46.5 -> 34.4    1024 x 1088, 6, 63: 20.6 -> 18.1
+// and beyond the limits 5056 x 832, 6, 146: 57.8 -> 61.7    768 x 2752, 9, 97 (946 tiles of f): 44.4 -> 46.7    2048 x 1408, 66, 2: 176 -> 181.
+// (4 up to 128 tiles: forward 0.97 of that, with the backward 1.02.)
+inline int few_rows_chunk_log2(long long row_tiles, int n_q_tiles, int Et) { return row_tiles * n_q_tiles <= 768 && row_tiles <= 3ll * Et ? 3 : 5; }
+// Their blocks: whole rounds of one chunk per XCD.
+inline unsigned few_rows_grid(long long tiles, int chunk_log2) {
+  const long long round = (long long)F_XCDS << chunk_log2;
+  return (unsigned)((tiles + round - 1) / round * round);
+}
 
 // Block `block` of `blocks`: one tile (or none); lds: WAVES * F_PATCH bytes.
 template <int KIND, int WAVES>
@@ -95,10 +104,11 @@ __device__ __forceinline__ void few_rows_block(const RowTileArgs& A, char* lds, 
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // ---- block id -> tile: chunks of 32 consecutive tiles (neighbouring columns of one expert, its row tiles side by side) are
+  // ---- block id -> tile: chunks of consecutive tiles (neighbouring columns of one expert, its row tiles side by side) are
   // dealt round-robin to the XCDs
   const int within = (int)(block / F_XCDS), xcd = (int)(block % F_XCDS);
-  const long long lid = ((long long)(within / F_CHUNK) * F_XCDS + xcd) * F_CHUNK + within % F_CHUNK;
+  const int cl = A.chunk_log2;
+  const long long lid = (((long long)(within >> cl) * F_XCDS + xcd) << cl) + (within & ((1 << cl) - 1));
   const int ut = (int)(lid / A.n_q_tiles);   // some row tile of the expert this block works for
   int expert, first, e_lo, e_hi;             // first: index of the expert's first row tile
   if (A.sched) {

@@ -11,7 +11,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void few_rows_kernel(const RowTil
 
 template <int KIND>
 static void launch_few(const char* label, hipStream_t st, const RowTileArgs& A, long long tiles) {
-  const dim3 grid(few_rows_grid(tiles) + (A.order ? 1u : 0u));
+  const dim3 grid(few_rows_grid(tiles, A.chunk_log2) + (A.order ? 1u : 0u));
   // 8 wavefronts per block, one block per CU, where that is all the blocks there are; else 4, two blocks per CU
   if (tiles <= 256) MOE_LAUNCH(label, st, (few_rows_kernel<KIND, 8>), grid, dim3(8 * kWave), 0, st, A);
   else MOE_LAUNCH(label, st, (few_rows_kernel<KIND, 4>), grid, dim3(4 * kWave), 0, st, A);
@@ -22,6 +22,7 @@ void launch_few_rows(const char* label, hipStream_t st, int kind, RowTileArgs A,
   A.n_q_tiles = A.q_dim / FQ;
   const long long tiles = row_tiles * A.n_q_tiles;
   if (tiles <= 0) return;
+  A.chunk_log2 = few_rows_chunk_log2(row_tiles, A.n_q_tiles, A.Et);
   switch (kind) {
     case ROWTILE_GATE_UP: launch_few<ROWTILE_GATE_UP>(label, st, A, tiles); break;
     case ROWTILE_DOWN: launch_few<ROWTILE_DOWN>(label, st, A, tiles); break;

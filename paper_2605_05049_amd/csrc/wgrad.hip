@@ -296,7 +296,7 @@ static void plan_wgrad(WgradProblem& B, int Et, long long rows) {
   B.chunks = (int)chunks;
 }
 
-// Launches the weight gradients of the pair and of the single tensor, and dX where it runs on 64-row tiles (at most dx_tiles of them;
+// Launches the weight gradients of the pair and of the single tensor, and dX where it runs on 64-row tiles (at most dx_tiles row tiles;
 // 0: it does not).
 void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles) {
   if (A.Et <= 0) return;
@@ -310,7 +310,8 @@ void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
       DxWgradArgs X = {};
       X.dx = dx; X.dw = A;
       X.dx.n_q_tiles = dx.q_dim / FQ;
-      X.dx_blocks = few_rows_grid(dx_tiles * X.dx.n_q_tiles);
+      X.dx.chunk_log2 = few_rows_chunk_log2(dx_tiles, X.dx.n_q_tiles, dx.Et);
+      X.dx_blocks = few_rows_grid(dx_tiles * X.dx.n_q_tiles, X.dx.chunk_log2);
       MOE_LAUNCH("ffn_bwd_dx_dw", st, dx_wgrad_kernel, dim3(X.dx_blocks + grid(A.a.chunks + A.b.chunks).x), block, 0, st, X);
       return;
     }
