@@ -171,7 +171,7 @@ struct WgradArgs {
   int Et, accumulate;
   long long rows;              // of all experts together
   size_t f_expert_stride;
-  WgradProblem a, b;           // dW_gate | dW_up and dW_down
+  WgradProblem problem[2];     // dW_gate | dW_up and dW_down
 };
 void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles);   // (dx_tiles > 0: and dX on 64-row tiles)
 

@@ -1206,13 +1206,13 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   W.offsets = offsets; W.order = G.experts_by_rows(); W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
   W.Et = D.Et; W.accumulate = accumulate ? 1 : 0; W.rows = D.N; W.f_expert_stride = (size_t)D.f * D.d;
   // dWg[e], dWu[e] = X_e^T dG_e, X_e^T dU_e   (rows d, columns f)
-  W.a.p0 = x_perm; W.a.p_ld = D.d; W.a.p_dim = D.d;
-  W.a.q0 = dg; W.a.q1 = du; W.a.q_ld = D.f; W.a.q_dim = D.f;
-  W.a.f0 = dw_gate; W.a.f1 = dw_up; W.a.c_ld = D.f;
+  W.problem[0].p0 = x_perm; W.problem[0].p_ld = D.d; W.problem[0].p_dim = D.d;
+  W.problem[0].q0 = dg; W.problem[0].q1 = du; W.problem[0].q_ld = D.f; W.problem[0].q_dim = D.f;
+  W.problem[0].f0 = dw_gate; W.problem[0].f1 = dw_up; W.problem[0].c_ld = D.f;
   // dWd[e] = H_e^T dY_e   (rows f, columns d)
-  W.b.p0 = h; W.b.p_ld = D.f; W.b.p_dim = D.f;
-  W.b.q0 = dy_perm; W.b.q_ld = D.d; W.b.q_dim = D.d;
-  W.b.f0 = dw_down; W.b.c_ld = D.d;
+  W.problem[1].p0 = h; W.problem[1].p_ld = D.f; W.problem[1].p_dim = D.f;
+  W.problem[1].q0 = dy_perm; W.problem[1].q_ld = D.d; W.problem[1].q_dim = D.d;
+  W.problem[1].f0 = dw_down; W.problem[1].c_ld = D.d;
   // dX needs dH's results as the weight gradients do, and on the 64-row tiles it may share their launch
   RowTileArgs X = G.dx_args(dg, du, w_gate, w_up, dx_perm);
   const bool dx_few = D.N > 0 && few_rows_pays(D, ROWTILE_DX);

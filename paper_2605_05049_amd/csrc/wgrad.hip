@@ -76,10 +76,14 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
   // round-robin to the XCDs, of each problem the experts with the most rows first (its last tiles are then short ones).
   const int within = (int)(block / W_XCDS), xcd = (int)(block % W_XCDS);
   const long long launch_chunk = (long long)(within / W_CHUNK) * W_XCDS + xcd;
-  const bool is_b = launch_chunk >= A.a.chunks;   // (a launch may carry two problems, the second's chunks after the first's)
-  const WgradProblem B = is_b ? A.b : A.a;
+  const bool is_b = launch_chunk >= A.problem[0].chunks;   // (a launch may carry two problems, the second's chunks after the first's)
+  // The index is kept from the compiler's sight: it would read each field by a chosen address of its own, one after the other, and not the
+  // problem in a few wide loads (4096 x 14336, 64 rows per expert, dW_down 308 -> 306 us; 1024 rows, the pair 1823 -> 1814).
+  int which = __builtin_amdgcn_readfirstlane((int)is_b);
+  asm("" : "+r"(which));
+  const WgradProblem B = A.problem[which];
   const long long tiles_per_e = (long long)B.n_p_tiles * B.n_q_tiles;
-  const long long lid = (launch_chunk - (is_b ? A.a.chunks : 0)) * W_CHUNK + within % W_CHUNK;
+  const long long lid = (launch_chunk - (is_b ? A.problem[0].chunks : 0)) * W_CHUNK + within % W_CHUNK;
   if (lid >= tiles_per_e * A.Et) return;
   const int expert = A.order[(int)(lid / tiles_per_e)];
   const int local = (int)(lid % tiles_per_e);
@@ -117,19 +121,30 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
   }
   const int nk = (k_len + WK - 1) / WK;
   // The 32 tiles of a chunk run together, and those that share a panel would ask for the same lines at the same time and all wait for
-  // the same misses.  So each begins at another step and goes round (of the first 8, 4 of many; along either direction of the chunk
-  // neighbours differ): a line is then waited for by one of them and in the L2 for the others.  (Further apart, by an eighth of the
-  // steps, the panels have left the L2 when the last tile comes to them: pair of 8 x 1024 rows, 4096 x 14336, 1800 -> 2450 us.  128
-  // experts of 0 .. 3100 rows, 4096 x 1024: dW_down 876 -> 765 us, the pair 1600 -> 1480 .. 1560; 3968 x 1536, 31 of 230: both 574 ->
-  // 543; 2048 x 8192, 8 of 2048: 1396 -> 1391, and 1372 over 8 steps, which costs 8 x 1024 rows of 4096 x 14336 1 %.)
-  const int ring_p = in_band % band_p, ring_q = in_band / band_p;
-  const int begin = B.band == 4 ? 2 * ring_p + ring_q : ring_p + 2 * ring_q;
-  const int rot = nk > 24 ? begin & 3 : nk >= 8 ? begin & 7 : nk >= 4 ? (begin & 7) * nk / 8 : 0;
-  auto issue = [&](int step, char* stage) __attribute__((always_inline)) {
-    const int turned = step + rot, k0 = (turned >= nk ? turned - nk : turned) * WK;
-    const uint16_t* const pb = p_base + (size_t)k0 * B.p_ld;
-    const uint16_t* const qb0 = q_base0 + (size_t)k0 * B.q_ld;
-    const uint16_t* const qb1 = q_base1 + (size_t)k0 * B.q_ld;
+  // the same misses.  So each begins at another of the first 4 steps and goes round (along either direction of the chunk neighbours
+  // differ): a line is then waited for by one of them and in the L2 for the others.  us, all from step 0 -> this: 128 experts of 500 rows,
+  // 4096 x 1024, dW_down 818 -> 745 and the pair 1448 -> 1430; 7168 x 2048, 32 of 128, 395 -> 354 and 708 -> 638; 2048 x 1408, 66 of 870,
+  // both 1146 -> 1123; 4096 x 14336, 8 of 1024, dW_down 992 -> 963, the pair 1758 -> 1770.  (Of the first 8 steps: the pair of
+  // 7168 x 2048, 32 of 128 681, of 4096 x 1024 1455.  Further apart, by an eighth of the steps, the panels have left the L2 when the last
+  // tile comes to them: pair of 8 x 1024 rows, 4096 x 14336, 1800 -> 2450.)
+  // The addresses of the next step's loads are carried along and moved on behind the loads that use them: made anew from the step they
+  // cost two 64-bit products between the barrier and the loads, which the whole step waits for (4096 x 14336, 8 of 1024 rows: dW_down
+  // 984 -> 968 us, the pair 1842 -> 1814).
+  const int k_end = nk * WK;
+  const size_t p_step = (size_t)WK * B.p_ld, q_step = (size_t)WK * B.q_ld;
+  int k0 = 0;
+  const uint16_t* pb = p_base;
+  const uint16_t* qb0 = q_base0;
+  const uint16_t* qb1 = q_base1;
+  if (nk >= 4) {
+    const int ring_p = in_band % band_p, ring_q = in_band / band_p;
+    const int begin = (B.band == 4 ? 2 * ring_p + ring_q : ring_p + 2 * ring_q) & 3;
+    k0 = begin * WK;
+    pb += begin * p_step;
+    qb0 += begin * q_step;
+    qb1 += begin * q_step;
+  }
+  auto issue = [&](char* stage) __attribute__((always_inline)) {
     char* const pl = stage + wave * 2048;
     char* const ql = stage + P_BYTES + wave * 4096;
     if (k0 + WK <= k_len) {
@@ -150,6 +165,12 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
         direct_load16(in ? reinterpret_cast<const char*>((i & 1) ? qb1 : qb0) + qvo[i] : zero, ql + i * 1024);
       }
     }
+    k0 += WK;
+    const bool around = k0 == k_end;
+    if (around) k0 = 0;
+    pb = around ? p_base : pb + p_step;
+    qb0 = around ? q_base0 : qb0 + q_step;
+    qb1 = around ? q_base1 : qb1 + q_step;
   };
 
   // The two blocks of a CU start together, and with experts of equal size they stay in step: both multiply, then both store, and
@@ -159,8 +180,8 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
   // rows there is nothing to cover, and the stores in step are 1 - 2 % faster.)
   if (nk >= 3 && ((within / W_CHUNK) & 1)) __builtin_amdgcn_s_setprio(1);
   const int wp = (wave & 1) * 64, wq = (wave >> 1) * WH;   // (wavefronts 0, 1 the first half, 2, 3 the second)
-  if (nk > 0) issue(0, ring);
-  if (nk > 1) issue(1, ring + W_STAGE);
+  if (nk > 0) issue(ring);
+  if (nk > 1) issue(ring + W_STAGE);
   unsigned p_off[4], q_off[8];
 #pragma unroll
   for (int b = 0; b < 4; b++) p_off[b] = w_frag_offset<1, true>(wp + 16 * b, lane);
@@ -180,7 +201,7 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
     if (kt + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0F76);   // vmcnt(6): all but the 6 loads of step kt + 1
     else __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();   // step kt has landed for everyone; everyone is done with step kt - 1, whose slot step kt + 2 takes
-    if (kt + 2 < nk) issue(kt + 2, fill);
+    if (kt + 2 < nk) issue(fill);
     const unsigned pa = (unsigned)(size_t)(lptr_t)cur, qa = pa + P_BYTES;
     if (idle) return;
     // Rolling fragments: three q fragments ahead of the four MFMAs that use one (all twelve fragments read before the first
@@ -300,19 +321,19 @@ static void plan_wgrad(WgradProblem& B, int Et, long long rows) {
 // 0: it does not).
 void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles) {
   if (A.Et <= 0) return;
-  plan_wgrad(A.a, A.Et, A.rows);
-  plan_wgrad(A.b, A.Et, A.rows);
+  plan_wgrad(A.problem[0], A.Et, A.rows);
+  plan_wgrad(A.problem[1], A.Et, A.rows);
   auto grid = [](long long chunks) { return dim3((unsigned)((chunks + W_XCDS - 1) / W_XCDS * W_XCDS * W_CHUNK)); };
   const dim3 block(WTHREADS);
   if (dx_tiles > 0) {
     // (2048 x 1408, 66 experts, 528 chunks, forward + backward: 837 us with dX in a launch of its own, 842 with one for all.)
-    if (A.a.chunks + A.b.chunks <= W_DX_CHUNKS) {
+    if (A.problem[0].chunks + A.problem[1].chunks <= W_DX_CHUNKS) {
       DxWgradArgs X = {};
       X.dx = dx; X.dw = A;
       X.dx.n_q_tiles = dx.q_dim / FQ;
       X.dx.chunk_log2 = few_rows_chunk_log2(dx_tiles, X.dx.n_q_tiles, dx.Et);
       X.dx_blocks = few_rows_grid(dx_tiles * X.dx.n_q_tiles, X.dx.chunk_log2);
-      MOE_LAUNCH("ffn_bwd_dx_dw", st, dx_wgrad_kernel, dim3(X.dx_blocks + grid(A.a.chunks + A.b.chunks).x), block, 0, st, X);
+      MOE_LAUNCH("ffn_bwd_dx_dw", st, dx_wgrad_kernel, dim3(X.dx_blocks + grid(A.problem[0].chunks + A.problem[1].chunks).x), block, 0, st, X);
       return;
     }
     launch_few_rows("ffn_bwd_dx", st, ROWTILE_DX, dx, dx_tiles);
@@ -320,14 +341,14 @@ void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
   // In one launch, unless it is long: two launches have two starts and two last rounds.  Time of the one against the two, 200
   // random shapes: 0.73 at fewer than 64 chunks, 0.91 at 64 .. 128, 0.94 up to 256, 0.97 up to 512, 0.98 up to 1024, 0.99 - 1.0
   // beyond.
-  if (A.a.chunks + A.b.chunks <= W_MERGE_CHUNKS) {
-    MOE_LAUNCH("ffn_bwd_dw", st, wgrad_kernel, grid(A.a.chunks + A.b.chunks), block, 0, st, A);
+  if (A.problem[0].chunks + A.problem[1].chunks <= W_MERGE_CHUNKS) {
+    MOE_LAUNCH("ffn_bwd_dw", st, wgrad_kernel, grid(A.problem[0].chunks + A.problem[1].chunks), block, 0, st, A);
     return;
   }
-  const dim3 pair_grid = grid(A.a.chunks), down_grid = grid(A.b.chunks);
-  A.a.chunks = A.b.chunks = INT_MAX;   // every block of these launches belongs to the first problem
+  const dim3 pair_grid = grid(A.problem[0].chunks), down_grid = grid(A.problem[1].chunks);
+  A.problem[0].chunks = A.problem[1].chunks = INT_MAX;   // every block of these launches belongs to the first problem
   WgradArgs down = A;
-  down.a = A.b;
+  down.problem[0] = A.problem[1];
   MOE_LAUNCH("ffn_bwd_dw_down", st, wgrad_kernel, down_grid, block, 0, st, down);
   MOE_LAUNCH("ffn_bwd_dw_gate_up", st, wgrad_kernel, pair_grid, block, 0, st, A);
 }
