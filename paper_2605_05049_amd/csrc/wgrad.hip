@@ -38,7 +38,8 @@ constexpr int Q_BYTES = WQ * WK * 2;         // 16 KB
 constexpr int W_STAGE = P_BYTES + Q_BYTES;   // 24 KB
 constexpr int W_XCDS = 8;
 constexpr int W_MERGE_CHUNKS = 1024;         // both problems in one launch up to here
-constexpr int W_DX_CHUNKS = 256;             // ... and dX on 64-row tiles with them up to here
+constexpr int W_DX_CHUNKS = 256;             // ... and dX on 64-row tiles with them up to here, ...
+constexpr int W_DX_SHORT_STEPS = 64, W_DX_STEPS = 240, W_DX_STEPS_PER_CHUNK = 8;   // ... if its contraction is not too long (dx_joins)
 constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
 
 // Position of 8 r-values (chunk c of 16) inside k-row k's 256 bytes: the four k-rows that a transposing read takes together
@@ -317,6 +318,17 @@ static void plan_wgrad(WgradProblem& B, int Et, long long rows) {
   B.chunks = (int)chunks;
 }
 
+// Whether dX on 64-row tiles shares the weight gradients' launch of `chunks` chunks.  There a tile has four wavefronts and a CU shared
+// with the weight gradients; in a launch of its own with at most 256 tiles it has eight and a CU to itself, half the chain of dependent
+// steps.  So a long chain joins only beside weight gradients that take as long.  Backward, graph of calls, time of one launch / of two,
+// 360 random shapes by the k-steps of dX: up to 64 0.73 .. 0.99, mean 0.87.  Up to 240: with at most 8 steps per chunk 0.81 .. 0.97, 0.90;
+// with more 0.90 .. 1.16, 1.02 (192 x 3328, 2 experts of 60 rows 1.02; 640 x 3968, one of 3 1.14; 192 x 7552, one of 120 1.16).  Beyond
+// 0.89 .. 1.18, 1.01, and no size tells them apart (1088 x 9856, 3 of 146 0.98; 3008 x 7744, 2 of 96 1.11; 192 x 12096, one of 133 1.18).
+static bool dx_joins(const RowTileArgs& dx, int chunks) {
+  const int steps = 2 * dx.k_dim / FK;
+  return chunks <= W_DX_CHUNKS && (steps <= W_DX_SHORT_STEPS || (steps <= W_DX_STEPS && steps <= W_DX_STEPS_PER_CHUNK * chunks));
+}
+
 // Launches the weight gradients of the pair and of the single tensor, and dX where it runs on 64-row tiles (at most dx_tiles row tiles;
 // 0: it does not).
 void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles) {
@@ -327,7 +339,7 @@ void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
   const dim3 block(WTHREADS);
   if (dx_tiles > 0) {
     // (2048 x 1408, 66 experts, 528 chunks, forward + backward: 837 us with dX in a launch of its own, 842 with one for all.)
-    if (A.problem[0].chunks + A.problem[1].chunks <= W_DX_CHUNKS) {
+    if (dx_joins(dx, A.problem[0].chunks + A.problem[1].chunks)) {
       DxWgradArgs X = {};
       X.dx = dx; X.dw = A;
       X.dx.n_q_tiles = dx.q_dim / FQ;

@@ -821,6 +821,21 @@ def test_dx_beside_the_weight_gradients(moe, E):
             assert bool(torch.isfinite(got).all()) and float((got - ref).norm()) <= 2.0 ** -8 * float(ref.norm())
 
 
+# k-steps of dX: 64 always, 66 beside 4 chunks not; 128 beside 16 chunks and not beside 12; 240 beside 31, 242 never
+@pytest.mark.parametrize("d,f,joined", [(64, 2048, True), (64, 2112, False), (640, 4096, True), (512, 4096, False), (640, 7680, True),
+                                        (640, 7744, False)])
+def test_long_dx_has_a_launch_of_its_own(moe, d, f, joined):
+    moe.profile_reset()
+    moe.profile_enable(True)
+    try:
+        test_grouped_ffn_every_tile_height(moe, d, f, [256, 0])
+        labels = [label for label, _ in moe.profile_records()]
+    finally:
+        moe.profile_enable(False)
+        moe.profile_reset()
+    assert ("ffn_bwd_dx_dw" in labels, "ffn_bwd_dx" in labels) == (joined, not joined)
+
+
 def test_grouped_ffn_with_no_rows(moe):
     """T = 0: nothing to compute, but overwritten weight gradients must be exact zeros and accumulated ones untouched."""
     shape = W.MoEShape(0, 128, 64, 4, 2)
