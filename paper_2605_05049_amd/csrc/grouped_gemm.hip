@@ -67,7 +67,7 @@ constexpr int kCusPerXcd = 32;
 #ifndef MOE_SPLIT_PART_STEPS
 #define MOE_SPLIT_PART_STEPS 16
 #endif
-constexpr int kRowCutRows = 128, kRowCutSteps = 96;
+constexpr int kRowCutRows = 128, kRowCutSteps = 96, kRowCutLeast = 64;   // (and tiles of fewer than kRowCutLeast rows on average not at all)
 enum Epilogue { EPI_BF16 = 0, EPI_SWIGLU = 1, EPI_DSWIGLU = 2, EPI_F32 = 3,
                 EPI_SWIGLU_H = 4, EPI_SWIGLU_GU = 5 };   // of the SwiGLU forward H alone (G and U are not kept), G and U alone (recomputed)
 
@@ -266,6 +266,11 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
   // Against the K split, 130 kernels (time of the pieces / of the parts): tiles of 128 rows or more on average, 48 .. 96 k-steps
   // 0.63 .. 1.01, 97 .. 118 0.79 .. 1.06, 124 .. 200 0.86 .. 1.38, beyond 0.96 .. 2.1; tiles of fewer rows, which give fewer pieces,
   // 1.1 .. 3.4.
+  // Tiles of fewer than 64 rows on average stay whole, since most have nothing to cut and pieces of the others read the same columns twice
+  // (576 x 3392, 49 experts of 62 rows: gate | up 101 -> 103 us in pieces; 576 x 2304, 87 of 25: 105 -> 111).  Long contractions
+  // of many tiles gain little, 0.974 of the time of whole tiles at the mean of 80 with 5 .. 46 full rounds, and may lose what the last
+  // round's start is uneven by: 4096 x 14336, 14 rounds and 14 tiles per XCD, eight experts of 1024 .. 1280 rows 0.994 .. 1.005, of
+  // 970 .. 1100, some tall 1.008 .. 1.014; 10 .. 12 rounds 0.985 .. 0.99.
   constexpr bool SPLIT_ROWS = KIND == 0 && !RAGGED_K;
   int split = 1, part = 0, part_slot = 0, row_parts = 1, row_part = 0;
   if (KIND == 0) {
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
         full = cnt - rem;
       }
     }
-    if (SPLIT_ROWS && full == cnt) {
+    if (SPLIT_ROWS && full == cnt && A.rows >= (long long)kRowCutLeast * n_row_tiles) {
       const int rem = (int)(cnt % kCusPerXcd);
       if (rem > 0 && rem <= kCusPerXcd / 2) {
         row_parts = min(kCusPerXcd / rem, (TILE + 64) / 64);
