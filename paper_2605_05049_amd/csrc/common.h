@@ -147,6 +147,7 @@ struct RowTileArgs {
   uint32_t* zero_page;     // ... and clears these 256 bytes
   int max_tiles;
   const int32_t* offsets;  // [E'+1]
+  long long rows;          // of all experts together
   int n_q_tiles, chunk_log2;   // filled by the launcher
   int q_dim, k_dim;        // output columns; contraction length (per pass)
   const uint16_t* p0; const uint16_t* p1; size_t p_ld;   // activations (p1: second pass of dX)

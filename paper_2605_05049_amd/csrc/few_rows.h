@@ -83,11 +83,17 @@ __device__ __forceinline__ void unpack8(const uint4& u, float (&x)[8]) {
 
 // Of at most `row_tiles` x `n_q_tiles` tiles: log2 of the consecutive ones that an XCD takes at a time.  With 32 of them a few hundred tiles
 // run on some of the XCDs only, or on some for one chunk longer; with 8 there is less that the tiles of an XCD share, which counts where
-// experts have more than 128 rows (2 tiles, besides the one that rounding up allows each).  Forward, us, 32 -> 8 (d x f, E, rows per expert):
+// experts have more than 64 rows (a tile).  Forward, us, 32 -> 8 (d x f, E, rows per expert):
 //   3136 x 832, 3, 10: 32.6 -> 22.6    512 x 1024, 8, 64: 21.5 -> 16.4    4096 x 576, 10, 15: 46.5 -> 34.4    1024 x 1088, 6, 63: 20.6 -> 18.1
-// and beyond the limits 5056 x 832, 6, 146: 57.8 -> 61.7    768 x 2752, 9, 97 (946 tiles of f): 44.4 -> 46.7    2048 x 1408, 66, 2: 176 -> 181.
+// and beyond the limits 5056 x 832, 6, 146: 57.8 -> 61.7    1472 x 1408, 15, 81: 55.1 -> 60.2    2048 x 1408, 66, 2: 176 -> 181.
+// Single kernels of 350 shapes, 8 / 32 by at most so many tiles: up to 64 rows per expert 0.82 .. 0.97 at the mean up to 768; 64 .. 128
+// rows 0.93 .. 0.98 up to 192, 0.97 .. 0.99 up to 256 and 0.98 beyond, where many lose (dH of 6208 x 320, 35 of 86, 410 tiles 1.06; forward
+// of 1152 x 4096, 5 of 117, uneven, 1.07); of 131 rows dH of 6784 x 1216, 9 experts 60 -> 76 us.
 // (4 up to 128 tiles: forward 0.97 of that, with the backward 1.02.)
-inline int few_rows_chunk_log2(long long row_tiles, int n_q_tiles, int Et) { return row_tiles * n_q_tiles <= 768 && row_tiles <= 3ll * Et ? 3 : 5; }
+inline int few_rows_chunk_log2(const RowTileArgs& A, long long row_tiles, int n_q_tiles) {
+  const int most_tiles = A.rows <= 64ll * A.Et ? 768 : A.rows <= 128ll * A.Et ? 192 : 0;
+  return row_tiles * n_q_tiles <= most_tiles ? 3 : 5;
+}
 // Their blocks: whole rounds of one chunk per XCD.
 inline unsigned few_rows_grid(long long tiles, int chunk_log2) {
   const long long round = (long long)F_XCDS << chunk_log2;

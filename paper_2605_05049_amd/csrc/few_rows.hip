@@ -22,7 +22,7 @@ void launch_few_rows(const char* label, hipStream_t st, int kind, RowTileArgs A,
   A.n_q_tiles = A.q_dim / FQ;
   const long long tiles = row_tiles * A.n_q_tiles;
   if (tiles <= 0) return;
-  A.chunk_log2 = few_rows_chunk_log2(row_tiles, A.n_q_tiles, A.Et);
+  A.chunk_log2 = few_rows_chunk_log2(A, row_tiles, A.n_q_tiles);
   switch (kind) {
     case ROWTILE_GATE_UP: launch_few<ROWTILE_GATE_UP>(label, st, A, tiles); break;
     case ROWTILE_DOWN: launch_few<ROWTILE_DOWN>(label, st, A, tiles); break;

@@ -1081,7 +1081,7 @@ struct RowGemms {
     R.max_tiles = max_tiles; R.offsets = offsets;
     R.q_expert_stride = (size_t)D.d * D.f;
     R.sched = self_scheduled() ? nullptr : sched_few;
-    R.Et = D.Et;
+    R.Et = D.Et; R.rows = D.N;
   }
   long long few_row_tiles() const { return D.N / kFewRows + (D.N < D.Et ? D.N : D.Et); }   // sum_e ceil(n_e / 64) <= N / 64 + experts with rows
 

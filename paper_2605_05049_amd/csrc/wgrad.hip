@@ -343,7 +343,7 @@ void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
       DxWgradArgs X = {};
       X.dx = dx; X.dw = A;
       X.dx.n_q_tiles = dx.q_dim / FQ;
-      X.dx.chunk_log2 = few_rows_chunk_log2(dx_tiles, X.dx.n_q_tiles, dx.Et);
+      X.dx.chunk_log2 = few_rows_chunk_log2(dx, dx_tiles, X.dx.n_q_tiles);
       X.dx_blocks = few_rows_grid(dx_tiles * X.dx.n_q_tiles, X.dx.chunk_log2);
       MOE_LAUNCH("ffn_bwd_dx_dw", st, dx_wgrad_kernel, dim3(X.dx_blocks + grid(A.problem[0].chunks + A.problem[1].chunks).x), block, 0, st, X);
       return;
