@@ -331,7 +331,10 @@ __global__ __launch_bounds__(256) void perm_scatter_kernel(const u32x4* __restri
         rows[j] = 0;
       }
       const int N = T * KP;
-      constexpr int AHEAD = 8;   // groups of 64 keys in flight
+      // Groups of 64 keys in flight.  Their ballots are scalar registers, of which 8 groups of 6 and more slots have too few (29 .. 65 were
+      // spilt).  moe_permute, time of that of three launches, 8 groups / 4: 8 slots per token 0.75 .. 1.04 / 0.69 .. 0.95, 7: 0.76 .. 0.97 /
+      // 0.71 .. 0.95, 6: 0.71 .. 0.91 / 0.67 .. 0.91; 5, with 4 spilt: 0.67 .. 1.03 / 0.66 .. 1.05.
+      constexpr int AHEAD = KP <= 5 ? 8 : 4;
       for (int i0 = 0; i0 < N; i0 += AHEAD * kWave) {
         int id[AHEAD];
 #pragma unroll
