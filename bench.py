@@ -93,7 +93,7 @@ def gemm_bytes_per_launch(label, shape, n_active):
             "ffn_bwd_dh_dswiglu": act_d + w1 + 2 * act_f + 3 * act_f, "ffn_bwd_dx": 2 * act_f + 2 * w1 + act_d,
             "ffn_bwd_dw_down": act_f + act_d + Et * d * f * 4, "ffn_bwd_dw_gate_up": act_d + 2 * act_f + 2 * Et * d * f * 4,
             "ffn_bwd_dw": 2 * act_d + 3 * act_f + 3 * Et * d * f * 4,
-            "ffn_bwd_dx_dw": 3 * act_d + 5 * act_f + 2 * w1 + 3 * Et * d * f * 4}.get(label)
+            "ffn_bwd_dx_dw": 3 * act_d + 3 * act_f + 2 * w1 + 3 * Et * d * f * 4}.get(label)   # (dG and dU are operands of both, read once)
 
 
 def gemm_roofline(label, shape, n_active, avg_ms):

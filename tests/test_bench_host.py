@@ -34,6 +34,11 @@ def test_flop_and_byte_counts():
     # weight gradients: operands once + fp32 dW of every expert
     by = bench.gemm_bytes_per_launch("ffn_bwd_dw_gate_up", sh, sh.E_total)
     assert by == sh.N * sh.d_model * 2 + 2 * sh.N * sh.d_ffn * 2 + 2 * sh.E_total * sh.d_model * sh.d_ffn * 4
+    # launches of several problems: what these share is read once (dG and dU, of dX and of dW_gate | dW_up)
+    act_d, act_f, w1, dw = sh.N * sh.d_model * 2, sh.N * sh.d_ffn * 2, sh.E_total * sh.d_model * sh.d_ffn * 2, 3 * sh.E_total * sh.d_model * sh.d_ffn * 4
+    assert bench.gemm_flops_per_launch("ffn_bwd_dw", sh) == 3 * unit and bench.gemm_flops_per_launch("ffn_bwd_dx_dw", sh) == 5 * unit
+    assert bench.gemm_bytes_per_launch("ffn_bwd_dw", sh, sh.E_total) == 2 * act_d + 3 * act_f + dw                    # x, dY; dG, dU, H
+    assert bench.gemm_bytes_per_launch("ffn_bwd_dx_dw", sh, sh.E_total) == 3 * act_d + 3 * act_f + 2 * w1 + dw        # and dX; W_gate, W_up
     # the Mixtral-shaped GEMMs are MFMA-bound, the expert shard's are HBM-bound (weights streamed for ~128 rows each)
     assert bench.gemm_roofline("ffn_fwd_gate_up_swiglu", sh, 8, 2.0)["bound"] == "mfma"
     shard = W.WORKLOADS["shard"].shape
