@@ -393,7 +393,7 @@ def run_router_bench(moe, W, workload, steps):
 
 
 def run_graph_bench(moe, W, steps):
-    """The launch-bound end of the range: the tiny workload's whole step (about 20 kernels) issued call by call and
+    """The launch-bound end of the range: the tiny workload's whole step (about ten kernels) issued call by call and
     replayed as one captured HIP graph."""
     import torch
     wl = W.WORKLOADS["tiny"]

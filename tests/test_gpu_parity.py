@@ -87,6 +87,13 @@ ROUTE_CASES = [
     (50, 384, 16, 3, 0, "ties"),
     (40, 1000, 70, 0, 1, "normal"),
     (1, 8, 2, 0, 1, "normal"),
+    # a wavefront per token and two or four logits per lane: equal logits on different lanes and in different slots of a lane, also
+    # where fewer than k experts are alive and equal -1e30 and one -inf are chosen among
+    (200, 128, 8, 0, 1, "ties"),
+    (200, 256, 8, 1, 0, "ties"),
+    (60, 64, 60, 0, 0, "dead"),
+    (60, 128, 120, 0, 1, "dead"),
+    (60, 250, 240, 2, 0, "dead"),
 ]
 
 
@@ -226,11 +233,27 @@ def test_permute_maps_rows_and_streams(moe, T, d, E, k, Es, kind):
                  O.unpermute_combine_scale(np.abs(y64), ros_ref, np.ones((T, Kp))), what="permute_bwd")
 
 
-# the one-launch counting sort: a slot, one sub-group of 64 and its neighbours, 1024-slot blocks, and sizes just past it
+# few slots: one, a sub-group of 64 and its neighbours, several sub-groups and slots per token (ranked by the scatter), and sizes past it
 @pytest.mark.parametrize("T,E,k,Es", [(1, 1, 1, 0), (64, 3, 1, 0), (65, 7, 1, 0), (341, 9, 3, 0), (1025, 5, 1, 1), (4096, 256, 1, 0),
                                       (4096, 257, 1, 0), (4097, 4, 1, 0), (100, 1000, 2, 1)])
 def test_permute_few_slots(moe, T, E, k, Es):
     test_permute_maps_rows_and_streams(moe, T, 64, E, k, Es, "skewed")
+
+
+# the counting sort in two launches, where the scatter does not rank the slots itself (more than 128 experts, 8 slots per token or
+# N K' = 16384): a slot, one sub-group of 64 and its neighbours, tokens whose slots cross sub-groups and blocks of 1024 slots, its limits
+@pytest.mark.parametrize("T,E,k,Es", [(1, 129, 1, 0), (64, 129, 1, 0), (65, 130, 1, 0), (7, 20, 8, 1), (1023, 129, 1, 0), (1025, 129, 1, 0),
+                                      (114, 9, 9, 0), (1024, 200, 2, 1), (455, 11, 9, 0), (512, 12, 8, 0)])
+def test_permute_in_two_launches(moe, T, E, k, Es):
+    moe.profile_reset()
+    moe.profile_enable(True)
+    try:
+        test_permute_maps_rows_and_streams(moe, T, 64, E, k, Es, "skewed")
+        labels = {label for label, _ in moe.profile_records()}
+    finally:
+        moe.profile_enable(False)
+        moe.profile_reset()
+    assert labels >= {"perm_rank_scan", "perm_scatter_gather"} and not labels & {"perm_rank", "perm_sort_scatter_gather"}
 
 
 # on which side of the one-launch sort's rule a size lies: up to 3072 slots (4096 with at most 12 experts) and 64 x 256 table entries
