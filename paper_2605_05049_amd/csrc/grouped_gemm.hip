@@ -1086,8 +1086,6 @@ struct RowGemms {
   long long few_row_tiles() const { return D.N / kFewRows + (D.N < D.Et ? D.N : D.Et); }   // sum_e ceil(n_e / 64) <= N / 64 + experts with rows
 
   int launch(const char* label, RowTileKind kind, RowTileArgs R) const {
-    R.max_tiles = max_tiles; R.offsets = offsets;
-    R.q_expert_stride = (size_t)D.d * D.f;
     if (few_rows_pays(D, kind)) {
       prepare_few(R);
       if (kind == ROWTILE_DH && self_scheduled()) {
@@ -1103,7 +1101,7 @@ struct RowGemms {
     A.partial = reinterpret_cast<float*>(ws + L.splitk_partial); A.counters = counters;
     A.q_dim = R.q_dim; A.k_dim = R.k_dim;
     A.p0 = R.p0; A.p1 = R.p1; A.p_ld = R.p_ld;
-    A.q0 = R.q0; A.q1 = R.q1; A.q_ld = R.q_ld; A.q_expert_stride = R.q_expert_stride;
+    A.q0 = R.q0; A.q1 = R.q1; A.q_ld = R.q_ld; A.q_expert_stride = (size_t)D.d * D.f;
     A.c0 = R.c0; A.c1 = R.c1; A.c2 = R.c2; A.c_ld = R.c_ld; A.g_in = R.g_in; A.u_in = R.u_in;
     const int tq = kind == ROWTILE_GATE_UP ? TILE / 2 : TILE;
     A.n_q_tiles = (A.q_dim + tq - 1) / tq;

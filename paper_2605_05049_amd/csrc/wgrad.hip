@@ -122,15 +122,16 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
   }
   const int nk = (k_len + WK - 1) / WK;
   // The 32 tiles of a chunk run together, and those that share a panel would ask for the same lines at the same time and all wait for
-  // the same misses.  So each begins at another of the first 4 steps and goes round (along either direction of the chunk neighbours
-  // differ): a line is then waited for by one of them and in the L2 for the others.  us, all from step 0 -> this: 128 experts of 500 rows,
-  // 4096 x 1024, dW_down 818 -> 745 and the pair 1448 -> 1430; 7168 x 2048, 32 of 128, 395 -> 354 and 708 -> 638; 2048 x 1408, 66 of 870,
-  // both 1146 -> 1123; 4096 x 14336, 8 of 1024, dW_down 992 -> 963, the pair 1758 -> 1770.  (Of the first 8 steps: the pair of
-  // 7168 x 2048, 32 of 128 681, of 4096 x 1024 1455.  Further apart, by an eighth of the steps, the panels have left the L2 when the last
-  // tile comes to them: pair of 8 x 1024 rows, 4096 x 14336, 1800 -> 2450.)
+  // the same misses.  So each begins at another step and goes round (of the first 8, 4 of many; along either direction of the chunk
+  // neighbours differ): a line is then waited for by one of them and in the L2 for the others.  us, all from step 0 -> this: 128 experts
+  // of 500 rows, 4096 x 1024, dW_down 818 -> 745, the pair 1448 -> 1455; 7168 x 2048, 32 of 128, 395 -> 356 and 708 -> 681; 2048 x 1408,
+  // 66 of 870, both 1146 -> 1125; 4096 x 14336, 8 of 1024, dW_down 992 -> 968, the pair 1758 -> 1778.  (Of the first 4 whatever the steps:
+  // 3968 x 1536, 31 of 230 both 557 -> 586, 128 of 0 .. 3100 rows dW_down 786 -> 820; of 8 in long contractions too 4096 x 14336 1 %
+  // slower.  Further apart, by an eighth of the steps, the panels have left the L2 when the last tile comes to them: the pair of
+  // 8 x 1024 rows, 4096 x 14336, 1800 -> 2450.)
   // The addresses of the next step's loads are carried along and moved on behind the loads that use them: made anew from the step they
   // cost two 64-bit products between the barrier and the loads, which the whole step waits for (4096 x 14336, 8 of 1024 rows: dW_down
-  // 984 -> 968 us, the pair 1842 -> 1814).
+  // 994 -> 978 us, the pair 1821 -> 1801).
   const int k_end = nk * WK;
   const size_t p_step = (size_t)WK * B.p_ld, q_step = (size_t)WK * B.q_ld;
   int k0 = 0;
@@ -139,7 +140,8 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
   const uint16_t* qb1 = q_base1;
   if (nk >= 4) {
     const int ring_p = in_band % band_p, ring_q = in_band / band_p;
-    const int begin = (B.band == 4 ? 2 * ring_p + ring_q : ring_p + 2 * ring_q) & 3;
+    const int raw = B.band == 4 ? 2 * ring_p + ring_q : ring_p + 2 * ring_q;
+    const int begin = nk > 24 ? raw & 3 : nk >= 8 ? raw & 7 : (raw & 7) * nk / 8;
     k0 = begin * WK;
     pb += begin * p_step;
     qb0 += begin * q_step;
