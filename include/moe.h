@@ -162,8 +162,8 @@ int moe_permute_bwd_add(const moe_shape* shape, const uint16_t* dx_perm, const i
  *   w_gate, w_up [E',d,f] bf16 in;  w_down [E',f,d] bf16 in
  *   y_perm [N,d] bf16 out;  save_g, save_u [N,f] bf16 out (the activations backward needs; together with
  *   x_perm this is the 3*d_ffn + d_model values per row of the paper's activation-memory model).  save_g and
- *   save_u may be NULL together: G and U then live in the workspace only (checkpointed forward, to be followed by
- *   moe_grouped_ffn_bwd_recompute)
+ *   save_u may be NULL together: G and U are then not stored anywhere (checkpointed forward, to be followed by
+ *   moe_grouped_ffn_bwd_recompute, which makes them again)
  * Experts with no rows cost nothing and touch nothing. */
 int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_perm, const int32_t* offsets,
                         const uint16_t* w_gate, const uint16_t* w_up, const uint16_t* w_down,
@@ -185,7 +185,7 @@ int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_perm, const u
 
 /* The same backward without saved activations (the selective activation checkpointing used for the full-model
  * training runs of Section VII-B; in the activation-memory model of Section III-A the layer's share then drops to
- * d_model values per row): G and U are recomputed from x_perm with the forward's own kernel (4*d*f extra FLOP per row, bit-identical
+ * d_model values per row): G and U are recomputed from x_perm by the forward's own tiles and sums (4*d*f extra FLOP per row, bit-identical
  * to what forward produced), then everything is as in moe_grouped_ffn_bwd. */
 int moe_grouped_ffn_bwd_recompute(const moe_shape* shape, const uint16_t* dy_perm, const uint16_t* x_perm,
                                   const int32_t* offsets, const uint16_t* w_gate, const uint16_t* w_up,

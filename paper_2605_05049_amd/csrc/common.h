@@ -57,7 +57,7 @@ struct WsLayout {
   size_t splitk_counters;   // kSplitCounters int32: arrivals per split tile
   size_t splitk_partial;    // kSplitParts fp32 tiles of up to 320 x 256: partial sums of the tiles whose K range is split
   size_t h, dg, du, nf_bytes;
-  size_t g_re, u_re;        // G, U when the caller does not keep them (checkpointed forward, recomputing backward): = dg, du
+  size_t g_re, u_re;        // G, U of a recomputing backward: = dg, du
   size_t router_offsets;    // 64 int32: {0, T}, {0, E} (one-segment "offsets" of the router's GEMMs) and the bounds of the parts of T
   size_t dl_hi, dl_lo;      // [T, Epad] bf16: head and remainder of the fp32 dlogits (Epad = E rounded up to 64)
   size_t w_router_t;        // [d, 128] bf16 at most: W_r transposed and zero-padded (router backward, E <= 128)

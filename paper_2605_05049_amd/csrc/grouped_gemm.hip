@@ -1015,9 +1015,10 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 //   down       2048 x 1408, 4, 256: 17 / 32   32, 8: 41 / 37     7168 x 512, 8, 1024: 173 / 84      4096 x 14336, 1, 8: 71 / 33
 //   dH         2048 x 1408, 4, 256: 22 / 51   32, 8: 35 / 32     7168 x 2048, 8, 8: 37 / 41         7168 x 1024, 8, 512: 105 / 111
 //   dX         2048 x 1408, 4, 256: 24 / 54   32, 8: 65 / 67     7168 x 512, 8, 1024: 248 / 126     4096 x 14336, 1, 8: 97 / 53
-// (The fit is older than the 256-row kernel's present loop.  With that, on 6000 shapes drawn around the limits: 0.86 of its time at
-// the mean, more than 1.05 on 7 %, where the better kernel for each GEMM would give 0.84.  Furthest off is gate | up of 16 .. 96
-// rows per expert: 1.08 of the better one where down is on these tiles too, 1.13 where it is not.  In the first case the other
+// (The fit is older than both kernels: than the 256-row kernel's present loop and its pieces of left-over tiles, and than the small chunks
+// of few_rows.hip and dX beside the weight gradients.  With that loop, before the rest, on 6000 shapes drawn around the limits: 0.86 of
+// its time at the mean, more than 1.05 on 7 %, where the better kernel for each GEMM would give 0.84.  Furthest off was gate | up of
+// 16 .. 96 rows per expert: 1.08 of the better one where down is on these tiles too, 1.13 where it is not.  In the first case the other
 // kernel would need a schedule, 5 us, which takes most of the gain back, if there are at most kFewSelfExperts experts; where the
 // call has one anyway the limits are too high.)
 constexpr int kRowClasses = 5, kStepClasses = 5;
@@ -1315,7 +1316,7 @@ extern "C" int moe_grouped_ffn_bwd_recompute(const moe_shape* shape, const uint1
   uint16_t* const g_re = G.rows_f(L.g_re);
   uint16_t* const u_re = G.rows_f(L.u_re);
   if (D.N > 0) {
-    // G, U = X Wg, X Wu once more (the same kernel as in forward, hence the same bits); the backward makes its own H
+    // G, U = X Wg, X Wu once more (tiles, parts and the order of their sums as in forward, hence the same bits); the backward makes its own H
     G.schedule();
     MOE_TRY(G.gate_up("ffn_bwd_recompute_gate_up", x_perm, w_gate, w_up, g_re, u_re, nullptr));
   }

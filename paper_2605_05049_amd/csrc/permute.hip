@@ -147,13 +147,14 @@ __global__ __launch_bounds__(1024) void perm_scan_kernel(int32_t* __restrict__ b
   }
 }
 
-// 1 + 2 in one launch for few slots that the scatter does not rank itself (below): one block of 16 wavefronts ranks all of them (sub-groups of 64 slots as above, the
-// expert's counts of all sub-groups chained in LDS).  The base of a slot's rank is then its expert's offset whatever its
-// block of 1024, and that is what block_base holds for each of them.  Two launches of 3 .. 6 us each are latency only, and
-// grow little with the slots, where the one block's time does; few experts make the general path's scatter slow as well.  Maps
-// of N slots and E' experts, us, three launches / two: 512, 8: 10.3 / 5.3   2048, 64: 9.3 / 7.8   3072, 24: 9.9 / 9.3
-// 3072, 128: 9.8 / 9.8   3072, 256: 10.4 / 10.2   3500, 64: 9.7 / 10.2   4096, 2: 18.8 / 10.1   4096, 12: 10.9 / 10.7
-// 4096, 16: 10.4 / 10.7   4096, 256: 10.6 / 11.9.
+// 1 + 2 in one launch for few slots that the scatter does not rank itself (more than 128 experts or 8 slots per token, or too many
+// slots for it: below): one block of 16 wavefronts ranks all of them (sub-groups of 64 slots as above, the expert's counts of all
+// sub-groups chained in LDS).  The base of a slot's rank is then its expert's offset whatever its block of 1024, and that is what
+// block_base holds for each of them.  Two launches of 3 .. 6 us each are latency only, and grow little with the slots, where the one
+// block's time does; few experts make the general path's scatter slow as well.  Maps of N slots, K' per token, E' experts, us, three
+// launches / two: 512, 1, 200: 9.1 / 5.6   1024, 1, 1000: 12.4 / 7.3   2048, 1, 129: 9.8 / 8.1   3072, 1, 129: 10.2 / 10.0
+// 3072, 1, 341: 11.2 / 10.5   2043, 9, 130: 11.0 / 9.2   3069, 9, 24: 10.9 / 10.2   4096, 8, 8: 11.3 / 10.4   4096, 8, 12: 10.9 / 10.7
+// and beyond the limits 4096, 8, 16: 10.4 / 10.6   3496, 8, 64: 9.9 / 10.3   4000, 1, 129: 10.4 / 11.7   4096, 1, 256: 10.7 / 11.9.
 constexpr int kSmallPermSlots = 4096;                              // at most (what the kernel's wavefronts hold in registers)
 constexpr int kSmallPermSlotsMany = 3072, kSmallPermExperts = 12;  // ... with more experts than this
 constexpr int kSmallPermTable = 16384;                             // entries of the table at most (32 KB)
@@ -261,10 +262,10 @@ template <bool NT> __device__ __forceinline__ void st_row(u32x4* p, u32x4 v) {
 // keys, which ballots count 64 at a time for all K' slots of a token: one round trip to memory, and neither LDS nor a barrier.  One block
 // more adds up the experts' counts.  A wavefront's time grows with N K' and that of all of them with their number times N, hence the two
 // limits.  Graph of calls, us, N slots, K' per token, E' experts, d (before / ranked here):
-//   128, 8, 66, 2048: 7.0 / 4.8     512, 2, 8, 512: 5.6 / 3.1       1024, 2, 64, 2048: 7.1 / 4.3     1536, 1, 64, 4096: 9.2 / 8.0
-//   2048, 8, 128, 4096: 12.2 / 11.5     2896, 2, 100, 1024: 10.6 / 8.5     4012, 4, 14, 1088: 12.4 / 11.4    4096, 4, 8, 512: 10.9 / 9.0
-// and beyond them 2880, 8, 64, 7168: 18.3 / 19.3   3500, 5, 100, 2048: 13.2 / 13.2    4096, 8, 66, 512: 11.4 / 14.4 (N K')
-//   2048, 1, 64, 4096: 11.0 / 11.2 (2048 tokens of 4 wavefronts).
+//   128, 8, 66, 2048: 7.1 / 3.8     512, 2, 8, 512: 5.8 / 3.2       1024, 2, 64, 2048: 7.2 / 4.5     1536, 1, 64, 4096: 9.5 / 8.3
+//   2048, 8, 128, 4096: 12.5 / 10.8     2896, 2, 100, 1024: 10.8 / 8.9     4012, 4, 14, 1088: 12.6 / 11.8    4096, 4, 8, 512: 11.2 / 9.1
+// and beyond them 2880, 8, 64, 7168: 18.6 / 18.3   3500, 5, 100, 2048: 13.2 / 13.7    4096, 8, 66, 512: 11.7 / 13.2 (N K')
+//   2048, 1, 64, 4096: 11.3 / 11.8 (2048 tokens of 4 wavefronts)   4096, 1, 64, 512: 10.3 / 11.6 (4096 tokens).
 constexpr int kRankedSlots = 4096, kRankedExperts = 128, kRankedSlotsPerToken = 8;   // at most
 constexpr int kRankedOwnKeys = 16384;          // N K' at most
 constexpr int kRankedSlotsAlways = 1536;

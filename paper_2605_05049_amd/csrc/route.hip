@@ -1,8 +1,9 @@
 // Top-k softmax gating and its derivative (Section II-A: learned gating function; Section III-A: E, E_s, k).
 //
 // One group of W lanes (W = 8..64, a power of two) owns one token; lane g holds logits g, g+W, g+2W, ...
-// Max, sum-of-exp and each of the k arg-max rounds are butterfly reductions inside the group, so a 64-wide
-// wavefront serves 64/W tokens at once when E is small.  HBM traffic is T*E*4 bytes in, T*K'*8 out: trivial.
+// Max, sum-of-exp and each of the k arg-max rounds are butterfly reductions inside the group (route.h; where a whole wavefront
+// serves a token of 33 .. 256 experts the maxima are lane moves and the arg-max a ballot), so a 64-wide wavefront serves 64/W
+// tokens at once when E is small.  HBM traffic is T*E*4 bytes in, T*K'*8 out: trivial.
 #include "route.h"
 
 namespace moe {

@@ -26,8 +26,9 @@ constexpr int kRouterWaves = 8;          // parts of K per block
 constexpr int kRouterExpertTile = 128;   // experts per block at most (grid.y walks the tiles)
 
 // ROUTE: and the gating of the block's 16 tokens, whose logits (up to 32 of each) it holds when the partial sums have been added: what
-// a launch of its own would read back (step of 256 tokens, 8 experts, as a graph: 79.5 -> 75.9 us).  More experts are spread over blocks
-// or take more lanes than the block has for its tokens, more tokens fill the chip anyway.
+// a launch of its own would read back (step of 256 tokens, 8 experts, as a graph: 79.5 -> 75.9 us).  That is up to 16 experts below 8192
+// tokens, up to 32 from 4081 tokens on (with fewer, 17 .. 32 experts are spread over two blocks); more experts are spread over blocks or
+// take more lanes than the block has for its tokens, more tokens fill the chip anyway.
 struct RouterGateArgs {
   int32_t* topk_idx;
   float* topk_w;

@@ -490,8 +490,9 @@ def test_weight_gradient_edges(moe, d, f):
 
 @pytest.mark.parametrize("d,f", [(320, 576), (1152, 192)])
 def test_weight_gradient_begins(moe, d, f):
-    """The tiles of a chunk begin at different steps of the contraction and go round: row counts on either side of the step counts
-    where the rule changes (4, 8, 24 steps of 32), whole and ragged, so that the short last step comes first, last and in between."""
+    """The tiles of a chunk begin at different steps of the contraction and go round, with the addresses of the next step's loads
+    carried along: row counts on either side of the step counts where the rule changes (4, 8, 24 steps of 32), whole and ragged, so
+    that the short last step comes first, last and in between."""
     test_grouped_ffn_every_tile_height(moe, d, f, [96, 97, 128, 161, 0, 224, 225, 256, 257, 300, 768, 769, 801])
 
 
