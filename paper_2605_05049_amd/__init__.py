@@ -5,7 +5,7 @@ entry point of the same name declared in include/moe.h.  There is no CPU or eage
 library is missing, calls raise.
 """
 from .binding import (  # noqa: F401
-    MoeError, Shape, abi_version, load_library, library_path, status_str, workspace_bytes, grouped_ffn_small_tiles,
+    MoeError, Shape, abi_version, load_library, library_path, status_str, workspace_bytes, grouped_ffn_small_tiles, grouped_ffn_mid_tiles,
     moe_route_topk, moe_route_topk_bwd, moe_permute, moe_permute_noalloc, moe_permute_bwd, moe_permute_bwd_add, moe_router_fwd,
     moe_router_route_fwd,
     moe_router_bwd, moe_grouped_ffn_bwd_recompute, moe_grouped_ffn_fwd,

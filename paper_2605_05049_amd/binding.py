@@ -11,7 +11,7 @@ _LIB_NAME = "libmoe_gfx950.so"
 _lib = None
 
 EXPORTED_SYMBOLS = (
-    "moe_status_str", "moe_workspace_bytes", "moe_grouped_ffn_small_tiles", "moe_abi_version",
+    "moe_status_str", "moe_workspace_bytes", "moe_grouped_ffn_small_tiles", "moe_grouped_ffn_mid_tiles", "moe_abi_version",
     "moe_profile_enable", "moe_profile_count", "moe_profile_get", "moe_profile_reset",
     "moe_route_topk", "moe_route_topk_bwd", "moe_permute", "moe_permute_noalloc", "moe_permute_bwd", "moe_permute_bwd_add",
     "moe_router_fwd", "moe_router_route_fwd", "moe_router_bwd", "moe_grouped_ffn_fwd", "moe_grouped_ffn_bwd", "moe_grouped_ffn_bwd_recompute",
@@ -80,6 +80,8 @@ def load_library():
     lib.moe_workspace_bytes.argtypes = [sp]
     lib.moe_grouped_ffn_small_tiles.restype = c_int
     lib.moe_grouped_ffn_small_tiles.argtypes = [sp]
+    lib.moe_grouped_ffn_mid_tiles.restype = c_int
+    lib.moe_grouped_ffn_mid_tiles.argtypes = [sp]
     lib.moe_abi_version.restype = c_int
     lib.moe_abi_version.argtypes = []
     lib.moe_profile_enable.restype = c_int
@@ -134,10 +136,19 @@ def workspace_bytes(shape) -> int:
     return int(load_library().moe_workspace_bytes(ctypes.byref(Shape.of(shape)._c)))
 
 
-def grouped_ffn_small_tiles(shape) -> tuple:
-    """The GEMMs of the grouped FFN that run on 64-row tiles at this shape, out of "gate_up", "down", "dh", "dx"."""
-    bits = load_library().moe_grouped_ffn_small_tiles(ctypes.byref(Shape.of(shape)._c))
+def _gemm_names(bits: int) -> tuple:
     return tuple(name for i, name in enumerate(("gate_up", "down", "dh", "dx")) if bits >> i & 1)
+
+
+def grouped_ffn_small_tiles(shape) -> tuple:
+    """The small GEMMs of the grouped FFN at this shape, out of "gate_up", "down", "dh", "dx": on 64-row tiles, the others on 256-row tiles, but
+    for those of either kind that `grouped_ffn_mid_tiles` names."""
+    return _gemm_names(load_library().moe_grouped_ffn_small_tiles(ctypes.byref(Shape.of(shape)._c)))
+
+
+def grouped_ffn_mid_tiles(shape) -> tuple:
+    """The GEMMs of the grouped FFN that run on tiles of 128 columns and up to 192 rows at this shape."""
+    return _gemm_names(load_library().moe_grouped_ffn_mid_tiles(ctypes.byref(Shape.of(shape)._c)))
 
 
 def profile_enable(on: bool) -> None:

@@ -91,4 +91,13 @@ extern "C" int moe_grouped_ffn_small_tiles(const moe_shape* shape) {
   return bits;
 }
 
+extern "C" int moe_grouped_ffn_mid_tiles(const moe_shape* shape) {
+  moe::Dims D;
+  if (moe::check_shape(shape, &D) != MOE_OK) return 0;
+  int bits = 0;
+  for (int kind = moe::ROWTILE_GATE_UP; kind <= moe::ROWTILE_DX; kind++)
+    if (moe::mid_rows_for(D, (moe::RowTileKind)kind)) bits |= 1 << kind;
+  return bits;
+}
+
 extern "C" int moe_abi_version(void) { return 1; }

@@ -135,10 +135,11 @@ void launch_router_bwd_small(hipStream_t st, const uint16_t* x, const uint16_t* 
                              int E, int d, int accumulate);
 void launch_router_dw_reduce(hipStream_t st, const float* partial, float* dw, int S, int E, int d, int ldp, int accumulate);
 
-// Row-tile GEMMs of the expert FFNs in small problems (few_rows.hip).
+// Row-tile GEMMs of the expert FFNs in small problems (few_rows.hip) and in those between them and the 256-row tiles (mid_rows.hip).
 constexpr int kFewRows = 64, kFewCols = 64;   // rows and columns of a tile
+constexpr int kMidCols = 128;                 // columns of a tile (of a pair 64 of either) of mid_rows.hip
 enum RowTileKind { ROWTILE_GATE_UP = 0, ROWTILE_DOWN = 1, ROWTILE_DH = 2, ROWTILE_DX = 3 };
-constexpr int kFewSelfExperts = 2 * kWave;    // experts at most for whose tiles the kernel needs no schedule
+constexpr int kFewSelfExperts = 2 * kWave;    // experts at most for whose tiles the kernels need no schedule
 struct RowTileArgs {
   const int32_t* sched;    // [0] = number of row tiles; [64 + u] = expert of tile u; [64 + max_tiles + u] = its first tile.  Null: the
                            // blocks find their tiles from the offsets of Et <= kFewSelfExperts experts
@@ -149,14 +150,19 @@ struct RowTileArgs {
   const int32_t* offsets;  // [E'+1]
   long long rows;          // of all experts together
   int n_q_tiles, chunk_log2;   // filled by the launcher
+  int mid_rows;                // rows of a tile at most, 128 or 192 (mid_rows.hip; 0: few_rows.hip)
   int q_dim, k_dim;        // output columns; contraction length (per pass)
   const uint16_t* p0; const uint16_t* p1; size_t p_ld;   // activations (p1: second pass of dX)
   const uint16_t* q0; const uint16_t* q1; size_t q_ld; size_t q_expert_stride;   // weights (q1: W_up)
   uint16_t* c0; uint16_t* c1; uint16_t* c2; size_t c_ld; // outputs: G, U, H / Y / dG, dU, H / dX
   const uint16_t* g_in; const uint16_t* u_in;            // saved G, U (dH)
 };
+void launch_mid_rows(const char* label, hipStream_t st, int kind, RowTileArgs A, long long row_tiles);   // at most kFewSelfExperts experts
 void launch_few_rows(const char* label, hipStream_t st, int kind, RowTileArgs A, long long row_tiles);
-bool few_rows_pays(const Dims& D, RowTileKind kind);   // (grouped_gemm.hip)
+// Which kernel a GEMM runs on (grouped_gemm.hip): mid_rows.hip if mid_rows_for() (rows of its tiles at most) is not 0, else few_rows.hip if
+// few_rows_pays(), else the 256-row tiles.
+int mid_rows_for(const Dims& D, RowTileKind kind);
+bool few_rows_pays(const Dims& D, RowTileKind kind);
 
 // Weight gradients of the expert FFNs (wgrad.hip): f0[e] (and f1[e]) = p0_e^T q0_e (p0_e^T q1_e) over the rows of expert e.
 struct WgradProblem {
@@ -174,7 +180,7 @@ struct WgradArgs {
   size_t f_expert_stride;
   WgradProblem problem[2];     // dW_gate | dW_up and dW_down
 };
-void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles);   // (dx_tiles > 0: and dX on 64-row tiles)
+void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles);   // (dx_tiles > 0: and dX on 64-row tiles, or those of mid_rows.hip)
 
 // Optional per-launch timing (moe_profile_* in the ABI).  While enabled, every kernel launch of the library is
 // bracketed by two HIP events on the launch stream; disabled (the default) it costs one branch.

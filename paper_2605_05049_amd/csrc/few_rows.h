@@ -79,6 +79,65 @@ __device__ __forceinline__ void unpack8(const uint4& u, float (&x)[8]) {
   x[4] = bf16lo(u.z); x[5] = bf16hi(u.z); x[6] = bf16lo(u.w); x[7] = bf16hi(u.w);
 }
 
+// dH (x) and the saved G, U -> dG, dU, H
+__device__ __forceinline__ void dswiglu8(const float (&x)[8], const float (&g)[8], const float (&u)[8], float (&dg)[8], float (&du)[8], float (&h)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    const float sg = sigmoid(g[j]);
+    const float sl = g[j] * sg;
+    h[j] = sl * u[j];
+    du[j] = x[j] * sl;
+    dg[j] = x[j] * u[j] * (sg * (1.0f + g[j] * (1.0f - sg)));
+  }
+}
+
+// Row tiles of at most kFewSelfExperts experts, found without a schedule: one expert per lane, twice, and where the running sum of
+// their row tiles passes a tile's index is its expert.  (A schedule is a launch of its own, 4 - 5 us, and three loads that wait for each
+// other in every block; these are four that do not, and a sum over the lanes.  Replayed step of 256 tokens, top-2 of 8 experts, 512 x 1024:
+// 94.5 -> 89.7 us)
+struct ExpertTiles {
+  int lo[2], hi[2], nt[2], incl[2];   // of this lane's two experts: rows, tiles, and the tiles up to and with them of its 64
+  int half, total;                    // tiles of the first 64 experts, of all
+  template <class F>   // tiles_of(rows) = an expert's tiles
+  __device__ __forceinline__ ExpertTiles(const int32_t* offsets, int Et, int lane, F tiles_of) {
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const int e = j * kWave + lane;
+      lo[j] = offsets[min(e, Et)];
+      hi[j] = offsets[min(e + 1, Et)];
+    }
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      nt[j] = tiles_of(hi[j] - lo[j]);
+      incl[j] = wave_prefix_sum(nt[j]);
+    }
+    half = __builtin_amdgcn_readlane(incl[0], kWave - 1);
+    total = half + __builtin_amdgcn_readlane(incl[1], kWave - 1);
+  }
+  // the expert of tile u < total, the index of its first tile, its rows
+  __device__ __forceinline__ void find(int u, int& expert, int& first, int& e_lo, int& e_hi) const {
+    const bool upper = u >= half;
+    const int l = __builtin_ctzll(__ballot((upper ? half + incl[1] : incl[0]) > u));
+    expert = (upper ? kWave : 0) + l;
+    first = upper ? half + __builtin_amdgcn_readlane(incl[1] - nt[1], l) : __builtin_amdgcn_readlane(incl[0] - nt[0], l);
+    e_lo = __builtin_amdgcn_readlane(upper ? lo[1] : lo[0], l);
+    e_hi = __builtin_amdgcn_readlane(upper ? hi[1] : hi[0], l);
+  }
+};
+// What the weight gradients read of a schedule, where there is none: the experts by descending row count (ties: lower id first), a zero page.
+__device__ __forceinline__ void write_expert_order(const RowTileArgs& A, char* lds, int tid) {
+  int* const rows_of = reinterpret_cast<int*>(lds);
+  const int n = tid < A.Et ? A.offsets[tid + 1] - A.offsets[tid] : 0;
+  if (tid < kFewSelfExperts) rows_of[tid] = n;
+  if (tid < 64) A.zero_page[tid] = 0u;
+  __syncthreads();
+  if (tid < A.Et) {
+    int rank = 0;
+    for (int o = 0; o < A.Et; o++) rank += (rows_of[o] > n) || (rows_of[o] == n && o < tid);
+    A.order[rank] = tid;
+  }
+}
+
 }  // namespace
 
 // Of at most `row_tiles` x `n_q_tiles` tiles: log2 of the consecutive ones that an XCD takes at a time.  With 32 of them a few hundred tiles
@@ -128,38 +187,12 @@ __device__ __forceinline__ void few_rows_block(const RowTileArgs& A, char* lds, 
     // own, 4 - 5 us, and three loads that wait for each other in every block; these are four that do not, and a sum over the
     // lanes.  Replayed step of 256 tokens, top-2 of 8 experts, 512 x 1024: 94.5 -> 89.7 us)
     if (KIND == ROWTILE_DH && A.order && block == blocks - 1) {   // one block more: what the weight gradients read of a schedule
-      int* const rows_of = reinterpret_cast<int*>(lds);
-      const int n = tid < A.Et ? A.offsets[tid + 1] - A.offsets[tid] : 0;
-      if (tid < kFewSelfExperts) rows_of[tid] = n;
-      if (tid < 64) A.zero_page[tid] = 0u;
-      __syncthreads();
-      if (tid < A.Et) {
-        int rank = 0;   // (ties: lower id first)
-        for (int o = 0; o < A.Et; o++) rank += (rows_of[o] > n) || (rows_of[o] == n && o < tid);
-        A.order[rank] = tid;
-      }
+      write_expert_order(A, lds, tid);
       return;
     }
-    int lo[2], hi[2], nt[2], incl[2];
-#pragma unroll
-    for (int j = 0; j < 2; j++) {
-      const int e = j * kWave + lane;
-      lo[j] = A.offsets[min(e, A.Et)];
-      hi[j] = A.offsets[min(e + 1, A.Et)];
-    }
-#pragma unroll
-    for (int j = 0; j < 2; j++) {
-      nt[j] = (hi[j] - lo[j] + FP - 1) / FP;
-      incl[j] = wave_prefix_sum(nt[j]);
-    }
-    const int half = __builtin_amdgcn_readlane(incl[0], kWave - 1);   // row tiles of the first 64 experts
-    if (ut >= half + __builtin_amdgcn_readlane(incl[1], kWave - 1)) return;
-    const bool upper = ut >= half;
-    const int l = __builtin_ctzll(__ballot((upper ? half + incl[1] : incl[0]) > ut));
-    expert = (upper ? kWave : 0) + l;
-    first = upper ? half + __builtin_amdgcn_readlane(incl[1] - nt[1], l) : __builtin_amdgcn_readlane(incl[0] - nt[0], l);
-    e_lo = __builtin_amdgcn_readlane(upper ? lo[1] : lo[0], l);
-    e_hi = __builtin_amdgcn_readlane(upper ? hi[1] : hi[0], l);
+    const ExpertTiles X(A.offsets, A.Et, lane, [](int n) { return (n + FP - 1) / FP; });
+    if (ut >= X.total) return;
+    X.find(ut, expert, first, e_lo, e_hi);
   }
   const int e_tiles = (e_hi - e_lo + FP - 1) / FP;
   const int local = (int)(lid - (long long)first * A.n_q_tiles);
@@ -303,14 +336,7 @@ __device__ __forceinline__ void few_rows_block(const RowTileArgs& A, char* lds, 
           float g[8], u[8], dg[8], du[8], h[8];
           unpack8(gi[i], g);
           unpack8(ui[i], u);
-#pragma unroll
-          for (int j = 0; j < 8; j++) {
-            const float sg = sigmoid(g[j]);
-            const float sl = g[j] * sg;
-            h[j] = sl * u[j];
-            du[j] = x[0][i][j] * sl;
-            dg[j] = x[0][i][j] * u[j] * (sg * (1.0f + g[j] * (1.0f - sg)));
-          }
+          dswiglu8(x[0][i], g, u, dg, du, h);
           *reinterpret_cast<uint4*>(A.c0 + o) = pack8(dg);
           *reinterpret_cast<uint4*>(A.c1 + o) = pack8(du);
           *reinterpret_cast<uint4*>(A.c2 + o) = pack8(h);

@@ -1044,6 +1044,61 @@ bool few_rows_pays(const Dims& D, RowTileKind kind) {
   return tiles <= (kind == ROWTILE_GATE_UP ? kFewTilesGateUp[rc] : kFewTiles[kind - ROWTILE_DOWN][rc][sc]);
 }
 
+// Which GEMMs run on the tiles of 128 columns and up to 128 or 192 rows of mid_rows.hip: rows of a tile at most, 0 for the other two
+// kernels.  Against few_rows.hip a tile moves half the operand bytes per multiply, so it wins as soon as there are tiles for a good half
+// of the CUs.  Against the 256-row tiles it moves 1.7 to 2 times the bytes, but two tiles share a CU, one in its epilogue or start while the other multiplies,
+// and a problem has 3 .. 4 times as many: it wins for short contractions, where epilogues weigh most (dH reads and writes five rows of f for one of d: below 24 steps
+// at any size), for up to 1 .. 2 tiles per CU, and where experts have so few rows that either streams the weights.  The limits are where it
+// crosses the better of the two on 7000 random shapes (64 .. 7168 x 64 .. 14336, 2 .. 128 experts, 64 .. 65536 rows; even, mild and Zipf
+// counts, shared experts), a loss counted one and a half times; time of it / of the other where it is taken, by kind: 0.89, 0.88, 0.88, 0.92 at the mean
+// (dX with the weight gradients, whose launch it shares), more than 1.05 on 6, 6, 4 and 2 % of the shapes.  Us, even counts, here / before (d x f, E, rows per expert):
+//   down  1088 x 1984, 14, 287: 30 / 45      640 x 2816, 7, 800: 33 / 43       6784 x 1024, 24, 176: 83 / 91
+//   dH    1088 x 1984, 14, 287: 37 / 44      832 x 2624, 24, 1968: 378 / 403   2048 x 1408, 66, 186: 130 / 147
+//   dX    1408 x 4736, 5, 310: 92 / 108      512 x 3200, 12, 934: 99 / 122 (both in launches of their own)
+// and left out: gate | up 2048 x 1408, 66, 186: 196 / 184   down 832 x 2624, 24, 1968: 248 / 200   dX 2048 x 1408, 66, 993: 739 / 614.
+constexpr int kMidRowClasses = 4, kMidStepClasses = 6, kMidAny = 1 << 30;
+constexpr int kMidRowsBelow[kMidRowClasses - 1] = {16, 96, 320};                // rows per expert on average
+constexpr int kMidStepsBelow[kMidStepClasses - 1] = {12, 24, 40, 64, 128};      // k-steps of 64, both passes of dX counted
+constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                  // tiles of 128 rows: fewer than this
+    // gate | up
+    {{kMidAny, kMidAny, kMidAny, 3072, 0, 0}, {kMidAny, 4096, 1408, 1024, 1280, 1280}, {kMidAny, 2048, 1280, 512, 512, 512}, {8192, 768, 768, 768, 640, 640}},
+    // down
+    {{kMidAny, kMidAny, 3072, 512, 256, 256}, {kMidAny, 4096, 2048, 1280, 512, 384}, {kMidAny, 2048, 1280, 768, 512, 320}, {kMidAny, 2048, 768, 640, 768, 640}},
+    // dH
+    {{kMidAny, kMidAny, 512, 512, 256, 256}, {kMidAny, kMidAny, 2560, 1024, 640, 640}, {kMidAny, kMidAny, 4096, 1280, 768, 768}, {kMidAny, kMidAny, 4096, 768, 640, 640}},
+    // dX
+    {{kMidAny, kMidAny, kMidAny, 3072, 1536, 0}, {kMidAny, kMidAny, 3072, 3072, 2048, 768}, {kMidAny, kMidAny, kMidAny, 3072, 3072, 1536}, {4096, 4096, 3072, 1280, 768, 768}}};
+int mid_rows_for(const Dims& D, RowTileKind kind) {
+  if (D.Et > kFewSelfExperts || D.N == 0) return 0;   // (its blocks find their tiles from the offsets alone)
+  const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;
+  const long long active = D.N < D.Et ? D.N : D.Et, cols = ((to_f ? D.f : D.d) / 64 + (kind != ROWTILE_GATE_UP)) / (kind == ROWTILE_GATE_UP ? 1 : 2);
+  auto tiles_of = [&](int rows) { return std::max(D.N / rows + active / 2, active) * cols; };
+  const long long tiles = tiles_of(128), tiles192 = tiles_of(192);
+  const int steps = (to_f ? D.d : D.f) / 64 * (kind == ROWTILE_DX ? 2 : 1);
+  int rc = 0, sc = 0;
+  while (rc < kMidRowClasses - 1 && D.N >= (long long)kMidRowsBelow[rc] * D.Et) rc++;
+  while (sc < kMidStepClasses - 1 && steps >= kMidStepsBelow[sc]) sc++;
+  int least;
+  switch (kind) {
+    case ROWTILE_GATE_UP: least = steps < 12 ? 32 : 144; break;
+    case ROWTILE_DOWN: least = 144; break;
+    case ROWTILE_DH: least = rc == 0 ? (steps < 12 ? 208 : 256) : rc == 1 ? 208 : 160; break;   // (few_rows.hip requests G and U before the sums)
+    default: least = steps < 128 ? 80 : 128; break;                                             // (beside the weight gradients it need not fill the chip)
+  }
+  if (tiles < least || tiles >= kMidMost[kind][rc][sc]) return 0;
+  // Tiles of 192 rows move fewer operand bytes (12.7 KB per million multiply-adds for 15.3) and leave fewer remainders, but make fewer tiles:
+  // taken where they save about a round of the 512 that the chip runs at a time, or all run at once with room.  (186 rows per expert, 66 of
+  // 2048 x 1408, four GEMMs: 1244 us on 128, 1169 on 192; 310 rows, 5 of 1408 x 4736, dX 92 and 108.)
+  if (D.N < 128ll * D.Et) return 128;
+  if (kind == ROWTILE_DX) return tiles >= 192 ? 192 : 128;
+  const long long rounds = (tiles + 511) / 512, rounds192 = (tiles192 + 511) / 512;
+  return 13 * rounds192 <= 10 * rounds || (tiles > 256 && tiles <= 384) ? 192 : 128;
+}
+enum RowTiles { ROWTILES_TALL, ROWTILES_FEW, ROWTILES_MID };
+static RowTiles row_tiles_for(const Dims& D, RowTileKind kind) {
+  return mid_rows_for(D, kind) ? ROWTILES_MID : few_rows_pays(D, kind) ? ROWTILES_FEW : ROWTILES_TALL;
+}
+
 // The row-tile GEMMs of one call of the expert FFN: of the forward (gate | up and down), of the backward (dH and dX) or the
 // recomputed gate | up alone.
 struct RowGemms {
@@ -1061,14 +1116,15 @@ struct RowGemms {
 
   RowGemms(const Dims& D_, const WsLayout& L_, void* ws_, hipStream_t st_, const int32_t* offsets_, RowTileKind first, RowTileKind second)
       : D(D_), L(L_), ws(static_cast<char*>(ws_)), st(st_), offsets(offsets_), max_tiles((int)sched_max_tiles(D_)),
-        any_few(few_rows_pays(D_, first) || few_rows_pays(D_, second)), any_tall(!few_rows_pays(D_, first) || !few_rows_pays(D_, second)),
+        any_few(row_tiles_for(D_, first) == ROWTILES_FEW || row_tiles_for(D_, second) == ROWTILES_FEW),
+        any_tall(row_tiles_for(D_, first) == ROWTILES_TALL || row_tiles_for(D_, second) == ROWTILES_TALL),
         sched_tall(reinterpret_cast<int32_t*>(ws + L_.sched)), sched_few(reinterpret_cast<int32_t*>(ws + L_.sched_few)),
         zero_page(reinterpret_cast<uint32_t*>(ws + L_.zero_page)),
         counters(reinterpret_cast<int32_t*>(ws + L_.splitk_counters)) {}
 
   uint16_t* rows_f(size_t region) const { return reinterpret_cast<uint16_t*>(ws + region); }   // a bf16 [N, f] region of the workspace
 
-  // A call whose GEMMs all run on the 64-row tiles needs no schedule, up to kFewSelfExperts experts.
+  // A call without a GEMM on the 256-row tiles needs no schedule, up to kFewSelfExperts experts.
   bool self_scheduled() const { return !any_tall && D.Et <= kFewSelfExperts && D.N > 0; }
   void schedule() const {
     if (self_scheduled()) return;
@@ -1084,15 +1140,28 @@ struct RowGemms {
     R.sched = self_scheduled() ? nullptr : sched_few;
     R.Et = D.Et; R.rows = D.N;
   }
+  // ... and on those of mid_rows.hip; their number at most
+  long long prepare_mid(RowTileArgs& R, RowTileKind kind) const {
+    R.offsets = offsets; R.q_expert_stride = (size_t)D.d * D.f;
+    R.Et = D.Et; R.rows = D.N;
+    R.mid_rows = mid_rows_for(D, kind);
+    return D.N / R.mid_rows + (D.N < D.Et ? D.N : D.Et);
+  }
   long long few_row_tiles() const { return D.N / kFewRows + (D.N < D.Et ? D.N : D.Et); }   // sum_e ceil(n_e / 64) <= N / 64 + experts with rows
 
   int launch(const char* label, RowTileKind kind, RowTileArgs R) const {
-    if (few_rows_pays(D, kind)) {
+    const RowTiles on = row_tiles_for(D, kind);
+    if (kind == ROWTILE_DH && self_scheduled()) {
+      R.order = sched_few + 64 + 2 * max_tiles;
+      R.zero_page = zero_page;
+    }
+    if (on == ROWTILES_MID) {
+      const long long row_tiles = prepare_mid(R, kind);
+      launch_mid_rows(label, st, kind, R, row_tiles);
+      return MOE_OK;
+    }
+    if (on == ROWTILES_FEW) {
       prepare_few(R);
-      if (kind == ROWTILE_DH && self_scheduled()) {
-        R.order = sched_few + 64 + 2 * max_tiles;
-        R.zero_page = zero_page;
-      }
       launch_few_rows(label, st, kind, R, few_row_tiles());
       return MOE_OK;
     }
@@ -1217,12 +1286,19 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   W.problem[1].p0 = h; W.problem[1].p_ld = D.f; W.problem[1].p_dim = D.f;
   W.problem[1].q0 = dy_perm; W.problem[1].q_ld = D.d; W.problem[1].q_dim = D.d;
   W.problem[1].f0 = dw_down; W.problem[1].c_ld = D.d;
-  // dX needs dH's results as the weight gradients do, and on the 64-row tiles it may share their launch
+  // dX needs dH's results as the weight gradients do, and on the smaller tiles it may share their launch
   RowTileArgs X = G.dx_args(dg, du, w_gate, w_up, dx_perm);
-  const bool dx_few = D.N > 0 && few_rows_pays(D, ROWTILE_DX);
-  if (dx_few) G.prepare_few(X);
-  else if (D.N > 0) MOE_TRY(G.launch("ffn_bwd_dx", ROWTILE_DX, X));
-  launch_wgrad(st, W, X, dx_few ? G.few_row_tiles() : 0);
+  const RowTiles dx_on = D.N > 0 ? row_tiles_for(D, ROWTILE_DX) : ROWTILES_TALL;
+  long long dx_tiles = 0;
+  if (dx_on == ROWTILES_FEW) {
+    G.prepare_few(X);
+    dx_tiles = G.few_row_tiles();
+  } else if (dx_on == ROWTILES_MID) {
+    dx_tiles = G.prepare_mid(X, ROWTILE_DX);
+  } else if (D.N > 0) {
+    MOE_TRY(G.launch("ffn_bwd_dx", ROWTILE_DX, X));
+  }
+  launch_wgrad(st, W, X, dx_tiles);
   return launch_status();
 }
 

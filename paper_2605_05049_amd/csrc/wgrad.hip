@@ -17,7 +17,7 @@
 // stage, a ring of three stages (72 KB, two blocks fit the CU's 160 KB), two steps ahead.  P is the MFMA's A operand, so
 // that 16 lanes of an accumulator register hold 16 consecutive columns of one row of dW; two registers exchange lane rows, and a
 // store instruction writes whole 128-byte lines from registers, without a bounce through LDS and without a barrier.
-#include "few_rows.h"
+#include "mid_rows.h"
 
 #include <limits.h>
 
@@ -40,6 +40,7 @@ constexpr int W_XCDS = 8;
 constexpr int W_MERGE_CHUNKS = 1024;         // both problems in one launch up to here
 constexpr int W_DX_CHUNKS = 256;             // ... and dX on 64-row tiles with them up to here, ...
 constexpr int W_DX_SHORT_STEPS = 64, W_DX_STEPS = 240, W_DX_STEPS_PER_CHUNK = 8;   // ... if its contraction is not too long (dx_joins)
+constexpr long long W_DX_MID_ROWS = 4096;    // and dX on the tiles of mid_rows.hip below so many rows per expert
 constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
 
 // Position of 8 r-values (chunk c of 16) inside k-row k's 256 bytes: the four k-rows that a transposing read takes together
@@ -301,6 +302,13 @@ __global__ __launch_bounds__(WTHREADS, 2) void dx_wgrad_kernel(const DxWgradArgs
   else wgrad_block(A.dw, lds, blockIdx.x - A.dx_blocks);
 }
 
+__global__ __launch_bounds__(WTHREADS, 2) void mid_dx_wgrad_kernel(const DxWgradArgs A) {
+  __shared__ __attribute__((aligned(1024))) char lds[M_LDS];
+  static_assert(WTHREADS == 4 * kWave && 3 * W_STAGE <= M_LDS, "the ring fits");
+  if (blockIdx.x < A.dx_blocks) mid_rows_block<ROWTILE_DX>(A.dx, lds, blockIdx.x, A.dx_blocks);
+  else wgrad_block(A.dw, lds, blockIdx.x - A.dx_blocks);
+}
+
 // Fills in how a problem is cut into tiles and chunks.
 static void plan_wgrad(WgradProblem& B, int Et, long long rows) {
   B.n_p_tiles = (B.p_dim + WP - 1) / WP;
@@ -331,15 +339,27 @@ static bool dx_joins(const RowTileArgs& dx, int chunks) {
   return chunks <= W_DX_CHUNKS && (steps <= W_DX_SHORT_STEPS || (steps <= W_DX_STEPS && steps <= W_DX_STEPS_PER_CHUNK * chunks));
 }
 
-// Launches the weight gradients of the pair and of the single tensor, and dX where it runs on 64-row tiles (at most dx_tiles row tiles;
-// 0: it does not).
+// Launches the weight gradients of the pair and of the single tensor, and dX where it does not run on 256-row tiles (at most dx_tiles row
+// tiles; 0: it does).
 void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles) {
   if (A.Et <= 0) return;
   plan_wgrad(A.problem[0], A.Et, A.rows);
   plan_wgrad(A.problem[1], A.Et, A.rows);
   auto grid = [](long long chunks) { return dim3((unsigned)((chunks + W_XCDS - 1) / W_XCDS * W_XCDS * W_CHUNK)); };
   const dim3 block(WTHREADS);
-  if (dx_tiles > 0) {
+  if (dx_tiles > 0 && dx.mid_rows) {
+    // (dX first: its tiles run on either side of a CU's weight gradients, whose stores leave its matrix pipes idle.  One launch / two, 4000
+    // random shapes with dX on these tiles: 0.7 - 0.92 of the time below 512 rows per expert, 0.8 - 0.93 up to 2048, 0.87 - 0.96 up to 4096; beyond
+    // 0.94 - 1.16, where the weight gradients are few and long and begin late.)
+    if (A.rows < W_DX_MID_ROWS * A.Et) {
+      DxWgradArgs X = {};
+      X.dx = dx; X.dw = A;
+      X.dx_blocks = mid_rows_plan(X.dx, ROWTILE_DX, dx_tiles);
+      MOE_LAUNCH("ffn_bwd_dx_dw", st, mid_dx_wgrad_kernel, dim3(X.dx_blocks + grid(A.problem[0].chunks + A.problem[1].chunks).x), block, 0, st, X);
+      return;
+    }
+    launch_mid_rows("ffn_bwd_dx", st, ROWTILE_DX, dx, dx_tiles);
+  } else if (dx_tiles > 0) {
     // (2048 x 1408, 66 experts, 528 chunks, forward + backward: 837 us with dX in a launch of its own, 842 with one for all.)
     if (dx_joins(dx, A.problem[0].chunks + A.problem[1].chunks)) {
       DxWgradArgs X = {};

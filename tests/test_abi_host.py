@@ -152,5 +152,23 @@ def test_which_gemms_run_on_small_tiles(lib, T, d, f, E, k, expected):
     assert moe.grouped_ffn_small_tiles(moe.Shape(T, d, f, E, k)) == expected
 
 
+# (T, d, f, E, k) -> the GEMMs on the tiles of 128 columns: both sides of the least and the most tiles, by rows per expert and k-steps
+@pytest.mark.parametrize("T,d,f,E,k,expected", [
+    (256, 512, 1024, 8, 2, ("gate_up",)),                  # 128 tiles of gate | up, 64 of the others
+    (1003, 1088, 1984, 14, 4, ("gate_up", "down", "dh", "dx")),
+    (4096, 4096, 14336, 8, 2, ()),                         # 8000 tiles, contractions of 64 steps and more
+    (8192, 2048, 1408, 66, 8, ()),                         # 32 steps of dH, 6000 tiles
+    (2048, 2048, 1408, 66, 8, ("dh", "dx")),               # ... and 1400
+    (7871, 832, 2624, 24, 6, ("dh",)),                     # 13 steps of dH: any number of tiles
+    (16, 2048, 1408, 66, 8, ("gate_up", "down", "dx")),    # 726 tiles of dH, 32 steps, two rows per expert
+    (512, 4096, 14336, 8, 1, ("down", "dx")),              # 1792 tiles of gate | up, 256 of down and dX
+    (300, 512, 1024, 129, 1, ()),                          # more experts than a block finds its tile among
+    (0, 512, 1024, 8, 2, ()),
+])
+def test_which_gemms_run_on_mid_tiles(lib, T, d, f, E, k, expected):
+    assert moe.grouped_ffn_mid_tiles(moe.Shape(T, d, f, E, k)) == expected
+
+
 def test_small_tiles_of_an_invalid_shape(lib):
+    assert moe.grouped_ffn_mid_tiles(moe.Shape(8, 500, 64, 4, 1)) == ()
     assert moe.grouped_ffn_small_tiles(moe.Shape(8, 500, 64, 4, 1)) == ()

@@ -875,3 +875,64 @@ def test_grouped_ffn_with_no_rows(moe):
     assert all(bool((t == 3.0).all()) for t in dws)
     moe.moe_grouped_ffn_bwd(s, z, z, off, wts[0], wts[1], wts[2], z, z, z, dws[0], dws[1], dws[2], 0, ws)
     assert all(not bool(t.any()) for t in dws)
+
+
+MID_COUNTS = [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 0, 256, 257, 385, 500]
+
+
+# Tiles of 128 columns and up to 128 or 192 rows: rows on both sides of every class of 32 and of a second and third tile, a last column tile of
+# 64 (d = 1088), contractions of 1, 2, 3 and more k-steps, experts of more than 12 row tiles (walked in bands), 128 experts with
+# empty first and last ones (found from the offsets; the order of the experts is written by dH), dX in a launch of its own (4096 rows per expert)
+@pytest.mark.parametrize("d,f,counts,mid", [
+    (1088, 1600, MID_COUNTS, ALL_GEMMS),                          # up to 128 rows
+    (1088, 1152, MID_COUNTS, ALL_GEMMS),                          # up to 192
+    (64, 1088, 2 * MID_COUNTS, ("gate_up", "dh")),                # one k-step of gate | up and dH
+    (1088, 64, 2 * MID_COUNTS, ("down", "dx")),                   # one of down, two of dX
+    (192, 704, [2600, 0, 77, 1700], ("gate_up", "dh")),           # 3 k-steps; 21 row tiles of one expert
+    (576, 192, [0, 0, 130] + 61 * [33, 2] + [1, 64, 0], ALL_GEMMS),
+    (320, 320, [8200, 0], ALL_GEMMS),
+])
+def test_mid_row_tiles(moe, d, f, counts, mid):
+    s = moe.Shape(sum(counts), d, f, len(counts), 1)
+    assert moe.grouped_ffn_mid_tiles(s) == mid
+    moe.profile_reset()
+    moe.profile_enable(True)
+    try:
+        test_grouped_ffn_every_tile_height(moe, d, f, counts)
+        labels = [label for label, _ in moe.profile_records()]
+    finally:
+        moe.profile_enable(False)
+        moe.profile_reset()
+    assert ("ffn_schedule" in labels) == (not set(mid) | set(moe.grouped_ffn_small_tiles(s)) >= set(ALL_GEMMS))
+    if "dx" in mid:
+        assert ("ffn_bwd_dx" in labels) == (s.N >= 4096 * len(counts))
+
+
+# The 256-row tiles where the smaller ones do not take over: every height class in all four GEMMs, left-over tiles (gate | up, down, dH, dX) in
+# 2, 2, 2 and 2 pieces, whole and in 3, 5 and 3
+@pytest.mark.parametrize("n_large", [8, 11])
+def test_large_problem_on_256_row_tiles(moe, n_large):
+    """Against fp32 on the device, expert by expert."""
+    d, f, counts = 2560, 1600, CLASS_COUNTS + n_large * [2000]
+    s, x, dy, off, w, ws, y, sg, su = ffn_on_device(moe, d, f, counts)
+    assert moe.grouped_ffn_mid_tiles(s) == () and moe.grouped_ffn_small_tiles(s) == ()
+    dx = torch.full((s.N, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dw = [torch.full(t.shape, float("nan"), device="cuda") for t in w]
+    moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, sg, su, dx, *dw, False, ws)
+    bounds = off.tolist()
+    for e, n in enumerate(counts):
+        r = slice(bounds[e], bounds[e + 1])
+        if n == 0:
+            assert not any(bool(t[e].any()) for t in dw)
+            continue
+        xe, dye, we = x[r].float(), dy[r].float(), [t[e].float() for t in w]
+        # (a result rounded to bf16, of operands of which some were: 2^-9 each, so 2^-8 of the norm bounds them with room)
+        g, u = sg[r].float(), su[r].float()
+        sig = torch.sigmoid(g)
+        dh = dye @ we[2].T
+        h, du, dg = (z.to(torch.bfloat16).float() for z in (g * sig * u, dh * g * sig, dh * u * sig * (1 + g * (1 - sig))))
+        want = (xe @ we[0], xe @ we[1], h @ we[2], dg @ we[0].T + du @ we[1].T, xe.T @ dg, xe.T @ du, h.T @ dye)
+        for got, ref in zip((g, u, y[r].float(), dx[r].float(), dw[0][e], dw[1][e], dw[2][e]), want):
+            assert bool(torch.isfinite(got).all()) and float((got - ref).norm()) <= 2.0 ** -8 * float(ref.norm()), (e, n)
+            rows = (got - ref).norm(dim=1) / ref.norm(dim=1)   # (no row is lost in the norm of the whole)
+            assert float(rows.max()) <= 2.0 ** -6, (e, n, float(rows.max()))
