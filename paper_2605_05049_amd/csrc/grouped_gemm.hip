@@ -1056,18 +1056,22 @@ bool few_rows_pays(const Dims& D, RowTileKind kind) {
 //   dH    1088 x 1984, 14, 287: 37 / 44      832 x 2624, 24, 1968: 378 / 403   2048 x 1408, 66, 186: 130 / 147
 //   dX    1408 x 4736, 5, 310: 92 / 108      512 x 3200, 12, 934: 99 / 122 (both in launches of their own)
 // and left out: gate | up 2048 x 1408, 66, 186: 196 / 184   down 832 x 2624, 24, 1968: 248 / 200   dX 2048 x 1408, 66, 993: 739 / 614.
-constexpr int kMidRowClasses = 4, kMidStepClasses = 6, kMidAny = 1 << 30;
-constexpr int kMidRowsBelow[kMidRowClasses - 1] = {16, 96, 320};                // rows per expert on average
-constexpr int kMidStepsBelow[kMidStepClasses - 1] = {12, 24, 40, 64, 128};      // k-steps of 64, both passes of dX counted
-constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                  // tiles of 128 rows: fewer than this
+constexpr int kMidRowClasses = 4, kMidStepClasses = 7, kMidAny = 1 << 30;
+constexpr int kMidRowsBelow[kMidRowClasses - 1] = {16, 96, 320};                   // rows per expert on average
+constexpr int kMidStepsBelow[kMidStepClasses - 1] = {12, 24, 32, 40, 64, 128};     // k-steps of 64, both passes of dX counted
+constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                     // tiles of 128 rows: fewer than this
     // gate | up
-    {{kMidAny, kMidAny, kMidAny, 3072, 0, 0}, {kMidAny, 4096, 1408, 1024, 1280, 1280}, {kMidAny, 2048, 1280, 512, 512, 512}, {8192, 768, 768, 768, 640, 640}},
+    {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 0, 0}, {kMidAny, 4096, 1408, 1408, 1024, 1280, 1280},
+     {kMidAny, 2048, 1280, 1280, 512, 512, 512}, {4096, 768, 768, 768, 768, 640, 640}},
     // down
-    {{kMidAny, kMidAny, 3072, 512, 256, 256}, {kMidAny, 4096, 2048, 1280, 512, 384}, {kMidAny, 2048, 1280, 768, 512, 320}, {kMidAny, 2048, 768, 640, 768, 640}},
+    {{kMidAny, kMidAny, 3072, 3072, 512, 256, 256}, {kMidAny, 4096, 2048, 2048, 1280, 512, 384},
+     {kMidAny, 2048, 1280, 1280, 768, 512, 320}, {kMidAny, 1536, 768, 768, 640, 768, 640}},
     // dH
-    {{kMidAny, kMidAny, 512, 512, 256, 256}, {kMidAny, kMidAny, 2560, 1024, 640, 640}, {kMidAny, kMidAny, 4096, 1280, 768, 768}, {kMidAny, kMidAny, 4096, 768, 640, 640}},
+    {{kMidAny, kMidAny, 512, 512, 512, 256, 256}, {kMidAny, kMidAny, 2560, 2560, 1024, 640, 640},
+     {kMidAny, kMidAny, 4096, 2048, 1280, 768, 768}, {kMidAny, kMidAny, 3072, 768, 768, 640, 640}},
     // dX
-    {{kMidAny, kMidAny, kMidAny, 3072, 1536, 0}, {kMidAny, kMidAny, 3072, 3072, 2048, 768}, {kMidAny, kMidAny, kMidAny, 3072, 3072, 1536}, {4096, 4096, 3072, 1280, 768, 768}}};
+    {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 1536, 0}, {kMidAny, kMidAny, 3072, 3072, 3072, 2048, 768},
+     {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1536}, {4096, 4096, 3072, 3072, 1280, 768, 768}}};
 int mid_rows_for(const Dims& D, RowTileKind kind) {
   if (D.Et > kFewSelfExperts || D.N == 0) return 0;   // (its blocks find their tiles from the offsets alone)
   const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;
@@ -1086,6 +1090,7 @@ int mid_rows_for(const Dims& D, RowTileKind kind) {
     default: least = steps < 128 ? 80 : 128; break;                                             // (beside the weight gradients it need not fill the chip)
   }
   if (tiles < least || tiles >= kMidMost[kind][rc][sc]) return 0;
+  if (kind == ROWTILE_DOWN && rc == 3 && sc > 0 && tiles >= 768 && tiles < 1024) return 0;   // (1.5 .. 2 rounds of either height: 1.03, on both sides 0.85 and 0.93)
   // Tiles of 192 rows move fewer operand bytes (12.7 KB per million multiply-adds for 15.3) and leave fewer remainders, but make fewer tiles:
   // taken where they save about a round of the 512 that the chip runs at a time, or all run at once with room.  (186 rows per expert, 66 of
   // 2048 x 1408, four GEMMs: 1244 us on 128, 1169 on 192; 310 rows, 5 of 1408 x 4736, dX 92 and 108.)
