@@ -15,6 +15,7 @@ EXPORTED_SYMBOLS = (
     "moe_profile_enable", "moe_profile_count", "moe_profile_get", "moe_profile_reset",
     "moe_route_topk", "moe_route_topk_bwd", "moe_permute", "moe_permute_noalloc", "moe_permute_bwd", "moe_permute_bwd_add",
     "moe_router_fwd", "moe_router_route_fwd", "moe_router_bwd", "moe_grouped_ffn_fwd", "moe_grouped_ffn_bwd", "moe_grouped_ffn_bwd_recompute",
+    "moe_grouped_ffn_router_bwd",
     "moe_unpermute_combine", "moe_unpermute_combine_bwd", "moe_unpermute_combine_route_bwd",
     "moe_load_accumulate", "moe_load_imbalance", "moe_rebalance_experts",
     "moe_halo_pack_remote", "moe_halo_repack", "moe_halo_unpack",
@@ -102,6 +103,7 @@ def load_library():
         "moe_permute_bwd_add": [sp, V, V, V, V, V],
         "moe_router_fwd": [sp, V, V, V, V, c_size_t, V],
         "moe_router_route_fwd": [sp, V, V, V, V, V, V, V, c_size_t, V],
+        "moe_grouped_ffn_router_bwd": [sp] + [V] * 17 + [c_int, V, c_size_t, V],
         "moe_router_bwd": [sp, V, V, V, V, V, c_int, V, c_size_t, V],
         "moe_grouped_ffn_fwd": [sp, V, V, V, V, V, V, V, V, V, c_size_t, V],
         "moe_grouped_ffn_bwd": [sp, V, V, V, V, V, V, V, V, V, V, V, V, c_int, V, c_size_t, V],
@@ -384,6 +386,25 @@ def moe_grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, s
         _ptr(dw_up, torch.float32, nw, "dw_up"), _ptr(dw_down, torch.float32, nw, "dw_down"), int(bool(accumulate)),
         _ptr(ws, None, None, "ws"), ws.numel() * ws.element_size(), _stream(stream))
     _check("moe_grouped_ffn_bwd", rc)
+
+
+def moe_grouped_ffn_router_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, save_g, save_u, dx_perm, dw_gate, dw_up, dw_down,
+                               x, w_router, dlogits, dx_router, dw_router, accumulate, ws, stream=None):
+    torch = _torch_module or _torch()
+    s = Shape.of(shape)
+    bf = _bf16_types()
+    nw = s.E_total * s.d_model * s.d_ffn
+    rc = load_library().moe_grouped_ffn_router_bwd(
+        ctypes.byref(s._c), _ptr(dy_perm, bf, s.N * s.d_model, "dy_perm"), _ptr(x_perm, bf, s.N * s.d_model, "x_perm"),
+        _ptr(offsets, torch.int32, s.E_total + 1, "offsets"), _ptr(w_gate, bf, nw, "w_gate"), _ptr(w_up, bf, nw, "w_up"),
+        _ptr(w_down, bf, nw, "w_down"), _ptr(save_g, bf, s.N * s.d_ffn, "save_g"), _ptr(save_u, bf, s.N * s.d_ffn, "save_u"),
+        _ptr(dx_perm, bf, s.N * s.d_model, "dx_perm"), _ptr(dw_gate, torch.float32, nw, "dw_gate"),
+        _ptr(dw_up, torch.float32, nw, "dw_up"), _ptr(dw_down, torch.float32, nw, "dw_down"),
+        _ptr(x, bf, s.T * s.d_model, "x"), _ptr(w_router, bf, s.E * s.d_model, "w_router"),
+        _ptr(dlogits, torch.float32, s.T * s.E, "dlogits"), _ptr(dx_router, bf, s.T * s.d_model, "dx_router"),
+        _ptr(dw_router, torch.float32, s.E * s.d_model, "dw_router"), int(bool(accumulate)),
+        _ptr(ws, None, None, "ws"), ws.numel() * ws.element_size(), _stream(stream))
+    _check("moe_grouped_ffn_router_bwd", rc)
 
 
 def moe_unpermute_combine(shape, y_perm, row_of_slot, topk_w, out, stream=None):

@@ -131,8 +131,13 @@ void launch_router_prepare(hipStream_t st, const float* dlogits, const uint16_t*
 void launch_router_bwd_dx(hipStream_t st, const uint16_t* dl_hi, const uint16_t* dl_lo, const uint16_t* w_t, uint16_t* dx, int T, int d,
                           int E, int Epad);
 bool router_bwd_is_small(int T, int E, int d);
-void launch_router_bwd_small(hipStream_t st, const uint16_t* x, const uint16_t* w_router, const float* dlogits, uint16_t* dx, float* dw, int T,
-                             int E, int d, int accumulate);
+struct RouterSmallArgs {   // (router_small.h)
+  const uint16_t* x; const uint16_t* w_router; const float* dlogits;
+  uint16_t* dx; float* dw;
+  int T, E, d, accumulate;
+  int n_dw;                // filled by the launcher
+};
+void launch_router_bwd_small(hipStream_t st, RouterSmallArgs R);
 void launch_router_dw_reduce(hipStream_t st, const float* partial, float* dw, int S, int E, int d, int ldp, int accumulate);
 
 // Row-tile GEMMs of the expert FFNs in small problems (few_rows.hip) and in those between them and the 256-row tiles (mid_rows.hip).
@@ -180,7 +185,9 @@ struct WgradArgs {
   size_t f_expert_stride;
   WgradProblem problem[2];     // dW_gate | dW_up and dW_down
 };
-void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles);   // (dx_tiles > 0: and dX on 64-row tiles, or those of mid_rows.hip)
+// The weight gradients; with dx_tiles > 0 also dX on 64-row tiles, or those of mid_rows.hip; with `router` also the router's backward, if it fits
+// one of their launches (returns whether it did).
+bool launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles, const RouterSmallArgs* router);
 
 // Optional per-launch timing (moe_profile_* in the ABI).  While enabled, every kernel launch of the library is
 // bracketed by two HIP events on the launch stream; disabled (the default) it costs one branch.

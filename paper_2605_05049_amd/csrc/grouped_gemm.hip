@@ -1255,12 +1255,14 @@ extern "C" int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_per
   return launch_status();
 }
 
-extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_perm, const uint16_t* x_perm,
+namespace moe {
+
+// `router`: the router's backward may share a launch of this call; *router_done tells whether it does.
+static int grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_perm, const uint16_t* x_perm,
                                    const int32_t* offsets, const uint16_t* w_gate, const uint16_t* w_up,
                                    const uint16_t* w_down, const uint16_t* save_g, const uint16_t* save_u,
                                    uint16_t* dx_perm, float* dw_gate, float* dw_up, float* dw_down, int accumulate,
-                                   void* ws, size_t ws_bytes, void* stream) {
-  using namespace moe;
+                                   void* ws, size_t ws_bytes, void* stream, const RouterSmallArgs* router, bool* router_done) {
   Dims D;
   WsLayout L;
   int rc = common_checks(shape, &D, ws, ws_bytes, &L);
@@ -1303,8 +1305,20 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
   } else if (D.N > 0) {
     MOE_TRY(G.launch("ffn_bwd_dx", ROWTILE_DX, X));
   }
-  launch_wgrad(st, W, X, dx_tiles);
+  const bool done = launch_wgrad(st, W, X, dx_tiles, router);
+  if (router) *router_done = done;
   return launch_status();
+}
+
+}  // namespace moe
+
+extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_perm, const uint16_t* x_perm,
+                                   const int32_t* offsets, const uint16_t* w_gate, const uint16_t* w_up,
+                                   const uint16_t* w_down, const uint16_t* save_g, const uint16_t* save_u,
+                                   uint16_t* dx_perm, float* dw_gate, float* dw_up, float* dw_down, int accumulate,
+                                   void* ws, size_t ws_bytes, void* stream) {
+  return moe::grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, save_g, save_u, dx_perm, dw_gate, dw_up, dw_down, accumulate,
+                              ws, ws_bytes, stream, nullptr, nullptr);
 }
 
 extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const uint16_t* w_router, const float* dlogits,
@@ -1320,7 +1334,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   if (D.T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;
   if (router_bwd_is_small(D.T, D.E, D.d)) {
-    launch_router_bwd_small(st, x, w_router, dlogits, dx_router, dw_router, D.T, D.E, D.d, accumulate ? 1 : 0);
+    launch_router_bwd_small(st, {x, w_router, dlogits, dx_router, dw_router, D.T, D.E, D.d, accumulate ? 1 : 0, 0});
     return launch_status();
   }
   char* wsb = static_cast<char*>(ws);
@@ -1376,6 +1390,30 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   MOE_TRY((launch_gemm<1, true, true, 2, 1, EPI_F32>("router_bwd_dw", B, wgrad_blocks(B.Et, B.n_p_tiles, B.n_q_tiles), st)));
   launch_router_dw_reduce(st, partial, dw_router, (int)S, (int)D.E, (int)D.d, ldp, accumulate ? 1 : 0);
   return launch_status();
+}
+
+extern "C" int moe_grouped_ffn_router_bwd(const moe_shape* shape, const uint16_t* dy_perm, const uint16_t* x_perm,
+                                          const int32_t* offsets, const uint16_t* w_gate, const uint16_t* w_up,
+                                          const uint16_t* w_down, const uint16_t* save_g, const uint16_t* save_u,
+                                          uint16_t* dx_perm, float* dw_gate, float* dw_up, float* dw_down,
+                                          const uint16_t* x, const uint16_t* w_router, const float* dlogits,
+                                          uint16_t* dx_router, float* dw_router, int accumulate,
+                                          void* ws, size_t ws_bytes, void* stream) {
+  using namespace moe;
+  Dims D;
+  WsLayout L;
+  int rc = common_checks(shape, &D, ws, ws_bytes, &L);
+  if (rc != MOE_OK) return rc;
+  // (the router's arguments are checked before the first launch)
+  MOE_REQUIRE_PTR(x); MOE_REQUIRE_PTR(w_router); MOE_REQUIRE_PTR(dlogits); MOE_REQUIRE_PTR(dx_router); MOE_REQUIRE_PTR(dw_router);
+  MOE_REQUIRE_ALIGNED(x); MOE_REQUIRE_ALIGNED(w_router); MOE_REQUIRE_ALIGNED(dlogits); MOE_REQUIRE_ALIGNED(dx_router);
+  MOE_REQUIRE_ALIGNED(dw_router);
+  const RouterSmallArgs R = {x, w_router, dlogits, dx_router, dw_router, D.T, D.E, D.d, accumulate ? 1 : 0, 0};
+  bool done = false;
+  MOE_TRY(grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, save_g, save_u, dx_perm, dw_gate, dw_up, dw_down, accumulate,
+                          ws, ws_bytes, stream, D.T > 0 ? &R : nullptr, &done));
+  if (done || D.T == 0) return MOE_OK;
+  return moe_router_bwd(shape, x, w_router, dlogits, dx_router, dw_router, accumulate, ws, ws_bytes, stream);
 }
 
 extern "C" int moe_grouped_ffn_bwd_recompute(const moe_shape* shape, const uint16_t* dy_perm, const uint16_t* x_perm,

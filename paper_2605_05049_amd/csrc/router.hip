@@ -14,6 +14,7 @@
 // MFMA 16x16x32 bf16: A = 16 experts x 32 k (lane l: expert l%16, k = 8 (l/16) .. +7), B = 16 tokens x 32 k (same
 // pattern), D[expert][token]: lane l holds token l%16 and experts 4 (l/16) .. +3, i.e. 4 consecutive logits of a row.
 #include "route.h"
+#include "router_small.h"
 
 #include <type_traits>
 
@@ -465,99 +466,11 @@ __global__ __launch_bounds__(256) void router_dw_reduce_kernel(const float* __re
   }
 }
 
-// Both results of the backward for few experts and few tokens, in one launch and in fp32 throughout: the four launches of
-// the general path (prepare, dx, dW_r parts, their sum) are 20 us of fixed cost for a problem of a few million multiplies
-// (256 tokens, E = 8, d = 512).  Blocks of 16 wavefronts in two roles:
-//   blocks 0 .. n_dw - 1: dW_r for 128 columns.  A lane owns 2 columns and all (up to EP) experts, a wavefront the tokens
-//     w, w + 16, ...: x arrives 256 bytes per token, dlogits spread over the lanes and read across them; the 16 partial sums meet in LDS, 4 experts at a time, and are added in wavefront order.
-//   the others: dx.  A wavefront owns 512 columns (16 bytes of dx per lane) of kSmallTokens tokens and keeps W_r's 8 columns
-//     of each expert in registers.
-constexpr int kSmallWaves = 16, kSmallTokens = 4, kSmallDwCols = 2 * kWave, kSmallDxCols = 8 * kWave;
-__device__ __forceinline__ float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+constexpr int kSmallWaves = 16;
 template <int EP>
-__global__ __launch_bounds__(kSmallWaves * kWave) void router_bwd_small_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router,
-                                                                               const float* __restrict__ dlogits, uint16_t* __restrict__ dx,
-                                                                               float* __restrict__ dw, int T, int E, int d, int accumulate, int n_dw) {
-  __shared__ float part[kSmallWaves][4][kSmallDwCols];   // 32 KB
-  const int lane = threadIdx.x % kWave;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if ((int)blockIdx.x < n_dw) {
-    const int c0 = blockIdx.x * kSmallDwCols;
-    const int c = min(c0 + 2 * lane, d - 2);   // (d is even: lanes past the end repeat its last pair, never stored)
-    float acc[EP][2];
-#pragma unroll
-    for (int e = 0; e < EP; e++) acc[e][0] = acc[e][1] = 0.f;
-    constexpr int DEPTH = 16, PER = kWave / EP;   // tokens in flight; tokens whose dlogits one load fetches
-    for (int t0 = wave; t0 < T; t0 += DEPTH * kSmallWaves) {
-      uint32_t xv[DEPTH];
-      float g[DEPTH / PER];
-#pragma unroll
-      for (int j = 0; j < DEPTH; j++)
-        xv[j] = *reinterpret_cast<const uint32_t*>(x + (size_t)min(t0 + j * kSmallWaves, T - 1) * d + c);
-#pragma unroll
-      for (int i = 0; i < DEPTH / PER; i++) {
-        const int t = t0 + (i * PER + lane / EP) * kSmallWaves;
-        g[i] = (t < T && lane % EP < E) ? dlogits[(size_t)t * E + lane % EP] : 0.f;
-      }
-#pragma unroll
-      for (int j = 0; j < DEPTH; j++) {
-        if (t0 + j * kSmallWaves < T) {
-          const float a = bf16lo(xv[j]), b = bf16hi(xv[j]);
-#pragma unroll
-          for (int e = 0; e < EP; e++) {
-            const float ge = lane_value(g[j / PER], (j % PER) * EP + e);
-            acc[e][0] += ge * a;
-            acc[e][1] += ge * b;
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int e0 = 0; e0 < EP; e0 += 4) {
-      if (e0 > 0) __syncthreads();   // the previous four experts' sums have been read
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        part[wave][i][2 * lane] = acc[e0 + i][0];
-        part[wave][i][2 * lane + 1] = acc[e0 + i][1];
-      }
-      __syncthreads();
-      const int e = e0 + threadIdx.x / kSmallDwCols, cc = threadIdx.x % kSmallDwCols;
-      if (threadIdx.x < 4 * kSmallDwCols && e < E && c0 + cc < d) {
-        float sum = 0.f;
-#pragma unroll
-        for (int w = 0; w < kSmallWaves; w++) sum += part[w][threadIdx.x / kSmallDwCols][cc];
-        float* const dst = dw + (size_t)e * d + c0 + cc;
-        *dst = accumulate ? *dst + sum : sum;
-      }
-    }
-    return;
-  }
-  const int chunks = (d + kSmallDxCols - 1) / kSmallDxCols;
-  const int task = ((int)blockIdx.x - n_dw) * kSmallWaves + wave;
-  const int c_lane = (task % chunks) * kSmallDxCols + 8 * lane, c = c_lane < d ? c_lane : 0;
-  const int t_begin = task / chunks * kSmallTokens, t_end = min(T, t_begin + kSmallTokens);
-  if (t_begin >= T) return;   // (lanes past the last column stay: their dlogits are read across lanes)
-  uint4 w[EP];
-  float g[kSmallTokens];   // lane e: dlogits of expert e
-#pragma unroll
-  for (int e = 0; e < EP; e++) w[e] = e < E ? *reinterpret_cast<const uint4*>(w_router + (size_t)e * d + c) : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-  for (int j = 0; j < kSmallTokens; j++) g[j] = (lane < E && t_begin + j < t_end) ? dlogits[(size_t)(t_begin + j) * E + lane] : 0.f;
-#pragma unroll
-  for (int j = 0; j < kSmallTokens; j++) {
-    if (t_begin + j < t_end) {
-      float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int e = 0; e < EP; e++) {
-        const float ge = lane_value(g[j], e);
-        a[0] += ge * bf16lo(w[e].x); a[1] += ge * bf16hi(w[e].x); a[2] += ge * bf16lo(w[e].y); a[3] += ge * bf16hi(w[e].y);
-        a[4] += ge * bf16lo(w[e].z); a[5] += ge * bf16hi(w[e].z); a[6] += ge * bf16lo(w[e].w); a[7] += ge * bf16hi(w[e].w);
-      }
-      if (c_lane < d)
-        *reinterpret_cast<uint4*>(dx + (size_t)(t_begin + j) * d + c) =
-            make_uint4(pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), pack_bf16(a[4], a[5]), pack_bf16(a[6], a[7]));
-    }
-  }
+__global__ __launch_bounds__(kSmallWaves * kWave) void router_bwd_small_kernel(const RouterSmallArgs R) {
+  __shared__ __attribute__((aligned(16))) char lds[router_small_lds(kSmallWaves)];   // 32 KB
+  router_small_block<EP, kSmallWaves>(R, lds, blockIdx.x);
 }
 
 // One block of the dW_r role does T x EP multiply-adds for its 128 columns on one CU, so the launch's time grows with T (and, as
@@ -569,13 +482,10 @@ bool router_bwd_is_small(int T, int E, int d) {
   if (E <= 8) return T <= 1024;
   return E <= 16 && T <= (d >= 128 && d <= 8192 ? 512 : 64);
 }
-void launch_router_bwd_small(hipStream_t st, const uint16_t* x, const uint16_t* w_router, const float* dlogits, uint16_t* dx, float* dw, int T,
-                             int E, int d, int accumulate) {
-  const int n_dw = (d + kSmallDwCols - 1) / kSmallDwCols;
-  const long long tasks = (long long)((T + kSmallTokens - 1) / kSmallTokens) * ((d + kSmallDxCols - 1) / kSmallDxCols);
-  const dim3 grid((unsigned)(n_dw + (tasks + kSmallWaves - 1) / kSmallWaves)), block(kSmallWaves * kWave);
-  if (E <= 8) MOE_LAUNCH("router_bwd", st, (router_bwd_small_kernel<8>), grid, block, 0, st, x, w_router, dlogits, dx, dw, T, E, d, accumulate, n_dw);
-  else MOE_LAUNCH("router_bwd", st, (router_bwd_small_kernel<16>), grid, block, 0, st, x, w_router, dlogits, dx, dw, T, E, d, accumulate, n_dw);
+void launch_router_bwd_small(hipStream_t st, RouterSmallArgs R) {
+  const dim3 grid(router_small_plan(R, kSmallWaves)), block(kSmallWaves * kWave);
+  if (R.E <= 8) MOE_LAUNCH("router_bwd", st, router_bwd_small_kernel<8>, grid, block, 0, st, R);
+  else MOE_LAUNCH("router_bwd", st, router_bwd_small_kernel<16>, grid, block, 0, st, R);
 }
 
 void launch_router_prepare(hipStream_t st, const float* dlogits, const uint16_t* w_router, uint16_t* hi, uint16_t* lo, uint16_t* w_t,

@@ -18,6 +18,7 @@
 // that 16 lanes of an accumulator register hold 16 consecutive columns of one row of dW; two registers exchange lane rows, and a
 // store instruction writes whole 128-byte lines from registers, without a bounce through LDS and without a barrier.
 #include "mid_rows.h"
+#include "router_small.h"
 
 #include <limits.h>
 
@@ -41,6 +42,7 @@ constexpr int W_MERGE_CHUNKS = 1024;         // both problems in one launch up t
 constexpr int W_DX_CHUNKS = 256;             // ... and dX on 64-row tiles with them up to here, ...
 constexpr int W_DX_SHORT_STEPS = 64, W_DX_STEPS = 240, W_DX_STEPS_PER_CHUNK = 8;   // ... if its contraction is not too long (dx_joins)
 constexpr long long W_DX_MID_ROWS = 4096;    // and dX on the tiles of mid_rows.hip below so many rows per expert
+constexpr double W_ROUTER_US8 = 0.02, W_ROUTER_US16 = 0.04, W_STORE_BYTES_PER_US = 6e6, W_ROUTER_SLACK_US = 5;   // (router_joins)
 constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
 
 // Position of 8 r-values (chunk c of 16) inside k-row k's 256 bytes: the four k-rows that a transposing read takes together
@@ -293,23 +295,37 @@ __global__ __launch_bounds__(WTHREADS, 2) void wgrad_kernel(const WgradArgs A) {
 // (eight, one block per CU, where dX has a launch of its own and at most 256 tiles).  us of the two launches -> of this one (forward +
 // backward: 512 x 512, 4 experts of 16 rows 68.9 -> 59.2; 512 x 1024, 8 of 64 74.2 -> 69.9; 1472 x 576, 8 of 233 134 -> 124;
 // 640 x 640, 63 of 12 163 -> 155; 1024 x 1600, 45 of 19 384 -> 374.)
-struct DxWgradArgs {
+struct JoinedArgs {
+  RouterSmallArgs router;
   RowTileArgs dx;
   WgradArgs dw;
-  unsigned dx_blocks;
+  unsigned router_blocks, dx_blocks;   // (multiples of 8: the others find their XCD by their index)
 };
-__global__ __launch_bounds__(WTHREADS, 2) void dx_wgrad_kernel(const DxWgradArgs A) {
-  __shared__ __attribute__((aligned(1024))) char lds[3 * W_STAGE];
-  static_assert(WTHREADS == 4 * kWave && 4 * F_PATCH <= 3 * W_STAGE, "a dX tile of four wavefronts fits");
-  if (blockIdx.x < A.dx_blocks) few_rows_block<ROWTILE_DX, 4>(A.dx, lds, blockIdx.x, A.dx_blocks);
-  else wgrad_block(A.dw, lds, blockIdx.x - A.dx_blocks);
+enum JoinedDx { JOINED_NO_DX, JOINED_DX_FEW, JOINED_DX_MID };
+// The router's backward for up to EP experts (0: none), dX and the weight gradients
+template <int EP, JoinedDx DX>
+__global__ __launch_bounds__(WTHREADS, 2) void joined_wgrad_kernel(const JoinedArgs A) {
+  constexpr int LDS = DX == JOINED_DX_MID ? M_LDS : 3 * W_STAGE;
+  __shared__ __attribute__((aligned(1024))) char lds[LDS];
+  static_assert(WTHREADS == 4 * kWave && 4 * F_PATCH <= 3 * W_STAGE && 3 * W_STAGE <= M_LDS && router_small_lds(4) <= 3 * W_STAGE, "each of them fits");
+  unsigned block = blockIdx.x;
+  if constexpr (EP > 0) {
+    if (block < A.router_blocks) {
+      router_small_block<EP, 4>(A.router, lds, block);
+      return;
+    }
+    block -= A.router_blocks;
+  }
+  if (DX == JOINED_NO_DX || block >= A.dx_blocks) wgrad_block(A.dw, lds, block - A.dx_blocks);
+  else if constexpr (DX == JOINED_DX_FEW) few_rows_block<ROWTILE_DX, 4>(A.dx, lds, block, A.dx_blocks);
+  else if constexpr (DX == JOINED_DX_MID) mid_rows_block<ROWTILE_DX>(A.dx, lds, block, A.dx_blocks);
 }
-
-__global__ __launch_bounds__(WTHREADS, 2) void mid_dx_wgrad_kernel(const DxWgradArgs A) {
-  __shared__ __attribute__((aligned(1024))) char lds[M_LDS];
-  static_assert(WTHREADS == 4 * kWave && 3 * W_STAGE <= M_LDS, "the ring fits");
-  if (blockIdx.x < A.dx_blocks) mid_rows_block<ROWTILE_DX>(A.dx, lds, blockIdx.x, A.dx_blocks);
-  else wgrad_block(A.dw, lds, blockIdx.x - A.dx_blocks);
+template <JoinedDx DX>
+static void launch_joined(hipStream_t st, const char* label, const JoinedArgs& J, unsigned dw_blocks) {
+  const dim3 grid(J.router_blocks + J.dx_blocks + dw_blocks), block(WTHREADS);
+  if (J.router_blocks == 0) MOE_LAUNCH(label, st, (joined_wgrad_kernel<0, DX>), grid, block, 0, st, J);
+  else if (J.router.E <= 8) MOE_LAUNCH(label, st, (joined_wgrad_kernel<8, DX>), grid, block, 0, st, J);
+  else MOE_LAUNCH(label, st, (joined_wgrad_kernel<16, DX>), grid, block, 0, st, J);
 }
 
 // Fills in how a problem is cut into tiles and chunks.
@@ -342,45 +358,60 @@ static bool dx_joins(const RowTileArgs& dx, int chunks) {
   return chunks <= W_DX_CHUNKS && (steps <= W_DX_SHORT_STEPS || (steps <= W_DX_STEPS && steps <= W_DX_STEPS_PER_CHUNK * chunks));
 }
 
-// Launches the weight gradients of the pair and of the single tensor, and dX where it does not run on 256-row tiles (at most dx_tiles row
-// tiles; 0: it does).
-void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles) {
-  if (A.Et <= 0) return;
+// Whether the router's backward shares the weight gradients' launch: with at most 16 experts, and if its longest block, dW_r of 128 columns over
+// all tokens (JOIN_US per token, measured alone), is done long before the stores of the weight gradients can be.
+static bool router_joins(const RouterSmallArgs& R, const WgradArgs& A) {
+  if (R.E > 16) return false;
+  const double longest = R.T * (R.E <= 8 ? W_ROUTER_US8 : W_ROUTER_US16), stores = 12.0 * A.Et * A.f_expert_stride / W_STORE_BYTES_PER_US;
+  return longest <= W_ROUTER_SLACK_US + 0.7 * stores;
+}
+
+// Launches the weight gradients of the pair and of the single tensor, dX where it does not run on 256-row tiles (at most dx_tiles row
+// tiles; 0: it does), and the router's backward where it shares their launch (returns whether it does).
+bool launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long dx_tiles, const RouterSmallArgs* router) {
+  if (A.Et <= 0) return false;
   plan_wgrad(A.problem[0], A.Et, A.rows);
   plan_wgrad(A.problem[1], A.Et, A.rows);
   auto grid = [](long long chunks) { return dim3((unsigned)((chunks + W_XCDS - 1) / W_XCDS * W_XCDS * W_CHUNK)); };
   const dim3 block(WTHREADS);
-  if (dx_tiles > 0 && dx.mid_rows) {
-    // (dX first: its tiles run on either side of a CU's weight gradients, whose stores leave its matrix pipes idle.  One launch / two, 4000
-    // random shapes with dX on these tiles: 0.7 - 0.92 of the time below 512 rows per expert, 0.8 - 0.93 up to 2048, 0.87 - 0.96 up to 4096; beyond
-    // 0.94 - 1.16, where the weight gradients are few and long and begin late.)
-    if (A.rows < W_DX_MID_ROWS * A.Et) {
-      DxWgradArgs X = {};
-      X.dx = dx; X.dw = A;
-      X.dx_blocks = mid_rows_plan(X.dx, ROWTILE_DX, dx_tiles);
-      MOE_LAUNCH("ffn_bwd_dx_dw", st, mid_dx_wgrad_kernel, dim3(X.dx_blocks + grid(A.problem[0].chunks + A.problem[1].chunks).x), block, 0, st, X);
-      return;
+  const int chunks = A.problem[0].chunks + A.problem[1].chunks;
+  JoinedArgs J = {};
+  J.dw = A;
+  if (router && router_joins(*router, A)) {
+    J.router = *router;
+    J.router_blocks = (router_small_plan(J.router, 4) + W_XCDS - 1) / W_XCDS * W_XCDS;
+  }
+  if (dx_tiles > 0) {
+    J.dx = dx;
+    // dX on the tiles of mid_rows.hip: its tiles run on either side of a CU's weight gradients, whose stores leave its matrix pipes idle.  One
+    // launch / two, 4000 random shapes: 0.7 - 0.92 of the time below 512 rows per expert, 0.8 - 0.93 up to 2048, 0.87 - 0.96 up to 4096; beyond
+    // 0.94 - 1.16, where the weight gradients are few and long and begin late.
+    if (dx.mid_rows && A.rows < W_DX_MID_ROWS * A.Et) {
+      J.dx_blocks = mid_rows_plan(J.dx, ROWTILE_DX, dx_tiles);
+      launch_joined<JOINED_DX_MID>(st, "ffn_bwd_dx_dw", J, grid(chunks).x);
+      return J.router_blocks > 0;
     }
-    launch_mid_rows("ffn_bwd_dx", st, ROWTILE_DX, dx, dx_tiles);
-  } else if (dx_tiles > 0) {
-    // (2048 x 1408, 66 experts, 528 chunks, forward + backward: 837 us with dX in a launch of its own, 842 with one for all.)
-    if (dx_joins(dx, A.problem[0].chunks + A.problem[1].chunks)) {
-      DxWgradArgs X = {};
-      X.dx = dx; X.dw = A;
-      X.dx.n_q_tiles = dx.q_dim / FQ;
-      X.dx.chunk_log2 = few_rows_chunk_log2(dx, dx_tiles, X.dx.n_q_tiles);
-      X.dx_blocks = few_rows_grid(dx_tiles * X.dx.n_q_tiles, X.dx.chunk_log2);
-      MOE_LAUNCH("ffn_bwd_dx_dw", st, dx_wgrad_kernel, dim3(X.dx_blocks + grid(A.problem[0].chunks + A.problem[1].chunks).x), block, 0, st, X);
-      return;
+    // (On 64-row tiles: 2048 x 1408, 66 experts, 528 chunks, forward + backward: 837 us with dX in a launch of its own, 842 with one for all.)
+    if (!dx.mid_rows && dx_joins(dx, chunks)) {
+      J.dx.n_q_tiles = dx.q_dim / FQ;
+      J.dx.chunk_log2 = few_rows_chunk_log2(dx, dx_tiles, J.dx.n_q_tiles);
+      J.dx_blocks = few_rows_grid(dx_tiles * J.dx.n_q_tiles, J.dx.chunk_log2);
+      launch_joined<JOINED_DX_FEW>(st, "ffn_bwd_dx_dw", J, grid(chunks).x);
+      return J.router_blocks > 0;
     }
-    launch_few_rows("ffn_bwd_dx", st, ROWTILE_DX, dx, dx_tiles);
+    if (dx.mid_rows) launch_mid_rows("ffn_bwd_dx", st, ROWTILE_DX, dx, dx_tiles);
+    else launch_few_rows("ffn_bwd_dx", st, ROWTILE_DX, dx, dx_tiles);
   }
   // In one launch, unless it is long: two launches have two starts and two last rounds.  Time of the one against the two, 200
   // random shapes: 0.73 at fewer than 64 chunks, 0.91 at 64 .. 128, 0.94 up to 256, 0.97 up to 512, 0.98 up to 1024, 0.99 - 1.0
   // beyond.
-  if (A.problem[0].chunks + A.problem[1].chunks <= W_MERGE_CHUNKS) {
-    MOE_LAUNCH("ffn_bwd_dw", st, wgrad_kernel, grid(A.problem[0].chunks + A.problem[1].chunks), block, 0, st, A);
-    return;
+  if (chunks <= W_MERGE_CHUNKS) {
+    if (J.router_blocks > 0) {
+      launch_joined<JOINED_NO_DX>(st, "ffn_bwd_dw", J, grid(chunks).x);
+      return true;
+    }
+    MOE_LAUNCH("ffn_bwd_dw", st, wgrad_kernel, grid(chunks), block, 0, st, A);
+    return false;
   }
   const dim3 pair_grid = grid(A.problem[0].chunks), down_grid = grid(A.problem[1].chunks);
   A.problem[0].chunks = A.problem[1].chunks = INT_MAX;   // every block of these launches belongs to the first problem
@@ -388,6 +419,7 @@ void launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
   down.problem[0] = A.problem[1];
   MOE_LAUNCH("ffn_bwd_dw_down", st, wgrad_kernel, down_grid, block, 0, st, down);
   MOE_LAUNCH("ffn_bwd_dw_gate_up", st, wgrad_kernel, pair_grid, block, 0, st, A);
+  return false;
 }
 
 }  // namespace moe

@@ -64,8 +64,8 @@ def layer_forward(buf: MoeLayerBuffers, x, w_gate, w_up, w_down, logits=None, w_
 def layer_backward(buf: MoeLayerBuffers, dout, w_gate, w_up, w_down, accumulate=False, with_router=True, x=None,
                    w_router=None, stream=None):
     """combine_bwd and route_bwd (one launch) -> grouped FFN bwd -> permute_bwd.  Results land in buf.dx, buf.dw_*,
-    buf.dtopk_w, buf.dlogits.  With `x` and `w_router` the layer is closed from x: router_bwd comes before the
-    un-permutation, buf.dx then holds the expert-path term plus the router's term, and buf.dw_router is filled."""
+    buf.dtopk_w, buf.dlogits.  With `x` and `w_router` the layer is closed from x: router_bwd comes with the
+    experts' backward, buf.dx then holds the expert-path term plus the router's term, and buf.dw_router is filled."""
     s = buf.shape
     gated = with_router and buf.dlogits is not None
     if gated or w_router is not None:   # (a token's dlogits need no more than its dtopk_w: made with it, not after the experts' backward)
@@ -73,12 +73,12 @@ def layer_backward(buf: MoeLayerBuffers, dout, w_gate, w_up, w_down, accumulate=
                                           buf.dlogits, stream)
     else:
         B.moe_unpermute_combine_bwd(s, dout, buf.y_perm, buf.row_of_slot, buf.topk_w, buf.dy_perm, buf.dtopk_w, stream)
-    B.moe_grouped_ffn_bwd(s, buf.dy_perm, buf.x_perm, buf.offsets, w_gate, w_up, w_down, buf.save_g, buf.save_u,
-                          buf.dx_perm, buf.dw_gate, buf.dw_up, buf.dw_down, accumulate, buf.ws, stream)
+    ffn = (buf.dy_perm, buf.x_perm, buf.offsets, w_gate, w_up, w_down, buf.save_g, buf.save_u, buf.dx_perm, buf.dw_gate, buf.dw_up, buf.dw_down)
     if w_router is not None:
-        B.moe_router_bwd(s, x, w_router, buf.dlogits, buf.dx_router, buf.dw_router, accumulate, buf.ws, stream)
+        B.moe_grouped_ffn_router_bwd(s, *ffn, x, w_router, buf.dlogits, buf.dx_router, buf.dw_router, accumulate, buf.ws, stream)
         B.moe_permute_bwd_add(s, buf.dx_perm, buf.row_of_slot, buf.dx_router, buf.dx, stream)
     else:
+        B.moe_grouped_ffn_bwd(s, *ffn, accumulate, buf.ws, stream)
         B.moe_permute_bwd(s, buf.dx_perm, buf.row_of_slot, buf.dx, stream)
 
 
