@@ -42,7 +42,7 @@ constexpr int W_MERGE_CHUNKS = 1024;         // both problems in one launch up t
 constexpr int W_DX_CHUNKS = 256;             // ... and dX on 64-row tiles with them up to here, ...
 constexpr int W_DX_SHORT_STEPS = 64, W_DX_STEPS = 240, W_DX_STEPS_PER_CHUNK = 8;   // ... if its contraction is not too long (dx_joins)
 constexpr long long W_DX_MID_ROWS = 4096;    // and dX on the tiles of mid_rows.hip below so many rows per expert
-constexpr double W_ROUTER_US8 = 0.02, W_ROUTER_US16 = 0.04, W_STORE_BYTES_PER_US = 6e6, W_ROUTER_SLACK_US = 5;   // (router_joins)
+constexpr double W_ROUTER_US8 = 0.012, W_ROUTER_US16 = 0.024, W_STORE_BYTES_PER_US = 6e6, W_ROUTER_SLACK_US = 5;   // (router_joins)
 constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
 
 // Position of 8 r-values (chunk c of 16) inside k-row k's 256 bytes: the four k-rows that a transposing read takes together
@@ -359,7 +359,9 @@ static bool dx_joins(const RowTileArgs& dx, int chunks) {
 }
 
 // Whether the router's backward shares the weight gradients' launch: with at most 16 experts, and if its longest block, dW_r of 128 columns over
-// all tokens (JOIN_US per token, measured alone), is done long before the stores of the weight gradients can be.
+// all tokens, is done before the stores of the weight gradients can be.  Step of 3181 random shapes (2 .. 16 experts, 64 .. 16384 tokens, 64 .. 4096 x
+// 64 .. 4096), joined / not: below the limit 0.944 at the mean and more than 1.03 on 0.2 %, up to twice as many tokens 0.98 and 17 %,
+// beyond 1.7.
 static bool router_joins(const RouterSmallArgs& R, const WgradArgs& A) {
   if (R.E > 16) return false;
   const double longest = R.T * (R.E <= 8 ? W_ROUTER_US8 : W_ROUTER_US16), stores = 12.0 * A.Et * A.f_expert_stride / W_STORE_BYTES_PER_US;

@@ -112,6 +112,11 @@ def test_argument_checks_run_before_any_launch(lib):
     assert lib.moe_router_fwd(sp, FAKE, None, FAKE, FAKE, 1 << 40, None) == -1
     assert lib.moe_router_fwd(sp, FAKE, FAKE, FAKE, FAKE, 16, None) == -4
     assert lib.moe_router_fwd(bad, FAKE, FAKE, FAKE, FAKE, 1 << 40, None) == -2
+    ffn = [FAKE] * 12
+    assert lib.moe_grouped_ffn_router_bwd(sp, *ffn, FAKE, FAKE, FAKE, FAKE, None, 0, FAKE, 1 << 40, None) == -1
+    assert lib.moe_grouped_ffn_router_bwd(sp, *ffn, FAKE, FAKE, ODD, FAKE, FAKE, 0, FAKE, 1 << 40, None) == -3
+    assert lib.moe_grouped_ffn_router_bwd(sp, *ffn[:11], None, FAKE, FAKE, FAKE, FAKE, FAKE, 0, FAKE, 1 << 40, None) == -1
+    assert lib.moe_grouped_ffn_router_bwd(sp, *ffn, FAKE, FAKE, FAKE, FAKE, FAKE, 0, FAKE, 256, None) == -4
     assert lib.moe_router_bwd(sp, FAKE, FAKE, FAKE, FAKE, None, 0, FAKE, 1 << 40, None) == -1
     assert lib.moe_router_bwd(sp, FAKE, FAKE, ODD, FAKE, FAKE, 0, FAKE, 1 << 40, None) == -3
     assert lib.moe_router_bwd(sp, FAKE, FAKE, FAKE, FAKE, FAKE, 0, None, 0, None) == -1

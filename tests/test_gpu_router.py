@@ -14,7 +14,7 @@ import torch
 
 import workloads as W
 from oracle import moe_oracle as O
-from test_gpu_parity import TOL, TOL_GATE, assert_close, dev, dev_bf16, f32w, host_f32, ws_for
+from test_gpu_parity import TOL, TOL_GATE, assert_close, dev, dev_bf16, f32w, ffn_on_device, host_f32, ws_for
 
 pytestmark = pytest.mark.gpu
 
@@ -206,3 +206,45 @@ def test_router_and_gating_in_one(moe, T, d, E, k, Es, renorm, one_launch):
     moe.profile_reset()
     assert labels == (["router_route_fwd"] if one_launch else ["router_fwd", "route_topk"])
     assert torch.equal(idx, idx1) and all(torch.equal(a, b) for a, b in zip(two, one))
+
+
+# the router's blocks before dX on 64-row tiles and on those of 128 columns, and with dX in a launch of its own, for up to 8 and 16 experts;
+# too many tokens for the weight gradients beside them, too many experts
+@pytest.mark.parametrize("d,f,counts,joined", [
+    (512, 1024, [64] * 8, True), (64, 128, [5] * 15 + [0], True), (1088, 1984, [100] * 13, True), (2560, 1600, [500, 0, 700, 1], True),
+    (4096, 8192, [2048, 2048], True), (64, 64, [512] * 8, False), (1024, 1024, [4] * 17, False),
+])
+def test_router_backward_beside_the_weight_gradients(moe, d, f, counts, joined):
+    """What the two calls give: the experts' results bit for bit, the router's against fp64 (dx is one rounding to bf16 of sums in fp32 or of
+    operands of 16 bits, 2^-9 of each element; dW_r sums of T products in fp32 or of 16 bits, 2^-16 of the norm)."""
+    s, x, dy, off, w, ws, _, sg, su = ffn_on_device(moe, d, f, counts)
+    T, E = s.T, s.E
+    g = torch.Generator(device="cuda").manual_seed(1)
+    wr = (torch.randn(E, d, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    dl = torch.randn(T, E, device="cuda", generator=g) * 0.3
+    want = torch.full_like(x, float("nan")), [torch.full(t.shape, float("nan"), device="cuda") for t in w]
+    moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, sg, su, want[0], *want[1], False, ws)
+    start = torch.randn(E, d, device="cuda", generator=g)
+    over = None
+    for accumulate in (False, True):
+        dx, dxr = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+        dw = [torch.zeros(t.shape, device="cuda") if accumulate else torch.full(t.shape, float("nan"), device="cuda") for t in w]
+        dwr = start.clone() if accumulate else torch.full((E, d), float("nan"), device="cuda")
+        ws.fill_(255)
+        moe.profile_reset()
+        moe.profile_enable(True)
+        moe.moe_grouped_ffn_router_bwd(s, dy, x, off, *w, sg, su, dx, *dw, x, wr, dl, dxr, dwr, accumulate, ws)
+        torch.cuda.synchronize()
+        labels = [label for label, _ in moe.profile_records()]
+        moe.profile_enable(False)
+        moe.profile_reset()
+        assert any(label.startswith("router") for label in labels) == (not joined)
+        assert torch.equal(dx.view(torch.int16), want[0].view(torch.int16)) and all(torch.equal(a, b) for a, b in zip(dw, want[1]))
+        if accumulate:
+            assert torch.equal(dwr, start + over)
+        else:
+            over = dwr.clone()
+            ref = dl.double().T @ x.double()
+            assert float((dwr.double() - ref).norm()) <= 2.0 ** -16 * float(ref.norm())
+        ref = dl.double() @ wr.double()
+        assert float((dxr.double() - ref).norm()) <= 2.0 ** -8 * float(ref.norm()) and bool(torch.isfinite(dxr.float()).all())
