@@ -1068,10 +1068,10 @@ constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                  
      {kMidAny, 2048, 1280, 1280, 768, 512, 320}, {kMidAny, 1536, 768, 768, 640, 768, 640}},
     // dH
     {{kMidAny, kMidAny, 512, 512, 512, 256, 256}, {kMidAny, kMidAny, 2560, 2560, 1024, 640, 640},
-     {kMidAny, kMidAny, 4096, 2048, 1280, 768, 768}, {kMidAny, kMidAny, 3072, 768, 768, 640, 640}},
+     {kMidAny, kMidAny, 4096, 2048, 1280, 768, 768}, {kMidAny, kMidAny, 1536, 768, 768, 640, 640}},
     // dX
     {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 1536, 0}, {kMidAny, kMidAny, 3072, 3072, 3072, 2048, 768},
-     {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1536}, {4096, 4096, 3072, 3072, 1280, 768, 768}}};
+     {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1536}, {3072, 3072, 2048, 2048, 1280, 768, 768}}};
 int mid_rows_for(const Dims& D, RowTileKind kind) {
   if (D.Et > kFewSelfExperts || D.N == 0) return 0;   // (its blocks find their tiles from the offsets alone)
   const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;
@@ -1087,7 +1087,7 @@ int mid_rows_for(const Dims& D, RowTileKind kind) {
     case ROWTILE_GATE_UP: least = steps < 12 ? 32 : 144; break;
     case ROWTILE_DOWN: least = 144; break;
     case ROWTILE_DH: least = rc == 0 ? (steps < 12 ? 208 : 256) : rc == 1 ? 208 : 160; break;   // (few_rows.hip requests G and U before the sums)
-    default: least = steps < 128 ? 80 : 128; break;                                             // (beside the weight gradients it need not fill the chip)
+    default: least = steps < 128 ? 96 : 128; break;                                             // (beside the weight gradients it need not fill the chip)
   }
   if (tiles < least || tiles >= kMidMost[kind][rc][sc]) return 0;
   if (kind == ROWTILE_DOWN && rc == 3 && sc > 0 && tiles >= 768 && tiles < 1024) return 0;   // (1.5 .. 2 rounds of either height: 1.03, on both sides 0.85 and 0.93)

@@ -483,7 +483,7 @@ bool router_bwd_is_small(int T, int E, int d) {
   return E <= 16 && T <= (d >= 128 && d <= 8192 ? 512 : 64);
 }
 void launch_router_bwd_small(hipStream_t st, RouterSmallArgs R) {
-  const dim3 grid(router_small_plan(R, kSmallWaves)), block(kSmallWaves * kWave);
+  const dim3 grid(router_small_plan(R, kSmallWaves, R.E <= 8 ? 8 : 16)), block(kSmallWaves * kWave);
   if (R.E <= 8) MOE_LAUNCH("router_bwd", st, router_bwd_small_kernel<8>, grid, block, 0, st, R);
   else MOE_LAUNCH("router_bwd", st, router_bwd_small_kernel<16>, grid, block, 0, st, R);
 }

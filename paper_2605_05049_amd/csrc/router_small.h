@@ -13,8 +13,8 @@ constexpr int kSmallTokens = 4, kSmallDwCols = 2 * kWave, kSmallDxCols = 8 * kWa
 constexpr int router_small_lds(int waves) { return waves * 4 * kSmallDwCols * (int)sizeof(float); }
 
 // Fills in the plan of a block size; returns the blocks.
-inline unsigned router_small_plan(RouterSmallArgs& R, int waves) {
-  R.n_dw = (R.d + kSmallDwCols - 1) / kSmallDwCols;
+inline unsigned router_small_plan(RouterSmallArgs& R, int waves, int ep) {
+  R.n_dw = (R.d + kSmallDwCols - 1) / kSmallDwCols * ((R.E + ep - 1) / ep);
   const long long tasks = (long long)((R.T + kSmallTokens - 1) / kSmallTokens) * ((R.d + kSmallDxCols - 1) / kSmallDxCols);
   return (unsigned)(R.n_dw + (tasks + waves - 1) / waves);
 }
@@ -22,11 +22,11 @@ inline unsigned router_small_plan(RouterSmallArgs& R, int waves) {
 __device__ __forceinline__ float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
 
 // Blocks in two roles:
-//   blocks 0 .. n_dw - 1: dW_r for 128 columns.  A lane owns 2 columns and all (up to EP) experts, a wavefront the tokens
+//   blocks 0 .. n_dw - 1: dW_r for 128 columns and up to EP experts.  A lane owns 2 columns and these experts, a wavefront the tokens
 //     w, w + WAVES, ...: x arrives 256 bytes per token, dlogits spread over the lanes and read across them; the WAVES partial sums meet in
 //     LDS, 4 experts at a time, and are added in wavefront order.
 //   the others: dx.  A wavefront owns 512 columns (16 bytes of dx per lane) of kSmallTokens tokens and keeps W_r's 8 columns
-//     of each expert in registers.
+//     of EP experts at a time in registers.
 template <int EP, int WAVES>
 __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, char* lds, unsigned block) {
   const uint16_t* __restrict__ const x = R.x;
@@ -36,7 +36,8 @@ __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, cha
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if ((int)block < R.n_dw) {
-    const int c0 = (int)block * kSmallDwCols;
+    const int groups = (E + EP - 1) / EP;
+    const int e_lo = (int)block % groups * EP, c0 = (int)block / groups * kSmallDwCols;
     const int c = min(c0 + 2 * lane, d - 2);   // (d is even: lanes past the end repeat its last pair, never stored)
     float acc[EP][2];
 #pragma unroll
@@ -51,7 +52,7 @@ __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, cha
 #pragma unroll
       for (int i = 0; i < DEPTH / PER; i++) {
         const int t = t0 + (i * PER + lane / EP) * WAVES;
-        g[i] = (t < T && lane % EP < E) ? dlogits[(size_t)t * E + lane % EP] : 0.f;
+        g[i] = (t < T && e_lo + lane % EP < E) ? dlogits[(size_t)t * E + e_lo + lane % EP] : 0.f;
       }
 #pragma unroll
       for (int j = 0; j < DEPTH; j++) {
@@ -76,7 +77,7 @@ __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, cha
       }
       __syncthreads();
       for (int i = threadIdx.x; i < 4 * kSmallDwCols; i += WAVES * kWave) {
-        const int e = e0 + i / kSmallDwCols, cc = i % kSmallDwCols;
+        const int e = e_lo + e0 + i / kSmallDwCols, cc = i % kSmallDwCols;
         if (e < E && c0 + cc < d) {
           float sum = 0.f;
 #pragma unroll
@@ -93,27 +94,31 @@ __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, cha
   const int c_lane = (task % chunks) * kSmallDxCols + 8 * lane, c = c_lane < d ? c_lane : 0;
   const int t_begin = task / chunks * kSmallTokens, t_end = min(T, t_begin + kSmallTokens);
   if (t_begin >= T) return;   // (lanes past the last column stay: their dlogits are read across lanes)
-  uint4 w[EP];
-  float g[kSmallTokens];   // lane e: dlogits of expert e
+  float a[kSmallTokens][8] = {};
+  for (int e_lo = 0; e_lo < E; e_lo += EP) {
+    uint4 w[EP];
+    float g[kSmallTokens];   // lane e: dlogits of expert e_lo + e
 #pragma unroll
-  for (int e = 0; e < EP; e++) w[e] = e < E ? *reinterpret_cast<const uint4*>(R.w_router + (size_t)e * d + c) : make_uint4(0u, 0u, 0u, 0u);
+    for (int e = 0; e < EP; e++) w[e] = e_lo + e < E ? *reinterpret_cast<const uint4*>(R.w_router + (size_t)(e_lo + e) * d + c) : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-  for (int j = 0; j < kSmallTokens; j++) g[j] = (lane < E && t_begin + j < t_end) ? dlogits[(size_t)(t_begin + j) * E + lane] : 0.f;
+    for (int j = 0; j < kSmallTokens; j++) g[j] = (lane < EP && e_lo + lane < E && t_begin + j < t_end) ? dlogits[(size_t)(t_begin + j) * E + e_lo + lane] : 0.f;
 #pragma unroll
-  for (int j = 0; j < kSmallTokens; j++) {
-    if (t_begin + j < t_end) {
-      float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < kSmallTokens; j++) {
+      if (t_begin + j < t_end) {
 #pragma unroll
-      for (int e = 0; e < EP; e++) {
-        const float ge = lane_value(g[j], e);
-        a[0] += ge * bf16lo(w[e].x); a[1] += ge * bf16hi(w[e].x); a[2] += ge * bf16lo(w[e].y); a[3] += ge * bf16hi(w[e].y);
-        a[4] += ge * bf16lo(w[e].z); a[5] += ge * bf16hi(w[e].z); a[6] += ge * bf16lo(w[e].w); a[7] += ge * bf16hi(w[e].w);
+        for (int e = 0; e < EP; e++) {
+          const float ge = lane_value(g[j], e);
+          a[j][0] += ge * bf16lo(w[e].x); a[j][1] += ge * bf16hi(w[e].x); a[j][2] += ge * bf16lo(w[e].y); a[j][3] += ge * bf16hi(w[e].y);
+          a[j][4] += ge * bf16lo(w[e].z); a[j][5] += ge * bf16hi(w[e].z); a[j][6] += ge * bf16lo(w[e].w); a[j][7] += ge * bf16hi(w[e].w);
+        }
       }
-      if (c_lane < d)
-        *reinterpret_cast<uint4*>(R.dx + (size_t)(t_begin + j) * d + c) =
-            make_uint4(pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), pack_bf16(a[4], a[5]), pack_bf16(a[6], a[7]));
     }
   }
+#pragma unroll
+  for (int j = 0; j < kSmallTokens; j++)
+    if (t_begin + j < t_end && c_lane < d)
+      *reinterpret_cast<uint4*>(R.dx + (size_t)(t_begin + j) * d + c) =
+          make_uint4(pack_bf16(a[j][0], a[j][1]), pack_bf16(a[j][2], a[j][3]), pack_bf16(a[j][4], a[j][5]), pack_bf16(a[j][6], a[j][7]));
 }
 
 }  // namespace moe

@@ -42,6 +42,8 @@ constexpr int W_MERGE_CHUNKS = 1024;         // both problems in one launch up t
 constexpr int W_DX_CHUNKS = 256;             // ... and dX on 64-row tiles with them up to here, ...
 constexpr int W_DX_SHORT_STEPS = 64, W_DX_STEPS = 240, W_DX_STEPS_PER_CHUNK = 8;   // ... if its contraction is not too long (dx_joins)
 constexpr long long W_DX_MID_ROWS = 4096;    // and dX on the tiles of mid_rows.hip below so many rows per expert
+constexpr int W_ROUTER_EXPERTS = 128;
+constexpr double W_ROUTER_MACS = 2e8;
 constexpr double W_ROUTER_US8 = 0.012, W_ROUTER_US16 = 0.024, W_STORE_BYTES_PER_US = 6e6, W_ROUTER_SLACK_US = 5;   // (router_joins)
 constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
 
@@ -358,12 +360,14 @@ static bool dx_joins(const RowTileArgs& dx, int chunks) {
   return chunks <= W_DX_CHUNKS && (steps <= W_DX_SHORT_STEPS || (steps <= W_DX_STEPS && steps <= W_DX_STEPS_PER_CHUNK * chunks));
 }
 
-// Whether the router's backward shares the weight gradients' launch: with at most 16 experts, and if its longest block, dW_r of 128 columns over
-// all tokens, is done before the stores of the weight gradients can be.  Step of 3181 random shapes (2 .. 16 experts, 64 .. 16384 tokens, 64 .. 4096 x
-// 64 .. 4096), joined / not: below the limit 0.944 at the mean and more than 1.03 on 0.2 %, up to twice as many tokens 0.98 and 17 %,
-// beyond 1.7.
+// Whether the router's backward shares the weight gradients' launch: with at most 128 experts, and if its longest block, dW_r of 128 columns and
+// 16 experts over all tokens, is done before the stores of the weight gradients can be.  Step of random shapes (64 .. 4096 x 64 .. 4096), joined
+// / not: 2 .. 16 experts, 64 .. 16384 tokens (3181 shapes) below the limit 0.944 at the mean and more than 1.03 on 0.2 %, up to twice as
+// many tokens 0.98 and 17 %, beyond 1.7; 17 .. 128 experts, 16 .. 4096 tokens (2128) 0.88 and 0.1 %, 0.98, 1.2 - 2.  It multiplies on the
+// vector units, so large ones stay on the matrix cores: 8192 tokens, 64 experts, d 2048 (1.1e9 multiply-adds of either result) lengthened
+// the weight gradients by 100 us for 53 us of launches.
 static bool router_joins(const RouterSmallArgs& R, const WgradArgs& A) {
-  if (R.E > 16) return false;
+  if (R.E > W_ROUTER_EXPERTS || (double)R.T * R.E * R.d > W_ROUTER_MACS) return false;
   const double longest = R.T * (R.E <= 8 ? W_ROUTER_US8 : W_ROUTER_US16), stores = 12.0 * A.Et * A.f_expert_stride / W_STORE_BYTES_PER_US;
   return longest <= W_ROUTER_SLACK_US + 0.7 * stores;
 }
@@ -381,7 +385,7 @@ bool launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
   J.dw = A;
   if (router && router_joins(*router, A)) {
     J.router = *router;
-    J.router_blocks = (router_small_plan(J.router, 4) + W_XCDS - 1) / W_XCDS * W_XCDS;
+    J.router_blocks = (router_small_plan(J.router, 4, router->E <= 8 ? 8 : 16) + W_XCDS - 1) / W_XCDS * W_XCDS;
   }
   if (dx_tiles > 0) {
     J.dx = dx;

@@ -208,11 +208,12 @@ def test_router_and_gating_in_one(moe, T, d, E, k, Es, renorm, one_launch):
     assert torch.equal(idx, idx1) and all(torch.equal(a, b) for a, b in zip(two, one))
 
 
-# the router's blocks before dX on 64-row tiles and on those of 128 columns, and with dX in a launch of its own, for up to 8 and 16 experts;
-# too many tokens for the weight gradients beside them, too many experts
+# the router's blocks before dX on 64-row tiles and on those of 128 columns, and with dX in a launch of its own, for up to 8, 16 and several
+# times 16 experts; too many tokens for the weight gradients beside them, too many experts
 @pytest.mark.parametrize("d,f,counts,joined", [
     (512, 1024, [64] * 8, True), (64, 128, [5] * 15 + [0], True), (1088, 1984, [100] * 13, True), (2560, 1600, [500, 0, 700, 1], True),
-    (4096, 8192, [2048, 2048], True), (64, 64, [512] * 8, False), (1024, 1024, [4] * 17, False),
+    (4096, 8192, [2048, 2048], True), (1024, 1024, [4] * 17, True), (192, 320, [0, 7] * 50, True),
+    (64, 64, [512] * 8, False), (128, 128, [2] * 129, False),
 ])
 def test_router_backward_beside_the_weight_gradients(moe, d, f, counts, joined):
     """What the two calls give: the experts' results bit for bit, the router's against fp64 (dx is one rounding to bf16 of sums in fp32 or of
