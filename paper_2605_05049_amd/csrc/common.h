@@ -44,8 +44,10 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Workspace carve-up.  Every region starts 256-byte aligned.
 //   perm_hist : per-block expert histograms of the counting sort, then turned into per-block bases
 //   perm_rank : rank of every slot among the same-expert slots of its block
-//   sched     : tile schedule of the grouped GEMMs (header + two int arrays + experts by row count)
+//   sched     : tile schedule of the grouped GEMMs (64 int32, {expert, its first tile, its first row, the row after its last} of every tile; the
+//               router's segments)
 //   sched_few : the same for those GEMMs of a call that run on the 64-row tiles
+//   order     : {expert, its first row, the row after its last} by descending row count, for the weight gradients
 //   zero_page : 256 zero bytes, the source of k-rows past the end of a ragged contraction
 //   h, dg, du : bf16 [N,f] intermediates of the expert FFN (H in forward; H, dG, dU in backward): with x_perm these are
 //               the 3 d_ffn + d_model values per row of the activation-memory model of Section III-A
@@ -53,6 +55,7 @@ struct WsLayout {
   size_t perm_hist, perm_hist_bytes;
   size_t perm_rank, perm_rank_bytes;
   size_t sched, sched_few, sched_bytes;
+  size_t order;
   size_t zero_page;
   size_t splitk_counters;   // kSplitCounters int32: arrivals per split tile
   size_t splitk_partial;    // kSplitParts fp32 tiles of up to 320 x 256: partial sums of the tiles whose K range is split
@@ -91,9 +94,10 @@ inline WsLayout ws_layout(const Dims& D) {
   L.perm_rank = off;
   L.perm_rank_bytes = round_up((size_t)D.N * sizeof(int32_t) + 256, 256);
   off += L.perm_rank_bytes;
-  L.sched_bytes = round_up((size_t)(64 + 2 * sched_max_tiles(D) + kMaxExperts) * sizeof(int32_t), 256);
+  L.sched_bytes = round_up((size_t)(64 + 4 * sched_max_tiles(D) + kMaxExperts) * sizeof(int32_t), 256);
   L.sched = off; off += L.sched_bytes;
   L.sched_few = off; off += L.sched_bytes;
+  L.order = off; off += kMaxExperts * sizeof(int4);
   L.zero_page = off;
   off += 256;
   L.splitk_counters = off;
@@ -146,12 +150,11 @@ constexpr int kMidCols = 128;                 // columns of a tile (of a pair 64
 enum RowTileKind { ROWTILE_GATE_UP = 0, ROWTILE_DOWN = 1, ROWTILE_DH = 2, ROWTILE_DX = 3 };
 constexpr int kFewSelfExperts = 2 * kWave;    // experts at most for whose tiles the kernels need no schedule
 struct RowTileArgs {
-  const int32_t* sched;    // [0] = number of row tiles; [64 + u] = expert of tile u; [64 + max_tiles + u] = its first tile.  Null: the
+  const int32_t* sched;    // [0] = number of row tiles; [64 + 4 u ..] = expert of tile u, its first tile, its rows.  Null: the
                            // blocks find their tiles from the offsets of Et <= kFewSelfExperts experts
   int Et;
-  int32_t* order;          // dH without a schedule writes what the weight gradients read of one: [Et] experts by descending row count
+  int4* order;             // dH without a schedule writes what the weight gradients read: [Et] experts and their rows by descending row count
   uint32_t* zero_page;     // ... and clears these 256 bytes
-  int max_tiles;
   const int32_t* offsets;  // [E'+1]
   long long rows;          // of all experts together
   int n_q_tiles, chunk_log2;   // filled by the launcher
@@ -177,8 +180,7 @@ struct WgradProblem {
   int n_p_tiles, n_q_tiles, band, chunks;   // filled by the launcher
 };
 struct WgradArgs {
-  const int32_t* offsets;      // [Et + 1]
-  const int32_t* order;        // [Et] experts by descending row count
+  const int4* order;           // [Et] {expert, its first row, the row after its last} by descending row count
   const uint16_t* zero_page;   // 256 zeroed bytes: source of k-rows past the end of a ragged contraction
   int Et, accumulate;
   long long rows;              // of all experts together

@@ -127,14 +127,14 @@ struct ExpertTiles {
 // What the weight gradients read of a schedule, where there is none: the experts by descending row count (ties: lower id first), a zero page.
 __device__ __forceinline__ void write_expert_order(const RowTileArgs& A, char* lds, int tid) {
   int* const rows_of = reinterpret_cast<int*>(lds);
-  const int n = tid < A.Et ? A.offsets[tid + 1] - A.offsets[tid] : 0;
+  const int lo = tid < A.Et ? A.offsets[tid] : 0, n = tid < A.Et ? A.offsets[tid + 1] - lo : 0;
   if (tid < kFewSelfExperts) rows_of[tid] = n;
   if (tid < 64) A.zero_page[tid] = 0u;
   __syncthreads();
   if (tid < A.Et) {
     int rank = 0;
     for (int o = 0; o < A.Et; o++) rank += (rows_of[o] > n) || (rows_of[o] == n && o < tid);
-    A.order[rank] = tid;
+    A.order[rank] = make_int4(tid, lo, lo + n, 0);
   }
 }
 
@@ -173,15 +173,17 @@ __device__ __forceinline__ void few_rows_block(const RowTileArgs& A, char* lds, 
   // dealt round-robin to the XCDs
   const int within = (int)(block / F_XCDS), xcd = (int)(block % F_XCDS);
   const int cl = A.chunk_log2;
-  const long long lid = (((long long)(within >> cl) * F_XCDS + xcd) << cl) + (within & ((1 << cl) - 1));
-  const int ut = (int)(lid / A.n_q_tiles);   // some row tile of the expert this block works for
+  // (a grid has fewer than 2^32 threads, so its tiles are counted in 32 bits; see wgrad_block)
+  const int lid = (((within >> cl) * F_XCDS + xcd) << cl) + (within & ((1 << cl) - 1));
+  const int ut = lid / A.n_q_tiles;          // some row tile of the expert this block works for
   int expert, first, e_lo, e_hi;             // first: index of the expert's first row tile
   if (A.sched) {
     if (ut >= A.sched[0]) return;
-    expert = A.sched[64 + ut];
-    first = A.sched[64 + A.max_tiles + ut];
-    e_lo = A.offsets[expert];
-    e_hi = A.offsets[expert + 1];
+    const int4 tile = reinterpret_cast<const int4*>(A.sched + 64)[ut];
+    expert = tile.x;
+    first = tile.y;
+    e_lo = tile.z;
+    e_hi = tile.w;
   } else {
     // One expert per lane, twice: where the running sum of their row tiles passes ut is the expert.  (A schedule is a launch of its
     // own, 4 - 5 us, and three loads that wait for each other in every block; these are four that do not, and a sum over the
@@ -195,7 +197,7 @@ __device__ __forceinline__ void few_rows_block(const RowTileArgs& A, char* lds, 
     X.find(ut, expert, first, e_lo, e_hi);
   }
   const int e_tiles = (e_hi - e_lo + FP - 1) / FP;
-  const int local = (int)(lid - (long long)first * A.n_q_tiles);
+  const int local = lid - first * A.n_q_tiles;
   const int qt = local / e_tiles, mt = local - qt * e_tiles;
   const int p_row0 = e_lo + mt * FP, p_valid = min(FP, e_hi - p_row0);
   const int q0_col = qt * FQ;   // (widths are multiples of 64: a tile has all its columns)

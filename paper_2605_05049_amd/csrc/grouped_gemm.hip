@@ -73,9 +73,9 @@ enum Epilogue { EPI_BF16 = 0, EPI_SWIGLU = 1, EPI_DSWIGLU = 2, EPI_F32 = 3,
 
 struct GemmArgs {
   // row-tile problems (forward / dgrad): schedule built on the device
-  const int32_t* sched;    // [0] = number of row tiles; [64 + u] = expert of tile u; [64 + max_tiles + u] = its first tile
+  const int32_t* sched;    // [0] = number of row tiles; [64 + 4 u ..] = expert of tile u, its first tile, its first row, the row after its last
   int max_tiles;
-  const int32_t* offsets;  // [E'+1]
+  const int32_t* offsets;  // [E'+1]  (router)
   int n_q_tiles;           // tiles along q
   int q_dim;               // extent of q (output columns)
   int k_dim;               // contraction length per pass (row-tile problems); unused for the weight gradient
@@ -279,18 +279,19 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     // heights (contiguous runs had handed a whole expert, with its tall or short tiles, to one XCD).  What is left after
     // the last complete deal of 8 groups (fewer than 256 tiles) is cut into 8 equal runs, one per XCD.
     const int n_row_tiles = A.sched[0];
-    const long long total = (long long)n_row_tiles * A.n_q_tiles;
-    const long long within = blockIdx.x / kNumXcd;
+    // (a grid has fewer than 2^32 threads, so its tiles are counted in 32 bits; see wgrad_block)
+    const int total = n_row_tiles * A.n_q_tiles;
+    const int within = blockIdx.x / kNumXcd;
     const int xcd = blockIdx.x % kNumXcd;
-    const long long deals = total / (kCusPerXcd * kNumXcd);          // rounds of 32 tiles every XCD gets
-    const long long dealt = deals * kCusPerXcd;                       // ... = tiles per XCD from the deals
-    const long long rest = total - dealt * kNumXcd;                   // < 256 tiles left over
-    const long long chunk = (rest + kNumXcd - 1) / kNumXcd;           // <= 32 per XCD
-    const long long lo = dealt * kNumXcd + (long long)xcd * chunk;
-    const long long cnt = max(min(chunk, total - lo), 0LL);           // left-over tiles of this XCD
-    long long full = cnt;
+    const int deals = total / (kCusPerXcd * kNumXcd);          // rounds of 32 tiles every XCD gets
+    const int dealt = deals * kCusPerXcd;                       // ... = tiles per XCD from the deals
+    const int rest = total - dealt * kNumXcd;                   // < 256 tiles left over
+    const int chunk = (rest + kNumXcd - 1) / kNumXcd;           // <= 32 per XCD
+    const int lo = dealt * kNumXcd + xcd * chunk;
+    const int cnt = max(min(chunk, total - lo), 0);             // left-over tiles of this XCD
+    int full = cnt;
     if (SPLITK) {
-      const int rem = (int)(cnt % kCusPerXcd);
+      const int rem = cnt % kCusPerXcd;
       const int nk_all = ((A.k_dim + BK - 1) / BK) * NPASS;
       const bool rows_first = SPLIT_ROWS && A.rows >= (long long)kRowCutRows * n_row_tiles;
       if (rem > 0 && rem <= kCusPerXcd / 2 && nk_all >= (rows_first ? kRowCutSteps : MOE_SPLIT_MIN_STEPS)) {
@@ -299,13 +300,13 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
       }
     }
     if (SPLIT_ROWS && full == cnt && A.rows >= (long long)kRowCutLeast * n_row_tiles) {
-      const int rem = (int)(cnt % kCusPerXcd);
+      const int rem = cnt % kCusPerXcd;
       if (rem > 0 && rem <= kCusPerXcd / 2) {
         row_parts = min(kCusPerXcd / rem, (TILE + 64) / 64);
         full = cnt - rem;
       }
     }
-    long long lid;
+    int lid;
     if (within < dealt) {
       lid = ((within / kCusPerXcd) * kNumXcd + xcd) * kCusPerXcd + within % kCusPerXcd;
       split = row_parts = 1;
@@ -313,29 +314,29 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
       lid = lo + (within - dealt);
       split = row_parts = 1;
     } else if (SPLIT_ROWS && row_parts > 1) {
-      const long long u = within - dealt - full;
+      const int u = within - dealt - full;
       if (u >= (cnt - full) * row_parts) return;
       lid = lo + full + u / row_parts;
-      row_part = (int)(u % row_parts);
+      row_part = u % row_parts;
     } else {
-      const long long u = within - dealt - full;
+      const int u = within - dealt - full;
       if (u >= (cnt - full) * split) return;
       lid = lo + full + u / split;
-      part = (int)(u % split);
-      part_slot = xcd * kCusPerXcd + (int)u;
+      part = u % split;
+      part_slot = xcd * kCusPerXcd + u;
     }
-    const int u = (int)(lid / A.n_q_tiles);  // some row tile of the expert this block works for
-    expert = A.sched[64 + u];
-    const int e_lo = A.offsets[expert], e_hi = A.offsets[expert + 1];
+    const int4 tile = reinterpret_cast<const int4*>(A.sched + 64)[lid / A.n_q_tiles];   // some row tile of the expert this block works for
+    expert = tile.x;
+    const int first = tile.y;   // index of the expert's first row tile
+    const int e_lo = tile.z, e_hi = tile.w;
     const int e_tiles = row_tiles_of(e_hi - e_lo, A.sched[1]);
-    const int first = A.sched[64 + A.max_tiles + u];  // index of the expert's first row tile
     // Order inside an expert: column tile after column tile, each with all its row tiles (32 consecutive tiles, which
     // an XCD runs together, are then about 8 row tiles x 4 column tiles: 8 + 4 panels), a tall last row tile first.
     // Blocks are handed to CUs in order as CUs become free, so a tile that takes longer should come early in its
     // group of 32: an expert of at most 4 row tiles, whose 8 column tiles fill a group, is therefore walked row
     // tile after row tile inside each band of 8 column tiles (the same 32 tiles, the 8 tall ones first: the CUs that
     // ran the previous group's tall tiles then get ordinary ones).
-    const int local = (int)(lid - (long long)first * A.n_q_tiles);
+    const int local = lid - first * A.n_q_tiles;
     int qt, m;
     if (e_tiles <= 4) {
       const int band = local / (e_tiles * 8), in_band = local % (e_tiles * 8);
@@ -382,7 +383,7 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
     const long long within = blockIdx.x / kNumXcd;
     const long long sid = (within >> 5) * kNumXcd + (blockIdx.x % kNumXcd);
     if (sid >= n_super) return;
-    expert = A.sched[64 + 2 * A.max_tiles + (int)(sid / supers_per_e)];  // the (sid / supers_per_e)-th largest expert
+    expert = A.sched[64 + 4 * A.max_tiles + (int)(sid / supers_per_e)];  // the (sid / supers_per_e)-th largest expert
     const int super = (int)(sid % supers_per_e), in_super = (int)(within & 31);
     const int pt = (super % sp) * 8 + (in_super & 7);
     const int qt = (super / sp) * 4 + (in_super >> 3);
@@ -900,8 +901,8 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 }
 
 // Row-tile schedule: one thread per expert.  sched[0] = number of row tiles; sched[1] = how experts are cut into
-// row tiles (TileMode); sched[2] = the XCD that block 0 runs on; sched[64 + u] = expert of tile u;
-// sched[64 + max_tiles + u] = index of that expert's first tile; sched[64 + 2 max_tiles + i] = expert with the i-th most rows.
+// row tiles (TileMode); sched[2] = the XCD that block 0 runs on; sched[64 + 4 u ..] = expert of tile u, its first tile,
+// its first row and the row after its last; `order` (may be null) = the experts and their rows by descending row count.
 // Block 0 builds `sched` and also clears the zero page and the split-tile counters; block 1, of a call whose GEMMs do not all
 // run on the same tiles, builds `sched_few` for the 64-row ones.
 // (A launch in front of the GEMMs of every FFN call that has one on 256-row tiles, or more than kFewSelfExperts experts: bound
@@ -909,11 +910,11 @@ __global__ __launch_bounds__(NTHREADS) void grouped_gemm_kernel(const GemmArgs A
 // shuffles, two barriers: 3.7 -> 2.5 us at E' = 8, 5.4 -> 4.8 at 66, 8.3 -> 7.1 at 128 against 1024 threads and a scan in LDS.)
 __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
                                                               int32_t* __restrict__ sched_few, uint32_t* __restrict__ zero_page,
-                                                              int32_t* __restrict__ counters, int Et, int max_tiles, int mode) {
+                                                              int32_t* __restrict__ counters, int4* __restrict__ order, int Et, int max_tiles, int mode) {
   __shared__ int32_t rows_of[kMaxExperts];
   __shared__ int32_t wave_total[kMaxExperts / kWave];
   const int e = threadIdx.x, lane = e % kWave, wv = e / kWave;
-  const int n = (e < Et) ? offsets[e + 1] - offsets[e] : 0;
+  const int lo = (e < Et) ? offsets[e] : 0, n = (e < Et) ? offsets[e + 1] - lo : 0;
   if (blockIdx.x == 0) {
     if (e < 64) zero_page[e] = 0u;
     for (int i = e; i < kSplitCounters; i += blockDim.x) counters[i] = 0;
@@ -938,37 +939,33 @@ __global__ __launch_bounds__(1024) void build_schedule_kernel(const int32_t* __r
     sched[2] = (int)((xcc_id() + kNumXcd - blockIdx.x) % kNumXcd);
   }
   if (e == (int)blockDim.x - 1) sched[0] = incl;
-  if (e < Et) {
-    // experts by descending row count (ties: lower id first): sched[64 + 2 max_tiles + rank] = expert
+  if (e < Et && blockIdx.x == 0 && order) {   // experts by descending row count (ties: lower id first)
     int rank = 0;
 #pragma unroll 8
     for (int o = 0; o < Et; o++) {
       const int r = rows_of[o];
       rank += (r > n) || (r == n && o < e);
     }
-    sched[64 + 2 * max_tiles + rank] = e;
+    order[rank] = make_int4(e, lo, lo + n, 0);
   }
   // An expert's first tiles are written by its own thread, the others by its wavefront: a thread needs 0.05 us per tile of its
   // own, the wavefront 0.15 per expert (one expert of 24838 rows in 64-row tiles: 25 us by its thread alone, 6.9 this way;
   // 128 experts of 469 rows: 8, and 18 with 4 tiles each left to the thread).
   constexpr int OWN = 32;
-  auto put = [&](int u, int expert, int its_first) __attribute__((always_inline)) {
-    if (u < max_tiles) {
-      sched[64 + u] = expert;
-      sched[64 + max_tiles + u] = its_first;
-    }
+  auto put = [&](int u, int4 tile) __attribute__((always_inline)) {
+    if (u < max_tiles) reinterpret_cast<int4*>(sched + 64)[u] = tile;
   };
-  for (int i = 0; i < min(nt, OWN); i++) put(first + i, e, first);
+  for (int i = 0; i < min(nt, OWN); i++) put(first + i, make_int4(e, first, lo, lo + n));
   for (unsigned long long big = __ballot(nt > OWN); big != 0; big &= big - 1) {
     const int l = __builtin_ctzll(big);
-    const int b_first = __shfl(first, l, kWave), b_nt = __shfl(nt, l, kWave);
-    for (int i = OWN + lane; i < b_nt; i += kWave) put(b_first + i, e - lane + l, b_first);
+    const int b_first = __shfl(first, l, kWave), b_nt = __shfl(nt, l, kWave), b_lo = __shfl(lo, l, kWave), b_n = __shfl(n, l, kWave);
+    for (int i = OWN + lane; i < b_nt; i += kWave) put(b_first + i, make_int4(e - lane + l, b_first, b_lo, b_lo + b_n));
   }
 }
 static void launch_schedule(const char* label, hipStream_t st, const int32_t* offsets, int32_t* sched, int32_t* sched_few, uint32_t* zero_page,
-                            int32_t* counters, int Et, int max_tiles, TileMode mode) {
+                            int32_t* counters, int4* order, int Et, int max_tiles, TileMode mode) {
   const dim3 grid(sched_few ? 2 : 1), block((unsigned)round_up((size_t)Et, kWave));   // (Et <= kMaxExperts = 1024)
-  MOE_LAUNCH(label, st, build_schedule_kernel, grid, block, 0, st, offsets, sched, sched_few, zero_page, counters, Et, max_tiles, mode);
+  MOE_LAUNCH(label, st, build_schedule_kernel, grid, block, 0, st, offsets, sched, sched_few, zero_page, counters, order, Et, max_tiles, mode);
 }
 
 // Blocks of a weight-gradient launch: whole rounds of one 32-tile super-tile per XCD.
@@ -1114,6 +1111,7 @@ struct RowGemms {
   const int32_t* offsets;
   int max_tiles;
   bool any_few, any_tall;   // GEMMs of this call on either kind of tile
+  bool backward;            // (with weight gradients, which read the experts by rows)
   int32_t* sched_tall;
   int32_t* sched_few;
   uint32_t* zero_page;
@@ -1123,7 +1121,7 @@ struct RowGemms {
       : D(D_), L(L_), ws(static_cast<char*>(ws_)), st(st_), offsets(offsets_), max_tiles((int)sched_max_tiles(D_)),
         any_few(row_tiles_for(D_, first) == ROWTILES_FEW || row_tiles_for(D_, second) == ROWTILES_FEW),
         any_tall(row_tiles_for(D_, first) == ROWTILES_TALL || row_tiles_for(D_, second) == ROWTILES_TALL),
-        sched_tall(reinterpret_cast<int32_t*>(ws + L_.sched)), sched_few(reinterpret_cast<int32_t*>(ws + L_.sched_few)),
+        backward(first == ROWTILE_DH), sched_tall(reinterpret_cast<int32_t*>(ws + L_.sched)), sched_few(reinterpret_cast<int32_t*>(ws + L_.sched_few)),
         zero_page(reinterpret_cast<uint32_t*>(ws + L_.zero_page)),
         counters(reinterpret_cast<int32_t*>(ws + L_.splitk_counters)) {}
 
@@ -1134,13 +1132,13 @@ struct RowGemms {
   void schedule() const {
     if (self_scheduled()) return;
     launch_schedule("ffn_schedule", st, offsets, any_tall ? sched_tall : sched_few, any_tall && any_few ? sched_few : nullptr, zero_page, counters,
-                    D.Et, max_tiles, any_tall ? TILES_TALL : TILES_FEW);
+                    backward ? experts_by_rows() : nullptr, D.Et, max_tiles, any_tall ? TILES_TALL : TILES_FEW);
   }
-  const int32_t* experts_by_rows() const { return (any_tall ? sched_tall : sched_few) + 64 + 2 * max_tiles; }
+  int4* experts_by_rows() const { return reinterpret_cast<int4*>(ws + L.order); }
 
   // what every launch on the 64-row tiles takes
   void prepare_few(RowTileArgs& R) const {
-    R.max_tiles = max_tiles; R.offsets = offsets;
+    R.offsets = offsets;
     R.q_expert_stride = (size_t)D.d * D.f;
     R.sched = self_scheduled() ? nullptr : sched_few;
     R.Et = D.Et; R.rows = D.N;
@@ -1157,7 +1155,7 @@ struct RowGemms {
   int launch(const char* label, RowTileKind kind, RowTileArgs R) const {
     const RowTiles on = row_tiles_for(D, kind);
     if (kind == ROWTILE_DH && self_scheduled()) {
-      R.order = sched_few + 64 + 2 * max_tiles;
+      R.order = experts_by_rows();
       R.zero_page = zero_page;
     }
     if (on == ROWTILES_MID) {
@@ -1283,7 +1281,7 @@ static int grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_perm, cons
     MOE_TRY(G.dh("ffn_bwd_dh_dswiglu", dy_perm, w_down, save_g, save_u, dg, du, h));
   }
   WgradArgs W = {};
-  W.offsets = offsets; W.order = G.experts_by_rows(); W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
+  W.order = G.experts_by_rows(); W.zero_page = reinterpret_cast<const uint16_t*>(G.zero_page);
   W.Et = D.Et; W.accumulate = accumulate ? 1 : 0; W.rows = D.N; W.f_expert_stride = (size_t)D.f * D.d;
   // dWg[e], dWu[e] = X_e^T dG_e, X_e^T dU_e   (rows d, columns f)
   W.problem[0].p0 = x_perm; W.problem[0].p_ld = D.d; W.problem[0].p_dim = D.d;
@@ -1356,7 +1354,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   const int ldp = (int)round_up((size_t)D.E, 4);
   const int S = router_dw_parts(D);
   const int part_rows = (int)round_up((size_t)((D.T + S - 1) / S), 64);
-  launch_router_prepare(st, dlogits, w_router, dl_hi, dl_lo, skinny_dx ? w_t : nullptr, offs, sched + 64 + 2 * max_tiles, zero_page,
+  launch_router_prepare(st, dlogits, w_router, dl_hi, dl_lo, skinny_dx ? w_t : nullptr, offs, sched + 64 + 4 * max_tiles, zero_page,
                         (int)D.T, (int)D.E, Epad, Ek, (int)D.d, (int)S, part_rows);
   GemmArgs A = {};
   A.sched = sched; A.max_tiles = max_tiles; A.Et = 1;
@@ -1367,7 +1365,7 @@ extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const u
   } else {
     // dx_router[T,d] = dlogits W_r on the grouped GEMM kernel: rows = tokens, columns = d, K = E in two passes (head,
     // remainder of dlogits); P K-contiguous in the padded copies, Q = W_r read with k = expert row (R-contiguous)
-    launch_schedule("router_schedule", st, offs, sched, nullptr, zero_page, counters, 1, max_tiles, TILES_PLAIN);
+    launch_schedule("router_schedule", st, offs, sched, nullptr, zero_page, counters, nullptr, 1, max_tiles, TILES_PLAIN);
     A.offsets = offs;
     A.n_q_tiles = (D.d + TILE - 1) / TILE; A.q_dim = D.d; A.k_dim = D.E;
     A.p0 = dl_hi; A.p1 = dl_lo; A.p_ld = Epad;
