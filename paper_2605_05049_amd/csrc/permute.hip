@@ -12,6 +12,8 @@
 // The copy kernels are pure HBM streaming with 16-byte accesses per lane.
 #include "common.h"
 
+#include <type_traits>
+
 #include <mutex>
 
 namespace moe {
@@ -257,29 +259,39 @@ template <bool NT> __device__ __forceinline__ void st_row(u32x4* p, u32x4 v) {
 // ---------------------------------------------------------------------------------------------------------
 // 3. scatter the maps and gather the rows
 // ---------------------------------------------------------------------------------------------------------
-// RANKS: the whole sort in this launch, for so few slots that ranking them again in every wavefront costs less than the launches in
+// RANKS: the whole sort in this launch, for so few slots that ranking them again in every block costs less than the launches in
 // front (3 .. 5 us each with their gaps, bound by latency).  With key = expert x 4096 + slot the row of a slot is the number of smaller
-// keys, which ballots count 64 at a time for all K' slots of a token: one round trip to memory, and neither LDS nor a barrier.  One block
-// more adds up the experts' counts.  A wavefront's time grows with N K' and that of all of them with their number times N, hence the two
-// limits.  Graph of calls, us, N slots, K' per token, E' experts, d (before / ranked here):
-//   128, 8, 66, 2048: 7.1 / 3.8     512, 2, 8, 512: 5.8 / 3.2       1024, 2, 64, 2048: 7.2 / 4.5     1536, 1, 64, 4096: 9.5 / 8.3
-//   2048, 8, 128, 4096: 12.5 / 10.8     2896, 2, 100, 1024: 10.8 / 8.9     4012, 4, 14, 1088: 12.6 / 11.8    4096, 4, 8, 512: 11.2 / 9.1
-// and beyond them 2880, 8, 64, 7168: 18.6 / 18.3   3500, 5, 100, 2048: 13.2 / 13.7    4096, 8, 66, 512: 11.7 / 13.2 (N K')
-//   2048, 1, 64, 4096: 11.3 / 11.8 (2048 tokens of 4 wavefronts)   4096, 1, 64, 512: 10.3 / 11.6 (4096 tokens).
+// keys, which ballots count 64 at a time.  Up to 512 slots every wavefront compares all keys with the K' slots of its token (kRankAlone): one
+// round trip to memory, and neither LDS nor a barrier.  With more the four wavefronts of a block take a quarter of the keys each, for the
+// slots of all its RANKS = 4 / parts tokens, and the counts meet in LDS: a quarter of the round trips, and where a row has several parts their
+// wavefronts no longer all rank the same token.  One block more adds up the experts' counts.  Graph of calls, us, N slots, K' per token, E'
+// experts, d (launches before the scatter / every wavefront by itself / quarters):
+//   128, 8, 66, 2048: 7.0 / 3.8 / 4.2     512, 2, 8, 512: 5.6 / 3.1 / 3.6       1024, 2, 64, 2048: 6.9 / 4.4 / 3.6    1024, 4, 14, 1088: 7.2 / 4.7 / 4.4
+//   2048, 8, 128, 4096: 12.2 / 10.6 / 7.2    2896, 2, 100, 1024: 10.5 / 8.7 / 5.3   4012, 4, 14, 1088: 12.5 / 11.4 / 6.9    4096, 4, 8, 512: 11.1 / 8.8 / 7.0
+//   4096, 1, 64, 4096: 19.3 before / 13.4    4096, 8, 66, 4096: 16.8 / 10.6   3500, 5, 100, 2048: 12.7 / 7.0
+// Rows of one part keep the limits that the first form had, on what all wavefronts compare (N K' and tokens x N).
+constexpr int kRankAlone = 8, kRankedAlone = 512;
 constexpr int kRankedSlots = 4096, kRankedExperts = 128, kRankedSlotsPerToken = 8;   // at most
 constexpr int kRankedOwnKeys = 16384;          // N K' at most
 constexpr int kRankedSlotsAlways = 1536;
-constexpr long long kRankedKeys = 1ll << 23;   // with more slots than that: wavefronts x N at most
+constexpr long long kRankedKeys = 1ll << 23;   // with more slots than that: tokens x N at most
 static bool perm_is_ranked_by_scatter(const Dims& D, int parts) {
-  return D.N > 0 && D.N <= kRankedSlots && D.Et <= kRankedExperts && D.Kp <= kRankedSlotsPerToken && D.N * D.Kp <= kRankedOwnKeys &&
-         (D.N <= kRankedSlotsAlways || (long long)D.T * parts * D.N <= kRankedKeys);
+  return D.N > 0 && D.N <= kRankedSlots && D.Et <= kRankedExperts && D.Kp <= kRankedSlotsPerToken &&
+         (parts > 1 || (D.N * D.Kp <= kRankedOwnKeys && (D.N <= kRankedSlotsAlways || (long long)D.T * D.N <= kRankedKeys)));
 }
 __device__ __forceinline__ void count_experts(const int32_t* __restrict__ topk_idx, int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int N, int Et) {
   __shared__ int32_t hist[kRankedExperts];   // (sums of ones: the same whatever their order)
   const int tid = threadIdx.x;
   if (tid < kRankedExperts) hist[tid] = 0;
   __syncthreads();
-  for (int i = tid; i < N; i += 256) atomicAdd(&hist[clamp_expert(topk_idx[i], Et)], 1);
+  for (int i0 = 0; i0 < N; i0 += 8 * 256) {
+    int id[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) id[j] = topk_idx[min(i0 + j * 256 + tid, N - 1)];
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+      if (i0 + j * 256 + tid < N) atomicAdd(&hist[clamp_expert(id[j], Et)], 1);
+  }
   __syncthreads();
   if (tid >= kWave) return;
   static_assert(kRankedExperts == 2 * kWave, "two experts per lane");
@@ -301,29 +313,65 @@ __device__ __forceinline__ void count_experts(const int32_t* __restrict__ topk_i
   if (tid == 0) offsets[Et] = N;
 }
 
-template <int KP, bool RANKS>
+template <int KP, int RANKS>
 __global__ __launch_bounds__(256) void perm_scatter_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ topk_idx,
                                                            const int32_t* __restrict__ lrank, const int32_t* __restrict__ block_base,
                                                            u32x4* __restrict__ x_perm, int32_t* __restrict__ row_of_slot,
                                                            int32_t* __restrict__ slot_of_row, int32_t* __restrict__ counts,
                                                            int32_t* __restrict__ offsets, int T, int Kp, int Et, int dvec, int parts) {
   static_assert(!RANKS || KP > 0, "the ranking form keeps a token's slots in registers");
-  if constexpr (RANKS) {
+  constexpr bool SHARED = RANKS > 0 && RANKS != kRankAlone;
+  if constexpr (RANKS > 0) {
     if (blockIdx.x == gridDim.x - 1) {
       count_experts(topk_idx, counts, offsets, T * KP, Et);
       return;
     }
   }
   const int lane = threadIdx.x % kWave;
-  const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + threadIdx.x / kWave);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int wid = blockIdx.x * 4 + wave;
   const int t = wid / parts, part = wid % parts;
+  __shared__ int32_t smaller[4][SHARED ? RANKS * KP : 1];   // [quarter of the keys][slot of the block's]
+  if constexpr (SHARED) {
+    constexpr int OWN = RANKS * KP;
+    const int N = T * KP, s0 = blockIdx.x * OWN;
+    const int mine = min(s0 + lane % OWN, N - 1);
+    const int my_key = clamp_expert(topk_idx[mine], Et) * kRankedSlots + mine;   // lane i: of slot s0 + i (repeated)
+    const int quarter = (N + 4 * kWave - 1) / (4 * kWave) * kWave;
+    const int end = min(N, (wave + 1) * quarter);
+    int count[OWN];
+#pragma unroll
+    for (int i = 0; i < OWN; i++) count[i] = 0;
+    constexpr int AHEAD = 8;
+    for (int i0 = wave * quarter; i0 < end; i0 += AHEAD * kWave) {
+      int key[AHEAD];
+#pragma unroll
+      for (int g = 0; g < AHEAD; g++) key[g] = topk_idx[min(i0 + g * kWave + lane, N - 1)];
+#pragma unroll
+      for (int g = 0; g < AHEAD; g++) {
+        const int i = i0 + g * kWave + lane;
+        key[g] = i < end ? clamp_expert(key[g], Et) * kRankedSlots + i : 0x7fffffff;
+      }
+#pragma unroll
+      for (int i = 0; i < OWN; i++) {
+        const int own = __builtin_amdgcn_readlane(my_key, i);
+#pragma unroll
+        for (int g = 0; g < AHEAD; g++) count[i] += __popcll(__ballot(key[g] < own));
+      }
+    }
+    int all = count[0];
+#pragma unroll
+    for (int i = 1; i < OWN; i++) all = lane == i ? count[i] : all;
+    if (lane < OWN) smaller[wave][lane] = all;
+    __syncthreads();
+  }
   if (t >= T) return;
   const int part_len = (dvec + parts - 1) / parts;
   const int v_begin = part * part_len, v_end = min(dvec, v_begin + part_len);
   const u32x4* src = x ? x + (size_t)t * dvec : nullptr;
   if (KP > 0) {
     int rows[KP > 0 ? KP : 1];
-    if constexpr (RANKS) {
+    if constexpr (RANKS == kRankAlone) {
       int own[KP];
 #pragma unroll
       for (int j = 0; j < KP; j++) {
@@ -332,9 +380,7 @@ __global__ __launch_bounds__(256) void perm_scatter_kernel(const u32x4* __restri
         rows[j] = 0;
       }
       const int N = T * KP;
-      // Groups of 64 keys in flight.  Their ballots are scalar registers, of which 8 groups of 6 and more slots have too few (29 .. 65 were
-      // spilt).  moe_permute, time of that of three launches, 8 groups / 4: 8 slots per token 0.75 .. 1.04 / 0.69 .. 0.95, 7: 0.76 .. 0.97 /
-      // 0.71 .. 0.95, 6: 0.71 .. 0.91 / 0.67 .. 0.91; 5, with 4 spilt: 0.67 .. 1.03 / 0.66 .. 1.05.
+      // Groups of 64 keys in flight.  (Their ballots are scalar registers, of which 8 groups of 6 and more slots have too few.)
       constexpr int AHEAD = KP <= 5 ? 8 : 4;
       for (int i0 = 0; i0 < N; i0 += AHEAD * kWave) {
         int id[AHEAD];
@@ -347,6 +393,14 @@ __global__ __launch_bounds__(256) void perm_scatter_kernel(const u32x4* __restri
 #pragma unroll
           for (int j = 0; j < KP; j++) rows[j] += __popcll(__ballot(key < own[j]));
         }
+      }
+    } else if constexpr (SHARED) {
+#pragma unroll
+      for (int j = 0; j < KP; j++) {
+        int sum = 0;
+#pragma unroll
+        for (int w = 0; w < 4; w++) sum += smaller[w][(t % RANKS) * KP + j];
+        rows[j] = __builtin_amdgcn_readfirstlane(sum);
       }
     } else {
 #pragma unroll
@@ -640,10 +694,17 @@ static int permute_launch(const Dims& D, const uint16_t* x, const int32_t* topk_
                           hipStream_t st) {
   const int parts = x ? row_parts(D.d / 8) : 1;
   if (perm_is_ranked_by_scatter(D, parts)) {
-    MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("perm_sort_scatter_gather", st, (perm_scatter_kernel<(KP > 0 ? KP : 1), true>), dim3(token_blocks(D.T, parts) + 1),
-                                     dim3(256), 0, st, reinterpret_cast<const u32x4*>(x), topk_idx, (const int32_t*)nullptr,
-                                     (const int32_t*)nullptr, reinterpret_cast<u32x4*>(x_perm), row_of_slot, slot_of_row, counts, offsets, D.T,
-                                     D.Kp, D.Et, D.d / 8, parts));
+    auto ranked = [&](auto tokens) {
+      constexpr int TOKENS = decltype(tokens)::value;   // of a block
+      MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("perm_sort_scatter_gather", st, (perm_scatter_kernel<(KP > 0 ? KP : 1), TOKENS>),
+                                       dim3(token_blocks(D.T, parts) + 1), dim3(256), 0, st, reinterpret_cast<const u32x4*>(x), topk_idx,
+                                       (const int32_t*)nullptr, (const int32_t*)nullptr, reinterpret_cast<u32x4*>(x_perm), row_of_slot, slot_of_row,
+                                       counts, offsets, D.T, D.Kp, D.Et, D.d / 8, parts));
+    };
+    if (D.N <= kRankedAlone) ranked(std::integral_constant<int, kRankAlone>{});
+    else if (parts == 4) ranked(std::integral_constant<int, 1>{});
+    else if (parts == 2) ranked(std::integral_constant<int, 2>{});
+    else ranked(std::integral_constant<int, 4>{});
     return launch_status();
   }
   const int nblk = perm_num_blocks(D.N);
@@ -661,7 +722,7 @@ static int permute_launch(const Dims& D, const uint16_t* x, const int32_t* topk_
     MOE_LAUNCH("perm_scan", st, perm_scan_kernel, dim3(1), dim3(1024), 0, st, block_hist, counts, offsets, nblk, D.Et);
   }
   if (D.T > 0) {
-    MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("perm_scatter_gather", st, (perm_scatter_kernel<KP, false>), dim3(token_blocks(D.T, parts)), dim3(256), 0, st,
+    MOE_DISPATCH_KP(D.Kp, MOE_LAUNCH("perm_scatter_gather", st, (perm_scatter_kernel<KP, 0>), dim3(token_blocks(D.T, parts)), dim3(256), 0, st,
                                      reinterpret_cast<const u32x4*>(x), topk_idx, lrank, block_hist, reinterpret_cast<u32x4*>(x_perm),
                                      row_of_slot, slot_of_row, counts, offsets, D.T, D.Kp, D.Et, D.d / 8, parts));
   }

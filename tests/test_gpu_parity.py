@@ -289,6 +289,23 @@ def test_permute_ranked_by_the_scatter(moe, T, d, E, k, Es, one_launch):
     assert ("perm_sort_scatter_gather" in labels, "perm_scatter_gather" in labels) == (one_launch, not one_launch)
 
 
+# the keys ranked in quarters by the wavefronts of a block (more than 512 slots): quarters of 128 + 1 and of whole groups of 64, blocks of 1, 2
+# and 4 tokens of which the last is not full, one to eight slots per token, and the most slots where a row has parts
+@pytest.mark.parametrize("T,d,E,k,Es,ranked", [(513, 2048, 5, 1, 0, True), (257, 1024, 7, 2, 0, True), (171, 64, 9, 3, 0, True), (256, 2048, 3, 2, 1, True),
+                                               (4096, 2048, 128, 1, 0, True), (4096, 1024, 2, 1, 0, True), (512, 2048, 12, 8, 0, True),
+                                               (585, 1024, 100, 7, 0, True), (1023, 512, 16, 4, 0, True), (683, 1088, 9, 5, 1, False)])
+def test_permute_ranked_in_quarters(moe, T, d, E, k, Es, ranked):
+    moe.profile_reset()
+    moe.profile_enable(True)
+    try:
+        test_permute_maps_rows_and_streams(moe, T, d, E, k, Es, "skewed")
+        labels = {label for label, _ in moe.profile_records()}
+    finally:
+        moe.profile_enable(False)
+        moe.profile_reset()
+    assert ("perm_sort_scatter_gather" in labels) == ranked   # (the maps alone, without rows, are a problem of one part)
+
+
 def test_permute_is_deterministic_over_100_runs(moe):
     """The order of equal keys never depends on scheduling: 100 runs of one larger shape (64 rank blocks, 128
     experts of which a fifth are empty and a tenth are hot), every output bit for bit the first run's and the oracle's."""
