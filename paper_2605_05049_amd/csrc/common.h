@@ -183,6 +183,7 @@ struct WgradArgs {
   const int4* order;           // [Et] {expert, its first row, the row after its last} by descending row count
   const uint16_t* zero_page;   // 256 zeroed bytes: source of k-rows past the end of a ragged contraction
   int Et, accumulate;
+  int chunk_log2;              // filled by the launcher
   long long rows;              // of all experts together
   size_t f_expert_stride;
   WgradProblem problem[2];     // dW_gate | dW_up and dW_down

@@ -45,7 +45,8 @@ constexpr long long W_DX_MID_ROWS = 4096;    // and dX on the tiles of mid_rows.
 constexpr int W_ROUTER_EXPERTS = 128;
 constexpr double W_ROUTER_MACS = 2e8;
 constexpr double W_ROUTER_US8 = 0.012, W_ROUTER_US16 = 0.024, W_STORE_BYTES_PER_US = 6e6, W_ROUTER_SLACK_US = 5;   // (router_joins)
-constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes: `band` along p x 32 / band along q
+constexpr int W_SHORT_CHUNKS = 20, W_SHORT_CHUNKS_FEW = 48;   // chunks of 8 tiles up to here (launch_wgrad), with fewer than 64 rows per expert
+constexpr int W_CHUNK = 32;                  // consecutive tiles that one XCD takes (else): `band` along p x 32 / band along q
 
 // Position of 8 r-values (chunk c of 16) inside k-row k's 256 bytes: the four k-rows that a transposing read takes together
 // lie in different quarters of the LDS banks, and so do, pair by pair, the k-rows 8 apart that its lane groups take.
@@ -81,7 +82,8 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
   // ---- block id -> tile.  Chunks of 32 consecutive tiles (B.band p x 32 / B.band q of one expert, which share panels) are dealt
   // round-robin to the XCDs, of each problem the experts with the most rows first (its last tiles are then short ones).
   const int within = (int)(block / W_XCDS), xcd = (int)(block % W_XCDS);
-  const int launch_chunk = within / W_CHUNK * W_XCDS + xcd;
+  const int cl = A.chunk_log2;
+  const int launch_chunk = (within >> cl) * W_XCDS + xcd;
   const bool is_b = launch_chunk >= A.problem[0].chunks;   // (a launch may carry two problems, the second's chunks after the first's)
   // The index is kept from the compiler's sight: it would read each field by a chosen address of its own, one after the other, and not the
   // problem in a few wide loads (4096 x 14336, 64 rows per expert, dW_down 308 -> 306 us; 1024 rows, the pair 1823 -> 1814).
@@ -92,7 +94,7 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& A, char* ring, unsi
   // behind a load stood in front of every block's first stage.  With the same in the row tiles, steps: 512 x 640, 4 experts of 371 rows 78.7 ->
   // 77.7 us, 704 x 2816, 12 of 962 671 -> 666, 832 x 1472, 6 of 3150 636 -> 631, 256 tokens of 512 x 1024 replayed 63.0 -> 62.7.)
   const unsigned tiles_per_e = (unsigned)B.n_p_tiles * (unsigned)B.n_q_tiles;
-  const unsigned lid = (unsigned)(launch_chunk - (is_b ? A.problem[0].chunks : 0)) * W_CHUNK + within % W_CHUNK;
+  const unsigned lid = ((unsigned)(launch_chunk - (is_b ? A.problem[0].chunks : 0)) << cl) + (within & ((1 << cl) - 1));
   const unsigned nth = lid / tiles_per_e;
   if (nth >= (unsigned)A.Et) return;
   const int4 entry = A.order[nth];
@@ -383,9 +385,19 @@ bool launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
   if (A.Et <= 0) return false;
   plan_wgrad(A.problem[0], A.Et, A.rows);
   plan_wgrad(A.problem[1], A.Et, A.rows);
-  auto grid = [](long long chunks) { return dim3((unsigned)((chunks + W_XCDS - 1) / W_XCDS * W_XCDS * W_CHUNK)); };
+  auto grid = [&](long long chunks) { return dim3((unsigned)((chunks + W_XCDS - 1) / W_XCDS * W_XCDS << A.chunk_log2)); };
   const dim3 block(WTHREADS);
-  const int chunks = A.problem[0].chunks + A.problem[1].chunks;
+  int chunks = A.problem[0].chunks + A.problem[1].chunks;
+  const bool dx_few_joins = dx_tiles > 0 && !dx.mid_rows && dx_joins(dx, chunks), merged = chunks <= W_MERGE_CHUNKS;
+  A.chunk_log2 = 5;
+  // Chunks of 8 tiles where there are few of 32: 12 of those are two on half of the XCDs and one on the others, which store half as much.  Backward
+  // of 10964 random shapes, 8 / 32: up to the limits 0.968 at the mean and more than 1.03 on 3 %, up to 12 chunks 0.954 (512 x 1280, 2 experts of
+  // 1496 rows 60.7 -> 45.9 us; 2880 x 384, 3 of 52 27.5 -> 24.6; 1984 x 512, 4 of 456 45.9 -> 43.0); with at least 64 rows per expert 1.00 - 1.04 at 24 .. 128 chunks, whose tiles share panels, with fewer rows 0.997 - 1.003.
+  if (chunks <= (A.rows < 64ll * A.Et ? W_SHORT_CHUNKS_FEW : W_SHORT_CHUNKS)) {
+    A.chunk_log2 = 3;
+    for (WgradProblem& B : A.problem) B.chunks = (A.Et * B.n_p_tiles * B.n_q_tiles + 7) / 8;
+    chunks = A.problem[0].chunks + A.problem[1].chunks;
+  }
   JoinedArgs J = {};
   J.dw = A;
   if (router && router_joins(*router, A)) {
@@ -403,7 +415,7 @@ bool launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
       return J.router_blocks > 0;
     }
     // (On 64-row tiles: 2048 x 1408, 66 experts, 528 chunks, forward + backward: 837 us with dX in a launch of its own, 842 with one for all.)
-    if (!dx.mid_rows && dx_joins(dx, chunks)) {
+    if (dx_few_joins) {
       J.dx.n_q_tiles = dx.q_dim / FQ;
       J.dx.chunk_log2 = few_rows_chunk_log2(dx, dx_tiles, J.dx.n_q_tiles);
       J.dx_blocks = few_rows_grid(dx_tiles * J.dx.n_q_tiles, J.dx.chunk_log2);
@@ -416,7 +428,7 @@ bool launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
   // In one launch, unless it is long: two launches have two starts and two last rounds.  Time of the one against the two, 200
   // random shapes: 0.73 at fewer than 64 chunks, 0.91 at 64 .. 128, 0.94 up to 256, 0.97 up to 512, 0.98 up to 1024, 0.99 - 1.0
   // beyond.
-  if (chunks <= W_MERGE_CHUNKS) {
+  if (merged) {
     if (J.router_blocks > 0) {
       launch_joined<JOINED_NO_DX>(st, "ffn_bwd_dw", J, grid(chunks).x);
       return true;
