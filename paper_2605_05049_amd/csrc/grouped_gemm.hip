@@ -1018,17 +1018,20 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 // 16 .. 96 rows per expert: 1.08 of the better one where down is on these tiles too, 1.13 where it is not.  In the first case the other
 // kernel would need a schedule, 5 us, which takes most of the gain back, if there are at most kFewSelfExperts experts; where the
 // call has one anyway the limits are too high.)
-constexpr int kRowClasses = 5, kStepClasses = 5;
+// (Of few rows per expert and 64 .. 128 k-steps the limits of down and dX are from 7000 shapes with all of that: down of fewer than 16 rows, up to 200
+// tiles 0.76 - 0.91 of the 256-row kernel's time; dX of fewer than 40, 96 .. 200 steps, with the weight
+// gradients, 0.74 - 0.93.  A call may also be left without a schedule then: 512 x 3584, 10 experts of 30 rows, forward + backward 108 -> 89 us.)
+constexpr int kRowClasses = 5, kStepClasses = 6;
 constexpr int kRowsBelow[kRowClasses - 1] = {16, 40, 64, 96};     // rows per expert on average
-constexpr int kStepsBelow[kStepClasses - 1] = {48, 64, 96, 128};  // k-steps of 64, both passes of dX counted
+constexpr int kStepsBelow[kStepClasses - 1] = {48, 64, 96, 128, 200};  // k-steps of 64, both passes of dX counted
 constexpr int kFewTilesGateUp[kRowClasses] = {288, 1600, 1600, 1024, 768};   // (the 256-row kernel never cuts these along k)
 constexpr int kFewTiles[3][kRowClasses][kStepClasses] = {
     // down
-    {{1024, 256, 20, 12, 0}, {2560, 2048, 1600, 0, 0}, {2560, 2560, 1536, 1280, 0}, {2048, 2048, 1152, 1280, 512}, {1280, 1152, 1024, 512, 448}},
+    {{1024, 256, 200, 200, 0, 0}, {2560, 2048, 1600, 0, 0, 0}, {2560, 2560, 1536, 1280, 0, 0}, {2048, 2048, 1152, 1280, 512, 512}, {1280, 1152, 1024, 512, 448, 448}},
     // dH
-    {{4096, 256, 20, 12, 0}, {4096, 2048, 1792, 768, 0}, {4096, 3072, 2176, 1536, 0}, {4096, 2560, 2048, 1536, 0}, {1920, 1536, 1280, 1024, 256}},
+    {{4096, 256, 20, 12, 0, 0}, {4096, 2048, 1792, 768, 0, 0}, {4096, 3072, 2176, 1536, 0, 0}, {4096, 2560, 2048, 1536, 0, 0}, {1920, 1536, 1280, 1024, 256, 256}},
     // dX
-    {{4096, 256, 20, 12, 0}, {4096, 3072, 2048, 0, 0}, {3584, 3072, 2048, 1792, 0}, {2304, 2560, 1792, 1536, 0}, {1280, 1280, 1152, 512, 256}}};
+    {{4096, 256, 20, 256, 256, 0}, {4096, 3072, 2048, 256, 256, 0}, {3584, 3072, 2048, 1792, 0, 0}, {2304, 2560, 1792, 1536, 0, 0}, {1280, 1280, 1152, 512, 256, 256}}};
 bool few_rows_pays(const Dims& D, RowTileKind kind) {
   const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;   // output columns f, contraction over d; else the other way round
   const long long active = D.N < D.Et ? D.N : D.Et;                  // experts with rows, at most
