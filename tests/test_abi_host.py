@@ -157,6 +157,21 @@ def test_which_gemms_run_on_small_tiles(lib, T, d, f, E, k, expected):
     assert moe.grouped_ffn_small_tiles(moe.Shape(T, d, f, E, k)) == expected
 
 
+# Both sides of the limits of few rows per expert and long contractions: 200 tiles and 128 k-steps of down, 256 tiles and 200 of dX
+@pytest.mark.parametrize("T,d,f,E,k,down,dx", [
+    (200, 512, 6144, 25, 1, True, True),       # 200 tiles of 96 and 192 steps
+    (200, 512, 6144, 26, 1, False, True),      # 208
+    (200, 512, 6144, 33, 1, False, False),     # 264
+    (200, 512, 6400, 25, 1, True, False),      # 100 and 200 steps
+    (200, 512, 8192, 25, 1, False, False),     # 128 and 256
+    (600, 512, 3584, 20, 1, True, True),       # 30 rows per expert: 160 tiles of dX, 112 steps
+    (990, 512, 3584, 33, 1, True, False),      # 264, and of down, 56 steps
+])
+def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down, dx):
+    small = moe.grouped_ffn_small_tiles(moe.Shape(T, d, f, E, k))
+    assert ("down" in small, "dx" in small) == (down, dx)
+
+
 # (T, d, f, E, k) -> the GEMMs on the tiles of 128 columns: both sides of the least and the most tiles, by rows per expert and k-steps
 @pytest.mark.parametrize("T,d,f,E,k,expected", [
     (256, 512, 1024, 8, 2, ("gate_up",)),                  # 128 tiles of gate | up, 64 of the others
