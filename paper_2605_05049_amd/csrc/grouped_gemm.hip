@@ -3,7 +3,8 @@
 // per-expert GEMMs of uneven, often small row counts that the abstract and Section II-A single out).
 //
 // One kernel template serves the four row-tile contractions of the FFN and two of the router's backward (the FFN's weight
-// gradients have a kernel of their own, wgrad.hip, and small problems another, few_rows.hip).  Every output tile is
+// gradients have a kernel of their own, wgrad.hip, small problems another, few_rows.hip, and those between them and the tiles of this file a
+// third, mid_rows.hip).  Every output tile is
 //     C[p, q] = sum_k  P[p, k] * Q[q, k]          (p: 256 values, q: 256 values, k in steps of 64)
 // where P is the operand whose index becomes the lane-column of the MFMA accumulator and Q the operand whose
 // index becomes the accumulator register (so that each lane owns 4 consecutive q = 4 consecutive output
@@ -1012,13 +1013,10 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 //   down       2048 x 1408, 4, 256: 17 / 32   32, 8: 41 / 37     7168 x 512, 8, 1024: 173 / 84      4096 x 14336, 1, 8: 71 / 33
 //   dH         2048 x 1408, 4, 256: 22 / 51   32, 8: 35 / 32     7168 x 2048, 8, 8: 37 / 41         7168 x 1024, 8, 512: 105 / 111
 //   dX         2048 x 1408, 4, 256: 24 / 54   32, 8: 65 / 67     7168 x 512, 8, 1024: 248 / 126     4096 x 14336, 1, 8: 97 / 53
-// (The fit is older than both kernels: than the 256-row kernel's present loop and its pieces of left-over tiles, and than the small chunks
-// of few_rows.hip and dX beside the weight gradients.  With that loop, before the rest, on 6000 shapes drawn around the limits: 0.86 of
-// its time at the mean, more than 1.05 on 7 %, where the better kernel for each GEMM would give 0.84.  Furthest off was gate | up of
-// 16 .. 96 rows per expert: 1.08 of the better one where down is on these tiles too, 1.13 where it is not.  In the first case the other
-// kernel would need a schedule, 5 us, which takes most of the gain back, if there are at most kFewSelfExperts experts; where the
-// call has one anyway the limits are too high.)
-// (Of few rows per expert and 64 .. 128 k-steps the limits of down and dX are from 7000 shapes with all of that: down of fewer than 16 rows, up to 200
+// (The fit is older than the tiles of mid_rows.hip, which are asked first and have taken most of what lay around these limits, and than the
+// 256-row kernel's present loop and its pieces of left-over tiles, the small chunks of few_rows.hip and dX beside the weight gradients.  On 7000
+// random shapes with all of that, forward and backward as calls, schedules counted: 1.02 of the best choice for each GEMM.)
+// (Of few rows per expert and 64 .. 128 k-steps the limits of down and dX are from those 7000: down of fewer than 16 rows, up to 200
 // tiles 0.76 - 0.91 of the 256-row kernel's time; dX of fewer than 40, 96 .. 200 steps, with the weight
 // gradients, 0.74 - 0.93.  A call may also be left without a schedule then: 512 x 3584, 10 experts of 30 rows, forward + backward 108 -> 89 us.)
 constexpr int kRowClasses = 5, kStepClasses = 6;
@@ -1090,7 +1088,9 @@ int mid_rows_for(const Dims& D, RowTileKind kind) {
     default: least = steps < 128 ? 96 : 128; break;                                             // (beside the weight gradients it need not fill the chip)
   }
   if (tiles < least || tiles >= kMidMost[kind][rc][sc]) return 0;
-  if (kind == ROWTILE_DOWN && rc == 3 && sc > 0 && tiles >= 768 && tiles < 1024) return 0;   // (1.5 .. 2 rounds of either height: 1.03, on both sides 0.85 and 0.93)
+  // (1.5 .. 2 rounds of either height: 1.03, on both sides 0.85 and 0.93; up to 2.2 rounds 0.96, but where even experts fill one round of 256-row
+  // tiles, as 8 of 1024 rows, 2048 x 1408: 59 / 44 us)
+  if (kind == ROWTILE_DOWN && rc == 3 && sc > 0 && tiles >= 768 && tiles < 1152) return 0;
   // Tiles of 192 rows move fewer operand bytes (12.7 KB per million multiply-adds for 15.3) and leave fewer remainders, but make fewer tiles:
   // taken where they save about a round of the 512 that the chip runs at a time, or all run at once with room.  (186 rows per expert, 66 of
   // 2048 x 1408, four GEMMs: 1244 us on 128, 1169 on 192; 310 rows, 5 of 1408 x 4736, dX 92 and 108.)

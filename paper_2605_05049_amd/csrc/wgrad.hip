@@ -392,7 +392,8 @@ bool launch_wgrad(hipStream_t st, WgradArgs A, const RowTileArgs& dx, long long 
   A.chunk_log2 = 5;
   // Chunks of 8 tiles where there are few of 32: 12 of those are two on half of the XCDs and one on the others, which store half as much.  Backward
   // of 10964 random shapes, 8 / 32: up to the limits 0.968 at the mean and more than 1.03 on 3 %, up to 12 chunks 0.954 (512 x 1280, 2 experts of
-  // 1496 rows 60.7 -> 45.9 us; 2880 x 384, 3 of 52 27.5 -> 24.6; 1984 x 512, 4 of 456 45.9 -> 43.0); with at least 64 rows per expert 1.00 - 1.04 at 24 .. 128 chunks, whose tiles share panels, with fewer rows 0.997 - 1.003.
+  // 1496 rows 60.7 -> 45.9 us; 2880 x 384, 3 of 52 27.5 -> 24.6; 1984 x 512, 4 of 456 45.9 -> 43.0); with at least 64 rows
+  // per expert 1.00 - 1.04 at 24 .. 128 chunks, whose tiles share panels, with fewer rows 0.997 - 1.003.
   if (chunks <= (A.rows < 64ll * A.Et ? W_SHORT_CHUNKS_FEW : W_SHORT_CHUNKS)) {
     A.chunk_log2 = 3;
     for (WgradProblem& B : A.problem) B.chunks = (A.Et * B.n_p_tiles * B.n_q_tiles + 7) / 8;
