@@ -1104,8 +1104,8 @@ static RowTiles row_tiles_for(const Dims& D, RowTileKind kind) {
   return mid_rows_for(D, kind) ? ROWTILES_MID : few_rows_pays(D, kind) ? ROWTILES_FEW : ROWTILES_TALL;
 }
 
-// The row-tile GEMMs of one call of the expert FFN: of the forward (gate | up and down), of the backward (dH and dX) or the
-// recomputed gate | up alone.
+// The row-tile GEMMs of one call of the expert FFN: of the forward (gate | up and down) or of the backward (dH and dX; of a recomputing one
+// gate | up too: with a schedule of its own, a launch of 5 .. 6 us more).
 struct RowGemms {
   const Dims& D;
   const WsLayout& L;
@@ -1120,10 +1120,10 @@ struct RowGemms {
   uint32_t* zero_page;
   int32_t* counters;
 
-  RowGemms(const Dims& D_, const WsLayout& L_, void* ws_, hipStream_t st_, const int32_t* offsets_, RowTileKind first, RowTileKind second)
+  RowGemms(const Dims& D_, const WsLayout& L_, void* ws_, hipStream_t st_, const int32_t* offsets_, RowTileKind first, RowTileKind second, RowTileKind third)
       : D(D_), L(L_), ws(static_cast<char*>(ws_)), st(st_), offsets(offsets_), max_tiles((int)sched_max_tiles(D_)),
-        any_few(row_tiles_for(D_, first) == ROWTILES_FEW || row_tiles_for(D_, second) == ROWTILES_FEW),
-        any_tall(row_tiles_for(D_, first) == ROWTILES_TALL || row_tiles_for(D_, second) == ROWTILES_TALL),
+        any_few(row_tiles_for(D_, first) == ROWTILES_FEW || row_tiles_for(D_, second) == ROWTILES_FEW || row_tiles_for(D_, third) == ROWTILES_FEW),
+        any_tall(row_tiles_for(D_, first) == ROWTILES_TALL || row_tiles_for(D_, second) == ROWTILES_TALL || row_tiles_for(D_, third) == ROWTILES_TALL),
         backward(first == ROWTILE_DH), sched_tall(reinterpret_cast<int32_t*>(ws + L_.sched)), sched_few(reinterpret_cast<int32_t*>(ws + L_.sched_few)),
         zero_page(reinterpret_cast<uint32_t*>(ws + L_.zero_page)),
         counters(reinterpret_cast<int32_t*>(ws + L_.splitk_counters)) {}
@@ -1249,7 +1249,7 @@ extern "C" int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_per
   MOE_REQUIRE_ALIGNED(x_perm); MOE_REQUIRE_ALIGNED(offsets); MOE_REQUIRE_ALIGNED(w_gate); MOE_REQUIRE_ALIGNED(w_up);
   MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(y_perm); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   if (D.N == 0) return MOE_OK;
-  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, ROWTILE_GATE_UP, ROWTILE_DOWN);
+  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, ROWTILE_GATE_UP, ROWTILE_DOWN, ROWTILE_DOWN);
   G.schedule();
   MOE_TRY(G.gate_up("ffn_fwd_gate_up_swiglu", x_perm, w_gate, w_up, save_g, save_u, G.rows_f(L.h)));
   MOE_TRY(G.down("ffn_fwd_down", G.rows_f(L.h), w_down, y_perm));
@@ -1258,12 +1258,13 @@ extern "C" int moe_grouped_ffn_fwd(const moe_shape* shape, const uint16_t* x_per
 
 namespace moe {
 
-// `router`: the router's backward may share a launch of this call; *router_done tells whether it does.
+// recompute: G and U are made again first, in save_g and save_u.  `router`: the router's backward may share a launch of this call; *router_done
+// tells whether it does.
 static int grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_perm, const uint16_t* x_perm,
                                    const int32_t* offsets, const uint16_t* w_gate, const uint16_t* w_up,
                                    const uint16_t* w_down, const uint16_t* save_g, const uint16_t* save_u,
                                    uint16_t* dx_perm, float* dw_gate, float* dw_up, float* dw_down, int accumulate,
-                                   void* ws, size_t ws_bytes, void* stream, const RouterSmallArgs* router, bool* router_done) {
+                                   void* ws, size_t ws_bytes, void* stream, bool recompute, const RouterSmallArgs* router, bool* router_done) {
   Dims D;
   WsLayout L;
   int rc = common_checks(shape, &D, ws, ws_bytes, &L);
@@ -1275,12 +1276,14 @@ static int grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_perm, cons
   MOE_REQUIRE_ALIGNED(w_up); MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(save_g); MOE_REQUIRE_ALIGNED(save_u);
   MOE_REQUIRE_ALIGNED(dx_perm); MOE_REQUIRE_ALIGNED(dw_gate); MOE_REQUIRE_ALIGNED(dw_up); MOE_REQUIRE_ALIGNED(dw_down);
   hipStream_t st = (hipStream_t)stream;
-  const RowGemms G(D, L, ws, st, offsets, ROWTILE_DH, ROWTILE_DX);
+  const RowGemms G(D, L, ws, st, offsets, ROWTILE_DH, ROWTILE_DX, recompute ? ROWTILE_GATE_UP : ROWTILE_DX);
   uint16_t* const h = G.rows_f(L.h);
   uint16_t* const dg = G.rows_f(L.dg);
   uint16_t* const du = G.rows_f(L.du);
   G.schedule();   // (also with no rows at all: the weight gradients read the expert order from the schedule)
   if (D.N > 0) {
+    // (tiles, parts and the order of their sums as in forward, hence the same bits; the backward makes its own H)
+    if (recompute) MOE_TRY(G.gate_up("ffn_bwd_recompute_gate_up", x_perm, w_gate, w_up, G.rows_f(L.g_re), G.rows_f(L.u_re), nullptr));
     MOE_TRY(G.dh("ffn_bwd_dh_dswiglu", dy_perm, w_down, save_g, save_u, dg, du, h));
   }
   WgradArgs W = {};
@@ -1319,7 +1322,7 @@ extern "C" int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_pe
                                    uint16_t* dx_perm, float* dw_gate, float* dw_up, float* dw_down, int accumulate,
                                    void* ws, size_t ws_bytes, void* stream) {
   return moe::grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, save_g, save_u, dx_perm, dw_gate, dw_up, dw_down, accumulate,
-                              ws, ws_bytes, stream, nullptr, nullptr);
+                              ws, ws_bytes, stream, false, nullptr, nullptr);
 }
 
 extern "C" int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const uint16_t* w_router, const float* dlogits,
@@ -1412,7 +1415,7 @@ extern "C" int moe_grouped_ffn_router_bwd(const moe_shape* shape, const uint16_t
   const RouterSmallArgs R = {x, w_router, dlogits, dx_router, dw_router, D.T, D.E, D.d, accumulate ? 1 : 0, 0};
   bool done = false;
   MOE_TRY(grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, save_g, save_u, dx_perm, dw_gate, dw_up, dw_down, accumulate,
-                          ws, ws_bytes, stream, D.T > 0 ? &R : nullptr, &done));
+                          ws, ws_bytes, stream, false, D.T > 0 ? &R : nullptr, &done));
   if (done || D.T == 0) return MOE_OK;
   return moe_router_bwd(shape, x, w_router, dlogits, dx_router, dw_router, accumulate, ws, ws_bytes, stream);
 }
@@ -1426,20 +1429,7 @@ extern "C" int moe_grouped_ffn_bwd_recompute(const moe_shape* shape, const uint1
   WsLayout L;
   int rc = common_checks(shape, &D, ws, ws_bytes, &L);
   if (rc != MOE_OK) return rc;
-  // every argument is checked before the first launch (the call below checks them again)
-  MOE_REQUIRE_PTR(dy_perm); MOE_REQUIRE_PTR(x_perm); MOE_REQUIRE_PTR(offsets); MOE_REQUIRE_PTR(w_gate); MOE_REQUIRE_PTR(w_up);
-  MOE_REQUIRE_PTR(w_down); MOE_REQUIRE_PTR(dx_perm); MOE_REQUIRE_PTR(dw_gate); MOE_REQUIRE_PTR(dw_up); MOE_REQUIRE_PTR(dw_down);
-  MOE_REQUIRE_ALIGNED(dy_perm); MOE_REQUIRE_ALIGNED(x_perm); MOE_REQUIRE_ALIGNED(offsets); MOE_REQUIRE_ALIGNED(w_gate);
-  MOE_REQUIRE_ALIGNED(w_up); MOE_REQUIRE_ALIGNED(w_down); MOE_REQUIRE_ALIGNED(dx_perm); MOE_REQUIRE_ALIGNED(dw_gate);
-  MOE_REQUIRE_ALIGNED(dw_up); MOE_REQUIRE_ALIGNED(dw_down);
-  const RowGemms G(D, L, ws, (hipStream_t)stream, offsets, ROWTILE_GATE_UP, ROWTILE_GATE_UP);
-  uint16_t* const g_re = G.rows_f(L.g_re);
-  uint16_t* const u_re = G.rows_f(L.u_re);
-  if (D.N > 0) {
-    // G, U = X Wg, X Wu once more (tiles, parts and the order of their sums as in forward, hence the same bits); the backward makes its own H
-    G.schedule();
-    MOE_TRY(G.gate_up("ffn_bwd_recompute_gate_up", x_perm, w_gate, w_up, g_re, u_re, nullptr));
-  }
-  return moe_grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, g_re, u_re, dx_perm, dw_gate, dw_up, dw_down,
-                             accumulate, ws, ws_bytes, stream);
+  const char* const wsb = static_cast<const char*>(ws);
+  return grouped_ffn_bwd(shape, dy_perm, x_perm, offsets, w_gate, w_up, w_down, reinterpret_cast<const uint16_t*>(wsb + L.g_re),
+                         reinterpret_cast<const uint16_t*>(wsb + L.u_re), dx_perm, dw_gate, dw_up, dw_down, accumulate, ws, ws_bytes, stream, true, nullptr, nullptr);
 }

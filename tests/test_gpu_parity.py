@@ -657,6 +657,36 @@ def test_recomputing_backward_on_either_kernel(moe, d, f, counts, small):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("d,f,counts,schedules", [
+    (832, 1856, [372, 0, 744] + 5 * [372], 1),       # gate | up on 256-row tiles, dH and dX on those of 128 columns
+    (64, 3072, 15 * [300, 384], 1),                  # ... dX on 64-row tiles
+    (4160, 1600, [13], 1),                           # dH on 256-row tiles, gate | up and dX on 64-row tiles
+    (320, 64, 9 * [178, 100], 0),                    # none on 256-row tiles
+])
+def test_one_schedule_of_a_recomputing_backward(moe, d, f, counts, schedules):
+    """All GEMMs of a recomputing backward share a schedule, and give the saving pair's bits."""
+    s, x, dy, off, w, ws, y, sg, su = ffn_on_device(moe, d, f, counts)
+    outs = []
+    for recompute in (False, True):
+        ws.zero_()
+        dx, dws = torch.full_like(x, float("nan")), [torch.full(t.shape, float("nan"), device="cuda") for t in w]
+        moe.profile_reset()
+        moe.profile_enable(True)
+        try:
+            if recompute:
+                moe.moe_grouped_ffn_bwd_recompute(s, dy, x, off, *w, dx, *dws, 0, ws)
+            else:
+                moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, sg, su, dx, *dws, 0, ws)
+            labels = [label for label, _ in moe.profile_records()]
+        finally:
+            moe.profile_enable(False)
+            moe.profile_reset()
+        outs.append([dx.view(torch.int16)] + [t.view(torch.int32) for t in dws])
+    assert labels.count("ffn_schedule") == schedules
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
 # ---------------------------------------------------------------------------------------------------------
 # the whole layer, forward + backward, against the per-token definition
 # ---------------------------------------------------------------------------------------------------------
