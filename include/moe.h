@@ -116,7 +116,7 @@ int moe_router_route_fwd(const moe_shape* shape, const uint16_t* x, const uint16
  * dlogits [T,E] fp32 in.  dlogits enters the matrix cores as a bf16 head plus a bf16 remainder (two products), i.e.
  * with 16 significand bits; the products accumulate in fp32.  dw_router is the sum, in a fixed order, of the partial
  * sums of up to 32 equal parts of the token range (deterministic).  With at most 16 experts and few tokens both results
- * are computed in fp32 throughout, dw_router as the sum of 16 (in a launch shared with the experts: 4) partial sums in a fixed order. */
+ * are computed in fp32 throughout, dw_router as the sum of 16 partial sums in a fixed order. */
 int moe_router_bwd(const moe_shape* shape, const uint16_t* x, const uint16_t* w_router, const float* dlogits,
                    uint16_t* dx_router, float* dw_router, int accumulate, void* ws, size_t ws_bytes, void* stream);
 
@@ -185,8 +185,10 @@ int moe_grouped_ffn_bwd(const moe_shape* shape, const uint16_t* dy_perm, const u
                         uint16_t* dx_perm, float* dw_gate, float* dw_up, float* dw_down, int accumulate,
                         void* ws, size_t ws_bytes, void* stream);
 
-/* moe_grouped_ffn_bwd and moe_router_bwd in one: neither needs the other, and with few experts and tokens they share a launch.  Arguments as
- * those of the two calls, `accumulate` for both. */
+/* moe_grouped_ffn_bwd and moe_router_bwd in one: neither needs the other, and they share a launch with at most 128 experts where the router's
+ * part is the shorter one.  Arguments as those of the two calls, `accumulate` for both.  The experts' results have the bits of
+ * moe_grouped_ffn_bwd.  The router's are computed in fp32 throughout in a shared launch, dw_router as the sum of 16 partial sums: the bits of
+ * moe_router_bwd where that one computes so too, more exact ones (no 16-bit split of dlogits) where it uses the matrix cores. */
 int moe_grouped_ffn_router_bwd(const moe_shape* shape, const uint16_t* dy_perm, const uint16_t* x_perm,
                                const int32_t* offsets, const uint16_t* w_gate, const uint16_t* w_up,
                                const uint16_t* w_down, const uint16_t* save_g, const uint16_t* save_u,

@@ -469,7 +469,7 @@ __global__ __launch_bounds__(256) void router_dw_reduce_kernel(const float* __re
 constexpr int kSmallWaves = 16;
 template <int EP>
 __global__ __launch_bounds__(kSmallWaves * kWave) void router_bwd_small_kernel(const RouterSmallArgs R) {
-  __shared__ __attribute__((aligned(16))) char lds[router_small_lds(kSmallWaves)];   // 32 KB
+  __shared__ __attribute__((aligned(16))) char lds[kRouterSmallLds];
   router_small_block<EP, kSmallWaves>(R, lds, blockIdx.x);
 }
 

@@ -1,7 +1,7 @@
 // Backward of the router's linear map for few experts, both results in one launch and in fp32 throughout: the four launches of the general
 // path (prepare, dx, dW_r parts, their sum; router.hip) are 20 us of fixed cost for a problem of a few million multiplies (256 tokens,
-// E = 8, d = 512).  It has a launch of its own (blocks of 16 wavefronts), or shares that of the experts' weight gradients (blocks of 4,
-// wgrad.hip).
+// E = 8, d = 512).  It has a launch of its own (blocks of 16 wavefronts, at most 16 experts), or shares that of the experts' weight gradients
+// (blocks of 4, wgrad.hip).
 #pragma once
 
 #include "common.h"
@@ -9,8 +9,9 @@
 namespace moe {
 
 constexpr int kSmallTokens = 4, kSmallDwCols = 2 * kWave, kSmallDxCols = 8 * kWave;
-// LDS of a block of `waves` wavefronts
-constexpr int router_small_lds(int waves) { return waves * 4 * kSmallDwCols * (int)sizeof(float); }
+constexpr int kSmallSums = 16;   // partial sums of dW_r over the tokens, whatever the wavefronts of a block: either launch gives the same bits
+constexpr int kSmallMeet = 8;    // experts whose partial sums meet in LDS at a time
+constexpr int kRouterSmallLds = kSmallSums * kSmallMeet * kSmallDwCols * (int)sizeof(float);   // 64 KB
 
 // Fills in the plan of a block size; returns the blocks.
 inline unsigned router_small_plan(RouterSmallArgs& R, int waves, int ep) {
@@ -23,8 +24,8 @@ __device__ __forceinline__ float lane_value(float v, int lane) { return __int_as
 
 // Blocks in two roles:
 //   blocks 0 .. n_dw - 1: dW_r for 128 columns and up to EP experts.  A lane owns 2 columns and these experts, a wavefront the tokens
-//     w, w + WAVES, ...: x arrives 256 bytes per token, dlogits spread over the lanes and read across them; the WAVES partial sums meet in
-//     LDS, 4 experts at a time, and are added in wavefront order.
+//     w, w + WAVES, ...: x arrives 256 bytes per token, dlogits spread over the lanes and read across them; the 16 partial sums, of the
+//     tokens s, s + 16, ... (16 / WAVES of them in a wavefront), meet in LDS, 8 experts at a time, and are added in the order of s.
 //   the others: dx.  A wavefront owns 512 columns (16 bytes of dx per lane) of kSmallTokens tokens and keeps W_r's 8 columns
 //     of EP experts at a time in registers.
 template <int EP, int WAVES>
@@ -32,16 +33,19 @@ __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, cha
   const uint16_t* __restrict__ const x = R.x;
   const float* __restrict__ const dlogits = R.dlogits;
   const int T = R.T, E = R.E, d = R.d;
-  float(*const part)[4][kSmallDwCols] = reinterpret_cast<float(*)[4][kSmallDwCols]>(lds);
+  float2(*const part)[kSmallMeet][kWave] = reinterpret_cast<float2(*)[kSmallMeet][kWave]>(lds);
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if ((int)block < R.n_dw) {
     const int groups = (E + EP - 1) / EP;
     const int e_lo = (int)block % groups * EP, c0 = (int)block / groups * kSmallDwCols;
     const int c = min(c0 + 2 * lane, d - 2);   // (d is even: lanes past the end repeat its last pair, never stored)
-    float acc[EP][2];
+    constexpr int SUMS = kSmallSums / WAVES;
+    float acc[SUMS][EP][2];
 #pragma unroll
-    for (int e = 0; e < EP; e++) acc[e][0] = acc[e][1] = 0.f;
+    for (int s = 0; s < SUMS; s++)
+#pragma unroll
+      for (int e = 0; e < EP; e++) acc[s][e][0] = acc[s][e][1] = 0.f;
     constexpr int DEPTH = 16, PER = kWave / EP;   // tokens in flight; tokens whose dlogits one load fetches
     for (int t0 = wave; t0 < T; t0 += DEPTH * WAVES) {
       uint32_t xv[DEPTH];
@@ -61,29 +65,37 @@ __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, cha
 #pragma unroll
           for (int e = 0; e < EP; e++) {
             const float ge = lane_value(g[j / PER], (j % PER) * EP + e);
-            acc[e][0] += ge * a;
-            acc[e][1] += ge * b;
+            acc[j % SUMS][e][0] += ge * a;
+            acc[j % SUMS][e][1] += ge * b;
           }
         }
       }
     }
 #pragma unroll
-    for (int e0 = 0; e0 < EP; e0 += 4) {
-      if (e0 > 0) __syncthreads();   // the previous four experts' sums have been read
+    for (int e0 = 0; e0 < EP; e0 += kSmallMeet) {
+      if (e0 > 0) __syncthreads();   // the previous experts' sums have been read
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        part[wave][i][2 * lane] = acc[e0 + i][0];
-        part[wave][i][2 * lane + 1] = acc[e0 + i][1];
-      }
+      for (int s = 0; s < SUMS; s++)
+#pragma unroll
+        for (int i = 0; i < kSmallMeet; i++) part[s * WAVES + wave][i][lane] = make_float2(acc[s][e0 + i][0], acc[s][e0 + i][1]);
       __syncthreads();
-      for (int i = threadIdx.x; i < 4 * kSmallDwCols; i += WAVES * kWave) {
-        const int e = e_lo + e0 + i / kSmallDwCols, cc = i % kSmallDwCols;
-        if (e < E && c0 + cc < d) {
-          float sum = 0.f;
+      for (int i = wave; i < kSmallMeet; i += WAVES) {
+        const int e = e_lo + e0 + i;
+        if (e < E && c0 + 2 * lane < d) {
+          float2 sum = make_float2(0.f, 0.f);
 #pragma unroll
-          for (int w = 0; w < WAVES; w++) sum += part[w][i / kSmallDwCols][cc];
-          float* const dst = R.dw + (size_t)e * d + c0 + cc;
-          *dst = R.accumulate ? *dst + sum : sum;
+          for (int w = 0; w < kSmallSums; w++) {
+            const float2 p = part[w][i][lane];
+            sum.x += p.x;
+            sum.y += p.y;
+          }
+          float2* const dst = reinterpret_cast<float2*>(R.dw + (size_t)e * d + c0 + 2 * lane);
+          if (R.accumulate) {
+            const float2 old = *dst;
+            sum.x = old.x + sum.x;
+            sum.y = old.y + sum.y;
+          }
+          *dst = sum;
         }
       }
     }

@@ -316,7 +316,7 @@ template <int EP, JoinedDx DX>
 __global__ __launch_bounds__(WTHREADS, 2) void joined_wgrad_kernel(const JoinedArgs A) {
   constexpr int LDS = DX == JOINED_DX_MID ? M_LDS : 3 * W_STAGE;
   __shared__ __attribute__((aligned(1024))) char lds[LDS];
-  static_assert(WTHREADS == 4 * kWave && 4 * F_PATCH <= 3 * W_STAGE && 3 * W_STAGE <= M_LDS && router_small_lds(4) <= 3 * W_STAGE, "each of them fits");
+  static_assert(WTHREADS == 4 * kWave && 4 * F_PATCH <= 3 * W_STAGE && 3 * W_STAGE <= M_LDS && kRouterSmallLds <= 3 * W_STAGE, "each of them fits");
   unsigned block = blockIdx.x;
   if constexpr (EP > 0) {
     if (block < A.router_blocks) {

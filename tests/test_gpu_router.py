@@ -249,3 +249,34 @@ def test_router_backward_beside_the_weight_gradients(moe, d, f, counts, joined):
             assert float((dwr.double() - ref).norm()) <= 2.0 ** -16 * float(ref.norm())
         ref = dl.double() @ wr.double()
         assert float((dxr.double() - ref).norm()) <= 2.0 ** -8 * float(ref.norm()) and bool(torch.isfinite(dxr.float()).all())
+
+
+# tokens below, at and above the 16 partial sums and the 16 x 16 requested together, 1 .. 16 experts
+@pytest.mark.parametrize("d,f,counts", [(512, 1024, [3, 0, 4]), (512, 2048, [127, 129] * 4), (128, 1024, [5] * 15 + [0]), (1088, 1984, [39] * 13),
+                                        (2560, 1600, [16]), (192, 4096, [17] * 9)])
+def test_router_backward_has_the_same_bits_in_either_launch(moe, d, f, counts):
+    """dW_r of up to 16 experts is the same 16 sums over the tokens in the launch of its own and in that of the weight gradients."""
+    s, x, dy, off, w, ws, _, sg, su = ffn_on_device(moe, d, f, counts)
+    T, E = s.T, s.E
+    g = torch.Generator(device="cuda").manual_seed(2)
+    wr = (torch.randn(E, d, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    dl = torch.randn(T, E, device="cuda", generator=g) * 0.3
+    start = torch.randn(E, d, device="cuda", generator=g)
+    dx, dw = torch.empty_like(x), [torch.zeros(t.shape, device="cuda") for t in w]
+    for accumulate in (False, True):
+        got = []
+        for joined in (False, True):
+            dxr, dwr = torch.full_like(x, float("nan")), start.clone() if accumulate else torch.full_like(start, float("nan"))
+            moe.profile_reset()
+            moe.profile_enable(True)
+            if joined:
+                moe.moe_grouped_ffn_router_bwd(s, dy, x, off, *w, sg, su, dx, *dw, x, wr, dl, dxr, dwr, accumulate, ws)
+            else:
+                moe.moe_router_bwd(s, x, wr, dl, dxr, dwr, accumulate, ws)
+            torch.cuda.synchronize()
+            labels = [label for label, _ in moe.profile_records()]
+            moe.profile_enable(False)
+            moe.profile_reset()
+            assert ("router_bwd" in labels) == (not joined)
+            got.append((dxr.view(torch.int16), dwr.view(torch.int32)))
+        assert all(torch.equal(a, b) for a, b in zip(*got))
