@@ -470,14 +470,14 @@ constexpr int kSmallWaves = 16;
 template <int EP>
 __global__ __launch_bounds__(kSmallWaves * kWave) void router_bwd_small_kernel(const RouterSmallArgs R) {
   __shared__ __attribute__((aligned(16))) char lds[kRouterSmallLds];
-  router_small_block<EP, kSmallWaves>(R, lds, blockIdx.x);
+  router_small_block<EP, kSmallWaves, false>(R, lds, blockIdx.x);
 }
 
 // One block of the dW_r role does T x EP multiply-adds for its 128 columns on one CU, so the launch's time grows with T (and, as
 // rounds of blocks, with d) where the general path's hardly does.  Both, us (E, d, T; one launch / general):
-//   8, 64: T = 256: 7.0 / 15.2   1024: 16.4 / 16.1     8, 512, 1024: 16.7 / 18.3     8, 65536, 1024: 0.89 of the general path
-//   16, 64: T = 64: 14.3 / 14.8   256: 17.7 / 15.6     16, 128 .. 8192: T = 256: 0.55 - 0.61 of it   512: 0.74 - 0.95   768: 1.0 - 1.3
-//   16, 65536: T = 64: 0.73 of it   192: 1.13   512: 1.53
+//   8, 64: T = 256: 5.5 / 14.5   1024: 16.0 / 15.3     8, 512, 1024: 16.4 / 16.6     8, 65536, 1024: 0.89 of the general path
+//   16, 64: T = 64: 14.3 / 14.0   256: 16.7 / 14.8     16, 128 .. 8192: T = 256: 0.59 - 0.63 of it   512: 0.77 - 0.95   768: 1.25 - 1.36
+//   16, 65536: T = 64: 0.75 of it   192: 1.16
 bool router_bwd_is_small(int T, int E, int d) {
   if (E <= 8) return T <= 1024;
   return E <= 16 && T <= (d >= 128 && d <= 8192 ? 512 : 64);

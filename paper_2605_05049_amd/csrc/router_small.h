@@ -28,16 +28,20 @@ __device__ __forceinline__ float lane_value(float v, int lane) { return __int_as
 //     tokens s, s + 16, ... (16 / WAVES of them in a wavefront), meet in LDS, 8 experts at a time, and are added in the order of s.
 //   the others: dx.  A wavefront owns 512 columns (16 bytes of dx per lane) of kSmallTokens tokens and keeps W_r's 8 columns
 //     of EP experts at a time in registers.
-template <int EP, int WAVES>
+// GROUPS: there may be more than EP experts.  (The sums of all tokens are then alive at once.  Where EP experts are all, a token's are stored
+// before the next one's begin: with all of them alive a block of 16 wavefronts, 128 registers each, spilt 2413 for EP = 16: 470 us for
+// 10 up to 256 tokens of 512 columns.)
+template <int EP, int WAVES, bool GROUPS>
 __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, char* lds, unsigned block) {
   const uint16_t* __restrict__ const x = R.x;
+  const uint16_t* __restrict__ const w_router = R.w_router;
   const float* __restrict__ const dlogits = R.dlogits;
   const int T = R.T, E = R.E, d = R.d;
   float2(*const part)[kSmallMeet][kWave] = reinterpret_cast<float2(*)[kSmallMeet][kWave]>(lds);
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if ((int)block < R.n_dw) {
-    const int groups = (E + EP - 1) / EP;
+    const int groups = GROUPS ? (E + EP - 1) / EP : 1;
     const int e_lo = (int)block % groups * EP, c0 = (int)block / groups * kSmallDwCols;
     const int c = min(c0 + 2 * lane, d - 2);   // (d is even: lanes past the end repeat its last pair, never stored)
     constexpr int SUMS = kSmallSums / WAVES;
@@ -104,33 +108,64 @@ __device__ __forceinline__ void router_small_block(const RouterSmallArgs& R, cha
   const int chunks = (d + kSmallDxCols - 1) / kSmallDxCols;
   const int task = ((int)block - R.n_dw) * WAVES + wave;
   const int c_lane = (task % chunks) * kSmallDxCols + 8 * lane, c = c_lane < d ? c_lane : 0;
-  const int t_begin = task / chunks * kSmallTokens, t_end = min(T, t_begin + kSmallTokens);
+  const int t_begin = (task / chunks) * kSmallTokens, t_end = min(T, t_begin + kSmallTokens);
   if (t_begin >= T) return;   // (lanes past the last column stay: their dlogits are read across lanes)
-  float a[kSmallTokens][8] = {};
-  for (int e_lo = 0; e_lo < E; e_lo += EP) {
-    uint4 w[EP];
-    float g[kSmallTokens];   // lane e: dlogits of expert e_lo + e
+  uint4 w[EP];
+  float g[kSmallTokens];   // lane e: dlogits of expert e_lo + e
+  // (Every load is made, of a row and token that exist, and what does not belong is cleared: loads under a condition wait for each other.)
+  auto load = [&](int e_lo) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < EP; e++) w[e] = e_lo + e < E ? *reinterpret_cast<const uint4*>(R.w_router + (size_t)(e_lo + e) * d + c) : make_uint4(0u, 0u, 0u, 0u);
+    for (int e = 0; e < EP; e++) w[e] = *reinterpret_cast<const uint4*>(w_router + (size_t)min(e_lo + e, E - 1) * d + c);
 #pragma unroll
-    for (int j = 0; j < kSmallTokens; j++) g[j] = (lane < EP && e_lo + lane < E && t_begin + j < t_end) ? dlogits[(size_t)(t_begin + j) * E + e_lo + lane] : 0.f;
+    for (int j = 0; j < kSmallTokens; j++) g[j] = dlogits[(size_t)min(t_begin + j, T - 1) * E + min(e_lo + lane % EP, E - 1)];
+#pragma unroll
+    for (int e = 0; e < EP; e++)
+      if (e_lo + e >= E) w[e] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int j = 0; j < kSmallTokens; j++)
+      if (e_lo + lane % EP >= E) g[j] = 0.f;
+  };
+  auto add = [&](int j, float(&a)[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < EP; e++) {
+      const float ge = lane_value(g[j], e);
+      a[0] += ge * bf16lo(w[e].x); a[1] += ge * bf16hi(w[e].x); a[2] += ge * bf16lo(w[e].y); a[3] += ge * bf16hi(w[e].y);
+      a[4] += ge * bf16lo(w[e].z); a[5] += ge * bf16hi(w[e].z); a[6] += ge * bf16lo(w[e].w); a[7] += ge * bf16hi(w[e].w);
+    }
+  };
+  auto store = [&](int j, const float(&a)[8]) __attribute__((always_inline)) {
+    if (c_lane < d)
+      *reinterpret_cast<uint4*>(R.dx + (size_t)(t_begin + j) * d + c) =
+          make_uint4(pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), pack_bf16(a[4], a[5]), pack_bf16(a[6], a[7]));
+  };
+  if constexpr (!GROUPS) {
+    load(0);
 #pragma unroll
     for (int j = 0; j < kSmallTokens; j++) {
       if (t_begin + j < t_end) {
+        // (With 16 experts W_r is new to the compiler for every token after the first: it would else keep all of it unpacked to fp32 beside the
+        // packed values, 13 registers too many.)
+        if constexpr (EP > 8) {
 #pragma unroll
-        for (int e = 0; e < EP; e++) {
-          const float ge = lane_value(g[j], e);
-          a[j][0] += ge * bf16lo(w[e].x); a[j][1] += ge * bf16hi(w[e].x); a[j][2] += ge * bf16lo(w[e].y); a[j][3] += ge * bf16hi(w[e].y);
-          a[j][4] += ge * bf16lo(w[e].z); a[j][5] += ge * bf16hi(w[e].z); a[j][6] += ge * bf16lo(w[e].w); a[j][7] += ge * bf16hi(w[e].w);
+          for (int e = 0; e < (j > 0 ? EP : 0); e++) asm("" : "+v"(w[e].x), "+v"(w[e].y), "+v"(w[e].z), "+v"(w[e].w));
         }
+        float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        add(j, a);
+        store(j, a);
       }
     }
-  }
+  } else {
+    float a[kSmallTokens][8] = {};
+    for (int e_lo = 0; e_lo < E; e_lo += EP) {
+      load(e_lo);
 #pragma unroll
-  for (int j = 0; j < kSmallTokens; j++)
-    if (t_begin + j < t_end && c_lane < d)
-      *reinterpret_cast<uint4*>(R.dx + (size_t)(t_begin + j) * d + c) =
-          make_uint4(pack_bf16(a[j][0], a[j][1]), pack_bf16(a[j][2], a[j][3]), pack_bf16(a[j][4], a[j][5]), pack_bf16(a[j][6], a[j][7]));
+      for (int j = 0; j < kSmallTokens; j++)
+        if (t_begin + j < t_end) add(j, a[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < kSmallTokens; j++)
+      if (t_begin + j < t_end) store(j, a[j]);
+  }
 }
 
 }  // namespace moe

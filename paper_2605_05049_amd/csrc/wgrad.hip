@@ -320,7 +320,7 @@ __global__ __launch_bounds__(WTHREADS, 2) void joined_wgrad_kernel(const JoinedA
   unsigned block = blockIdx.x;
   if constexpr (EP > 0) {
     if (block < A.router_blocks) {
-      router_small_block<EP, 4>(A.router, lds, block);
+      router_small_block<EP, 4, (EP > 8)>(A.router, lds, block);
       return;
     }
     block -= A.router_blocks;
