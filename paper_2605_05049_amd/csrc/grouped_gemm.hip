@@ -1016,9 +1016,10 @@ static int common_checks(const moe_shape* shape, Dims* D, void* ws, size_t ws_by
 // (The fit is older than the tiles of mid_rows.hip, which are asked first and have taken most of what lay around these limits, and than the
 // 256-row kernel's present loop and its pieces of left-over tiles, the small chunks of few_rows.hip and dX beside the weight gradients.  On 7000
 // random shapes with all of that, forward and backward as calls, schedules counted: 1.02 of the best choice for each GEMM.)
-// (Of few rows per expert and 64 .. 128 k-steps the limits of down and dX are from those 7000: down of fewer than 16 rows, up to 200
-// tiles 0.76 - 0.91 of the 256-row kernel's time; dX of fewer than 40, 96 .. 200 steps, with the weight
-// gradients, 0.74 - 0.93.  A call may also be left without a schedule then: 512 x 3584, 10 experts of 30 rows, forward + backward 108 -> 89 us.)
+// (Of few rows per expert the limits of down at 64 .. 128 k-steps and of dX at 64 .. 200 are younger: down of fewer than 16 rows, up to 200
+// tiles 0.76 - 0.91 of the 256-row kernel's time; dX of fewer than 16 rows, 64 .. 96 steps, backward of 540 random shapes, up to 160 tiles 0.78, up
+// to 256 0.85, none above 1.03; of fewer than 40 rows, 96 .. 200 steps, 0.74 - 0.93.  A call may also be left without a schedule
+// then: 512 x 3584, 10 experts of 30 rows, forward + backward 108 -> 89 us.)
 constexpr int kRowClasses = 5, kStepClasses = 6;
 constexpr int kRowsBelow[kRowClasses - 1] = {16, 40, 64, 96};     // rows per expert on average
 constexpr int kStepsBelow[kStepClasses - 1] = {48, 64, 96, 128, 200};  // k-steps of 64, both passes of dX counted
@@ -1029,7 +1030,7 @@ constexpr int kFewTiles[3][kRowClasses][kStepClasses] = {
     // dH
     {{4096, 256, 20, 12, 0, 0}, {4096, 2048, 1792, 768, 0, 0}, {4096, 3072, 2176, 1536, 0, 0}, {4096, 2560, 2048, 1536, 0, 0}, {1920, 1536, 1280, 1024, 256, 256}},
     // dX
-    {{4096, 256, 20, 256, 256, 0}, {4096, 3072, 2048, 256, 256, 0}, {3584, 3072, 2048, 1792, 0, 0}, {2304, 2560, 1792, 1536, 0, 0}, {1280, 1280, 1152, 512, 256, 256}}};
+    {{4096, 256, 256, 256, 256, 0}, {4096, 3072, 2048, 256, 256, 0}, {3584, 3072, 2048, 1792, 0, 0}, {2304, 2560, 1792, 1536, 0, 0}, {1280, 1280, 1152, 512, 256, 256}}};
 bool few_rows_pays(const Dims& D, RowTileKind kind) {
   const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;   // output columns f, contraction over d; else the other way round
   const long long active = D.N < D.Et ? D.N : D.Et;                  // experts with rows, at most

@@ -145,7 +145,7 @@ def test_missing_library_fails_loudly(monkeypatch):
     (1024, 7168, 512, 1, 1, ("gate_up", "dh")),    # 128 tiles of gate | up and dH, 1792 of down and dX
     (8192, 7168, 512, 8, 1, ()),                   # 17000 tiles of down and dX, twice the time on them
     (64, 7168, 1024, 8, 1, ("gate_up", "down", "dx")),   # 112 k-steps of dH, which the other kernel cuts along k
-    (32, 512, 2048, 4, 1, ("gate_up", "down", "dh")),   # 64 k-steps of dX
+    (32, 512, 2048, 4, 1, ("gate_up", "down", "dh", "dx")),   # 64 k-steps of dX: 0.79 of the 256-row kernel's time
     (32, 512, 14336, 4, 1, ("dh",)),               # 32 tiles of down and dX, but 224 and 448 k-steps
     (8, 4096, 14336, 1, 1, ("gate_up",)),
     (4096, 1024, 2048, 1, 1, ("down", "dx")),      # 1024 tiles of down and dX, 2048 of the others
@@ -157,7 +157,8 @@ def test_which_gemms_run_on_small_tiles(lib, T, d, f, E, k, expected):
     assert moe.grouped_ffn_small_tiles(moe.Shape(T, d, f, E, k)) == expected
 
 
-# Both sides of the limits of few rows per expert and long contractions: 200 tiles and 128 k-steps of down, 256 tiles and 200 of dX
+# Both sides of the limits of few rows per expert and long contractions: 200 tiles and 128 k-steps of down, 256 tiles and 200 of dX, which are one
+# limit from 48 k-steps on
 @pytest.mark.parametrize("T,d,f,E,k,down,dx", [
     (200, 512, 6144, 25, 1, True, True),       # 200 tiles of 96 and 192 steps
     (200, 512, 6144, 26, 1, False, True),      # 208
@@ -166,6 +167,12 @@ def test_which_gemms_run_on_small_tiles(lib, T, d, f, E, k, expected):
     (200, 512, 8192, 25, 1, False, False),     # 128 and 256
     (600, 512, 3584, 20, 1, True, True),       # 30 rows per expert: 160 tiles of dX, 112 steps
     (990, 512, 3584, 33, 1, True, False),      # 264, and of down, 56 steps
+    (80, 512, 1984, 10, 1, True, True),        # 8 rows per expert: 80 tiles of dX of 62 steps,
+    (80, 512, 2048, 10, 1, True, True),        # 64,
+    (80, 512, 3008, 10, 1, True, True),        # 94
+    (80, 512, 3072, 10, 1, True, True),        # and 96
+    (256, 512, 2560, 32, 1, True, True),       # 256 tiles of 80 steps
+    (264, 512, 2560, 33, 1, True, False),      # 264
 ])
 def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down, dx):
     small = moe.grouped_ffn_small_tiles(moe.Shape(T, d, f, E, k))
