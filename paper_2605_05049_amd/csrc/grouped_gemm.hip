@@ -1055,22 +1055,24 @@ bool few_rows_pays(const Dims& D, RowTileKind kind) {
 //   dH    1088 x 1984, 14, 287: 37 / 44      832 x 2624, 24, 1968: 378 / 403   2048 x 1408, 66, 186: 130 / 147
 //   dX    1408 x 4736, 5, 310: 92 / 108      512 x 3200, 12, 934: 99 / 122 (both in launches of their own)
 // and left out: gate | up 2048 x 1408, 66, 186: 196 / 184   down 832 x 2624, 24, 1968: 248 / 200   dX 2048 x 1408, 66, 993: 739 / 614.
-constexpr int kMidRowClasses = 4, kMidStepClasses = 7, kMidAny = 1 << 30;
+constexpr int kMidRowClasses = 4, kMidStepClasses = 8, kMidAny = 1 << 30;
 constexpr int kMidRowsBelow[kMidRowClasses - 1] = {16, 96, 320};                   // rows per expert on average
-constexpr int kMidStepsBelow[kMidStepClasses - 1] = {12, 24, 32, 40, 64, 128};     // k-steps of 64, both passes of dX counted
+constexpr int kMidStepsBelow[kMidStepClasses - 1] = {12, 24, 32, 40, 64, 128, 300};     // k-steps of 64, both passes of dX counted
 constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                     // tiles of 128 rows: fewer than this
     // gate | up
-    {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 0, 0}, {kMidAny, 4096, 1408, 1408, 1024, 1280, 1280},
-     {kMidAny, 2048, 1280, 1280, 512, 512, 512}, {4096, 768, 768, 768, 768, 640, 640}},
+    {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 0, 0, 0}, {kMidAny, 4096, 1408, 1408, 1024, 1280, 1280, 1280},
+     {kMidAny, 2048, 1280, 1280, 512, 512, 512, 512}, {4096, 768, 768, 768, 768, 640, 640, 640}},
     // down
-    {{kMidAny, kMidAny, 3072, 3072, 512, 256, 256}, {kMidAny, 4096, 2048, 2048, 1280, 512, 384},
-     {kMidAny, 2048, 1280, 1280, 768, 512, 320}, {kMidAny, 1536, 768, 768, 640, 768, 640}},
+    {{kMidAny, kMidAny, 3072, 3072, 512, 256, 256, 256}, {kMidAny, 4096, 2048, 2048, 1280, 512, 384, 384},
+     {kMidAny, 2048, 1280, 1280, 768, 512, 320, 320}, {kMidAny, 1536, 768, 768, 640, 768, 640, 640}},
     // dH
-    {{kMidAny, kMidAny, 512, 512, 512, 256, 256}, {kMidAny, kMidAny, 2560, 2560, 1024, 640, 640},
-     {kMidAny, kMidAny, 4096, 2048, 1280, 768, 768}, {kMidAny, kMidAny, 1536, 768, 768, 640, 640}},
-    // dX
-    {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 1536, 0}, {kMidAny, kMidAny, 3072, 3072, 3072, 2048, 768},
-     {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1536}, {3072, 3072, 2048, 2048, 1280, 768, 768}}};
+    {{kMidAny, kMidAny, 512, 512, 512, 256, 256, 256}, {kMidAny, kMidAny, 2560, 2560, 1024, 640, 640, 640},
+     {kMidAny, kMidAny, 4096, 2048, 1280, 768, 768, 768}, {kMidAny, kMidAny, 1536, 768, 768, 640, 640, 640}},
+    // dX (from 128 steps on from 2900 shapes more: 96 .. 320 rows 0.88 - 0.97 of the time up to 1024 tiles and 1.00 beyond, of 300 and more steps 0.98
+    // up to 512 and 1.00; more rows 0.90 - 0.98 up to 768 and 1.02 - 1.06, of 300 and more steps 0.97 up to 512 and 0.99, 1.04 with even counts.
+    // Us, even counts, backward, here / 256-row tiles: 4096 x 14336, 8 of 256 2098 / 2043, 4 of 512 1664 / 1487)
+    {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 1536, 0, 0}, {kMidAny, kMidAny, 3072, 3072, 3072, 2048, 768, 768},
+     {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1024, 512}, {3072, 3072, 2048, 2048, 1280, 768, 768, 512}}};
 int mid_rows_for(const Dims& D, RowTileKind kind) {
   if (D.Et > kFewSelfExperts || D.N == 0) return 0;   // (its blocks find their tiles from the offsets alone)
   const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;

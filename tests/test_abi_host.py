@@ -190,6 +190,11 @@ def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down,
     (16, 2048, 1408, 66, 8, ("gate_up", "down", "dx")),    # 726 tiles of dH, 32 steps, two rows per expert
     (512, 4096, 14336, 8, 1, ("down", "dx")),              # 1792 tiles of gate | up, 256 of down and dX
     (8192, 2048, 1408, 8, 1, ("dh", "dx")),                # 1088 tiles of down: 1.5 to 2.25 rounds
+    (2048, 4096, 14336, 8, 1, ()),                         # 640 tiles of dX, 448 steps, 256 rows per expert
+    (2048, 4096, 9536, 8, 1, ("dx",)),                     # 298 steps,
+    (2048, 4096, 9600, 8, 1, ()),                          # 300
+    (2048, 3200, 14336, 8, 1, ("dx",)),                    # 500 tiles,
+    (2048, 3328, 14336, 8, 1, ()),                         # 520
     (300, 512, 1024, 129, 1, ()),                          # more experts than a block finds its tile among
     (0, 512, 1024, 8, 2, ()),
 ])
