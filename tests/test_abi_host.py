@@ -190,6 +190,9 @@ def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down,
     (16, 2048, 1408, 66, 8, ("gate_up", "down", "dx")),    # 726 tiles of dH, 32 steps, two rows per expert
     (512, 4096, 14336, 8, 1, ("down", "dx")),              # 1792 tiles of gate | up, 256 of down and dX
     (8192, 2048, 1408, 8, 1, ("dh", "dx")),                # 1088 tiles of down: 1.5 to 2.25 rounds
+    (1440, 1536, 640, 10, 1, ("gate_up", "down", "dx")),   # 160 tiles of gate | up, 24 steps,
+    (1440, 1536, 576, 10, 1, ("down", "dx")),              # 144; 192 of down and dX
+    (1440, 1472, 576, 10, 1, ("gate_up", "down", "dx")),   # 144 of 23 steps
     (2048, 4096, 14336, 8, 1, ()),                         # 640 tiles of dX, 448 steps, 256 rows per expert
     (2048, 4096, 9536, 8, 1, ("dx",)),                     # 298 steps,
     (2048, 4096, 9600, 8, 1, ()),                          # 300
