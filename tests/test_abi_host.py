@@ -189,7 +189,13 @@ def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down,
     (7871, 832, 2624, 24, 6, ("dh",)),                     # 13 steps of dH: any number of tiles
     (16, 2048, 1408, 66, 8, ("gate_up", "down", "dx")),    # 726 tiles of dH, 32 steps, two rows per expert
     (512, 4096, 14336, 8, 1, ("down", "dx")),              # 1792 tiles of gate | up, 256 of down and dX
-    (8192, 2048, 1408, 8, 1, ("dh", "dx")),                # 1088 tiles of down: 1.5 to 2.25 rounds
+    (8192, 2048, 1408, 8, 1, ("dx",)),                     # 1088 tiles of down; even counts fill one round of 256-row tiles of it, 0.75 of one of dH
+    (7168, 2048, 1408, 8, 1, ("dh", "dx")),                # 28 row tiles of 256
+    (9216, 2048, 1408, 8, 1, ("down", "dx")),              # 40
+    (4096, 2048, 1408, 4, 1, ("dh", "dx")),                # 176 and 128 tiles of 256 x 256 for gate | up and down, one round; dH else on 64-row tiles
+    (4608, 4096, 1024, 8, 1, ("down", "dh", "dx")),        # 576 rows: 512 are 2 tiles, and these with two standard deviations more are 3
+    (3584, 1088, 1984, 14, 1, ("down", "dh", "dx")),       # 256 rows: one tile of gate | up,
+    (4012, 1088, 1984, 14, 1, ("gate_up", "down", "dh", "dx")),   # 287: not with two standard deviations more
     (1440, 1536, 640, 10, 1, ("gate_up", "down", "dx")),   # 160 tiles of gate | up, 24 steps,
     (1440, 1536, 576, 10, 1, ("down", "dx")),              # 144; 192 of down and dX
     (1440, 1472, 576, 10, 1, ("gate_up", "down", "dx")),   # 144 of 23 steps
