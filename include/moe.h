@@ -61,10 +61,9 @@ typedef enum {
 const char* moe_status_str(int status);
 /* Bytes of scratch that any single call below may need for this shape (0 if the shape is invalid). */
 size_t moe_workspace_bytes(const moe_shape* shape);
-/* Which GEMMs of the grouped FFN calls below are small ones at this shape: bit 0 gate | up (forward and recomputation), bit 1
- * down, bit 2 dH, bit 3 dX; 0 if the shape is invalid.  They run on 64-row tiles and the others on 256-row tiles, except for those of
- * either kind that moe_grouped_ffn_mid_tiles names (the same bits), which run on tiles of 128 columns and up to 192 rows.  For tests and
- * benchmarks: the choice does not change what a call computes. */
+/* Which GEMMs of the grouped FFN calls below run on 64-row tiles at this shape, and which on tiles of 128 columns and up to 192 rows (all
+ * others: 256-row tiles): bit 0 gate | up (forward and recomputation), bit 1 down, bit 2 dH, bit 3 dX; 0 if the shape is invalid.  No bit is
+ * set in both.  For tests and benchmarks: the choice does not change what a call computes. */
 int moe_grouped_ffn_small_tiles(const moe_shape* shape);
 int moe_grouped_ffn_mid_tiles(const moe_shape* shape);
 /* Library version, for the binding's sanity check. */

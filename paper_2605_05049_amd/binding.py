@@ -143,8 +143,7 @@ def _gemm_names(bits: int) -> tuple:
 
 
 def grouped_ffn_small_tiles(shape) -> tuple:
-    """The small GEMMs of the grouped FFN at this shape, out of "gate_up", "down", "dh", "dx": on 64-row tiles, the others on 256-row tiles, but
-    for those of either kind that `grouped_ffn_mid_tiles` names."""
+    """The GEMMs of the grouped FFN that run on 64-row tiles at this shape, out of "gate_up", "down", "dh", "dx"."""
     return _gemm_names(load_library().moe_grouped_ffn_small_tiles(ctypes.byref(Shape.of(shape)._c)))
 
 

@@ -87,7 +87,7 @@ extern "C" int moe_grouped_ffn_small_tiles(const moe_shape* shape) {
   if (moe::check_shape(shape, &D) != MOE_OK) return 0;
   int bits = 0;
   for (int kind = moe::ROWTILE_GATE_UP; kind <= moe::ROWTILE_DX; kind++)
-    if (moe::few_rows_pays(D, (moe::RowTileKind)kind)) bits |= 1 << kind;
+    if (moe::few_rows_pays(D, (moe::RowTileKind)kind) && !moe::mid_rows_for(D, (moe::RowTileKind)kind)) bits |= 1 << kind;
   return bits;
 }
 

@@ -136,20 +136,20 @@ def test_missing_library_fails_loudly(monkeypatch):
         B.load_library()
 
 
-# (T, d, f, E, k) -> the GEMMs on 64-row tiles.  Each goes by its own output width and contraction: a layer that is small in
-# d_ffn is not small in its down projection and dX (and the other way round).
+# (T, d, f, E, k) -> the GEMMs on 64-row tiles, and not on those of 128 columns, which are asked first.  Each goes by its own output width and
+# contraction: a layer that is small in d_ffn is not small in its down projection and dX (and the other way round).
 @pytest.mark.parametrize("T,d,f,E,k,expected", [
-    (256, 512, 1024, 8, 2, ("gate_up", "down", "dh", "dx")),
+    (256, 512, 1024, 8, 2, ("down", "dh", "dx")),
     (8192, 7168, 512, 4, 1, ()),
-    (512, 7168, 512, 1, 1, ("gate_up", "down", "dh", "dx")),
+    (512, 7168, 512, 1, 1, ("gate_up", "dh")),
     (1024, 7168, 512, 1, 1, ("gate_up", "dh")),    # 128 tiles of gate | up and dH, 1792 of down and dX
     (8192, 7168, 512, 8, 1, ()),                   # 17000 tiles of down and dX, twice the time on them
-    (64, 7168, 1024, 8, 1, ("gate_up", "down", "dx")),   # 112 k-steps of dH, which the other kernel cuts along k
-    (32, 512, 2048, 4, 1, ("gate_up", "down", "dh", "dx")),   # 64 k-steps of dX: 0.79 of the 256-row kernel's time
-    (32, 512, 14336, 4, 1, ("dh",)),               # 32 tiles of down and dX, but 224 and 448 k-steps
+    (64, 7168, 1024, 8, 1, ("gate_up",)),          # 112 k-steps of dH, which the 256-row kernel cuts along k
+    (32, 512, 2048, 4, 1, ("down", "dh", "dx")),   # 64 k-steps of dX: 0.79 of the 256-row kernel's time
+    (32, 512, 14336, 4, 1, ()),                    # 32 tiles of down and dX, but 224 and 448 k-steps
     (8, 4096, 14336, 1, 1, ("gate_up",)),
-    (4096, 1024, 2048, 1, 1, ("down", "dx")),      # 1024 tiles of down and dX, 2048 of the others
-    (2048, 1024, 2048, 32, 1, ("down", "dh", "dx")),     # 1536 tiles of gate | up, 768 of down and dX
+    (4096, 1024, 2048, 1, 1, ()),                  # 1024 64-row tiles of down and dX, 2048 of the others
+    (2048, 1024, 2048, 32, 1, ()),                 # 768 and more
     (4096, 4096, 14336, 8, 2, ()),
     (0, 512, 1024, 8, 2, ("gate_up", "down", "dh", "dx")),
 ])
@@ -171,8 +171,8 @@ def test_which_gemms_run_on_small_tiles(lib, T, d, f, E, k, expected):
     (80, 512, 2048, 10, 1, True, True),        # 64,
     (80, 512, 3008, 10, 1, True, True),        # 94
     (80, 512, 3072, 10, 1, True, True),        # and 96
-    (256, 512, 2560, 32, 1, True, True),       # 256 tiles of 80 steps
-    (264, 512, 2560, 33, 1, True, False),      # 264
+    (1032, 128, 2560, 129, 1, True, False),    # 258 tiles of 80 steps (more than 128 experts: none of 128 columns)
+    (1032, 64, 2560, 129, 1, True, True),      # 129
 ])
 def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down, dx):
     small = moe.grouped_ffn_small_tiles(moe.Shape(T, d, f, E, k))

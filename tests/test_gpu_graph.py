@@ -13,13 +13,14 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     ("tiny", W.WORKLOADS["tiny"]),
-    ("imbalance_scaled", W.scaled_down(W.WORKLOADS["imbalance"])),      # empty experts, ragged tiles; down and dX on 256-row tiles
-    ("finegrained_scaled", W.scaled_down(W.WORKLOADS["finegrained"])),  # shared experts; gate | up on 256-row tiles
-    # few tokens on wide experts: dH and dX cut their tiles along k, on arrival counters that every replay finds as the last left them
+    ("imbalance_scaled", W.scaled_down(W.WORKLOADS["imbalance"])),      # empty experts, ragged tiles; all on tiles of 128 columns
+    ("finegrained_scaled", W.scaled_down(W.WORKLOADS["finegrained"])),  # shared experts; all on tiles of 128 columns
+    # few tokens on wide experts: dH cuts its tiles along k, on arrival counters that every replay finds as the last left them
     ("split", W.Workload("split", W.MoEShape(16, 4096, 2048, 4, 1), "router")),
 ]
-SMALL_TILES = {"tiny": ("gate_up", "down", "dh", "dx"), "imbalance_scaled": ("gate_up", "dh"), "finegrained_scaled": ("down", "dh", "dx"),
-               "split": ("gate_up", "down")}
+ALL_GEMMS = ("gate_up", "down", "dh", "dx")
+TILES = {"tiny": (("down", "dh", "dx"), ("gate_up",)), "imbalance_scaled": ((), ALL_GEMMS), "finegrained_scaled": ((), ALL_GEMMS),
+         "split": (("gate_up", "down"), ("dx",))}   # (on 64-row tiles, on tiles of 128 columns)
 
 
 def _tensors(buf, with_router):
@@ -34,7 +35,7 @@ def _tensors(buf, with_router):
 def test_graph_replays_match_eager(moe, name, wl):
     sh = wl.shape
     s = moe.Shape.of(sh)
-    assert moe.grouped_ffn_small_tiles(s) == SMALL_TILES[name]
+    assert (moe.grouped_ffn_small_tiles(s), moe.grouped_ffn_mid_tiles(s)) == TILES[name]
     inp = W.make_layer_inputs(wl, seed=0)
     if "logits" not in inp:
         pytest.skip("workload without router logits")

@@ -513,28 +513,34 @@ def test_weight_gradient_begins(moe, d, f):
     test_grouped_ffn_every_tile_height(moe, d, f, [96, 97, 128, 161, 0, 224, 225, 256, 257, 300, 768, 769, 801])
 
 
-# (d, f, counts, GEMMs on 64-row tiles)
-@pytest.mark.parametrize("d,f,counts,small", [
-    (64, 64, [1, 32, 33, 0], ALL_GEMMS),                     # one k-step: three of four, seven of eight wavefronts have none
-    (192, 576, [64, 65, 31, 0, 128], ALL_GEMMS),             # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
-    (1088, 128, [200, 0, 7], ALL_GEMMS),                     # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
-    (64, 64, [4500, 0, 257, 7], ALL_GEMMS),                  # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
+def assert_runs_on(moe, d, f, counts, small, mid):
+    """Exactly these GEMMs run on 64-row tiles and on tiles of 128 columns; all others on 256-row tiles."""
+    s = moe.Shape(sum(counts), d, f, len(counts), 1)
+    assert (moe.grouped_ffn_small_tiles(s), moe.grouped_ffn_mid_tiles(s)) == (small, mid)
+
+
+# (d, f, counts, GEMMs on 64-row tiles, those on tiles of 128 columns)
+@pytest.mark.parametrize("d,f,counts,small,mid", [
+    (64, 64, [1, 32, 33, 0], ALL_GEMMS, ()),                     # one k-step: three of four, seven of eight wavefronts have none
+    (192, 576, [64, 65, 31, 0, 128], ("down", "dh", "dx"), ("gate_up",)),   # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
+    (1088, 128, [200, 0, 7], ALL_GEMMS, ()),                     # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
+    (64, 64, [4500, 0, 257, 7], ("down", "dh", "dx"), ("gate_up",)),
     # tiles found without a schedule: experts on either side of a wavefront's 64 lanes, 128 of them, the first and last ones empty
     # or not; and one and two experts too many for that
-    (64, 128, [0, 65] + 61 * [3] + [130, 70, 0, 5], ALL_GEMMS),
-    (64, 64, [0] + 62 * [1] + [0, 0] + 62 * [2] + [129], ALL_GEMMS),
-    (64, 64, 64 * [0] + [3] + 63 * [0], ALL_GEMMS),
-    (64, 64, 128 * [2] + [0], ALL_GEMMS),
-    (64, 64, 129 * [2] + [0], ALL_GEMMS),
-    # 8 row tiles of gate | up and dH on either side of a limit (1600 tiles for gate | up), next to a dX of 212 .. 520 k-steps
-    (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100], ("gate_up", "down", "dh")),
-    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100], ("gate_up", "dh")),
-    (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100], ("dh",)),
+    (64, 128, [0, 65] + 61 * [3] + [130, 70, 0, 5], ("down", "dh", "dx"), ("gate_up",)),
+    (64, 64, [0] + 62 * [1] + [0, 0] + 62 * [2] + [129], ("down", "dh"), ("gate_up", "dx")),
+    (64, 64, 64 * [0] + [3] + 63 * [0], ALL_GEMMS, ()),
+    (64, 64, 128 * [2] + [0], ALL_GEMMS, ()),
+    (64, 64, 129 * [2] + [0], ALL_GEMMS, ()),
+    # few row tiles of many columns, next to a dX of 212 .. 520 k-steps
+    (128, 64 * 106, [1, 40, 63, 0, 64, 65, 100], ("down",), ("gate_up", "dh")),
+    (128, 64 * 160, [1, 40, 63, 0, 64, 65, 100], (), ("gate_up", "dh")),
+    (64, 64 * 260, [1, 40, 63, 0, 64, 65, 100], (), ("gate_up", "dh")),
 ])
-def test_small_problem_tiles(moe, d, f, counts, small):
-    """The kernel for small problems, alone and next to the other one in a call (two schedules), and both sides of the rule
-    that chooses it for each GEMM.  Only a call whose two GEMMs both run on it, with at most 128 experts, launches no schedule."""
-    assert moe.grouped_ffn_small_tiles(moe.Shape(sum(counts), d, f, len(counts), 1)) == small
+def test_small_problem_tiles(moe, d, f, counts, small, mid):
+    """The kernels for small problems, alone, together and next to the large one's in a call (two schedules), and both sides of the rules that
+    choose them for each GEMM.  Only a call without a GEMM on 256-row tiles, with at most 128 experts, launches no schedule."""
+    assert_runs_on(moe, d, f, counts, small, mid)
     moe.profile_reset()
     moe.profile_enable(True)
     try:
@@ -544,28 +550,26 @@ def test_small_problem_tiles(moe, d, f, counts, small):
         moe.profile_enable(False)
         moe.profile_reset()
     calls = ("gate_up", "down"), ("dh", "dx")
-    assert labels.count("ffn_schedule") == sum(len(counts) > 128 or not set(call) <= set(small) for call in calls)
+    assert labels.count("ffn_schedule") == sum(len(counts) > 128 or not set(call) <= set(small + mid) for call in calls)
 
 
-@pytest.mark.parametrize("d,f,counts,small", [
-    # every height class in all four GEMMs; column tiles of 64 (f) and 128 (d) at the end
-    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], ()),
-    # experts of more than four row tiles, which the kernel walks column tile by column tile with a tall tile first, next to one
-    # of four, walked in bands of 8 column tiles: 9 column tiles, i.e. a full band and a band of one
-    (1408, 2304, MANY_TILE_COUNTS, ()),
-    # experts of 18, 14, 13 (the last a tall one) and 11 row tiles: three and two bands of rows, of equal and of unequal height, and none
-    (640, 832, [4500, 0, 3400, 3392, 2817], ()),
+@pytest.mark.parametrize("d,f,counts,small,mid", [
+    # down on every height class; column tiles of 128 at the end.
+    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], (), ("gate_up", "dh", "dx")),
+    # gate | up of experts of more than four row tiles, which the kernel walks column tile by column tile with a tall tile first, next to
+    # one of four, walked in bands of 8 column tiles: 18 column tiles, i.e. two full bands and one of two
+    (1408, 2304, MANY_TILE_COUNTS, (), ("down", "dh", "dx")),
     # few tiles and 48 k-steps or more: cut along k.  dH of 128 steps in up to 8 parts, a tall tile, a short one and one of 65
     # rows among them, whose last part to arrive applies the d(SwiGLU) epilogue to the sums ...
-    (8192, 128, [300, 33, 0, 0, 65], ("gate_up", "down", "dx")),
+    (8192, 128, [300, 33, 0, 0, 65], ("gate_up",), ("down", "dx")),
     # ... down and dX, of 128 and 256 steps ...
-    (128, 8192, [300, 33, 0, 0, 0, 0, 65], ("gate_up", "dh")),
-    # ... and dH and dX (64 steps each, 16 and 32 tiles) in one backward call, on the same arrival counters
-    (4096, 2048, [12, 0, 31], ("gate_up", "down")),
+    (128, 8192, [300, 33, 0, 0, 0, 0, 65], (), ("gate_up", "dh")),
+    # ... and dH of 64 steps.
+    (4096, 2048, [12, 0, 31], ("gate_up", "down"), ("dx",)),
 ])
-def test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small):
+def test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small, mid):
     """The kernel of large problems at whole-tensor precision."""
-    assert moe.grouped_ffn_small_tiles(moe.Shape(sum(counts), d, f, len(counts), 1)) == small
+    assert_runs_on(moe, d, f, counts, small, mid)
     test_grouped_ffn_every_tile_height(moe, d, f, counts)
 
 
@@ -574,21 +578,23 @@ def test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small):
 CLASS_COUNTS = [64, 65, 128, 129, 161, 192, 193, 256, 257, 272, 288, 289, 320, 0, 512 + 33, 512 + 160, 321, 100, 224]
 
 
-@pytest.mark.parametrize("d,f,counts,small", [
-    (64, 4096, CLASS_COUNTS, ("down", "dx")),          # gate | up and dH of 1 step: fewer than the stages of any class
-    (192, 4096, CLASS_COUNTS, ("down", "dx")),         # of 3 steps
-    (4096, 128, CLASS_COUNTS, ("gate_up", "dh")),      # down of 2 steps, dX of 4
-    (1088, 1600, 4 * CLASS_COUNTS, ()),                # all four: 17, 25 and 50 steps
+@pytest.mark.parametrize("d,f,counts,small,mid", [
+    (1088, 1600, 4 * CLASS_COUNTS, (), ("dh", "dx")),         # gate | up and down: 17 and 25 steps
+    # the same rows on tiles of 128 columns
+    (64, 4096, CLASS_COUNTS, ("down", "dx"), ("gate_up", "dh")),
+    (192, 4096, CLASS_COUNTS, ("down", "dx"), ("gate_up", "dh")),
+    (4096, 128, CLASS_COUNTS, ("gate_up", "dh"), ("down", "dx")),
 ])
-def test_row_tile_classes(moe, d, f, counts, small):
-    test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small)
+def test_row_tile_classes(moe, d, f, counts, small, mid):
+    test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small, mid)
 
 
-# left-over tiles in pieces of whole 64 rows, (gate | up, down, dH, dX): 2, 3, none and 3 pieces (dX of 50 steps); 5, 4, 5 and 4, more
-# than some of the tiles have rows for; tall tiles, 2 .. 3 pieces of up to 192 rows
-@pytest.mark.parametrize("d,f,counts", [(1088, 1600, 3 * CLASS_COUNTS), (448, 1216, 7 * CLASS_COUNTS), (1088, 1600, 12 * [320] + [289, 0, 257, 200])])
-def test_row_tiles_cut_along_rows(moe, d, f, counts):
-    test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, ())
+# left-over tiles in pieces of whole 64 rows: gate | up and down in 2 and 3; (gate | up, down, dH, dX) in 5, 4, 5 and 4, more
+# than some of the tiles have rows for
+@pytest.mark.parametrize("d,f,counts,mid", [(1088, 1600, 3 * CLASS_COUNTS, ("dh", "dx")), (448, 1216, 7 * CLASS_COUNTS, ()),
+                                            (1088, 1600, 12 * [320] + [289, 0, 257, 200], ALL_GEMMS)])
+def test_row_tiles_cut_along_rows(moe, d, f, counts, mid):
+    test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, (), mid)
 
 
 def ffn_on_device(moe, d, f, counts, seed=0):
@@ -630,17 +636,17 @@ def test_weight_gradients_accumulate(moe, d, f, counts):
             assert bool(torch.isfinite(c).all()) and torch.equal(a, b + c), (name, recompute)
 
 
-@pytest.mark.parametrize("d,f,counts,small", [
-    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], ()),          # all on 256-row tiles
-    (256, 192, [248] * 64 + [2048, 2048], ("dh",)),               # 256-row forward, dH on 64-row tiles, dX on 256-row tiles
-    (4096, 1088, [3, 0, 31, 9, 1, 0, 12, 30, 2, 2, 0, 5, 1, 1, 1, 2, 4], ("dx",)),   # few rows; dH cut along k
-    (8192, 128, [300, 33, 0, 0, 65], ("gate_up", "down", "dx")),  # all but dH, cut along k, on 64-row tiles
-    (512, 1024, [64] * 8, ALL_GEMMS),
+@pytest.mark.parametrize("d,f,counts,small,mid", [
+    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], (), ("gate_up", "dh", "dx")),   # all but down on tiles of 128 columns
+    (256, 192, [248] * 64 + [2048, 2048], (), ALL_GEMMS),
+    (4096, 1088, [3, 0, 31, 9, 1, 0, 12, 30, 2, 2, 0, 5, 1, 1, 1, 2, 4], (), ("down", "dx")),   # few rows; dH cut along k
+    (8192, 128, [300, 33, 0, 0, 65], ("gate_up",), ("down", "dx")),  # dH, cut along k, on 256-row tiles
+    (512, 1024, [64] * 8, ("down", "dh", "dx"), ("gate_up",)),
 ])
-def test_recomputing_backward_on_either_kernel(moe, d, f, counts, small):
+def test_recomputing_backward_on_either_kernel(moe, d, f, counts, small, mid):
     """The recomputing backward gives the saving pair's bits whichever kernels its GEMMs run on (G and U, recomputed into the
     memory of dG and dU, are read and overwritten in place)."""
-    assert moe.grouped_ffn_small_tiles(moe.Shape(sum(counts), d, f, len(counts), 1)) == small
+    assert_runs_on(moe, d, f, counts, small, mid)
     s, x, dy, off, w, ws, y, sg, su = ffn_on_device(moe, d, f, counts)
     y2 = torch.full_like(y, float("nan"))
     moe.moe_grouped_ffn_fwd(s, x, off, *w, y2, None, None, ws)
@@ -931,13 +937,15 @@ MID_COUNTS = [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 0, 25
 # 64 (d = 1088), contractions of 1, 2, 3 and more k-steps, experts of more than 12 row tiles (walked in bands), 128 experts with
 # empty first and last ones (found from the offsets; the order of the experts is written by dH), dX in a launch of its own (4096 rows per expert)
 @pytest.mark.parametrize("d,f,counts,mid", [
-    (1088, 1600, MID_COUNTS, ALL_GEMMS),                          # up to 128 rows
+    (1088, 1728, MID_COUNTS, ALL_GEMMS),                          # up to 128 rows
     (1088, 1152, MID_COUNTS, ALL_GEMMS),                          # up to 192
     (64, 1088, 2 * MID_COUNTS, ("gate_up", "dh")),                # one k-step of gate | up and dH
     (1088, 64, 2 * MID_COUNTS, ("down", "dx")),                   # one of down, two of dX
     (192, 704, [2600, 0, 77, 1700], ("gate_up", "dh")),           # 3 k-steps; 21 row tiles of one expert
     (576, 192, [0, 0, 130] + 61 * [33, 2] + [1, 64, 0], ALL_GEMMS),
     (320, 320, [8200, 0], ALL_GEMMS),
+    # experts of 18 to 36 row tiles: up to five bands of rows, of equal and of unequal height
+    (640, 832, [4500, 0, 3400, 3392, 2817], ALL_GEMMS),
 ])
 def test_mid_row_tiles(moe, d, f, counts, mid):
     s = moe.Shape(sum(counts), d, f, len(counts), 1)
@@ -959,10 +967,13 @@ def test_mid_row_tiles(moe, d, f, counts, mid):
 # 2, 2, 2 and 2 pieces, whole and in 3, 5 and 3
 @pytest.mark.parametrize("n_large", [8, 11])
 def test_large_problem_on_256_row_tiles(moe, n_large):
+    compare_ffn_on_device(moe, 2560, 1600, CLASS_COUNTS + n_large * [2000], (), ())
+
+
+def compare_ffn_on_device(moe, d, f, counts, small, mid):
     """Against fp32 on the device, expert by expert."""
-    d, f, counts = 2560, 1600, CLASS_COUNTS + n_large * [2000]
+    assert_runs_on(moe, d, f, counts, small, mid)
     s, x, dy, off, w, ws, y, sg, su = ffn_on_device(moe, d, f, counts)
-    assert moe.grouped_ffn_mid_tiles(s) == () and moe.grouped_ffn_small_tiles(s) == ()
     dx = torch.full((s.N, d), float("nan"), dtype=torch.bfloat16, device="cuda")
     dw = [torch.full(t.shape, float("nan"), device="cuda") for t in w]
     moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, sg, su, dx, *dw, False, ws)
