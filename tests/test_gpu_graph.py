@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import workloads as W
-from test_gpu_parity import dev, dev_bf16
+from test_gpu_parity import dev, dev_bf16, ffn_on_device
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +59,36 @@ def test_graph_replays_match_eager(moe, name, wl):
                 a, b = a.view(torch.int16), b.view(torch.int16)
             assert torch.equal(a, b), f"{name}: replay {replay}: {n} differs from the eager result"
         assert int(buf_graph.counts.sum()) == s.N
+
+
+def test_replays_of_tiles_cut_along_k(moe):
+    """dH and dX of one backward both cut their tiles along k, on the same arrival counters, which every replay finds as the last left them."""
+    counts = [9, 20]
+    s, x, dy, off, w, ws, y, sg, su = ffn_on_device(moe, 4096, 6400, counts)
+    assert (moe.grouped_ffn_small_tiles(s), moe.grouped_ffn_mid_tiles(s)) == (("gate_up", "down"), ())
+
+    def call(ws, y, g, u, dx, dw):
+        moe.moe_grouped_ffn_fwd(s, x, off, *w, y, g, u, ws)
+        moe.moe_grouped_ffn_bwd(s, dy, x, off, *w, g, u, dx, *dw, False, ws)
+
+    def buffers():
+        return (torch.empty_like(ws), *(torch.full_like(t, float("nan")) for t in (y, sg, su, x)), [torch.full(t.shape, float("nan"), device="cuda") for t in w])
+
+    replayed, eager = buffers(), buffers()
+    call(*replayed)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(*replayed)
+    for replay in range(3):
+        print(f"[graph] cut along k: replay {replay}", flush=True)
+        g = torch.Generator(device="cuda").manual_seed(replay)
+        for t in (x, dy):
+            t.copy_(torch.randn(t.shape, device="cuda", generator=g))
+        for t in (*replayed[1:5], *replayed[5]):
+            t.fill_(float("nan"))
+        graph.replay()
+        call(*eager)
+        torch.cuda.synchronize()
+        for a, b in zip((*replayed[1:5], *replayed[5]), (*eager[1:5], *eager[5])):
+            assert bool(torch.isfinite(a).all()) and torch.equal(a, b)

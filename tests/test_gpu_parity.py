@@ -525,6 +525,8 @@ def assert_runs_on(moe, d, f, counts, small, mid):
     (192, 576, [64, 65, 31, 0, 128], ("down", "dh", "dx"), ("gate_up",)),   # 3 and 9 k-steps: unequal shares; tiles of one and two 32-row blocks
     (1088, 128, [200, 0, 7], ALL_GEMMS, ()),                     # 17 k-steps of dH and gate | up, 2 of down, 4 of dX
     (64, 64, [4500, 0, 257, 7], ("down", "dh", "dx"), ("gate_up",)),
+    # an expert of more tiles (71) than a wavefront has lanes, one of 5: the schedule's writers
+    (64, 64, [4500, 0, 257, 7] + 126 * [1], ALL_GEMMS, ()),
     # tiles found without a schedule: experts on either side of a wavefront's 64 lanes, 128 of them, the first and last ones empty
     # or not; and one and two experts too many for that
     (64, 128, [0, 65] + 61 * [3] + [130, 70, 0, 5], ("down", "dh", "dx"), ("gate_up",)),
@@ -554,7 +556,7 @@ def test_small_problem_tiles(moe, d, f, counts, small, mid):
 
 
 @pytest.mark.parametrize("d,f,counts,small,mid", [
-    # down on every height class; column tiles of 128 at the end.
+    # down on every height class; column tiles of 128 at the end.  (All four GEMMs: test_large_problem_on_256_row_tiles)
     (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], (), ("gate_up", "dh", "dx")),
     # gate | up of experts of more than four row tiles, which the kernel walks column tile by column tile with a tall tile first, next to
     # one of four, walked in bands of 8 column tiles: 18 column tiles, i.e. two full bands and one of two
@@ -564,7 +566,7 @@ def test_small_problem_tiles(moe, d, f, counts, small, mid):
     (8192, 128, [300, 33, 0, 0, 65], ("gate_up",), ("down", "dx")),
     # ... down and dX, of 128 and 256 steps ...
     (128, 8192, [300, 33, 0, 0, 0, 0, 65], (), ("gate_up", "dh")),
-    # ... and dH of 64 steps.
+    # ... and dH of 64 steps.  (dH and dX in one backward call, on the same arrival counters: test_dh_and_dx_cut_along_k)
     (4096, 2048, [12, 0, 31], ("gate_up", "down"), ("dx",)),
 ])
 def test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small, mid):
@@ -579,6 +581,10 @@ CLASS_COUNTS = [64, 65, 128, 129, 161, 192, 193, 256, 257, 272, 288, 289, 320, 0
 
 
 @pytest.mark.parametrize("d,f,counts,small,mid", [
+    # (more than 128 experts: none on tiles of 128 columns)
+    (64, 256, 7 * CLASS_COUNTS, ("down", "dx"), ()),          # gate | up and dH of 1 step: fewer than the stages of any class
+    (192, 256, 7 * CLASS_COUNTS, (), ()),                     # of 3 steps, down of 4, dX of 8
+    (256, 64, 7 * CLASS_COUNTS, ("gate_up", "dh"), ()),       # down of 1 step, dX of 2
     (1088, 1600, 4 * CLASS_COUNTS, (), ("dh", "dx")),         # gate | up and down: 17 and 25 steps
     # the same rows on tiles of 128 columns
     (64, 4096, CLASS_COUNTS, ("down", "dx"), ("gate_up", "dh")),
@@ -590,9 +596,9 @@ def test_row_tile_classes(moe, d, f, counts, small, mid):
 
 
 # left-over tiles in pieces of whole 64 rows: gate | up and down in 2 and 3; (gate | up, down, dH, dX) in 5, 4, 5 and 4, more
-# than some of the tiles have rows for
+# than some of the tiles have rows for; tall tiles, all four in 2 (more than 128 experts: none on tiles of 128 columns)
 @pytest.mark.parametrize("d,f,counts,mid", [(1088, 1600, 3 * CLASS_COUNTS, ("dh", "dx")), (448, 1216, 7 * CLASS_COUNTS, ()),
-                                            (1088, 1600, 12 * [320] + [289, 0, 257, 200], ALL_GEMMS)])
+                                            (256, 256, 122 * [320] + [289, 0, 257, 200, 0, 0, 0], ())])
 def test_row_tiles_cut_along_rows(moe, d, f, counts, mid):
     test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, (), mid)
 
@@ -637,11 +643,15 @@ def test_weight_gradients_accumulate(moe, d, f, counts):
 
 
 @pytest.mark.parametrize("d,f,counts,small,mid", [
+    (2560, 1600, CLASS_COUNTS + 8 * [2000], (), ()),              # all on 256-row tiles
     (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], (), ("gate_up", "dh", "dx")),   # all but down on tiles of 128 columns
     (256, 192, [248] * 64 + [2048, 2048], (), ALL_GEMMS),
+    (256, 192, [248] * 64 + [2048, 2048] + 63 * [0], ("dh",), ()),   # 256-row forward, dH on 64-row tiles, dX on 256-row tiles
     (4096, 1088, [3, 0, 31, 9, 1, 0, 12, 30, 2, 2, 0, 5, 1, 1, 1, 2, 4], (), ("down", "dx")),   # few rows; dH cut along k
     (8192, 128, [300, 33, 0, 0, 65], ("gate_up",), ("down", "dx")),  # dH, cut along k, on 256-row tiles
+    (4096, 6400, [9, 20], ("gate_up", "down"), ()),               # dH and dX cut along k
     (512, 1024, [64] * 8, ("down", "dh", "dx"), ("gate_up",)),
+    (512, 192, [16] * 8, ALL_GEMMS, ()),
 ])
 def test_recomputing_backward_on_either_kernel(moe, d, f, counts, small, mid):
     """The recomputing backward gives the saving pair's bits whichever kernels its GEMMs run on (G and U, recomputed into the
@@ -968,6 +978,17 @@ def test_mid_row_tiles(moe, d, f, counts, mid):
 @pytest.mark.parametrize("n_large", [8, 11])
 def test_large_problem_on_256_row_tiles(moe, n_large):
     compare_ffn_on_device(moe, 2560, 1600, CLASS_COUNTS + n_large * [2000], (), ())
+
+
+# experts of 18, 14, 13 (the last tile a tall one) and 11 row tiles: three and two bands of rows, of equal and of unequal height, and none; of 5
+# tiles with a tall last one, 6 with a short one and 4, walked in bands of 8 of 9 column tiles (dX and down; 18 of gate | up)
+def test_bands_of_256_row_tiles(moe):
+    compare_ffn_on_device(moe, 2304, 2304, [4500, 0, 3400, 3392, 2817] + MANY_TILE_COUNTS, (), ())
+
+
+# dH of 64 steps and dX of 200 in one backward, left-over tiles of both in 4 and 8 parts along k, on the same arrival counters
+def test_dh_and_dx_cut_along_k(moe):
+    compare_ffn_on_device(moe, 4096, 6400, [9, 20], ("gate_up", "down"), ())
 
 
 def compare_ffn_on_device(moe, d, f, counts, small, mid):
