@@ -1069,10 +1069,11 @@ constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                  
     // dH
     {{kMidAny, kMidAny, 512, 512, 512, 256, 256, 256}, {kMidAny, kMidAny, 2560, 2560, 1024, 640, 640, 640},
      {kMidAny, kMidAny, 4096, 2048, 1280, 768, 768, 768}, {kMidAny, kMidAny, 1536, 768, 768, 640, 640, 640}},
-    // dX (from 128 steps on from 2900 shapes more: 96 .. 320 rows 0.88 - 0.97 of the time up to 1024 tiles and 1.00 beyond, of 300 and more steps 0.98
-    // up to 512 and 1.00; more rows 0.90 - 0.98 up to 768 and 1.02 - 1.06, of 300 and more steps 0.97 up to 512 and 0.99, 1.04 with even counts.
+    // dX (from 128 steps on from 5300 shapes more: 96 .. 320 rows 0.88 - 0.97 of the time up to 1024 tiles and 1.00 beyond, of 300 and more steps 0.96 - 0.99
+    // up to 512 and 1.00; more rows 0.90 - 0.98 up to 768 and 1.02 - 1.06, of 300 and more steps 0.94 - 0.99 up to 512 and 0.99, 1.04 with even
+    // counts; 16 .. 96 rows and 300 and more steps 0.97 - 0.99 up to 320 and 1.01 - 1.02 beyond.
     // Us, even counts, backward, here / 256-row tiles: 4096 x 14336, 8 of 256 2098 / 2043, 4 of 512 1664 / 1487)
-    {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 1536, 0, 0}, {kMidAny, kMidAny, 3072, 3072, 3072, 2048, 768, 768},
+    {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 1536, 0, 0}, {kMidAny, kMidAny, 3072, 3072, 3072, 2048, 768, 320},
      {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1024, 512}, {3072, 3072, 2048, 2048, 1280, 768, 768, 512}}};
 // The limits above go by mean rows per expert and count every expert's last tile as half full; with even counts the tiles of both kernels
 // are known, and where the 256-row ones then fill their rounds the others can take 1.3 times as long (gate | up and down of 4 x 1024 rows,
@@ -1138,7 +1139,9 @@ int mid_rows_for(const Dims& D, RowTileKind kind) {
     case ROWTILE_GATE_UP: least = steps < 12 ? 32 : few; break;
     case ROWTILE_DOWN: least = few; break;
     case ROWTILE_DH: least = rc == 0 ? (steps < 12 ? 208 : 256) : rc == 1 ? 208 : 160; break;   // (few_rows.hip requests G and U before the sums)
-    default: least = steps < 128 ? 96 : 128; break;                                             // (beside the weight gradients it need not fill the chip)
+    // (beside the weight gradients dX need not fill the chip.  Of 300 and more steps, which the 256-row kernel cuts along k: 96 rows and more 1.03 - 1.07
+    // at 128 .. 192 tiles, 1.00 up to 256, 0.94 - 0.99 beyond; fewer rows 1.01 at 120 .. 144, 0.98 beyond)
+    default: least = steps < 128 ? 96 : steps < 300 ? 128 : rc < 2 ? 144 : 224; break;
   }
   if (tiles < least || tiles >= kMidMost[kind][rc][sc]) return 0;
   // Tiles of 192 rows move fewer operand bytes (12.7 KB per million multiply-adds for 15.3) and leave fewer remainders, but make fewer tiles:

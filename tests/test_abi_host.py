@@ -202,6 +202,12 @@ def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down,
     (2048, 4096, 14336, 8, 1, ()),                         # 640 tiles of dX, 448 steps, 256 rows per expert
     (2048, 4096, 9536, 8, 1, ("dx",)),                     # 298 steps,
     (2048, 4096, 9600, 8, 1, ()),                          # 300
+    (512, 4096, 14336, 4, 1, ("dh",)),                     # 192 tiles of dX, 128 rows
+    (768, 4096, 14336, 4, 1, ("dx",)),                     # 256
+    (256, 4096, 14336, 4, 1, ("gate_up", "dh")),           # 128, 64 rows
+    (320, 4096, 14336, 5, 1, ("gate_up", "down", "dh", "dx")),   # 160
+    (576, 4096, 14336, 9, 1, ("down", "dx")),              # 288,
+    (640, 4096, 14336, 10, 1, ("down",)),                  # 320
     (2048, 3200, 14336, 8, 1, ("dx",)),                    # 500 tiles,
     (2048, 3328, 14336, 8, 1, ()),                         # 520
     (300, 512, 1024, 129, 1, ()),                          # more experts than a block finds its tile among
