@@ -185,9 +185,6 @@ __device__ __forceinline__ void few_rows_block(const RowTileArgs& A, char* lds, 
     e_lo = tile.z;
     e_hi = tile.w;
   } else {
-    // One expert per lane, twice: where the running sum of their row tiles passes ut is the expert.  (A schedule is a launch of its
-    // own, 4 - 5 us, and three loads that wait for each other in every block; these are four that do not, and a sum over the
-    // lanes.  Replayed step of 256 tokens, top-2 of 8 experts, 512 x 1024: 94.5 -> 89.7 us)
     if (KIND == ROWTILE_DH && A.order && block == blocks - 1) {   // one block more: what the weight gradients read of a schedule
       write_expert_order(A, lds, tid);
       return;

@@ -1161,7 +1161,7 @@ static RowTiles row_tiles_for(const Dims& D, RowTileKind kind) {
 }
 
 // The row-tile GEMMs of one call of the expert FFN: of the forward (gate | up and down) or of the backward (dH and dX; of a recomputing one
-// gate | up too: with a schedule of its own, a launch of 5 .. 6 us more).
+// gate | up too, all by one schedule: one for the recomputation alone was a launch of 5 .. 6 us more).
 struct RowGemms {
   const Dims& D;
   const WsLayout& L;

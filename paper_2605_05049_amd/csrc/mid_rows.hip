@@ -1,4 +1,4 @@
-// The row-tile GEMMs of the SwiGLU expert FFNs (Section III-A) on tiles of 128 x 128: see mid_rows.h.
+// The row-tile GEMMs of the SwiGLU expert FFNs (Section III-A) on tiles of up to 128 or 192 rows x 128 columns: see mid_rows.h.
 #include "mid_rows.h"
 
 namespace moe {
