@@ -1133,11 +1133,9 @@ int mid_rows_for(const Dims& D, RowTileKind kind) {
   while (rc < kMidRowClasses - 1 && D.N >= (long long)kMidRowsBelow[rc] * D.Et) rc++;
   while (sc < kMidStepClasses - 1 && steps >= kMidStepsBelow[sc]) sc++;
   int least;
-  // (gate | up and down of 96 rows and more, 24 steps and more: 144 .. 160 tiles 1.00 - 1.05 of the better other kernel's time, 128 .. 144 1.02 - 1.14)
-  const int few = rc >= 2 && steps >= 24 ? 160 : 144;
   switch (kind) {
-    case ROWTILE_GATE_UP: least = steps < 12 ? 32 : few; break;
-    case ROWTILE_DOWN: least = few; break;
+    case ROWTILE_GATE_UP: least = steps < 12 ? 32 : 144; break;
+    case ROWTILE_DOWN: least = 144; break;
     case ROWTILE_DH: least = rc == 0 ? (steps < 12 ? 208 : 256) : rc == 1 ? 208 : 160; break;   // (few_rows.hip requests G and U before the sums)
     // (beside the weight gradients dX need not fill the chip.  Of 300 and more steps, which the 256-row kernel cuts along k: 96 rows and more 1.03 - 1.07
     // at 128 .. 192 tiles, 1.00 up to 256, 0.94 - 0.99 beyond; fewer rows 1.01 at 120 .. 144, 0.98 beyond)

@@ -196,9 +196,6 @@ def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down,
     (4608, 4096, 1024, 8, 1, ("down", "dh", "dx")),        # 576 rows: 512 are 2 tiles, and these with two standard deviations more are 3
     (3584, 1088, 1984, 14, 1, ("down", "dh", "dx")),       # 256 rows: one tile of gate | up,
     (4012, 1088, 1984, 14, 1, ("gate_up", "down", "dh", "dx")),   # 287: not with two standard deviations more
-    (1440, 1536, 640, 10, 1, ("gate_up", "down", "dx")),   # 160 tiles of gate | up, 24 steps,
-    (1440, 1536, 576, 10, 1, ("down", "dx")),              # 144; 192 of down and dX
-    (1440, 1472, 576, 10, 1, ("gate_up", "down", "dx")),   # 144 of 23 steps
     (2048, 4096, 14336, 8, 1, ()),                         # 640 tiles of dX, 448 steps, 256 rows per expert
     (2048, 4096, 9536, 8, 1, ("dx",)),                     # 298 steps,
     (2048, 4096, 9600, 8, 1, ()),                          # 300
