@@ -1075,38 +1075,42 @@ constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                  
     // Us, even counts, backward, here / 256-row tiles: 4096 x 14336, 8 of 256 2098 / 2043, 4 of 512 1664 / 1487)
     {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 1536, 0, 0}, {kMidAny, kMidAny, 3072, 3072, 3072, 2048, 768, 320},
      {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1024, 512}, {3072, 3072, 2048, 2048, 1280, 768, 768, 512}}};
-// The limits above go by mean rows per expert and count every expert's last tile as half full; with even counts the tiles of both kernels
-// are known, and where the 256-row ones then fill their rounds the others can take 1.3 times as long (gate | up and down of 4 x 1024 rows,
-// 2048 x 1408, 73 us for 95; of 8 x 512, 4096 x 1024, 103 for 131).  So such a GEMM is left to them if, for even counts, they take less than
-// 0.85 of the time by this reckoning, and for gate | up and down (where one expert of more than 320 rows may cost a second round) also with
-// two standard deviations of i.i.d. rows more.  In us: a 256-row tile takes `start` + k-steps x (step + step_rows x rows / 256) in each round
-// of 256, a left-over one its part of that (cut along k: + `cut` x parts x rows / 256 for the sums); those of 128 columns k-steps x
-// (mid_step + mid_step_rows x rows / 128) in each round of 512, `alone` of it in one of up to 256; with either the weights' transfer, `per_mb`,
-// partly overlaps.  The constants are fitted to the differences between the two measured on 7560 shapes (half of them products of the sizes that
-// layers have, rows in multiples of 64), 5 - 7 % of the call off; fitted on half of them the other half is decided as well.  Forward + backward,
-// with this / without, of the time before the tiles of 128 columns: layer sizes, even counts 0.947 / 0.951, i.i.d. experts 0.930 / 0.931, uneven
-// ones 0.921 / 0.917; random sizes 0.907, 0.905 and 0.914 / 0.913.  Forward more than 1.05 of it, layer sizes: even counts 5 / 13 %, i.i.d.
-// experts 2.5 / 6.6 %.  (The counts are on the device: Zipf ones where even ones fill rounds lose up to 14 % of a call, and stay ahead of that time.)
+// The limits above go by mean rows per expert and count every expert's last tile as half full; where even counts are whole 256-row tiles that fill
+// their rounds the others can take 1.3 times as long (gate | up and down of 4 x 1024 rows, 2048 x 1408, 73 us for 95; of 8 x 512,
+// 4096 x 1024, 103 for 131).  So with rows per expert within 3 % of a multiple of 256, and tiles of even counts for whole rounds of the CUs or, cut
+// in two, for half of one, such a GEMM is left to the 256-row kernel if, for even counts, it takes less than 0.85 of the time by this reckoning.
+// In us: a 256-row tile takes `start` + k-steps x (step + step_rows x rows / 256) in each round of 256, a left-over one its part of that (cut
+// along k: + `cut` x parts x rows / 256 for the sums); those of 128 columns k-steps x (mid_step + mid_step_rows x rows / 128) in each
+// round of 512, `alone` of it in one of up to 256; with either the weights' transfer, `per_mb`, partly overlaps.  The constants are fitted to the
+// differences between the two measured on 7560 shapes (half of them products of the sizes that layers have, rows in multiples of 64), 5 - 7 % of
+// the call off; fitted on half of them the other half is decided as well.  Forward + backward of those layer sizes, with this / without, of the
+// time before the tiles of 128 columns: even counts 0.947 / 0.951 (more than 1.02: 2 / 4.5 %), i.i.d. experts 0.9305 / 0.931, Zipf counts 0.921 /
+// 0.917; of random sizes as without.  (Other rows per expert: with the reckoning alone, cases drawn with i.i.d. and biased routers took 1.003 of the
+// time without it, up to 1.13, because a few uneven experts spoil the rounds: only whole tiles are a sign of even counts.)
 struct EvenCounts { double start, step, step_rows, cut, mid_step, mid_step_rows, alone, per_mb; };
 constexpr EvenCounts kEvenCounts[3] = {   // gate | up, down, dH
     {1.44, 0.26, 0.51, 0.00, 0.26, 0.39, 0.53, 0.07}, {1.71, 0.23, 0.79, 0.84, 0.30, 0.46, 0.55, 0.10}, {2.26, 0.23, 1.05, 3.98, 0.24, 0.54, 0.64, 0.05}};
-// `rows` of each of `active` experts
-static bool even_counts_fill_tall_tiles(const Dims& D, RowTileKind kind, int mid_rows, long long active, long long rows) {
+static bool even_counts_fill_tall_tiles(const Dims& D, RowTileKind kind, int mid_rows) {
+  if (kind == ROWTILE_DX) return false;   // (it shares a launch with the weight gradients: no such pattern)
   const EvenCounts& C = kEvenCounts[kind];
   auto cuts = [](long long a, long long b) { return (a + b - 1) / b; };
+  const long long active = std::min<long long>(D.N, D.Et), rows = cuts(D.N, active);
   const int pair = kind == ROWTILE_GATE_UP ? 2 : 1, width = kind == ROWTILE_DOWN ? D.d : D.f, steps = (kind == ROWTILE_DOWN ? D.f : D.d) / 64;
-  const double mb = 2e-6 * active * D.d * D.f * pair;
   const long long per_expert = row_tiles_of((int)rows, TILES_TALL), tiles = active * per_expert * cuts(width, TILE / pair);
-  const double height = std::min<long long>(TILE + 64, cuts(cuts(rows, per_expert), 32) * 32);
-  const long long full = tiles / 256, rest = cuts(tiles - full * 256, kNumXcd);   // left-over tiles of an XCD
+  if (rows < 248 * per_expert || rows > 264 * per_expert) return false;
+  const long long left = tiles % 256;
+  if (left > 0 && left < 160 && (left < 100 || left > 128)) return false;
+  const double mb = 2e-6 * active * D.d * D.f * pair;
+  const double height = cuts(cuts(rows, per_expert), 32) * 32;
+  const long long full = tiles / 256, rest = cuts(left, kNumXcd);   // left-over tiles of an XCD
   double part = rest ? 1 : 0, sums = 0;
   if (rest && rest <= kCusPerXcd / 2) {   // (as the kernel cuts them)
     if (kind != ROWTILE_GATE_UP && steps >= (rows >= kRowCutRows * per_expert ? kRowCutSteps : MOE_SPLIT_MIN_STEPS)) {
       const long long parts = std::min<long long>({kCusPerXcd / rest, 8, steps / MOE_SPLIT_PART_STEPS});
       part = 1.0 / parts;
-      if (parts > 1) sums = C.cut * parts * height / TILE;
+      sums = C.cut * parts * height / TILE;
     } else if (rows >= kRowCutLeast * per_expert) {
-      part = 1.0 / std::min<long long>({kCusPerXcd / rest, (long long)(height + 63) / 64, 5});
+      part = 1.0 / std::min<long long>(kCusPerXcd / rest, cuts(height, 64));
     }
   }
   const double step = C.step + C.step_rows * height / TILE;
@@ -1115,12 +1119,6 @@ static bool even_counts_fill_tall_tiles(const Dims& D, RowTileKind kind, int mid
   const double mid_height = cuts(cuts(rows, mid_per_expert), 32) * 32;
   const double rounds = mid_tiles / 512 + (mid_rest == 0 ? 0 : mid_rest <= 256 ? C.alone : 1);
   return tall < 0.85 * std::hypot(rounds * steps * (C.mid_step + C.mid_step_rows * mid_height / 128), mb * C.per_mb);
-}
-static bool tall_tiles_by_even_counts(const Dims& D, RowTileKind kind, int mid_rows) {
-  if (kind == ROWTILE_DX) return false;   // (it shares a launch with the weight gradients: no such pattern)
-  const long long active = std::min<long long>(D.N, D.Et), rows = (D.N + active - 1) / active;
-  return even_counts_fill_tall_tiles(D, kind, mid_rows, active, rows) &&
-         (kind == ROWTILE_DH || even_counts_fill_tall_tiles(D, kind, mid_rows, active, rows + 2 * (long long)std::ceil(std::sqrt((double)rows))));
 }
 int mid_rows_for(const Dims& D, RowTileKind kind) {
   if (D.Et > kFewSelfExperts || D.N == 0) return 0;   // (its blocks find their tiles from the offsets alone)
@@ -1151,7 +1149,7 @@ int mid_rows_for(const Dims& D, RowTileKind kind) {
     if (kind == ROWTILE_DX) rows = tiles >= 192 ? 192 : 128;
     else rows = 13 * rounds192 <= 10 * rounds || (tiles > 256 && tiles <= 384) ? 192 : 128;
   }
-  return !few_rows_pays(D, kind) && tall_tiles_by_even_counts(D, kind, rows) ? 0 : rows;
+  return !few_rows_pays(D, kind) && even_counts_fill_tall_tiles(D, kind, rows) ? 0 : rows;
 }
 enum RowTiles { ROWTILES_TALL, ROWTILES_FEW, ROWTILES_MID };
 static RowTiles row_tiles_for(const Dims& D, RowTileKind kind) {

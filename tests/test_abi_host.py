@@ -189,18 +189,20 @@ def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down,
     (7871, 832, 2624, 24, 6, ("dh",)),                     # 13 steps of dH: any number of tiles
     (16, 2048, 1408, 66, 8, ("gate_up", "down", "dx")),    # 726 tiles of dH, 32 steps, two rows per expert
     (512, 4096, 14336, 8, 1, ("down", "dx")),              # 1792 tiles of gate | up, 256 of down and dX
-    (8192, 2048, 1408, 8, 1, ("dx",)),                     # 1088 tiles of down; even counts fill one round of 256-row tiles of it, 0.75 of one of dH
-    (7168, 2048, 1408, 8, 1, ("dh", "dx")),                # 28 row tiles of 256
-    (9216, 2048, 1408, 8, 1, ("down", "dx")),              # 40
-    (4096, 2048, 1408, 4, 1, ("dh", "dx")),                # 176 and 128 tiles of 256 x 256 for gate | up and down, one round; dH else on 64-row tiles
-    (4608, 4096, 1024, 8, 1, ("down", "dh", "dx")),        # 576 rows: 512 are 2 tiles, and these with two standard deviations more are 3
-    (3584, 1088, 1984, 14, 1, ("down", "dh", "dx")),       # 256 rows: one tile of gate | up,
-    (4012, 1088, 1984, 14, 1, ("gate_up", "down", "dh", "dx")),   # 287: not with two standard deviations more
+    # even counts that fill rounds of 256-row tiles: 32 row tiles of 248 .. 264 rows, 256 tiles of down and 192 of dH
+    (7872, 2048, 1408, 8, 1, ("down", "dh", "dx")),        # 246 rows
+    (7936, 2048, 1408, 8, 1, ("dx",)),
+    (8448, 2048, 1408, 8, 1, ("dx",)),
+    (8640, 2048, 1408, 8, 1, ("down", "dx")),              # 270
+    (4096, 2048, 1408, 4, 1, ("dh", "dx")),                # 176 and 128 tiles of gate | up and down; dH else on 64-row tiles
+    (4096, 4096, 1024, 8, 1, ("dh", "dx")),                # 128 and 256
+    (2048, 7168, 2048, 8, 1, ("dh", "dx")),                # 224 tiles of down, 64 of dH
+    (4012, 1088, 1984, 14, 1, ("gate_up", "down", "dh", "dx")),   # 287 rows
     (2048, 4096, 14336, 8, 1, ()),                         # 640 tiles of dX, 448 steps, 256 rows per expert
     (2048, 4096, 9536, 8, 1, ("dx",)),                     # 298 steps,
     (2048, 4096, 9600, 8, 1, ()),                          # 300
-    (512, 4096, 14336, 4, 1, ("dh",)),                     # 192 tiles of dX, 128 rows
-    (768, 4096, 14336, 4, 1, ("dx",)),                     # 256
+    (512, 4096, 14336, 4, 1, ("down", "dh")),              # 192 tiles of dX, 128 rows
+    (768, 4096, 14336, 4, 1, ("down", "dx")),              # 256
     (256, 4096, 14336, 4, 1, ("gate_up", "dh")),           # 128, 64 rows
     (320, 4096, 14336, 5, 1, ("gate_up", "down", "dh", "dx")),   # 160
     (576, 4096, 14336, 9, 1, ("down", "dx")),              # 288,

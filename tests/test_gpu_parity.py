@@ -556,8 +556,8 @@ def test_small_problem_tiles(moe, d, f, counts, small, mid):
 
 
 @pytest.mark.parametrize("d,f,counts,small,mid", [
-    # down on every height class; column tiles of 128 at the end.  (All four GEMMs: test_large_problem_on_256_row_tiles)
-    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], (), ("gate_up", "dh", "dx")),
+    # every height class in all four GEMMs; column tiles of 64 (f) and 128 (d) at the end (more than 128 experts: none on tiles of 128 columns)
+    (384, 320, 9 * HEIGHT_COUNTS, (), ()),
     # gate | up of experts of more than four row tiles, which the kernel walks column tile by column tile with a tall tile first, next to
     # one of four, walked in bands of 8 column tiles: 18 column tiles, i.e. two full bands and one of two
     (1408, 2304, MANY_TILE_COUNTS, (), ("down", "dh", "dx")),
@@ -595,9 +595,9 @@ def test_row_tile_classes(moe, d, f, counts, small, mid):
     test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, small, mid)
 
 
-# left-over tiles in pieces of whole 64 rows: gate | up and down in 2 and 3; (gate | up, down, dH, dX) in 5, 4, 5 and 4, more
+# left-over tiles in pieces of whole 64 rows: gate | up in 2; (gate | up, down, dH, dX) in 5, 4, 5 and 4, more
 # than some of the tiles have rows for; tall tiles, all four in 2 (more than 128 experts: none on tiles of 128 columns)
-@pytest.mark.parametrize("d,f,counts,mid", [(1088, 1600, 3 * CLASS_COUNTS, ("dh", "dx")), (448, 1216, 7 * CLASS_COUNTS, ()),
+@pytest.mark.parametrize("d,f,counts,mid", [(1088, 1600, 3 * CLASS_COUNTS, ("down", "dh", "dx")), (448, 1216, 7 * CLASS_COUNTS, ()),
                                             (256, 256, 122 * [320] + [289, 0, 257, 200, 0, 0, 0], ())])
 def test_row_tiles_cut_along_rows(moe, d, f, counts, mid):
     test_grouped_ffn_on_256_row_tiles(moe, d, f, counts, (), mid)
@@ -644,7 +644,7 @@ def test_weight_gradients_accumulate(moe, d, f, counts):
 
 @pytest.mark.parametrize("d,f,counts,small,mid", [
     (2560, 1600, CLASS_COUNTS + 8 * [2000], (), ()),              # all on 256-row tiles
-    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], (), ("gate_up", "dh", "dx")),   # all but down on tiles of 128 columns
+    (640, 1088, HEIGHT_COUNTS + [1500, 2000, 1800], (), ALL_GEMMS),   # all on tiles of 128 columns
     (256, 192, [248] * 64 + [2048, 2048], (), ALL_GEMMS),
     (256, 192, [248] * 64 + [2048, 2048] + 63 * [0], ("dh",), ()),   # 256-row forward, dH on 64-row tiles, dX on 256-row tiles
     (4096, 1088, [3, 0, 31, 9, 1, 0, 12, 30, 2, 2, 0, 5, 1, 1, 1, 2, 4], (), ("down", "dx")),   # few rows; dH cut along k
