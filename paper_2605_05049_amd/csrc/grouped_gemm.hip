@@ -1069,12 +1069,10 @@ constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                  
     // dH
     {{kMidAny, kMidAny, 512, 512, 512, 256, 256, 256}, {kMidAny, kMidAny, 2560, 2560, 1024, 640, 640, 640},
      {kMidAny, kMidAny, 4096, 2048, 1280, 768, 768, 768}, {kMidAny, kMidAny, 1536, 768, 768, 640, 640, 640}},
-    // dX (from 128 steps on from 5300 shapes more: 96 .. 320 rows 0.88 - 0.97 of the time up to 1024 tiles and 1.00 beyond, of 300 and more steps 0.96 - 0.99
-    // up to 512 and 1.00; more rows 0.90 - 0.98 up to 768 and 1.02 - 1.06, of 300 and more steps 0.94 - 0.99 up to 512 and 0.99, 1.04 with even
-    // counts; 16 .. 96 rows and 300 and more steps 0.97 - 0.99 up to 320 and 1.01 - 1.02 beyond.
-    // Us, even counts, backward, here / 256-row tiles: 4096 x 14336, 8 of 256 2098 / 2043, 4 of 512 1664 / 1487)
+    // dX (from 128 steps on from 5300 shapes more: 96 .. 320 rows 0.88 - 0.97 of the time up to 1024 tiles and 1.00 beyond, of 300 and more steps 0.96 - 1.00
+    // up to 768 and 1.04; more rows 0.90 - 0.99 up to 768 and 1.02 - 1.10; 16 .. 96 rows and 300 and more steps 0.97 - 0.99 up to 320 and 1.01 - 1.02)
     {{kMidAny, kMidAny, kMidAny, kMidAny, 3072, 1536, 0, 0}, {kMidAny, kMidAny, 3072, 3072, 3072, 2048, 768, 320},
-     {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1024, 512}, {3072, 3072, 2048, 2048, 1280, 768, 768, 512}}};
+     {kMidAny, kMidAny, kMidAny, kMidAny, 3072, 3072, 1024, 768}, {3072, 3072, 2048, 2048, 1280, 768, 768, 768}}};
 // The limits above go by mean rows per expert and count every expert's last tile as half full; where even counts are whole 256-row tiles that fill
 // their rounds the others can take 1.3 times as long (gate | up and down of 4 x 1024 rows, 2048 x 1408, 73 us for 95; of 8 x 512,
 // 4096 x 1024, 103 for 131).  So with rows per expert within 3 % of a multiple of 256, and tiles of even counts for whole rounds of the CUs or, cut
@@ -1085,21 +1083,24 @@ constexpr int kMidMost[4][kMidRowClasses][kMidStepClasses] = {                  
 // differences between the two measured on 7560 shapes (half of them products of the sizes that layers have, rows in multiples of 64), 5 - 7 % of
 // the call off; fitted on half of them the other half is decided as well.  Forward + backward of those layer sizes, with this / without, of the
 // time before the tiles of 128 columns: even counts 0.947 / 0.951 (more than 1.02: 2 / 4.5 %), i.i.d. experts 0.9305 / 0.931, Zipf counts 0.921 /
-// 0.917; of random sizes as without.  (Other rows per expert: with the reckoning alone, cases drawn with i.i.d. and biased routers took 1.003 of the
+// 0.917; of random sizes as without.  dX, which shares a launch with the weight gradients, follows no such reckoning: there it is 300 and
+// more k-steps and 512 tiles of 128 columns and more, with even counts 1.06 of the 256-row kernel's time, i.i.d. 1.055, uneven 0.96 (backward of
+// 4096 x 14336, 8 of 256 2098 us here, 2043 there; 4 of 512 1664 and 1487).  (Other rows per expert: with the reckoning alone, cases drawn with i.i.d. and biased routers took 1.003 of the
 // time without it, up to 1.13, because a few uneven experts spoil the rounds: only whole tiles are a sign of even counts.)
 struct EvenCounts { double start, step, step_rows, cut, mid_step, mid_step_rows, alone, per_mb; };
 constexpr EvenCounts kEvenCounts[3] = {   // gate | up, down, dH
     {1.44, 0.26, 0.51, 0.00, 0.26, 0.39, 0.53, 0.07}, {1.71, 0.23, 0.79, 0.84, 0.30, 0.46, 0.55, 0.10}, {2.26, 0.23, 1.05, 3.98, 0.24, 0.54, 0.64, 0.05}};
-static bool even_counts_fill_tall_tiles(const Dims& D, RowTileKind kind, int mid_rows) {
-  if (kind == ROWTILE_DX) return false;   // (it shares a launch with the weight gradients: no such pattern)
-  const EvenCounts& C = kEvenCounts[kind];
+static bool even_counts_fill_tall_tiles(const Dims& D, RowTileKind kind, int mid_rows, long long tiles128) {
   auto cuts = [](long long a, long long b) { return (a + b - 1) / b; };
+  const bool to_f = kind == ROWTILE_GATE_UP || kind == ROWTILE_DH;
   const long long active = std::min<long long>(D.N, D.Et), rows = cuts(D.N, active);
-  const int pair = kind == ROWTILE_GATE_UP ? 2 : 1, width = kind == ROWTILE_DOWN ? D.d : D.f, steps = (kind == ROWTILE_DOWN ? D.f : D.d) / 64;
+  const int pair = kind == ROWTILE_GATE_UP ? 2 : 1, width = to_f ? D.f : D.d, steps = (to_f ? D.d : D.f) / 64 * (kind == ROWTILE_DX ? 2 : 1);
   const long long per_expert = row_tiles_of((int)rows, TILES_TALL), tiles = active * per_expert * cuts(width, TILE / pair);
   if (rows < 248 * per_expert || rows > 264 * per_expert) return false;
   const long long left = tiles % 256;
   if (left > 0 && left < 160 && (left < 100 || left > 128)) return false;
+  if (kind == ROWTILE_DX) return steps >= 300 && tiles128 >= 512;
+  const EvenCounts& C = kEvenCounts[kind];
   const double mb = 2e-6 * active * D.d * D.f * pair;
   const double height = cuts(cuts(rows, per_expert), 32) * 32;
   const long long full = tiles / 256, rest = cuts(left, kNumXcd);   // left-over tiles of an XCD
@@ -1136,8 +1137,9 @@ int mid_rows_for(const Dims& D, RowTileKind kind) {
     case ROWTILE_DOWN: least = 144; break;
     case ROWTILE_DH: least = rc == 0 ? (steps < 12 ? 208 : 256) : rc == 1 ? 208 : 160; break;   // (few_rows.hip requests G and U before the sums)
     // (beside the weight gradients dX need not fill the chip.  Of 300 and more steps, which the 256-row kernel cuts along k: 96 rows and more 1.03 - 1.07
-    // at 128 .. 192 tiles, 1.00 up to 256, 0.94 - 0.99 beyond; fewer rows 1.01 at 120 .. 144, 0.98 beyond)
-    default: least = steps < 128 ? 96 : steps < 300 ? 128 : rc < 2 ? 144 : 224; break;
+    // at 128 .. 192 tiles, 1.00 up to 224, 0.94 - 0.99 beyond, where the last of its column tiles is nearly empty 1.02 up to 160 and 0.90 - 0.98
+    // beyond; fewer rows 1.01 at 120 .. 144, 0.98 beyond)
+    default: least = steps < 128 ? 96 : steps < 300 ? 128 : rc < 2 ? 144 : (D.d + TILE - 1) / TILE * TILE * 10 >= D.d * 11 ? 160 : 224; break;
   }
   if (tiles < least || tiles >= kMidMost[kind][rc][sc]) return 0;
   // Tiles of 192 rows move fewer operand bytes (12.7 KB per million multiply-adds for 15.3) and leave fewer remainders, but make fewer tiles:
@@ -1149,7 +1151,7 @@ int mid_rows_for(const Dims& D, RowTileKind kind) {
     if (kind == ROWTILE_DX) rows = tiles >= 192 ? 192 : 128;
     else rows = 13 * rounds192 <= 10 * rounds || (tiles > 256 && tiles <= 384) ? 192 : 128;
   }
-  return !few_rows_pays(D, kind) && even_counts_fill_tall_tiles(D, kind, rows) ? 0 : rows;
+  return !few_rows_pays(D, kind) && even_counts_fill_tall_tiles(D, kind, rows, tiles) ? 0 : rows;
 }
 enum RowTiles { ROWTILES_TALL, ROWTILES_FEW, ROWTILES_MID };
 static RowTiles row_tiles_for(const Dims& D, RowTileKind kind) {

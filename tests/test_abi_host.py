@@ -198,9 +198,14 @@ def test_small_tiles_of_few_rows_and_long_contractions(lib, T, d, f, E, k, down,
     (4096, 4096, 1024, 8, 1, ("dh", "dx")),                # 128 and 256
     (2048, 7168, 2048, 8, 1, ("dh", "dx")),                # 224 tiles of down, 64 of dH
     (4012, 1088, 1984, 14, 1, ("gate_up", "down", "dh", "dx")),   # 287 rows
-    (2048, 4096, 14336, 8, 1, ()),                         # 640 tiles of dX, 448 steps, 256 rows per expert
+    (2048, 4096, 14336, 8, 1, ()),                         # 640 tiles of dX, 448 steps; even counts are 128 tiles, half a round
+    (2240, 4096, 14336, 8, 1, ("dx",)),                    # 280 rows
     (2048, 4096, 9536, 8, 1, ("dx",)),                     # 298 steps,
     (2048, 4096, 9600, 8, 1, ()),                          # 300
+    (2400, 4352, 14336, 8, 1, ("dx",)),                    # 748 tiles,
+    (2400, 4416, 14336, 8, 1, ()),                         # 770
+    (3600, 576, 11136, 12, 1, ("gate_up", "down", "dh", "dx")),   # 170 tiles, 348 steps; 2.25 column tiles of 256
+    (4800, 512, 11136, 16, 1, ("gate_up", "down", "dh")),   # 180; 2
     (512, 4096, 14336, 4, 1, ("down", "dh")),              # 192 tiles of dX, 128 rows
     (768, 4096, 14336, 4, 1, ("down", "dx")),              # 256
     (256, 4096, 14336, 4, 1, ("gate_up", "dh")),           # 128, 64 rows
